@@ -94,6 +94,18 @@ __device__ __forceinline__ T load_global(global_bytes p)
     return *(const __attribute__((address_space(1))) T *)p;
 }
 
+// A wavefront-uniform stretch of memory behind a buffer descriptor: loads address it with a 32-bit lane offset plus a
+// scalar offset, so a moving base costs scalar arithmetic only and no 64-bit lane address occupies registers.
+typedef __amdgpu_buffer_rsrc_t Stretch;
+constexpr int kStreamed = 2;   // cache policy nt: read once
+__device__ __forceinline__ Stretch stretch(const void *base, uint32_t bytes)
+{
+    const uint64_t v = reinterpret_cast<uint64_t>(base);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>(((uint64_t)hi << 32) | lo), 0, (int)bytes, 0x00020000);
+}
+
 // Symmetric weights (paper section 2.2: GPTQ quantises symmetrically, so every zero-point is the mid-code 8):
 // kernels instantiated with SYM never read the zero-points and use the constants below instead.
 constexpr uint32_t kSymZeros = 0x88888888u;      // the zero-point word such a weight holds
@@ -995,6 +1007,8 @@ __global__ __launch_bounds__(256, ((MT == 1 || (MT * TW <= 12 && !(MT == 3 && TW
     }
 }
 
+// One group with all TW tiles advancing through the four k steps together: an x fragment is read from LDS once per group
+// and lives for one step, so the registers it would hold for the whole group carry a second group of codes instead.
 // One quantisation group for this wavefront's TW column tiles, tile after tile with no software
 // pipelining: few live registers, so that several wavefronts share a SIMD and the hardware overlaps
 // one wavefront's code expansion (vector ALU) with another's matrix instructions.  The code
@@ -1038,6 +1052,103 @@ __device__ __forceinline__ void compute_group_lean(const u32x4 (&a)[MT][4], Quan
         // that the co-resident wavefronts need, and they are what hides this tile's latency
         __builtin_amdgcn_sched_barrier(0);
     }
+}
+
+// One quantisation group with all TW tiles advancing through the four k steps together, each tile's expansion beside
+// the products of the tile before it.  An x fragment is read from LDS once per group and lives for one step (two in
+// registers), x itself travels global -> LDS without passing through registers, and loads address through buffer
+// descriptors (no 64-bit lane addresses): that pays for the partial sums of all tiles and, with two tiles, for a second group
+// of codes in flight.  What bounds it at 64 rows is the power budget -- 2.35 GHz while the same kernel only streams
+// or only expands, 1.75 GHz with products and stream together -- so what helps is less work beside the products:
+// sixteen LDS reads of x and their waits at the head of every group, and the copies of x through registers, are gone.
+// Against the tile-by-tile form above, on weights that come from HBM: 70B gate_up 76.2 -> 72.8 us at 64 rows, 64.6 -> 62.0
+// at 48, 52.2 -> 51.4 at 32; 70B down at 64 rows 45.5 -> 42.8, 8B gate_up at 60 rows 24.8 -> 23.7.
+// The line between the two: the first x tiles reach the products about 1 us later here (8B qkv at 30 rows 10.3 -> 11.4 us,
+// 70B o_proj at 64 rows 20.3 -> 20.8), which short K ranges do not get back; those run with two tiles and one group
+// of codes in flight, and keep the form above.
+constexpr bool staged_steps(int tw, int depth) { return tw >= 4 || depth == 2; }
+
+// scales and zero-points of one group as the staged kernel keeps them: its own TW tiles only
+template <int TW>
+struct StagedQuant {
+    uint32_t s[TW / 2];   // fp16 scales, two tiles per word
+    uint32_t z;           // the record's eight 4-bit zero-points
+};
+template <int TW, bool SYM>
+__device__ __forceinline__ void load_quant(StagedQuant<TW> &q, Stretch recs, uint32_t rec, uint32_t scale_off, uint32_t zero_off)
+{
+    if constexpr (TW == 2) {
+        q.s[0] = __builtin_amdgcn_raw_buffer_load_b32(recs, scale_off, rec, 0);
+    } else if constexpr (TW == 4) {
+        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(recs, scale_off, rec, 0);
+        q.s[0] = v[0], q.s[1] = v[1];
+    } else {
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(recs, scale_off, rec, 0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) q.s[i] = v[i];
+    }
+    if constexpr (SYM) q.z = kSymZeros;
+    else q.z = __builtin_amdgcn_raw_buffer_load_b32(recs, zero_off, rec, 0);
+}
+
+constexpr int kFragRing = 2;   // x fragments in registers: the step in use and the next
+
+template <int MT, int TW, bool ALWAYS, bool SYM, typename ReadA>
+__device__ __forceinline__ void compute_group_staged(u32x4 (&a)[kFragRing][MT], StagedQuant<TW> &f, u32x4 (&w)[TW],
+                                                     float4v (&acc)[TW][MT], Stretch recs, uint32_t rec, uint32_t code_off,
+                                                     uint32_t scale_off, uint32_t zero_off, int t0, bool refill, ReadA read_a,
+                                                     const DequantConsts &magic)
+{
+    const StagedQuant<TW> q = f;
+    const uint32_t zbits = q.z >> (4 * t0);
+    half2v zneg[TW], zneg16[TW];
+#pragma unroll
+    for (int t = 0; t < TW; ++t) {
+        const uint32_t z = (zbits >> (4 * t)) & 0xFu;
+        const uint32_t zz = z | (z << 16);
+        zneg[t] = as_h2(SYM ? kSymZneg : (zz | 0xE400E400u));              // -(1024 + z)
+        zneg16[t] = as_h2(SYM ? kSymZneg16 : ((zz << 4) | 0xD400D400u));   // -(64 + z)
+    }
+    if (ALWAYS || refill) load_quant<TW, SYM>(f, recs, rec, scale_off, zero_off);
+    float4v part[TW][MT];
+    half8v b = dequant8(w[0][0], zneg[0], zneg16[0], magic);
+    auto fold = [&](int t) {
+        const uint32_t s2 = q.s[t >> 1];
+        const float s = (float)__builtin_bit_cast(_Float16, (uint16_t)((t & 1) ? (s2 >> 16) : (s2 & 0xFFFFu)));
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) acc[t][mt] += s * part[t][mt];
+    };
+#pragma unroll
+    for (int st = 0; st < 4; ++st) {
+#pragma unroll
+        for (int t = 0; t < TW; ++t) {
+            half8v bn = b;   // the next tile's codes (or the first tile's of the next step) are expanded beside these products
+            if (t + 1 < TW) bn = dequant8(w[t + 1 < TW ? t + 1 : 0][st], zneg[t + 1 < TW ? t + 1 : 0], zneg16[t + 1 < TW ? t + 1 : 0], magic);
+            else if (st < 3) bn = dequant8(w[0][st < 3 ? st + 1 : 0], zneg[0], zneg16[0], magic);
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+                part[t][mt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8v, a[st % kFragRing][mt]), b,
+                                                                     st == 0 ? (float4v){0.f, 0.f, 0.f, 0.f} : part[t][mt], 0, 0, 0);
+            if (st == 3 && t > 0) fold(t - 1);
+            if (t + 1 == TW) {
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) a[st % kFragRing][mt] = read_a(st + kFragRing >= 4, mt, (st + kFragRing) % 4);
+            }
+            if (st == 3 && (ALWAYS || refill))
+                w[t] = __builtin_amdgcn_raw_buffer_load_b128(recs, code_off + (uint32_t)(t * 1024), rec, kStreamed);
+#pragma unroll
+            for (int i = 0; i < MT; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                        // MFMA
+                if (st == 3) __builtin_amdgcn_sched_group_barrier(0x002, 4 + (10 + MT - 1) / MT, 0);      // VALU, with the fold
+                else __builtin_amdgcn_sched_group_barrier(0x002, (10 + MT - 1) / MT, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            b = bn;
+        }
+    }
+    fold(TW - 1);
+    __builtin_amdgcn_sched_barrier(0);
 }
 
 // High-occupancy variant for M > 16.  A workgroup of 4*KS wavefronts owns a column unit of 4*TW
@@ -1106,78 +1217,166 @@ __device__ __forceinline__ void cs_segment(const _Float16 *__restrict__ x, const
     const uint8_t *xbase = reinterpret_cast<const uint8_t *>(x + (size_t)(g_begin + kset) * kGroup);
     const uint8_t *recw = packed + record_offset(nb, g_begin + (kset < n ? kset : 0), groups);   // group 0 of this wavefront
 
+    const DequantConsts magic = dequant_consts();
     float4v acc[TW][MT];
 #pragma unroll
     for (int t = 0; t < TW; ++t)
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) acc[t][mt] = (float4v){0.f, 0.f, 0.f, 0.f};
 
-    u32x4 w[DEPTH][TW];
-    QuantWords qw[DEPTH];
-    u32x4 xreg[MT];
-    u32x4 a[MT][4];
-    const DequantConsts magic = dequant_consts();
-    auto load_x = [&](int i) {
-        const global_bytes xb = uniform_ptr(xbase + (size_t)i * (KS * kGroup * sizeof(_Float16)));
+    if constexpr (staged_steps(TW, DEPTH)) {
+        const Stretch recs = stretch(recw, (uint32_t)(groups - (g_begin + (kset < n ? kset : 0))) * kRecordBytes);
+        const Stretch xs = stretch(xbase, (uint32_t)(((size_t)(M - 1) * K + K - (g_begin + kset) * kGroup) * sizeof(_Float16)));
+        const uint32_t code_off = (uint32_t)(t0 * 1024 + lane * 16);
+        const uint32_t scale_off = (uint32_t)(kScalesOff + c * 16 + t0 * 2), zero_off = (uint32_t)(kZerosOff + c * 4);
+        u32x4 w[DEPTH][TW];
+        StagedQuant<TW> qw[DEPTH];
+        u32x4 a[kFragRing][MT];
+        auto read_a = [&](int buf, int mt, int j) {
+            return *reinterpret_cast<const u32x4 *>(reinterpret_cast<const uint8_t *>(xa + buf * kBufQuads + kset * MT * 4 * 64) +
+                                                    (xfrag[j & 1] + (mt * 4096 + (j >> 1) * 2048)));
+        };
+        // x tiles travel global -> LDS directly: lane l of a transfer fills bytes 16 l .. of its 1 KB block
+        auto copy_x = [&](int i, int buf) {
+            const uint32_t from = (uint32_t)i * (KS * kGroup * sizeof(_Float16));
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) xreg[mt] = load_global<u32x4>(xb + xoff[mt]);
-    };
-    auto park_x = [&](int buf) {
+            for (int blk = 0; blk < MT; ++blk)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(xs, (__attribute__((address_space(3))) void *)(xa + buf * kBufQuads + (kset * MT * 4 + colq * MT + blk) * 64),
+                                                         16, xoff[blk], from, 0, 0);
+        };
+        constexpr int kStepLoads = TW + 1 + (SYM ? 0 : 1);   // code, scale and zero-point loads of a step
+        if (mine > 0) copy_x(0, 0);
+        if (mine > 1) copy_x(1, 1);
 #pragma unroll
-        for (int i = 0; i < MT; ++i) xa[buf * kBufQuads + (kset * MT * 4 + colq * MT + i) * 64 + lane] = xreg[i];
-    };
-    auto fetch_a = [&](int buf) {
+        for (int d = 0; d < DEPTH; ++d)
+            if (d < mine) {
+                const uint32_t rec = (uint32_t)d * (KS * kRecordBytes);
+                load_quant<TW, SYM>(qw[d], recs, rec, scale_off, zero_off);
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
+                for (int t = 0; t < TW; ++t)
+                    w[d][t] = __builtin_amdgcn_raw_buffer_load_b128(recs, code_off + (uint32_t)(t * 1024), rec, kStreamed);
+            }
+        if (mine >= DEPTH) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(DEPTH * kStepLoads) : "memory");   // the x tiles, not the codes
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (mine > 0) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                a[mt][j] = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const uint8_t *>(xa + buf * kBufQuads + kset * MT * 4 * 64) +
-                                                           (mt * 2 + (j >> 1)) * 2048 + xfrag[j & 1]);
-    };
-    auto rec_of = [&](int i) { return recw + (size_t)i * (KS * kRecordBytes); };
+            for (int st = 0; st < kFragRing; ++st)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) a[st][mt] = read_a(0, mt, st);
+        }
+        constexpr int kAhead = DEPTH > 2 ? DEPTH : 2;   // how far the loads of a step reach
+        // tile gi is in buffer b_now, tile gi + 1 in b_next, tile gi + 2 goes to b_free: it held tile gi - 1, which every
+        // wavefront has finished reading when it passes the barrier of step gi
+        int b_now = 0, b_next = 1, b_free = 2;
+        auto rotate = [&]() {
+            const int t = b_now;
+            b_now = b_next;
+            b_next = b_free;
+            b_free = t;
+        };
+        auto read_ahead = [&](int later, int mt, int j) { return read_a(later ? b_next : b_now, mt, j); };
+        int i = 0;
+        // steady state: every wavefront has a group in this step and kAhead steps further on
+#pragma clang loop unroll(disable)
+        for (; i + DEPTH - 1 + kAhead < full; i += DEPTH) {
+#pragma unroll
+            for (int u = 0; u < DEPTH; ++u) {
+                const int gi = i + u;
+                // x tiles of step gi + 1 have landed (requested a step ago, before the loads that may still be under
+                // way); after the barrier everybody's have
+                if (gi > 0) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kStepLoads) : "memory");
+                __syncthreads();
+                copy_x(gi + 2, b_free);
+                __builtin_amdgcn_sched_barrier(0);
+                compute_group_staged<MT, TW, true, SYM>(a, qw[u], w[u], acc, recs, (uint32_t)(gi + DEPTH) * (KS * kRecordBytes), code_off, scale_off, zero_off,
+                                                      t0, true,
+                                                      read_ahead, magic);
+                rotate();
+            }
+        }
+        // drain
+#pragma unroll
+        for (int u = 0; u < DEPTH + kAhead; ++u) {   // at most DEPTH - 1 + kAhead full steps and a partial one
+            const int gi = i + u;
+            if (gi < steps) {   // uniform over the workgroup
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                __syncthreads();
+                if (gi + 2 < mine) copy_x(gi + 2, b_free);
+                if (gi < mine)
+                    compute_group_staged<MT, TW, false, SYM>(a, qw[u % DEPTH], w[u % DEPTH], acc, recs, (uint32_t)(gi + DEPTH) * (KS * kRecordBytes),
+                                                           code_off, scale_off, zero_off, t0, gi + DEPTH < mine,
+                                                           read_ahead, magic);
+                rotate();
+            }
+        }
+    } else {
+        u32x4 w[DEPTH][TW];
+        QuantWords qw[DEPTH];
+        u32x4 xreg[MT];
+        u32x4 a[MT][4];
+        auto load_x = [&](int i) {
+            const global_bytes xb = uniform_ptr(xbase + (size_t)i * (KS * kGroup * sizeof(_Float16)));
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) xreg[mt] = load_global<u32x4>(xb + xoff[mt]);
+        };
+        auto park_x = [&](int buf) {
+#pragma unroll
+            for (int i = 0; i < MT; ++i) xa[buf * kBufQuads + (kset * MT * 4 + colq * MT + i) * 64 + lane] = xreg[i];
+        };
+        auto fetch_a = [&](int buf) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    a[mt][j] = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const uint8_t *>(xa + buf * kBufQuads + kset * MT * 4 * 64) +
+                                                               (mt * 2 + (j >> 1)) * 2048 + xfrag[j & 1]);
+        };
+        auto rec_of = [&](int i) { return recw + (size_t)i * (KS * kRecordBytes); };
 
 #pragma unroll
-    for (int d = 0; d < DEPTH; ++d)
-        if (d < mine) {
-            const uint8_t *rec = rec_of(d);
-            qw[d].s = *reinterpret_cast<const u32x4 *>(rec + kScalesOff + c * 16);
-            if constexpr (SYM) qw[d].z = kSymZeros;
-            else qw[d].z = *reinterpret_cast<const uint32_t *>(rec + kZerosOff + c * 4);
+        for (int d = 0; d < DEPTH; ++d)
+            if (d < mine) {
+                const uint8_t *rec = rec_of(d);
+                qw[d].s = *reinterpret_cast<const u32x4 *>(rec + kScalesOff + c * 16);
+                if constexpr (SYM) qw[d].z = kSymZeros;
+                else qw[d].z = *reinterpret_cast<const uint32_t *>(rec + kZerosOff + c * 4);
 #pragma unroll
-            for (int t = 0; t < TW; ++t) w[d][t] = load_tile(rec, t0 + t, lane);
-        }
-    if (mine > 0) {
-        load_x(0);
-        park_x(0);
-    }
-    int i = 0;
-    // steady state: every wavefront has a group in this step and DEPTH steps further on
-    for (; i + 2 * DEPTH <= full; i += DEPTH) {
-#pragma unroll
-        for (int u = 0; u < DEPTH; ++u) {
-            const int gi = i + u;
-            __syncthreads();   // x tiles of step gi are parked; nobody still reads the other buffer
-            load_x(gi + 1);
-            fetch_a(gi & 1);
-            __builtin_amdgcn_sched_barrier(0);
-            compute_group_lean<MT, TW, true, SYM>(a, qw[u], w[u], acc, rec_of(gi + DEPTH), true, t0, c, lane, magic);
-            park_x((gi & 1) ^ 1);
-        }
-    }
-    // drain
-#pragma unroll
-    for (int u = 0; u < 2 * DEPTH; ++u) {
-        const int gi = i + u;
-        if (gi < steps) {   // uniform over the workgroup
-            __syncthreads();
-            const bool more = gi + 1 < mine;
-            if (more) load_x(gi + 1);
-            if (gi < mine) {
-                fetch_a(gi & 1);
-                compute_group_lean<MT, TW, false, SYM>(a, qw[u % DEPTH], w[u % DEPTH], acc, rec_of(gi + DEPTH),
-                                                  gi + DEPTH < mine, t0, c, lane, magic);
+                for (int t = 0; t < TW; ++t) w[d][t] = load_tile(rec, t0 + t, lane);
             }
-            if (more) park_x((gi & 1) ^ 1);
+        if (mine > 0) {
+            load_x(0);
+            park_x(0);
+        }
+        int i = 0;
+        // steady state: every wavefront has a group in this step and DEPTH steps further on
+        for (; i + 2 * DEPTH <= full; i += DEPTH) {
+#pragma unroll
+            for (int u = 0; u < DEPTH; ++u) {
+                const int gi = i + u;
+                __syncthreads();   // x tiles of step gi are parked; nobody still reads the other buffer
+                load_x(gi + 1);
+                fetch_a(gi & 1);
+                __builtin_amdgcn_sched_barrier(0);
+                compute_group_lean<MT, TW, true, SYM>(a, qw[u], w[u], acc, rec_of(gi + DEPTH), true, t0, c, lane, magic);
+                park_x((gi & 1) ^ 1);
+            }
+        }
+        // drain
+#pragma unroll
+        for (int u = 0; u < 2 * DEPTH; ++u) {
+            const int gi = i + u;
+            if (gi < steps) {   // uniform over the workgroup
+                __syncthreads();
+                const bool more = gi + 1 < mine;
+                if (more) load_x(gi + 1);
+                if (gi < mine) {
+                    fetch_a(gi & 1);
+                    compute_group_lean<MT, TW, false, SYM>(a, qw[u % DEPTH], w[u % DEPTH], acc, rec_of(gi + DEPTH),
+                                                      gi + DEPTH < mine, t0, c, lane, magic);
+                }
+                if (more) park_x((gi & 1) ^ 1);
+            }
         }
     }
 
@@ -1598,7 +1797,8 @@ static int launch_cs_sym(const void *x, const void *packed, const Out &y, int M,
                          void *workspace, hipStream_t stream)
 {
     static bool lds_ok = false;
-    const size_t lds_bytes = (size_t)KS * TW * MT * 4096;   // 4*KS wavefronts' results; the x tiles (KS * MT * 8 KB) fit inside
+    // 4*KS wavefronts' results, or the buffers of x tiles (KS * MT * 4 KB each): three staged, two otherwise
+    const size_t lds_bytes = (size_t)KS * (staged_steps(TW, DEPTH) && TW < 3 ? 3 : TW) * MT * 4096;
     if (lds_bytes > 160 * 1024) return W4A16_EUNSUP;
     if (!lds_ok && lds_bytes > 48 * 1024) {
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_cs_kernel<MT, TW, KS, DEPTH, SYM>),
