@@ -94,18 +94,6 @@ __device__ __forceinline__ T load_global(global_bytes p)
     return *(const __attribute__((address_space(1))) T *)p;
 }
 
-// A wavefront-uniform stretch of memory behind a buffer descriptor: loads address it with a 32-bit lane offset plus a
-// scalar offset, so a moving base costs scalar arithmetic only and no 64-bit lane address occupies registers.
-typedef __amdgpu_buffer_rsrc_t Stretch;
-constexpr int kStreamed = 2;   // cache policy nt: read once
-__device__ __forceinline__ Stretch stretch(const void *base, uint32_t bytes)
-{
-    const uint64_t v = reinterpret_cast<uint64_t>(base);
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>(((uint64_t)hi << 32) | lo), 0, (int)bytes, 0x00020000);
-}
-
 // Symmetric weights (paper section 2.2: GPTQ quantises symmetrically, so every zero-point is the mid-code 8):
 // kernels instantiated with SYM never read the zero-points and use the constants below instead.
 constexpr uint32_t kSymZeros = 0x88888888u;      // the zero-point word such a weight holds
@@ -1007,8 +995,6 @@ __global__ __launch_bounds__(256, ((MT == 1 || (MT * TW <= 12 && !(MT == 3 && TW
     }
 }
 
-// One group with all TW tiles advancing through the four k steps together: an x fragment is read from LDS once per group
-// and lives for one step, so the registers it would hold for the whole group carry a second group of codes instead.
 // One quantisation group for this wavefront's TW column tiles, tile after tile with no software
 // pipelining: few live registers, so that several wavefronts share a SIMD and the hardware overlaps
 // one wavefront's code expansion (vector ALU) with another's matrix instructions.  The code
@@ -1136,7 +1122,7 @@ __device__ __forceinline__ void compute_group_staged(u32x4 (&a)[kFragRing][MT], 
                 for (int mt = 0; mt < MT; ++mt) a[st % kFragRing][mt] = read_a(st + kFragRing >= 4, mt, (st + kFragRing) % 4);
             }
             if (st == 3 && (ALWAYS || refill))
-                w[t] = __builtin_amdgcn_raw_buffer_load_b128(recs, code_off + (uint32_t)(t * 1024), rec, kStreamed);
+                w[t] = stream_quad(recs, code_off + (uint32_t)(t * 1024), rec);
 #pragma unroll
             for (int i = 0; i < MT; ++i) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                        // MFMA
@@ -1241,8 +1227,7 @@ __device__ __forceinline__ void cs_segment(const _Float16 *__restrict__ x, const
             const uint32_t from = (uint32_t)i * (KS * kGroup * sizeof(_Float16));
 #pragma unroll
             for (int blk = 0; blk < MT; ++blk)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(xs, (__attribute__((address_space(3))) void *)(xa + buf * kBufQuads + (kset * MT * 4 + colq * MT + blk) * 64),
-                                                         16, xoff[blk], from, 0, 0);
+                quad_to_lds(xs, xa + buf * kBufQuads + (kset * MT * 4 + colq * MT + blk) * 64, xoff[blk], from);
         };
         constexpr int kStepLoads = TW + 1 + (SYM ? 0 : 1);   // code, scale and zero-point loads of a step
         if (mine > 0) copy_x(0, 0);
@@ -1254,7 +1239,7 @@ __device__ __forceinline__ void cs_segment(const _Float16 *__restrict__ x, const
                 load_quant<TW, SYM>(qw[d], recs, rec, scale_off, zero_off);
 #pragma unroll
                 for (int t = 0; t < TW; ++t)
-                    w[d][t] = __builtin_amdgcn_raw_buffer_load_b128(recs, code_off + (uint32_t)(t * 1024), rec, kStreamed);
+                    w[d][t] = stream_quad(recs, code_off + (uint32_t)(t * 1024), rec);
             }
         if (mine >= DEPTH) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(DEPTH * kStepLoads) : "memory");   // the x tiles, not the codes
         else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");

@@ -2,6 +2,7 @@
 // vocabulary-sized weight, HBM-bound), the log-softmax of its logits and their top-k.  Contract in
 // include/w4a16.h.
 #include "internal.h"
+#include "devscope.h"
 
 namespace w4 {
 
@@ -117,6 +118,150 @@ __global__ __launch_bounds__(256) void lm_head_logits_kernel(const _Float16 *__r
             }
         }
     }
+    // lane (r, c) holds the logits of tokens 16 tile + 4 r .. + 3 for hidden-state row 16 mt + c
+#pragma unroll
+    for (int t = 0; t < TWL; ++t)
+#pragma unroll
+        for (int mt = 0; mt < MTL; ++mt) {
+            const int v0 = (tile0 + t) * 16 + 4 * r, row = mt * 16 + c;
+            if (row < M && tile0 + t < tiles) {
+                float *dst = logits + (size_t)row * V + v0;
+                if ((V & 3) == 0 && v0 + 3 < V) {
+                    *reinterpret_cast<float4v *>(dst) = acc[t][mt];
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (v0 + i < V) dst[i] = acc[t][mt][i];
+                }
+            }
+        }
+}
+
+// Logits of more than 16 rows.  There the x fragments, not the weights, filled the load path of the kernel above: every
+// wavefront fetched its own (sixteen rows x 64 bytes a load, the costliest pattern for a compute unit's address path,
+// as many loads as for the weights).  Here the NW wavefronts of a workgroup walk k together on TWL tiles each and
+// share the x tile of a macro step through LDS: whole cache lines, global -> LDS directly, two steps ahead into three
+// buffers, one barrier per step.  The tile is kept as MTL * 4 blocks of 1 KB, block (mt, jp, h) = rows 16 mt + 8 h .. + 7
+// times the 128 bytes of blocks 2 jp and 2 jp + 1 of the step; the eight 16-byte chunks of a row sit at
+// chunk ^ (4 h + row / 2), which spreads a fragment read over all LDS banks.  Workgroups start their k walk at
+// different steps, as above.  What bounds it is the weight stream: V = 128256, 60 rows, K = 8192: 475 -> 330 us for the whole
+// call (6.6 TB/s of weights in this kernel), K = 4096: 249 -> 184; 24 rows, K = 8192: 359 -> 330, K = 4096: 185 -> 175.
+constexpr int kLmSharedMaxK = 1 << 20;   // its descriptors and offsets are 32-bit (M * K * 2 and TWL * K * 32 bytes); wider heads take the kernel above
+template <int MTL, int NW, int TWL, int DEPTH>
+__global__ __launch_bounds__(64 * NW, 2) void lm_head_logits_shared_kernel(const _Float16 *__restrict__ x,
+                                                                                    const u32x4 *__restrict__ packed,
+                                                                                    float *__restrict__ logits, int M, int V,
+                                                                                    int K, int tiles)
+{
+    constexpr int kTileQuads = MTL * 4 * 64;   // 16-byte pieces of one step's x tile
+    constexpr int kCopies = (MTL * 4 + NW - 1) / NW;
+    __shared__ u32x4 xa[3][kTileQuads];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r = lane >> 4, c = lane & 15;
+    const int tile0 = (blockIdx.x * NW + wave) * TWL;
+    const int steps = K / kLmStepK;
+    // a tile past the end repeats the last one; its logits are not stored
+    const uint32_t tile_bytes = (uint32_t)K * 32;
+    const int first = min(tile0, tiles - 1);
+    const Stretch ws = stretch(packed + (size_t)first * (K / 32) * 64, (uint32_t)TWL * tile_bytes);
+    uint32_t tile_off[TWL];
+#pragma unroll
+    for (int t = 0; t < TWL; ++t) tile_off[t] = (uint32_t)(min(tile0 + t, tiles - 1) - first) * tile_bytes;
+    const Stretch xs = stretch(x, (uint32_t)M * (uint32_t)K * 2);
+    uint32_t xoff[kCopies];
+#pragma unroll
+    for (int i = 0; i < kCopies; ++i) {
+        const int blk = wave + NW * i;
+        const int mt = blk >> 2, jp = (blk >> 1) & 1, h = blk & 1, row8 = lane >> 3;
+        const int chunk = (lane & 7) ^ (4 * h + (row8 >> 1));
+        const int row = min(mt * 16 + h * 8 + row8, M - 1);   // rows >= M repeat row M - 1; their products are never stored
+        xoff[i] = ((uint32_t)row * (uint32_t)K + (uint32_t)(jp * 64 + chunk * 8)) * 2;
+    }
+    const int rot = (int)(blockIdx.x % (unsigned)steps);
+    auto wrapped = [&](int s) {   // uniform: the step of k that step s of the walk takes, s < 2 * steps - rot
+        const int k = s + rot;
+        return (uint32_t)(k >= steps ? k - steps : k);
+    };
+    auto copy_x = [&](int s, int buf) {
+        const uint32_t from = wrapped(s) * (kLmStepK * 2);
+#pragma unroll
+        for (int i = 0; i < kCopies; ++i)
+            if (wave + NW * i < MTL * 4)   // uniform
+                quad_to_lds(xs, xa[buf] + (wave + NW * i) * 64, xoff[i], from);
+    };
+    u32x4 w[DEPTH][TWL][4];
+    const uint32_t lane_off = (uint32_t)lane * 16;
+    auto load_w = [&](int s, int slot, int t, int j) {
+        w[slot][t][j] = stream_quad(ws, lane_off + (uint32_t)j * 1024, tile_off[t] + wrapped(s) * 4096);
+    };
+    // fragment (mt, j): lane (r, c) reads row 16 mt + c, elements 32 j + 8 r .. + 7 of the step
+    uint32_t xfrag[2];
+    {
+        const int h = c >> 3, row8 = c & 7, sw = 4 * h + (row8 >> 1);
+        xfrag[0] = (uint32_t)(h * 64 + row8 * 8 + (r ^ sw));
+        xfrag[1] = (uint32_t)(h * 64 + row8 * 8 + ((4 + r) ^ sw));
+    }
+    float4v acc[TWL][MTL];
+#pragma unroll
+    for (int t = 0; t < TWL; ++t)
+#pragma unroll
+        for (int mt = 0; mt < MTL; ++mt) acc[t][mt] = (float4v){0.f, 0.f, 0.f, 0.f};
+    copy_x(0, 0);
+    if (steps > 1) copy_x(1, 1);
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d)
+        if (d < steps)   // uniform
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int t = 0; t < TWL; ++t) load_w(d, d, t, j);
+    int b_now = 0, b_next = 1, b_free = 2;   // tile s + 2 goes where tile s - 1 was: everybody has read that by the barrier of step s
+    auto step = [&](int s, int slot, bool more_w, bool more_x) {
+        __syncthreads();
+        if (more_x) copy_x(s + 2, b_free);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            u32x4 xf[MTL];
+#pragma unroll
+            for (int mt = 0; mt < MTL; ++mt) xf[mt] = xa[b_now][mt * 256 + (j >> 1) * 128 + xfrag[j & 1]];
+#pragma unroll
+            for (int t = 0; t < TWL; ++t) {
+#pragma unroll
+                for (int mt = 0; mt < MTL; ++mt)
+                    acc[t][mt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8v, w[slot][t][j]), __builtin_bit_cast(half8v, xf[mt]),
+                                                                        acc[t][mt], 0, 0, 0);
+                if (more_w) load_w(s + DEPTH, slot, t, j);
+            }
+        }
+        const int b = b_now;
+        b_now = b_next;
+        b_next = b_free;
+        b_free = b;
+    };
+    // A step's barrier says that its x tile is complete, so every wavefront first waits for its own share of it.  Newer
+    // than that share are, from the third step on, the weights requested in the two steps before and one x share; in
+    // the first two steps at least the DEPTH steps of weights the walk starts with.
+    constexpr int kStepLoads = 4 * TWL, kNewer = 2 * kStepLoads + MTL * 4 / NW;
+    static_assert(kNewer < 64 && DEPTH * kStepLoads < 64, "the wait counter has six bits");
+    constexpr int kAhead = DEPTH > 2 ? DEPTH : 2;   // how far the requests of a step reach
+    int s = 0;
+    if (steps >= DEPTH) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(DEPTH * kStepLoads) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma clang loop unroll(disable)
+    for (; s + DEPTH - 1 + kAhead < steps; s += DEPTH) {
+#pragma unroll
+        for (int u = 0; u < DEPTH; ++u) {
+            if (s + u > 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kNewer) : "memory");   // uniform
+            step(s + u, u, true, true);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < DEPTH - 1 + kAhead; ++u)
+        if (s + u < steps) {   // uniform
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            step(s + u, u % DEPTH, s + u + DEPTH < steps, s + u + 2 < steps);
+        }
     // lane (r, c) holds the logits of tokens 16 tile + 4 r .. + 3 for hidden-state row 16 mt + c
 #pragma unroll
     for (int t = 0; t < TWL; ++t)
@@ -351,6 +496,42 @@ __global__ __launch_bounds__(kLmThreads) void lm_head_merge_kernel(const float *
     }
 }
 
+// Which logits kernel, how many wavefronts share a workgroup and how many vocabulary tiles each takes.
+// Up to 16 rows every wavefront fetches its own x fragments from L2 and a fragment serves all its tiles, which matters once
+// the hidden-state rows differ (K = 4096: M = 16 240 -> 194 us with two); a single row is a broadcast and runs best with one.
+// More rows share x through LDS.  A workgroup then takes T = 4, 8, 16 or 32 tiles and a compute unit works on about one at a
+// time, so the call takes about rounds x T: the T with the least of it, where a smaller T also shares x less
+// (V = 128256, where 8, 16 and 32 tie at a multiple of 256 workgroups: 204 / 194 / 175 us at 24 rows, K = 4096).  With T by this
+// rule against four tiles per wavefront throughout: V = 4000 101 -> 32 us, 32000 110 -> 62, 50000 117 -> 82 (60 rows, K = 4096).
+// Short walks amortise the fill of the pipeline over too few steps: up to K = 1024 at most eight tiles (V = 128256, 60 rows:
+// 85 us with 32, 72 with 8, 73 in the kernel above), and with fewer rows the kernel above, whose wavefronts need no barrier, stays
+// ahead beyond one such round (V = 128256: K = 1024 55 against 62 us at 24 rows, 62 against 68 at 40; K = 2048 94 against 95 at
+// 24).  It also does where 16 tiles fill the chip and K is a power of two, so that all tiles of a workgroup ask the same memory
+// channels at any moment (V = 64000: K = 4096 91 against 99 us at 24 rows, K = 2048 57 against 72 at 40 and 68 against 70 at 60;
+// but K = 3840 89 against 84 at 24 rows, and K = 4096 104 against 100 at 40).
+struct LmPlan { bool shared; int nw, twl; };
+static LmPlan lm_plan(int M, int tiles, int K)
+{
+    const int knob = params().lm_tiles;
+    if (knob > 0 && knob != 1 && knob != 2 && !(knob == 4 && M > 16)) return {false, 0, 0};   // not compiled
+    if (M <= 16) return {false, 4, knob > 0 ? knob : (M <= 4 ? 1 : 2)};
+    if (K > kLmSharedMaxK) return {false, 4, 4};
+    if (knob > 0) return {true, 8, knob};
+    static const struct { int t, penalty; } kChoices[] = {{32, 100}, {16, 110}, {8, 117}, {4, 117}};   // penalty in percent
+    const int most = K <= 1024 ? 8 : 32;
+    int best_t = 0;
+    long long best_cost = 0;
+    for (const auto &ch : kChoices) {
+        if (ch.t > most) continue;
+        const long long rounds = ((tiles + ch.t - 1) / ch.t + 255) / 256, cost = rounds * ch.t * ch.penalty;
+        if (best_t == 0 || cost < best_cost) best_t = ch.t, best_cost = cost;
+    }
+    const bool one_channel = (K & (K - 1)) == 0 && best_t == 16 && (M <= 32 || K <= 2048);
+    const bool short_walk = tiles > 2048 && ((M <= 32 && K <= 2048) || (M <= 48 && K <= 1024));
+    if (one_channel || short_walk) return {false, 4, 4};
+    return best_t == 4 ? LmPlan{true, 4, 1} : LmPlan{true, 8, best_t / 8};
+}
+
 static int lm_chunks(int V) { return (V + kLmChunk - 1) / kLmChunk; }
 
 static int check_lm_head(int M, int V, int K, int top_k)
@@ -415,16 +596,22 @@ int lm_head_topk(const void *x, const void *packed, int M, int V, int K, int top
         lds_ok = true;
     }
     hipStream_t s = (hipStream_t)stream;
-    // tiles per wavefront: every x fragment fetched from L2 serves all of them, which matters once the
-    // hidden-state rows differ (K = 4096: M = 16 240 -> 194 us with two, M = 60 567 -> 278 us with four); a
-    // single row is a broadcast and runs best with one.  More than 16 rows: up to four row tiles and a
-    // ring of two macro steps (registers).
     const int mtl = (M + 15) / 16;
-    const int twl = params().lm_tiles > 0 ? params().lm_tiles : (M <= 4 ? 1 : M <= 16 ? 2 : 4);
-    if (twl != 1 && twl != 2 && !(twl == 4 && mtl >= 2)) return W4A16_EUNSUP;
-    const int depth = mtl > 1 ? 2 : kLmDepth;
-    const bool even = (K / kLmStepK) % depth == 0;
-    const dim3 grid((unsigned)((tiles + 4 * twl - 1) / (4 * twl)));
+    const LmPlan plan = lm_plan(M, tiles, K);
+    if (plan.nw == 0) return W4A16_EUNSUP;
+    const dim3 grid((unsigned)((tiles + plan.nw * plan.twl - 1) / (plan.nw * plan.twl)));
+    if (plan.shared) {
+#define W4_LM_SHARED(MTL_, NW_, TWL_, D_)                                                                               \
+    if (mtl == MTL_ && plan.nw == NW_ && plan.twl == TWL_)                                                              \
+        hipLaunchKernelGGL((lm_head_logits_shared_kernel<MTL_, NW_, TWL_, D_>), grid, dim3(64 * NW_), 0, s,             \
+                           (const _Float16 *)x, (const u32x4 *)packed, logits, M, V, K, tiles)
+        W4_LM_SHARED(2, 4, 1, 4); W4_LM_SHARED(2, 8, 1, 4); W4_LM_SHARED(2, 8, 2, 2); W4_LM_SHARED(2, 8, 4, 2);
+        W4_LM_SHARED(3, 4, 1, 4); W4_LM_SHARED(3, 8, 1, 4); W4_LM_SHARED(3, 8, 2, 2); W4_LM_SHARED(3, 8, 4, 2);
+        W4_LM_SHARED(4, 4, 1, 4); W4_LM_SHARED(4, 8, 1, 4); W4_LM_SHARED(4, 8, 2, 2); W4_LM_SHARED(4, 8, 4, 2);
+#undef W4_LM_SHARED
+    } else {
+        const int depth = mtl > 1 ? 2 : kLmDepth;
+        const bool even = (K / kLmStepK) % depth == 0;
 #define W4_LM_LAUNCH(TWL_, MTL_, DEPTH_)                                                                                \
     do {                                                                                                                \
         if (even)                                                                                                       \
@@ -434,18 +621,13 @@ int lm_head_topk(const void *x, const void *packed, int M, int V, int K, int top
             hipLaunchKernelGGL((lm_head_logits_kernel<false, TWL_, MTL_, DEPTH_>), grid, dim3(256), 0, s,               \
                                (const _Float16 *)x, (const u32x4 *)packed, logits, M, V, K, tiles);                     \
     } while (0)
-    if (mtl == 1 && twl == 1) W4_LM_LAUNCH(1, 1, kLmDepth);
-    else if (mtl == 1) W4_LM_LAUNCH(2, 1, kLmDepth);
-    else if (mtl == 2 && twl == 1) W4_LM_LAUNCH(1, 2, 2);
-    else if (mtl == 2 && twl == 2) W4_LM_LAUNCH(2, 2, 2);
-    else if (mtl == 2) W4_LM_LAUNCH(4, 2, 2);
-    else if (mtl == 3 && twl == 1) W4_LM_LAUNCH(1, 3, 2);
-    else if (mtl == 3 && twl == 2) W4_LM_LAUNCH(2, 3, 2);
-    else if (mtl == 3) W4_LM_LAUNCH(4, 3, 2);
-    else if (twl == 1) W4_LM_LAUNCH(1, 4, 2);
-    else if (twl == 2) W4_LM_LAUNCH(2, 4, 2);
-    else W4_LM_LAUNCH(4, 4, 2);
+        if (mtl == 1 && plan.twl == 1) W4_LM_LAUNCH(1, 1, kLmDepth);
+        else if (mtl == 1) W4_LM_LAUNCH(2, 1, kLmDepth);
+        else if (mtl == 2) W4_LM_LAUNCH(4, 2, 2);
+        else if (mtl == 3) W4_LM_LAUNCH(4, 3, 2);
+        else W4_LM_LAUNCH(4, 4, 2);
 #undef W4_LM_LAUNCH
+    }
     hipLaunchKernelGGL(lm_head_chunk_kernel, dim3((unsigned)((chunks + kLmThreads / 64 - 1) / (kLmThreads / 64)), (unsigned)M), dim3(kLmThreads), 0, s,
                        (const float *)logits, V, top_k, chunks, chunk_max, chunk_sum, cand_val, cand_idx);
     hipLaunchKernelGGL(lm_head_merge_kernel, dim3((unsigned)M), dim3(kLmThreads), (size_t)chunks * top_k * 8, s, (const float *)chunk_max,

@@ -83,6 +83,21 @@ def test_lm_head_parity(M, K, V, top_k):
     print(f"    logits max abs err {e:.3g}", flush=True)
 
 
+@pytest.mark.parametrize("M,K,V", [(17, 128, 1001), (33, 256, 70), (64, 384, 5003), (32, 512, 17000), (48, 640, 33001),
+                                   (64, 128, 66000), (17, 2048, 40000), (64, 1152, 66000)])
+def test_lm_head_shared_rows(M, K, V):
+    """more than 16 rows share x through LDS: walks shorter than the pipeline (1 to 5 steps), tiles that do not fill the
+    last workgroup, vocabularies that are no multiple of 4 (scalar stores), both kernels and every number of tiles per
+    workgroup of the size rule (fp32 sums: the tolerance of check())"""
+    x, W = I.make_lm_head(9900 + M + K + V, M, K, V)
+    try:
+        for tiles_per_wave in (0, 1, 2, 4):
+            B.w4a16_set_param("lm_tiles", tiles_per_wave)
+            check(x, W, 3, f"M={M} K={K} V={V} tiles per wavefront {tiles_per_wave}")
+    finally:
+        B.w4a16_set_param("lm_tiles", 0)
+
+
 def test_lm_head_full_vocabulary():
     """the benchmark's configuration: Llama-3 vocabulary, hidden size 4096, ten beams, top 10"""
     M, K, V, top_k = 10, 4096, 128256, 10
