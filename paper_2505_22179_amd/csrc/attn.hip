@@ -28,7 +28,8 @@ constexpr int kRowsPad = 64;
 // LDS of a workgroup of 4 * RG wavefronts with RT row tiles each: one exchange slot per wavefront
 // (8 * RT accumulator quads + 2 * RT state values per lane); the slots cover the 8 KB V tiles
 constexpr int attn_lds_bytes(int rt, int rg) { return 4 * rg * (8 * rt * 4 + 2 * rt) * 64 * 4; }
-constexpr int kMaxSplits = 16;   // key ranges per head (the merge keeps one value per range in registers)
+constexpr int kMaxSplits = 16;   // key ranges per query head that a workspace is sized for
+constexpr int kMaxRanges = 32;   // key ranges per row tile (the merge keeps one value per range in registers)
 
 // v_max3_f32 and v_max_f32 as they stand: fmaxf chains are compiled with a canonicalising v_max x, x per
 // operand, which doubles the instruction count of a row maximum; no score here is a NaN.
@@ -64,14 +65,44 @@ __device__ __forceinline__ float row_group_max(float v)
 
 constexpr float kLowest = -1.0e30f;   // "no key seen yet": finite, so differences of two of them are 0, not NaN
 
+// The rows of a row tile.  The group * M (head, query row) pairs that share a KV head, head by head, are cut into
+// tiles_per_kv tiles of tile_rows rows (the last may have fewer): M for one query head per tile, d * M for d heads, or any
+// other number up to 64, where a tile ends inside a head.  Row rho of tile `unit` is pair first + rho of its KV head.
+struct RowTile {
+    int kvh, group, M, Hq;
+    int first;    // pair of tile row 0
+    int rows;     // valid rows
+    int index;    // number of the tile in its KV head
+    bool whole;   // one query head per tile: no division
+    __device__ __forceinline__ RowTile(int unit, int M_, int Hq_, int group_, int tile_rows, int tiles_per_kv)
+    {
+        M = M_;
+        Hq = Hq_;
+        group = group_;
+        kvh = unit / tiles_per_kv;
+        index = unit - kvh * tiles_per_kv;
+        first = index * tile_rows;
+        rows = min(tile_rows, group * M - first);
+        whole = tile_rows == M;
+    }
+    // query row and head of a tile row; rows beyond the last repeat it (and are never stored)
+    __device__ __forceinline__ void locate(int rho, int &qrow, int &head) const
+    {
+        const int pair = first + min(rho, rows - 1);
+        const int j = whole ? index : pair / M;
+        qrow = pair - j * M;
+        head = kvh * group + j;
+    }
+};
+
 // Merge of the key ranges of one tile by the workgroup that finished last (fused mode): NS = compiled
 // upper bound of the number of ranges, IT = items a thread handles at once (all their loads are issued
 // together).  Loads are device-scope: other workgroups, on other XCDs, wrote the partials in this kernel.
 template <int NS, int IT>
 __device__ __forceinline__ void merge_ranges(PartialBuffer unit_o, PartialBuffer unit_ml, _Float16 *__restrict__ out,
-                                             int tid, int threads, int items, int M, int Hq, int nsplit, int rep,
-                                             int unit)
+                                             int tid, int threads, const RowTile &tile, int nsplit)
 {
+    const int items = tile.rows * (kHeadDim / 4);   // one item = four consecutive outputs of a tile row
     const float NEG_INF = -__builtin_inff();
     for (int base = tid; base < items; base += threads * IT) {
         float ms[IT][NS], ls[IT][NS];
@@ -109,14 +140,22 @@ __device__ __forceinline__ void merge_ranges(PartialBuffer unit_o, PartialBuffer
                 num += wgt * os[it][s];
             }
             const float inv = 1.f / den;
-            // tile row -> (query row, head): see tree_attn_kernel
-            const int j = rep ? trow / M : 0;
-            const int qrow = trow - j * M, h = rep ? unit * rep + j : unit;
+            int qrow, h;
+            tile.locate(trow, qrow, h);
             typedef _Float16 half4v __attribute__((ext_vector_type(4)));
             half4v hv = {(_Float16)(num[0] * inv), (_Float16)(num[1] * inv), (_Float16)(num[2] * inv), (_Float16)(num[3] * inv)};
-            *reinterpret_cast<half4v *>(out + ((size_t)qrow * Hq + h) * kHeadDim + d4 * 4) = hv;
+            *reinterpret_cast<half4v *>(out + ((size_t)qrow * tile.Hq + h) * kHeadDim + d4 * 4) = hv;
         }
     }
+}
+
+__device__ __forceinline__ void merge_tile(PartialBuffer unit_o, PartialBuffer unit_ml, _Float16 *__restrict__ out, int tid,
+                                           int threads, const RowTile &tile, int nsplit)
+{
+    if (nsplit <= 4) merge_ranges<4, 4>(unit_o, unit_ml, out, tid, threads, tile, nsplit);
+    else if (nsplit <= 8) merge_ranges<8, 2>(unit_o, unit_ml, out, tid, threads, tile, nsplit);
+    else if (nsplit <= 16) merge_ranges<16, 1>(unit_o, unit_ml, out, tid, threads, tile, nsplit);
+    else merge_ranges<kMaxRanges, 1>(unit_o, unit_ml, out, tid, threads, tile, nsplit);
 }
 
 // One workgroup = one 64-row tile (a query head, or the heads of a KV group) x one contiguous range
@@ -146,13 +185,13 @@ __global__ __launch_bounds__(256 * RG) void tree_attn_kernel(
     const _Float16 *__restrict__ q, const _Float16 *__restrict__ k, const _Float16 *__restrict__ v,
     const uint8_t *__restrict__ mask, _Float16 *__restrict__ out, float *__restrict__ part_o,
     float *__restrict__ part_ml, uint32_t *__restrict__ tickets, int M, int P, int Hq, int Hkv,
-    float scale_log2e, int nsplit, int bq, int brem, int rep, int fused)
+    int group, float scale_log2e, int nsplit, int bq, int brem, int tile_rows, int tiles_per_kv, int fused)
 {
     extern __shared__ float4v smem4[];
     // one batch of scalar loads instead of three dependent ones before the first K/V request goes out
     const unsigned grid = gridDim.x;
-    fetch_arguments_together(q, k, v, mask, out, part_o, part_ml, tickets, M, P, Hq, Hkv, scale_log2e, nsplit, bq, brem, rep,
-                             fused, grid);
+    fetch_arguments_together(q, k, v, mask, out, part_o, part_ml, tickets, M, P, Hq, Hkv, group, scale_log2e, nsplit, bq, brem, tile_rows,
+                             tiles_per_kv, fused, grid);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kw = wave & 3, rg = wave >> 2;   // key wavefront inside the row group, row group
@@ -162,12 +201,10 @@ __global__ __launch_bounds__(256 * RG) void tree_attn_kernel(
     // its K/V rows are fetched into one L2 instead of all eight.
     int lid = blockIdx.x;
     if ((grid & 7) == 0) lid = (blockIdx.x & 7) * (grid >> 3) + (blockIdx.x >> 3);
-    // A workgroup's row tile holds the M rows of one query head (rep == 0), or -- when they fit -- the M rows
-    // of rep consecutive query heads that share a KV head (tile row j * M + m = head unit * rep + j, query
-    // row m): few-row calls then read K and V once per rep heads instead of once per head.
+    // Tiles that hold the rows of several query heads of a KV group read K and V once for all of them.
     const int unit = lid / nsplit, sp = lid % nsplit;
-    const int kvh = (rep ? unit * rep : unit) / (Hq / Hkv);
-    const int R = rep ? M * rep : M;   // valid rows of the tile
+    const RowTile tile(unit, M, Hq, group, tile_rows, tiles_per_kv);
+    const int kvh = tile.kvh, R = tile.rows;
     const int T = P + M;
     // key steps of this split: bq = nblk / nsplit each, the first brem = nblk % nsplit one more (host-computed)
     const int b0 = sp * bq + (sp < brem ? sp : brem), b1 = b0 + bq + (sp < brem ? 1 : 0);
@@ -175,12 +212,7 @@ __global__ __launch_bounds__(256 * RG) void tree_attn_kernel(
 
     int row[RT], head[RT];   // query row and head of tile row 16 (rg RT + rt) + c; tile rows >= R repeat row R-1 and are never stored
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-        const int rho = min((rg * RT + rt) * 16 + c, R - 1);
-        const int j = rep ? rho / M : 0;
-        row[rt] = rho - j * M;
-        head[rt] = rep ? unit * rep + j : unit;
-    }
+    for (int rt = 0; rt < RT; ++rt) tile.locate((rg * RT + rt) * 16 + c, row[rt], head[rt]);
     // Tree mask as one 64-bit word per query row (bit j = draft key j visible), built once by the
     // workgroups whose key range reaches the draft keys: a byte load per key inside the step loop
     // would put some thirty dependent memory round trips on the critical path of the last steps.
@@ -440,13 +472,7 @@ __global__ __launch_bounds__(256 * RG) void tree_attn_kernel(
     __syncthreads();
     if (ticket_sh != (uint32_t)(nsplit - 1)) return;
     if (tid == 0) __hip_atomic_store(&tickets[unit], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const int items = R * (kHeadDim / 4);   // one item = four consecutive outputs of a tile row
-    if (nsplit <= 4)
-        merge_ranges<4, 4>(unit_o, unit_ml, out, tid, 256 * RG, items, M, Hq, nsplit, rep, unit);
-    else if (nsplit <= 8)
-        merge_ranges<8, 2>(unit_o, unit_ml, out, tid, 256 * RG, items, M, Hq, nsplit, rep, unit);
-    else
-        merge_ranges<kMaxSplits, 1>(unit_o, unit_ml, out, tid, 256 * RG, items, M, Hq, nsplit, rep, unit);
+    merge_tile(unit_o, unit_ml, out, tid, 256 * RG, tile, nsplit);
 }
 
 // ---- Row tiles of 33..64 rows: K and V tiles shared through LDS -------------------------------------
@@ -519,13 +545,13 @@ __global__ __launch_bounds__(64 * kSharedWaves) void tree_attn_shared_kernel(
     const _Float16 *__restrict__ q, const _Float16 *__restrict__ k, const _Float16 *__restrict__ v,
     const uint8_t *__restrict__ mask, _Float16 *__restrict__ out, float *__restrict__ part_o,
     float *__restrict__ part_ml, uint32_t *__restrict__ tickets, int M, int P, int Hq, int Hkv,
-    float scale_log2e, int nsplit, int bq, int brem, int rep, int fused)
+    int group, float scale_log2e, int nsplit, int bq, int brem, int tile_rows, int tiles_per_kv, int fused)
 {
     extern __shared__ float4v smem4[];
     uint8_t *lds = reinterpret_cast<uint8_t *>(smem4);
     const unsigned grid = gridDim.x;
-    fetch_arguments_together(q, k, v, mask, out, part_o, part_ml, tickets, M, P, Hq, Hkv, scale_log2e, nsplit, bq, brem, rep,
-                             fused, grid);
+    fetch_arguments_together(q, k, v, mask, out, part_o, part_ml, tickets, M, P, Hq, Hkv, group, scale_log2e, nsplit, bq, brem, tile_rows,
+                             tiles_per_kv, fused, grid);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kw = wave >> 1, rh = wave & 1;   // key wavefront, row half
@@ -533,20 +559,18 @@ __global__ __launch_bounds__(64 * kSharedWaves) void tree_attn_shared_kernel(
     int lid = blockIdx.x;   // workgroups of one KV head on one XCD (see tree_attn_kernel)
     if ((grid & 7) == 0) lid = (blockIdx.x & 7) * (grid >> 3) + (blockIdx.x >> 3);
     const int unit = lid / nsplit, sp = lid % nsplit;
-    const int kvh = (rep ? unit * rep : unit) / (Hq / Hkv);
-    const int R = rep ? M * rep : M;   // valid rows of the tile
+    const RowTile tile(unit, M, Hq, group, tile_rows, tiles_per_kv);
+    const int kvh = tile.kvh, R = tile.rows;
     const int T = P + M;
     const int b0 = sp * bq + (sp < brem ? sp : brem), b1 = b0 + bq + (sp < brem ? 1 : 0);
     const int rounds = (b1 - b0 + 3) >> 2;
     const size_t kv_row_bytes = (size_t)Hkv * kHeadDim * 2;
 
-    // tile row -> its query row and the element offset of its (query row, head) in q and out; rows >= R repeat
-    // row R - 1 and are never stored
+    // tile row -> its query row and the element offset of its (query row, head) in q and out
     auto locate = [&](int rho, int &qrow) {
-        rho = min(rho, R - 1);
-        const int j = rep ? rho / M : 0;
-        qrow = rho - j * M;
-        return (uint32_t)(qrow * Hq + (rep ? unit * rep + j : unit)) * kHeadDim;
+        int head;
+        tile.locate(rho, qrow, head);
+        return (uint32_t)(qrow * Hq + head) * kHeadDim;
     };
     // tree mask of the draft keys, one 64-bit word per query row, in the workgroups that reach them:
     // wavefront w asks for the bytes of rows 8 w .. 8 w + 7 first (lane = column) and turns them into words
@@ -805,13 +829,7 @@ __global__ __launch_bounds__(64 * kSharedWaves) void tree_attn_shared_kernel(
     __syncthreads();
     if (ticket_sh != (uint32_t)(nsplit - 1)) return;
     if (tid == 0) __hip_atomic_store(&tickets[unit], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const int items = R * (kHeadDim / 4);
-    if (nsplit <= 4)
-        merge_ranges<4, 4>(unit_o, unit_ml, out, tid, 64 * kSharedWaves, items, M, Hq, nsplit, rep, unit);
-    else if (nsplit <= 8)
-        merge_ranges<8, 2>(unit_o, unit_ml, out, tid, 64 * kSharedWaves, items, M, Hq, nsplit, rep, unit);
-    else
-        merge_ranges<kMaxSplits, 1>(unit_o, unit_ml, out, tid, 64 * kSharedWaves, items, M, Hq, nsplit, rep, unit);
+    merge_tile(unit_o, unit_ml, out, tid, 64 * kSharedWaves, tile, nsplit);
 }
 
 // merge of the key ranges: one thread per four consecutive output elements, ranges in order;
@@ -819,16 +837,23 @@ __global__ __launch_bounds__(64 * kSharedWaves) void tree_attn_shared_kernel(
 template <int NS>
 __global__ __launch_bounds__(256) void tree_attn_merge_kernel(const float *__restrict__ part_o,
                                                               const float *__restrict__ part_ml,
-                                                              _Float16 *__restrict__ out, int M, int Hq, int nsplit,
-                                                              int rep)
+                                                              _Float16 *__restrict__ out, int M, int Hq, int group, int nsplit,
+                                                              int tile_rows, int tiles_per_kv)
 {
-    fetch_arguments_together(part_o, part_ml, out, M, Hq, nsplit, rep);
+    fetch_arguments_together(part_o, part_ml, out, M, Hq, group, nsplit, tile_rows, tiles_per_kv);
     const int idx = blockIdx.x * 256 + threadIdx.x;   // over M * Hq * 32 quads
     if (idx >= M * Hq * (kHeadDim / 4)) return;
     const int d4 = idx % (kHeadDim / 4), h = (idx / (kHeadDim / 4)) % Hq, qrow = idx / (kHeadDim / 4) / Hq;
     const float NEG_INF = -__builtin_inff();
-    // where the first kernel left this (row, head): tile `unit`, tile row `row` (see tree_attn_kernel)
-    const int unit = rep ? h / rep : h, row = rep ? (h % rep) * M + qrow : qrow;
+    // where the first kernel left this (row, head): tile `unit`, tile row `row` (see RowTile)
+    const int kvh = h / group, head = h - kvh * group;
+    int index = head, row = qrow;
+    if (tile_rows != M) {   // uniform
+        const int pair = head * M + qrow;
+        index = pair / tile_rows;
+        row = pair - index * tile_rows;
+    }
+    const int unit = kvh * tiles_per_kv + index;
     const float *hml = part_ml + (size_t)unit * nsplit * kRowsPad * 2;
     const float4v *ho = reinterpret_cast<const float4v *>(part_o + (size_t)unit * nsplit * kRowsPad * kHeadDim);
     float ms[NS], ls[NS];
@@ -915,7 +940,16 @@ __global__ __launch_bounds__(256) void tree_accept_kernel(const int32_t *__restr
     }
 }
 
-// Query heads per row tile (0 = one head per tile).  The heads of a KV group can share a tile, which reads K
+static int key_steps(int M, int P) { return (P + M + kKeyBlock - 1) / kKeyBlock; }
+
+// How a call is cut up: row tiles (RowTile), key ranges per tile, who merges the ranges.
+struct AttnPlan { int tile_rows, tiles_per_kv, ranges, fused; };
+static size_t partial_bytes_of(int units, int ranges)
+{
+    return (size_t)units * ranges * kRowsPad * (kHeadDim + 2) * sizeof(float);
+}
+
+// Query heads per row tile of the plain plan.  The heads of a KV group can share a tile, which reads K
 // and V once for all of them; fewer tiles, on the other hand, mean more key ranges per tile to fill the chip,
 // and every range costs a partial result that has to be merged.  Measured over M = 1 .. 32 with 64/8 and 32/8
 // heads (prefix 2048), the best point is about 32 tiles (eight key ranges each, merged by the last workgroup):
@@ -923,15 +957,15 @@ __global__ __launch_bounds__(256) void tree_accept_kernel(const int32_t *__restr
 // to 12.9 us for M = 1 .. 16, against 12.7 to 13.2 unpacked), none with 32 heads (10.0 to 12.6 us for
 // M = 1 .. 32, against 10.7 to 18.6 with two per tile).  Calls of so few rows that a whole group fits eight
 // tile rows pack the group (plain decoding: 9.9 against 10.3 us).
-static int attn_rep(int M, int Hq, int Hkv)
+static int heads_per_tile(int M, int Hq, int Hkv, int knob)
 {
-    const int group = Hq / Hkv, knob = params().attn_pack;
-    if (knob == 1 || group < 2) return 0;
+    const int group = Hq / Hkv;
+    if (knob == 1 || group < 2) return 1;
     if (knob >= 10) {   // 10 + d: exactly d heads per tile, where that is possible
         const int d = knob - 10;
-        return (d >= 2 && group % d == 0 && M * d <= kRowsPad) ? d : 0;
+        return (d >= 2 && group % d == 0 && M * d <= kRowsPad) ? d : 1;
     }
-    if (knob == 2) return M * group <= kRowsPad ? group : 0;
+    if (knob == 2) return M * group <= kRowsPad ? group : 1;
     if (M * group <= 8) return group;
     int best = 1;
     for (int d = 1; d <= group; ++d) {
@@ -939,16 +973,108 @@ static int attn_rep(int M, int Hq, int Hkv)
         best = d;
         if (Hq / d <= 32) break;
     }
-    return best >= 2 ? best : 0;
+    return best;
 }
 
-static int attn_splits(int M, int P, int units)
+// the whole group cut evenly into as few tiles as 64 rows allow; a tile may end inside a head
+static void even_tiles(int pairs, int &tile_rows, int &tiles_per_kv)
 {
-    int nblk = (P + M + kKeyBlock - 1) / kKeyBlock;
-    int want = params().attn_splits > 0 ? params().attn_splits : (256 + units - 1) / units;   // about one workgroup per compute unit
-    if (want > nblk) want = nblk;
-    if (want > kMaxSplits) want = kMaxSplits;
-    return want < 1 ? 1 : want;
+    const int n = (pairs + kRowsPad - 1) / kRowsPad;
+    tile_rows = (pairs + n - 1) / n;
+    tiles_per_kv = (pairs + tile_rows - 1) / tile_rows;
+}
+
+// The plain plan, and what the knobs make of it.  The key ranges of a tile are merged by the last of its workgroups to
+// finish, or by a second kernel.  Fused saves a launch and the wait for it, but one workgroup then reads all the partials
+// of its tile (rows x ranges x 512 B), which pays while they are few.  Measured break-even points, prefix 2048: about 160
+// row-ranges with up to four ranges (64 heads, M = 33 .. 64: 14.7 fused against 14.9 us at 132, 16.3 against
+// 15.5 at 256); with five to eight ranges 512 for tiles of one head (32 heads, M = 64: 15.6 against 16.7 us)
+// and 256 for packed ones (64 heads in pairs: 12.9 against 13.1 us at M = 16, 14.4 against 13.6 at M = 24);
+// 256 with more ranges (M = 4 of 32 heads 10.7 against 11.0 us at 256, M = 8 of 64 heads 14.0 against 11.0
+// at 512).
+static AttnPlan plain_plan(int M, int P, int Hq, int Hkv, int pack, int splits, int most_ranges)
+{
+    const int group = Hq / Hkv, steps = key_steps(M, P);
+    AttnPlan p;
+    if (pack == 3) {
+        even_tiles(group * M, p.tile_rows, p.tiles_per_kv);
+    } else {
+        const int d = heads_per_tile(M, Hq, Hkv, pack);
+        p.tile_rows = d * M;
+        p.tiles_per_kv = group / d;
+    }
+    const int units = Hkv * p.tiles_per_kv;
+    int want = splits > 0 ? splits : (256 + units - 1) / units;   // about one workgroup per compute unit
+    want = want > steps ? steps : want;
+    p.ranges = want > most_ranges ? most_ranges : want < 1 ? 1 : want;
+    const int row_ranges = p.tile_rows * p.ranges;
+    p.fused = p.ranges > 1 && row_ranges <= (p.ranges <= 4 ? 160 : (p.ranges <= 8 && p.tile_rows == M) ? 512 : 256);
+    return p;
+}
+
+// Time of a plan in microseconds, up to errors of some ten percent: a least-squares fit to 2663 measured plans (64/8, 32/8,
+// 16/2 and 8/8 heads, M = 1 .. 60, prefixes of 100 .. 16000, every tiling, 1 .. 32 ranges, both merges).  A workgroup's key steps
+// cost more when the chip is full and with short tiles; a fused merge costs one memory round trip per pass of the last
+// workgroup over its rows, the second kernel its launch.
+static float plan_time(const AttnPlan &p, int M, int P, int Hkv)
+{
+    const int units = Hkv * p.tiles_per_kv, groups = units * p.ranges;
+    const float steps4 = 0.25f * (float)((key_steps(M, P) + p.ranges - 1) / p.ranges), fill = (float)(groups < 256 ? groups : 256) / 256.f;
+    float t = 5.1f + (float)((groups + 255) / 256) * steps4 * (1.4f + fill * (p.tile_rows > 32 ? 0.38f : 0.54f)) + 0.0235f * (float)p.tile_rows;
+    if (p.ranges > 1 && p.fused) {
+        const int per_pass = p.ranges <= 4 ? 64 : p.ranges <= 8 ? 32 : 16;   // rows
+        t += 0.95f + 0.25f * (float)((p.tile_rows + per_pass - 1) / per_pass) + 0.06f * (float)p.ranges + 0.006f * (float)(p.tile_rows * p.ranges);
+    } else if (p.ranges > 1) {
+        t += 2.f + 0.00006f * (float)(groups * p.tile_rows) + 0.08f * (float)p.ranges + (p.ranges > 16 ? 0.3f : 0.f);
+    }
+    return t;
+}
+
+// The plain plan, unless another one promises a tenth (and a microsecond) less: d heads per tile or even tiles, with one, two or four ranges or
+// as many as fill the chip (or half of it).  At long prefixes that is full tiles, which read K and V least often and
+// waste no rows, and up to 32 ranges; at short ones a single range and no merge; and where the plain plan's rounding up
+// makes more workgroups than compute units (40/8 heads: 280), as many as there are.  Over 360 other calls (also 12/2 and 40/8
+// heads, prefixes of 40 .. 32000) 13 % faster in the mean than the plain plan, at worst 3 % slower: P = 16000, 64/8 heads: M = 4 34.3 -> 21.8 us, M = 16 36.9 -> 25.7,
+// M = 24 39.2 -> 32.9, M = 40 61.9 -> 47.3; 32/8 heads: M = 8 34.6 -> 21.7, M = 24 36.6 -> 25.0; P = 100, 64/8 heads: M = 32 11.1 -> 8.1,
+// M = 60 11.3 -> 8.8; at prefix 2048 the plain plan stays but for M = 16 of 64/8 heads and the like.
+static AttnPlan attn_plan(const AttnPlan &plain, int M, int P, int Hq, int Hkv, size_t partial_room)
+{
+    const Params &pr = params();
+    const int group = Hq / Hkv, steps = key_steps(M, P);
+    auto most_ranges = [&](int units) {   // that the workspace holds
+        const size_t fit = partial_room / partial_bytes_of(units, 1);
+        return fit < 1 ? 1 : fit > (size_t)kMaxRanges ? kMaxRanges : (int)fit;
+    };
+    AttnPlan best = plain;
+    if (pr.attn_splits > kMaxSplits) best = plain_plan(M, P, Hq, Hkv, pr.attn_pack, pr.attn_splits, most_ranges(Hkv * best.tiles_per_kv));
+    if (pr.attn_pack == 0 && pr.attn_splits == 0) {
+        const float plain_time = plan_time(plain, M, P, Hkv);
+        float least = plain_time - (plain_time > 10.f ? 0.1f * plain_time : 1.f);
+        for (int d = 0; d <= group; ++d) {
+            AttnPlan p = {d * M, 0, 1, 0};
+            if (d == 0) {
+                even_tiles(group * M, p.tile_rows, p.tiles_per_kv);
+            } else {
+                if (group % d != 0 || M * d > kRowsPad) continue;
+                p.tiles_per_kv = group / d;
+            }
+            const int units = Hkv * p.tiles_per_kv;
+            int most = most_ranges(units);
+            most = most > steps ? steps : most;
+            most = most > 256 / units ? 256 / units : most;
+            const int choices[5] = {1, 2, 4, most / 2, most};
+            for (int i = 0; i < 5; ++i) {
+                p.ranges = choices[i];
+                if (p.ranges < 1 || p.ranges > most || (i > 2 && p.ranges <= 4)) continue;
+                for (p.fused = 0; p.fused < (p.ranges > 1 ? 2 : 1); ++p.fused) {
+                    const float t = plan_time(p, M, P, Hkv);
+                    if (t < least) least = t, best = p;
+                }
+            }
+        }
+    }
+    if (pr.attn_fused_merge != 0) best.fused = best.ranges > 1 && pr.attn_fused_merge == 2;
+    return best;
 }
 
 template <int RT, int RG, typename... Args>
@@ -1020,51 +1146,38 @@ int tree_verify_attn(const void *q, const void *k, const void *v, const uint8_t 
     if (!(scale > 0.f) || scale > 3.0e38f) return W4A16_EINVAL;   // the kernels take row maxima before scaling
     if (!q || !k || !v || !mask || !out) return W4A16_ENULL;
     if (misaligned(q) || misaligned(k) || misaligned(v) || misaligned(out) || workspace_misaligned(workspace)) return W4A16_EALIGN;
-    const int rep = attn_rep(M, Hq, Hkv);
-    const int units = rep ? Hq / rep : Hq;
-    const int ns = attn_splits(M, P, units);
-    const size_t need = kTicketBytes + (size_t)units * ns * kRowsPad * (kHeadDim + 2) * sizeof(float);
-    if (ns > 1 && (!workspace || workspace_bytes < need)) return W4A16_EWORKSPACE;
+    // the plain plan says what a workspace has to hold at least; another plan takes no more than there is
+    const AttnPlan plain = plain_plan(M, P, Hq, Hkv, params().attn_pack, params().attn_splits, kMaxSplits);
+    if (plain.ranges > 1 && (!workspace || workspace_bytes < kTicketBytes + partial_bytes_of(Hkv * plain.tiles_per_kv, plain.ranges)))
+        return W4A16_EWORKSPACE;
+    const AttnPlan pl = attn_plan(plain, M, P, Hq, Hkv, workspace && workspace_bytes > kTicketBytes ? workspace_bytes - kTicketBytes : 0);
+    const int units = Hkv * pl.tiles_per_kv, ns = pl.ranges, rows = pl.tile_rows;
     float *part_o = reinterpret_cast<float *>(reinterpret_cast<uint8_t *>(workspace) + kTicketBytes);
     float *part_ml = part_o + (size_t)units * ns * kRowsPad * kHeadDim;
     const float scale_log2e = scale * 1.4426950408889634f;
-    const int nblk = (P + M + kKeyBlock - 1) / kKeyBlock;
+    const int nblk = key_steps(M, P);
     // Every tile runs in the kernel that shares K and V tiles through LDS (rt = 0 below): it is the fastest
     // form at every tile height, with half of its rows padding too (prefix 2048, 64/8 heads: 11.2 against
     // 12.0 us at M = 8, 13.8 against 16.7 at M = 24, 15.7 against 22.3 at M = 64).  The older kernel stays
     // selectable for comparison: one wavefront per SIMD carrying all 64 rows (4), or 32 rows per wavefront,
     // in two row groups for taller tiles (2).
-    const int rows = rep ? M * rep : M;
     const int knob = params().attn_row_tiles;
     const int rt = knob == 4 ? 4 : knob == 2 ? 2 : 0, rgroups = (rt == 2 && rows > 32) ? 2 : 1;
-    // The key ranges of a tile are merged by the last of its workgroups to finish, or by a second kernel.  Fused
-    // saves a launch and the wait for it, but one workgroup then reads all the partials of its tile (rows x
-    // ranges x 512 B), which pays while they are few.  Measured break-even points, prefix 2048: about 160 row-
-    // ranges with up to four ranges (64 heads, M = 33 .. 64: 14.7 fused against 14.9 us at 132, 16.3 against
-    // 15.5 at 256); with five to eight ranges 512 for tiles of one head (32 heads, M = 64: 15.6 against 16.7 us)
-    // and 256 for packed ones (64 heads in pairs: 12.9 against 13.1 us at M = 16, 14.4 against 13.6 at M = 24);
-    // 256 with more ranges (M = 4 of 32 heads 10.7 against 11.0 us at 256, M = 8 of 64 heads 14.0 against 11.0
-    // at 512).
-    const int fm = params().attn_fused_merge;
-    const int row_ranges = rows * ns;
-    const bool few = row_ranges <= (ns <= 4 ? 160 : (ns <= 8 && !rep) ? 512 : 256);
-    const int fused = (ns > 1 && fm != 1 && (fm == 2 || few)) ? 1 : 0;
     rc = launch_attn(rt, rgroups, units * ns, (hipStream_t)stream, (const _Float16 *)q, (const _Float16 *)k,
                      (const _Float16 *)v, mask, (_Float16 *)out, part_o, part_ml, reinterpret_cast<uint32_t *>(workspace),
-                     M, P, Hq, Hkv, scale_log2e, ns, nblk / ns, nblk % ns, rep, fused);
+                     M, P, Hq, Hkv, Hq / Hkv, scale_log2e, ns, nblk / ns, nblk % ns, rows, pl.tiles_per_kv, pl.fused);
     if (rc != W4A16_OK) return rc;
-    if (ns > 1 && !fused) {
+    if (ns > 1 && !pl.fused) {
         const int quads = M * Hq * (kHeadDim / 4);
         const dim3 grid((unsigned)((quads + 255) / 256));
-        if (ns <= 4)
-            hipLaunchKernelGGL(tree_attn_merge_kernel<4>, grid, dim3(256), 0, (hipStream_t)stream, (const float *)part_o,
-                               (const float *)part_ml, (_Float16 *)out, M, Hq, ns, rep);
-        else if (ns <= 8)
-            hipLaunchKernelGGL(tree_attn_merge_kernel<8>, grid, dim3(256), 0, (hipStream_t)stream, (const float *)part_o,
-                               (const float *)part_ml, (_Float16 *)out, M, Hq, ns, rep);
-        else
-            hipLaunchKernelGGL(tree_attn_merge_kernel<kMaxSplits>, grid, dim3(256), 0, (hipStream_t)stream,
-                               (const float *)part_o, (const float *)part_ml, (_Float16 *)out, M, Hq, ns, rep);
+#define W4_ATTN_MERGE(NS_)                                                                                              \
+        hipLaunchKernelGGL(tree_attn_merge_kernel<NS_>, grid, dim3(256), 0, (hipStream_t)stream, (const float *)part_o,  \
+                           (const float *)part_ml, (_Float16 *)out, M, Hq, Hq / Hkv, ns, rows, pl.tiles_per_kv)
+        if (ns <= 4) W4_ATTN_MERGE(4);
+        else if (ns <= 8) W4_ATTN_MERGE(8);
+        else if (ns <= 16) W4_ATTN_MERGE(16);
+        else W4_ATTN_MERGE(kMaxRanges);
+#undef W4_ATTN_MERGE
     }
     return launch_status();
 }

@@ -87,6 +87,46 @@ def test_attn_parity(M, P, Hq, Hkv, tree):
     print("   ", stats, flush=True)
 
 
+@pytest.mark.parametrize("M,P,Hq,Hkv", [(1, 1100, 8, 2), (17, 40, 8, 2), (27, 1100, 12, 2), (33, 0, 10, 2), (64, 1100, 10, 2), (13, 300, 64, 8)])
+def test_even_tiles_and_many_ranges(M, P, Hq, Hkv):
+    """tiles that end inside a head (the group's rows cut evenly), one and up to 32 key ranges, both merges: against
+    the oracle, and the two merges bit for bit"""
+    print(f"even tiles M={M} P={P} Hq={Hq} Hkv={Hkv}", flush=True)
+    a = I.make_attn(8500 + M + P + Hq, M, P, Hq, Hkv, 128, depth=6 if M > 6 else max(M - 1, 0))
+    ref64, _ = R.tree_verify_attn(a.q, a.k, a.v, a.mask, a.scale)
+    for pack in (3, 0):
+        for splits in (1, 3, 17, 32):
+            for row_tiles in (0, 2):
+                B.w4a16_set_param("attn_pack", pack)
+                B.w4a16_set_param("attn_splits", splits)
+                B.w4a16_set_param("attn_row_tiles", row_tiles)
+                got = []
+                for merge in (1, 2):
+                    B.w4a16_set_param("attn_fused_merge", merge)
+                    got.append(run_attn(a))
+                    check(got[-1], ref64, f"pack={pack} splits={splits} row_tiles={row_tiles} merge={merge}")
+                assert np.array_equal(got[0].view(np.uint16), got[1].view(np.uint16)), (pack, splits, row_tiles)
+
+
+@pytest.mark.parametrize("M,P,Hq,Hkv", [(13, 4100, 40, 8), (24, 5000, 16, 2), (8, 6000, 16, 4), (32, 90, 64, 8), (5, 9000, 8, 8)])
+def test_plan_by_size(M, P, Hq, Hkv):
+    """calls whose plan the size rule takes away from the plain one, in workspaces of the stated size and of the least
+    accepted size, where the plan has to fit what there is"""
+    a = I.make_attn(8600 + M + P + Hq, M, P, Hq, Hkv, 128, depth=6 if M > 6 else max(M - 1, 0))
+    ref64, _ = R.tree_verify_attn(a.q, a.k, a.v, a.mask, a.scale)
+    check(run_attn(a), ref64, f"M={M} P={P} heads {Hq}/{Hkv}")
+    nbytes = B.tree_verify_attn_workspace_bytes(M, P, Hq, Hkv, 128)
+    lo, hi = 16384, nbytes   # the least accepted size, by bisection over calls that are refused before anything is enqueued
+    while hi - lo > 256:
+        mid = (lo + hi) // 512 * 256
+        try:
+            run_attn(a, B.new_workspace(mid))
+            hi = mid
+        except B.W4A16Error:
+            lo = mid
+    check(run_attn(a, B.new_workspace(hi)), ref64, f"M={M} P={P} heads {Hq}/{Hkv}, {hi} of {nbytes} bytes")
+
+
 def test_attn_determinism_and_workspace_reuse():
     a = I.make_attn(8100, 60, 2048, 64, 8, 128)
     ws = B.new_workspace(B.tree_verify_attn_workspace_bytes(a.M, a.P, a.Hq, a.Hkv, a.D))
