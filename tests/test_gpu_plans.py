@@ -159,3 +159,42 @@ def test_default_plans_rope_projection(cfg):
         torch.cuda.synchronize()
         for a, b, what in ((q1, q2, "q"), (k1, k2, "k_cache"), (v1, v2, "v_cache")):
             assert torch.equal(a.view(torch.int16), b.view(torch.int16)), f"{what}, M={M}"
+
+
+RULE_SHAPES = [(2560, 6912), (5120, 13000), (9216, 4608), (1280, 20000), (20480, 1000), (640, 5000)]   # (K, N), none of them tuned
+
+
+def test_plans_by_rule_fit_the_builtin_scratch():
+    """shapes without a measured row: every plan is compiled, and none asks for more than the built-in scratch holds
+    where w4a16_gemm_static used to run"""
+    for K, N in RULE_SHAPES:
+        for M in range(1, 65):
+            plan = B.w4a16_plan_describe(M, N, K)
+            assert plan[1] == (M + 15) // 16 and plan[5] >= 1, (M, K, N, plan)
+        assert B.w4a16_workspace_bytes(64, N, K) <= 16384 + (32 << 20), (K, N)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("K,N", RULE_SHAPES)
+def test_plans_by_rule_sampled_columns(K, N):
+    """the plan the fitted rule picks, at the row counts where its choice or its kernel changes, against the oracle"""
+    from oracle import reference as R
+    inp = I.make_linear(7700 + K + N, 64, K, N, m_max=64)
+    packed = B.pack_from_numpy(inp)
+    ws = B.new_workspace(B.w4a16_workspace_bytes(64, N, K))
+    cols = sample_columns(np.random.default_rng(K + N), N, 24)
+    sub = column_subproblem(inp, cols)
+    xd = torch.from_numpy(inp.x).to(DEV)
+    for M in (1, 7, 16, 20, 37, 64):
+        print(f"K={K} N={N} M={M} plan {dict(zip(B.PLAN_FIELDS, B.w4a16_plan_describe(M, N, K)))}", flush=True)
+        x = xd[:M].contiguous()
+        y = torch.full((M + 2, N), SENTINEL, dtype=torch.float16, device=DEV)
+        B.w4a16_gemm(x, packed, y, M, N, K, 128, ws)
+        ys = torch.full((M + 2, N), SENTINEL, dtype=torch.float16, device=DEV)
+        B.w4a16_gemm_static(x, packed, ys, M, N, K, 128)
+        torch.cuda.synchronize()
+        out = y.cpu().numpy()
+        assert (out[M:] == np.float16(SENTINEL)).all(), "rows >= M were written"
+        assert np.array_equal(out.view(np.uint16), ys.cpu().numpy().view(np.uint16)), "the static entry point differs"
+        y32, _, _ = R.w4a16_gemm(inp.x[:M], *sub, 128, want64=False)
+        check_gemm(out[:M, cols], y32, f"K={K} N={N} M={M}")
