@@ -101,7 +101,10 @@ def _ptr(t) -> int:
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    """handle of torch's current stream on the current device.  The handle is asked for directly: the Stream object that
+    torch.cuda.current_stream() builds around it is a good part of the host time of a small call."""
+    torch.cuda.init()
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _check(code: int, where: str) -> None:
