@@ -16,7 +16,8 @@
  *   - the return value is W4A16_OK or a negative W4A16_E* code; arguments are validated before any
  *     GPU call, so an invalid call enqueues nothing; nothing is printed, nothing aborts;
  *   - all pointers must be 16-byte aligned; buffers must not overlap;
- *   - the same inputs give bit-identical outputs on every call (no atomically ordered sums);
+ *   - the same inputs give bit-identical outputs on every call (no atomically ordered sums), whatever the
+ *     size of the workspace, as long as it is at least the one the *_workspace_bytes() function states;
  *   - one GPU per process: the library keeps a few process-wide one-time flags (kernel attributes
  *     set on first use) and the ablation knobs; calls may be issued from any one host thread at a
  *     time, on any stream of the current device.
@@ -147,7 +148,8 @@ int w4a16_weight_is_symmetric(const void *packed, int N, int K, int G, int32_t *
 int w4a16_pack_gate_up(const int32_t *qweight, const void *scales, const int32_t *qzeros, void *packed,
                        int N, int K, int G, void *stream);
 
-/* Scratch needed by tree_verify_attn for these sizes (partial softmax states of the key splits). */
+/* Scratch needed by tree_verify_attn for these sizes (partial softmax states of the key splits).  Grows with
+ * M and P: the size for the largest of them serves every smaller call of the same heads. */
 size_t tree_verify_attn_workspace_bytes(int M, int P, int Hq, int Hkv, int D);
 
 /* Attention of the tree-verification pass (paper section 2.1: the target model scores the n
@@ -158,7 +160,10 @@ size_t tree_verify_attn_workspace_bytes(int M, int P, int Hq, int Hkv, int D);
  * row-major.  Softmax and accumulation in fp32.  Requires D == 128, 1 <= M <= 64, Hq % Hkv == 0,
  * Hq/Hkv <= 8, P >= 0, a finite scale > 0 (W4A16_EINVAL otherwise), and every row must see at least
  * one key.  `workspace` as for w4a16_gemm,
- * sized by tree_verify_attn_workspace_bytes and initialised by w4a16_workspace_init. */
+ * sized by tree_verify_attn_workspace_bytes and initialised by w4a16_workspace_init.  How the call is split
+ * follows from its sizes alone, so every workspace of at least that size gives the same bits.  A smaller one is
+ * refused, or -- where it still holds a simpler split of the call -- served with that one: a result of the
+ * same accuracy with other roundings. */
 int tree_verify_attn(const void *q, const void *k, const void *v, const uint8_t *mask, void *out,
                      int M, int P, int Hq, int Hkv, int D, float scale,
                      void *workspace, size_t workspace_bytes, void *stream);
@@ -340,6 +345,13 @@ int w4a16_get_param(const char *name);
  * Host only: touches no GPU.  Errors as w4a16_gemm's shape checks; W4A16_EUNSUP if the knobs name a
  * variant that is not compiled. */
 int w4a16_plan_describe(int M, int N, int K, int G, int *out);
+
+/* How tree_verify_attn would split a call with a workspace of workspace_bytes (0: none) and the current knobs, so that
+ * a test can show that a larger workspace changes nothing and which splits have been compared with the oracle.
+ * out receives 5 ints: [0] rows of a row tile (the last may have fewer), [1] row tiles per KV head, [2] key ranges per
+ * tile, [3] 1 if the last workgroup of a tile merges its ranges, [4] 1 for the split that the least accepted
+ * workspace gets too.  Host only: touches no GPU.  Errors as tree_verify_attn's size and workspace checks. */
+int tree_verify_attn_plan_describe(int M, int P, int Hq, int Hkv, int D, size_t workspace_bytes, int *out);
 
 /* Measurement aid, not part of the method: enqueues a kernel that only reads the first
  * bytes - bytes % 16 bytes of `buf` with 16-byte streaming loads (one 32 KB chunk per workgroup)

@@ -18,6 +18,7 @@ EXPORTS = (
     "w4a16_gemm", "w4a16_gemm_fused", "w4a16_gemm_rope", "w4a16_pack_heads", "w4a16_pack_gate_up", "w4a16_read_probe", "tree_verify_attn_workspace_bytes",
     "tree_verify_attn", "tree_accept", "rms_norm", "rope_append", "lm_head_workspace_bytes", "lm_head_topk",
     "lm_head_packed_bytes", "lm_head_pack", "w4a16_decoder_layer", "w4a16_plan_describe", "w4a16_gemm_static", "w4a16_weight_is_symmetric",
+    "tree_verify_attn_plan_describe",
 )
 
 EPI_NONE, EPI_RESIDUAL, EPI_SILU_MUL = 0, 1, 2
@@ -77,6 +78,7 @@ def load() -> ctypes.CDLL:
     L.tree_verify_attn_workspace_bytes.restype = sz
     L.tree_verify_attn_workspace_bytes.argtypes = [i, i, i, i, i]
     L.tree_verify_attn.argtypes = [vp, vp, vp, vp, vp, i, i, i, i, i, ctypes.c_float, vp, sz, vp]
+    L.tree_verify_attn_plan_describe.argtypes = [i, i, i, i, i, sz, ctypes.POINTER(ctypes.c_int)]
     L.tree_accept.argtypes = [vp, vp, vp, i, vp, vp, vp, vp, i, i, i, vp]
     L.w4a16_gemm_fused.argtypes = [vp, vp, vp, i, i, i, i, i, vp, vp, sz, vp]
     L.w4a16_pack_gate_up.argtypes = [vp, vp, vp, vp, i, i, i, vp]
@@ -262,6 +264,16 @@ def w4a16_plan_describe(M: int, N: int, K: int, G: int = 128) -> tuple:
     """the eight plan fields of include/w4a16.h (see PLAN_FIELDS); host only"""
     out = (ctypes.c_int * 8)()
     _check(load().w4a16_plan_describe(M, N, K, G, out), "w4a16_plan_describe")
+    return tuple(out)
+
+
+ATTN_PLAN_FIELDS = ("tile_rows", "tiles_per_kv", "ranges", "fused_merge", "plain")
+
+
+def tree_verify_attn_plan_describe(M: int, P: int, Hq: int, Hkv: int, D: int, workspace_bytes: int) -> tuple:
+    """the five plan fields of include/w4a16.h (see ATTN_PLAN_FIELDS); host only"""
+    out = (ctypes.c_int * 5)()
+    _check(load().tree_verify_attn_plan_describe(M, P, Hq, Hkv, D, int(workspace_bytes), out), "tree_verify_attn_plan_describe")
     return tuple(out)
 
 

@@ -28,8 +28,9 @@ constexpr int kRowsPad = 64;
 // LDS of a workgroup of 4 * RG wavefronts with RT row tiles each: one exchange slot per wavefront
 // (8 * RT accumulator quads + 2 * RT state values per lane); the slots cover the 8 KB V tiles
 constexpr int attn_lds_bytes(int rt, int rg) { return 4 * rg * (8 * rt * 4 + 2 * rt) * 64 * 4; }
-constexpr int kMaxSplits = 16;   // key ranges per query head that a workspace is sized for
-constexpr int kMaxRanges = 32;   // key ranges per row tile (the merge keeps one value per range in registers)
+constexpr int kMaxSplits = 16;   // key ranges per row tile of the plain plan
+constexpr int kMaxRanges = 32;   // of any plan (the merge keeps one value per range in registers)
+constexpr int kChipTiles = 256;  // tiles x ranges of the plans that are picked by predicted time: one workgroup per compute unit
 
 // v_max3_f32 and v_max_f32 as they stand: fmaxf chains are compiled with a canonicalising v_max x, x per
 // operand, which doubles the instruction count of a row maximum; no score here is a NaN.
@@ -1036,43 +1037,73 @@ static float plan_time(const AttnPlan &p, int M, int P, int Hkv)
 // makes more workgroups than compute units (40/8 heads: 280), as many as there are.  Over 360 other calls (also 12/2 and 40/8
 // heads, prefixes of 40 .. 32000) 13 % faster in the mean than the plain plan, at worst 3 % slower: P = 16000, 64/8 heads: M = 4 34.3 -> 21.8 us, M = 16 36.9 -> 25.7,
 // M = 24 39.2 -> 32.9, M = 40 61.9 -> 47.3; 32/8 heads: M = 8 34.6 -> 21.7, M = 24 36.6 -> 25.0; P = 100, 64/8 heads: M = 32 11.1 -> 8.1,
-// M = 60 11.3 -> 8.8; at prefix 2048 the plain plan stays but for M = 16 of 64/8 heads and the like.
-static AttnPlan attn_plan(const AttnPlan &plain, int M, int P, int Hq, int Hkv, size_t partial_room)
+// M = 60 11.3 -> 8.8; at prefix 2048 the plain plan stays for 64/8 and 32/8 heads.
+static AttnPlan plan_by_size(const AttnPlan &plain, int M, int P, int Hq, int Hkv)
 {
-    const Params &pr = params();
     const int group = Hq / Hkv, steps = key_steps(M, P);
-    auto most_ranges = [&](int units) {   // that the workspace holds
-        const size_t fit = partial_room / partial_bytes_of(units, 1);
-        return fit < 1 ? 1 : fit > (size_t)kMaxRanges ? kMaxRanges : (int)fit;
-    };
     AttnPlan best = plain;
-    if (pr.attn_splits > kMaxSplits) best = plain_plan(M, P, Hq, Hkv, pr.attn_pack, pr.attn_splits, most_ranges(Hkv * best.tiles_per_kv));
-    if (pr.attn_pack == 0 && pr.attn_splits == 0) {
-        const float plain_time = plan_time(plain, M, P, Hkv);
-        float least = plain_time - (plain_time > 10.f ? 0.1f * plain_time : 1.f);
-        for (int d = 0; d <= group; ++d) {
-            AttnPlan p = {d * M, 0, 1, 0};
-            if (d == 0) {
-                even_tiles(group * M, p.tile_rows, p.tiles_per_kv);
-            } else {
-                if (group % d != 0 || M * d > kRowsPad) continue;
-                p.tiles_per_kv = group / d;
-            }
-            const int units = Hkv * p.tiles_per_kv;
-            int most = most_ranges(units);
-            most = most > steps ? steps : most;
-            most = most > 256 / units ? 256 / units : most;
-            const int choices[5] = {1, 2, 4, most / 2, most};
-            for (int i = 0; i < 5; ++i) {
-                p.ranges = choices[i];
-                if (p.ranges < 1 || p.ranges > most || (i > 2 && p.ranges <= 4)) continue;
-                for (p.fused = 0; p.fused < (p.ranges > 1 ? 2 : 1); ++p.fused) {
-                    const float t = plan_time(p, M, P, Hkv);
-                    if (t < least) least = t, best = p;
-                }
+    const float plain_time = plan_time(plain, M, P, Hkv);
+    float least = plain_time - (plain_time > 10.f ? 0.1f * plain_time : 1.f);
+    for (int d = 0; d <= group; ++d) {
+        AttnPlan p = {d * M, 0, 1, 0};
+        if (d == 0) {
+            even_tiles(group * M, p.tile_rows, p.tiles_per_kv);
+        } else {
+            if (group % d != 0 || M * d > kRowsPad) continue;
+            p.tiles_per_kv = group / d;
+        }
+        const int units = Hkv * p.tiles_per_kv;
+        int most = steps < kMaxRanges ? steps : kMaxRanges;
+        most = most > kChipTiles / units ? kChipTiles / units : most;
+        const int choices[5] = {1, 2, 4, most / 2, most};
+        for (int i = 0; i < 5; ++i) {
+            p.ranges = choices[i];
+            if (p.ranges < 1 || p.ranges > most || (i > 2 && p.ranges <= 4)) continue;
+            for (p.fused = 0; p.fused < (p.ranges > 1 ? 2 : 1); ++p.fused) {
+                const float t = plan_time(p, M, P, Hkv);
+                if (t < least) least = t, best = p;
             }
         }
     }
+    return best;
+}
+
+// Partial results (tiles x ranges) that the stated workspace holds: those of the plain plan at any knob setting, and those
+// of any plan_by_size() -- at most kChipTiles in all, at most Hq tiles.  Grows with M and P, so one workspace serves smaller calls.
+static size_t stated_partials(int M, int P, int Hq)
+{
+    const size_t steps = (size_t)key_steps(M, P), heads = (size_t)Hq;
+    const size_t plain = heads * (steps < kMaxSplits ? steps : kMaxSplits);
+    const size_t by_size = heads * (steps < kMaxRanges ? steps : kMaxRanges);
+    const size_t capped = by_size < kChipTiles ? by_size : kChipTiles;
+    return plain > capped ? plain : capped;
+}
+
+// bytes of partial results a plan writes; one range writes none
+static size_t plan_bytes(const AttnPlan &p, int Hkv)
+{
+    return p.ranges > 1 ? partial_bytes_of(Hkv * p.tiles_per_kv, p.ranges) : 0;
+}
+
+// The plan of a call whose workspace has `room` bytes for partial results.  It follows from the sizes of the call alone, so
+// that the bits of the result do not depend on how large a workspace the caller keeps.  Less than the stated size is
+// accepted as long as it holds the plain plan, which runs where the preferred one does not fit; ranges == 0: not even that.
+static AttnPlan attn_plan(int M, int P, int Hq, int Hkv, size_t room)
+{
+    const Params &pr = params();
+    AttnPlan plain = plain_plan(M, P, Hq, Hkv, pr.attn_pack, pr.attn_splits, kMaxSplits);
+    if (plan_bytes(plain, Hkv) > room) {
+        plain.ranges = 0;
+        return plain;
+    }
+    AttnPlan best = plain;
+    if (pr.attn_splits > kMaxSplits) {   // asked for: as many of them as the stated workspace holds
+        const size_t fit = stated_partials(M, P, Hq) / (size_t)(Hkv * plain.tiles_per_kv);
+        best = plain_plan(M, P, Hq, Hkv, pr.attn_pack, pr.attn_splits, fit < kMaxRanges ? (int)fit : kMaxRanges);
+    } else if (pr.attn_pack == 0 && pr.attn_splits == 0) {
+        best = plan_by_size(plain, M, P, Hq, Hkv);
+    }
+    if (plan_bytes(best, Hkv) > room) best = plain;
     if (pr.attn_fused_merge != 0) best.fused = best.ranges > 1 && pr.attn_fused_merge == 2;
     return best;
 }
@@ -1132,9 +1163,7 @@ extern "C" {
 size_t tree_verify_attn_workspace_bytes(int M, int P, int Hq, int Hkv, int D)
 {
     if (check_attn(M, P, Hq, Hkv, D) != W4A16_OK) return 0;
-    const int nblk = (P + M + kKeyBlock - 1) / kKeyBlock;
-    const int ns = nblk < kMaxSplits ? nblk : kMaxSplits;   // the most splits any setting of the knobs can ask for
-    return kTicketBytes + (size_t)Hq * ns * kRowsPad * (kHeadDim + 2) * sizeof(float);
+    return kTicketBytes + stated_partials(M, P, Hq) * partial_bytes_of(1, 1);
 }
 
 int tree_verify_attn(const void *q, const void *k, const void *v, const uint8_t *mask, void *out,
@@ -1146,11 +1175,8 @@ int tree_verify_attn(const void *q, const void *k, const void *v, const uint8_t 
     if (!(scale > 0.f) || scale > 3.0e38f) return W4A16_EINVAL;   // the kernels take row maxima before scaling
     if (!q || !k || !v || !mask || !out) return W4A16_ENULL;
     if (misaligned(q) || misaligned(k) || misaligned(v) || misaligned(out) || workspace_misaligned(workspace)) return W4A16_EALIGN;
-    // the plain plan says what a workspace has to hold at least; another plan takes no more than there is
-    const AttnPlan plain = plain_plan(M, P, Hq, Hkv, params().attn_pack, params().attn_splits, kMaxSplits);
-    if (plain.ranges > 1 && (!workspace || workspace_bytes < kTicketBytes + partial_bytes_of(Hkv * plain.tiles_per_kv, plain.ranges)))
-        return W4A16_EWORKSPACE;
-    const AttnPlan pl = attn_plan(plain, M, P, Hq, Hkv, workspace && workspace_bytes > kTicketBytes ? workspace_bytes - kTicketBytes : 0);
+    const AttnPlan pl = attn_plan(M, P, Hq, Hkv, workspace && workspace_bytes > kTicketBytes ? workspace_bytes - kTicketBytes : 0);
+    if (pl.ranges == 0) return W4A16_EWORKSPACE;
     const int units = Hkv * pl.tiles_per_kv, ns = pl.ranges, rows = pl.tile_rows;
     float *part_o = reinterpret_cast<float *>(reinterpret_cast<uint8_t *>(workspace) + kTicketBytes);
     float *part_ml = part_o + (size_t)units * ns * kRowsPad * kHeadDim;
@@ -1180,6 +1206,22 @@ int tree_verify_attn(const void *q, const void *k, const void *v, const uint8_t 
 #undef W4_ATTN_MERGE
     }
     return launch_status();
+}
+
+int tree_verify_attn_plan_describe(int M, int P, int Hq, int Hkv, int D, size_t workspace_bytes, int *out)
+{
+    if (!out) return W4A16_ENULL;
+    int rc = check_attn(M, P, Hq, Hkv, D);
+    if (rc != W4A16_OK) return rc;
+    const AttnPlan pl = attn_plan(M, P, Hq, Hkv, workspace_bytes > kTicketBytes ? workspace_bytes - kTicketBytes : 0);
+    if (pl.ranges == 0) return W4A16_EWORKSPACE;
+    const AttnPlan plain = plain_plan(M, P, Hq, Hkv, params().attn_pack, params().attn_splits, kMaxSplits);
+    out[0] = pl.tile_rows;
+    out[1] = pl.tiles_per_kv;
+    out[2] = pl.ranges;
+    out[3] = pl.fused;
+    out[4] = pl.tile_rows == plain.tile_rows && pl.tiles_per_kv == plain.tiles_per_kv && pl.ranges == plain.ranges;
+    return W4A16_OK;
 }
 
 int tree_accept(const int32_t *parent, const int32_t *token, const int32_t *target, int M, int32_t *path,

@@ -7,6 +7,7 @@ import torch
 from oracle import reference as R
 from paper_2505_22179_amd import binding as B
 from paper_2505_22179_amd import inputs as I
+from tests.test_attn_plan_host import least_workspace
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -108,23 +109,23 @@ def test_even_tiles_and_many_ranges(M, P, Hq, Hkv):
                 assert np.array_equal(got[0].view(np.uint16), got[1].view(np.uint16)), (pack, splits, row_tiles)
 
 
-@pytest.mark.parametrize("M,P,Hq,Hkv", [(13, 4100, 40, 8), (24, 5000, 16, 2), (8, 6000, 16, 4), (32, 90, 64, 8), (5, 9000, 8, 8)])
-def test_plan_by_size(M, P, Hq, Hkv):
-    """calls whose plan the size rule takes away from the plain one, in workspaces of the stated size and of the least
-    accepted size, where the plan has to fit what there is"""
+@pytest.mark.parametrize("M,P,Hq,Hkv,least_differs", [
+    (13, 4100, 40, 8, False), (32, 90, 64, 8, False), (40, 16001, 32, 8, False),   # another split, which the plain one's space holds
+    (1, 7699, 32, 8, True), (4, 16000, 8, 8, True), (4, 300, 40, 8, True), (34, 16000, 12, 2, True)])   # and does not hold
+def test_plan_by_size(M, P, Hq, Hkv, least_differs):
+    """calls whose split is not the plain one: it follows from the sizes alone, so the stated workspace and a much larger one
+    give the same bits; a workspace that does not hold it gets the plain split"""
+    stated = B.tree_verify_attn_workspace_bytes(M, P, Hq, Hkv, 128)
+    least = least_workspace(M, P, Hq, Hkv)
+    plans = [B.tree_verify_attn_plan_describe(M, P, Hq, Hkv, 128, n) for n in (least, stated, 4 * stated)]
+    print(f"M={M} P={P} heads {Hq}/{Hkv}: {least} bytes {plans[0]}, {stated} bytes {plans[1]}", flush=True)
+    assert plans[1][4] == 0 and plans[2] == plans[1] and (plans[0] != plans[1]) == least_differs and plans[0][4] == least_differs
     a = I.make_attn(8600 + M + P + Hq, M, P, Hq, Hkv, 128, depth=6 if M > 6 else max(M - 1, 0))
     ref64, _ = R.tree_verify_attn(a.q, a.k, a.v, a.mask, a.scale)
-    check(run_attn(a), ref64, f"M={M} P={P} heads {Hq}/{Hkv}")
-    nbytes = B.tree_verify_attn_workspace_bytes(M, P, Hq, Hkv, 128)
-    lo, hi = 16384, nbytes   # the least accepted size, by bisection over calls that are refused before anything is enqueued
-    while hi - lo > 256:
-        mid = (lo + hi) // 512 * 256
-        try:
-            run_attn(a, B.new_workspace(mid))
-            hi = mid
-        except B.W4A16Error:
-            lo = mid
-    check(run_attn(a, B.new_workspace(hi)), ref64, f"M={M} P={P} heads {Hq}/{Hkv}, {hi} of {nbytes} bytes")
+    got = run_attn(a)
+    check(got, ref64, f"M={M} P={P} heads {Hq}/{Hkv}")
+    assert np.array_equal(run_attn(a, B.new_workspace(4 * stated)).view(np.uint16), got.view(np.uint16)), "a larger workspace, other bits"
+    check(run_attn(a, B.new_workspace(least)), ref64, f"M={M} P={P} heads {Hq}/{Hkv}, {least} of {stated} bytes")
 
 
 def test_attn_determinism_and_workspace_reuse():
