@@ -1053,6 +1053,11 @@ __device__ __forceinline__ void compute_group_lean(const u32x4 (&a)[MT][4], Quan
 // 70B o_proj at 64 rows 20.3 -> 20.8), which short K ranges do not get back; those run with two tiles and one group
 // of codes in flight, and keep the form above.
 constexpr bool staged_steps(int tw, int depth) { return tw >= 4 || depth == 2; }
+// Its descriptors and offsets are 32-bit: 64 rows of x and the records of one column block have to fit.  Longer K take the
+// form above.
+constexpr int kStagedMaxK = (1 << 25) - kGroup;
+static_assert((uint64_t)W4A16_MAX_M * kStagedMaxK * 2 < (1ull << 32) && (uint64_t)(kStagedMaxK / kGroup) * kRecordBytes < (1ull << 32),
+              "byte offsets of the staged form fit 32 bits");
 
 // scales and zero-points of one group as the staged kernel keeps them: its own TW tiles only
 template <int TW>
@@ -1670,6 +1675,7 @@ static Plan predicted_plan(const Plan &plain, int M, int N, int K)
         {2, 0, 1, 2}, {2, 0, 2, 2}, {2, 0, 1, 3}, {2, 0, 2, 3}, {4, 0, 1, 2}, {4, 0, 2, 2}, {4, 0, 1, 3}};               // more
     for (const auto &v : kShapes) {
         if ((mt == 1) != (v.ks == 0) || !variant_exists(mt, v.tw, v.nw, v.depth, v.ks)) continue;
+        if (v.ks > 0 && staged_steps(v.tw, v.depth) && K > kStagedMaxK) continue;
         if (mt > 2 && v.depth == 2 && (v.tw != 2 || v.ks != 2)) continue;   // not among the measured ones
         const int units = v.ks ? (tiles / v.tw + 3) / 4 : tiles / v.tw, ways = v.ks ? v.ks : v.nw;
         int most = (v.ks ? 256 : 2048 / v.nw) / units;
@@ -1725,13 +1731,13 @@ static Plan choose_plan(int M, int N, int K)
         int s = p.split_k > 0 ? p.split_k : 1;
         if (s > groups) s = groups;
         if (p.even_split) s = 0;
-        if (variant_exists(mt, tw, 0, depth, p.k_sets)) best = {tw, 0, depth, s, p.fused_reduce == 1, p.k_sets, 0};
+        if (variant_exists(mt, tw, 0, depth, p.k_sets) && (!staged_steps(tw, depth) || K <= kStagedMaxK)) best = {tw, 0, depth, s, p.fused_reduce == 1, p.k_sets, 0};
         return best;
     }
     if (best.tw == 0 && free_choice && mt > 1) {
         // no measured row: the high-occupancy variant with two K sets, about one workgroup per
         // compute unit, wide tiles only when the columns alone fill the chip
-        const int tw = tiles / 16 >= 200 ? 4 : 2;
+        const int tw = tiles / 16 >= 200 && K <= kStagedMaxK ? 4 : 2;
         const int units = (tiles / tw + 3) / 4;
         int s = (256 + units / 2) / units;
         if (s > groups / 4) s = groups / 4;   // two groups per K set at least

@@ -6,6 +6,7 @@ tuned tables and the rules behind them; w4a16_plan_describe reports it.  The hos
 values used below reach every plan that any M in 1..64 reaches; the GPU tests then compare, for every
 shape and every such M, sampled output columns (all rows) with the oracle -- plain, and through the fused
 epilogue the decoder layer uses for that linear -- at the tolerance of tests/parity.py."""
+import ctypes
 import os
 import re
 
@@ -172,6 +173,29 @@ def test_plans_by_rule_fit_the_builtin_scratch():
             plan = B.w4a16_plan_describe(M, N, K)
             assert plan[1] == (M + 15) // 16 and plan[5] >= 1, (M, K, N, plan)
         assert B.w4a16_workspace_bytes(64, N, K) <= 16384 + (32 << 20), (K, N)
+
+
+def test_longest_contractions_stay_off_the_staged_kernels():
+    """the column-split kernels with four or more tiles per wavefront or two groups in flight address x with 32-bit byte
+    offsets: 64 rows of 2 ** 25 elements no longer fit"""
+    staged = lambda plan: plan[0] == 3 and (plan[2] >= 4 or plan[4] == 2)
+    reached = False
+    for K in (2 ** 25 - 128, 2 ** 25, 64_700_032, 2 ** 27):
+        for N in (8, 1280, 3328, 4096, 8192, 15872, 60000):
+            for M in (17, 32, 33, 48, 49, 64):
+                plan = B.w4a16_plan_describe(M, N, K)
+                assert K < 2 ** 25 or not staged(plan), (M, N, K, plan)
+                reached |= staged(plan)
+    assert reached
+    out = (ctypes.c_int * 8)()
+    for name, value in (("k_sets", 2), ("tiles_per_wave", 4), ("prefetch_depth", 1)):
+        B.w4a16_set_param(name, value)
+    try:
+        assert B.load().w4a16_plan_describe(64, 4096, 2 ** 25 - 128, 128, out) == 0
+        assert B.load().w4a16_plan_describe(64, 4096, 2 ** 25, 128, out) == -4
+    finally:
+        for name in ("k_sets", "tiles_per_wave", "prefetch_depth"):
+            B.w4a16_set_param(name, 0)
 
 
 @pytest.mark.gpu
