@@ -54,7 +54,8 @@ const char *w4a16_strerror(int code);
 size_t w4a16_packed_bytes(int N, int K, int G);
 
 /* Bytes of scratch w4a16_gemm may need for any 1 <= M <= M_max at this shape (split-K partial sums
- * and their tickets).  Never 0 for a supported shape. */
+ * and their tickets).  Never 0 for a supported shape.  A smaller workspace is refused, or -- where it still holds
+ * a simpler split of the call -- served with that one: a result of the same accuracy with other roundings. */
 size_t w4a16_workspace_bytes(int M_max, int N, int K, int G);
 
 /* Zero the ticket area at the start of a workspace.  Must be enqueued once before the first

@@ -222,3 +222,37 @@ def test_plans_by_rule_sampled_columns(K, N):
         assert np.array_equal(out.view(np.uint16), ys.cpu().numpy().view(np.uint16)), "the static entry point differs"
         y32, _, _ = R.w4a16_gemm(inp.x[:M], *sub, 128, want64=False)
         check_gemm(out[:M, cols], y32, f"K={K} N={N} M={M}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,K,N,least", [   # bytes beyond the tickets that the plain rule's split needs
+    (1, 8192, 10240, 0), (8, 8192, 10240, 0), (36, 1280, 48, 49152), (1, 7680, 20776, 0), (64, 7680, 20776, 10682368),
+    (1, 11776, 9424, 1212416)])
+def test_least_workspaces_are_still_accepted(M, K, N, least):
+    """calls whose default plan splits K further than the plain rule did: a workspace that holds only the plain rule's
+    partial sums is taken, one below it refused, and the stated one and a larger one give the same bits"""
+    from oracle import reference as R
+    stated = B.w4a16_workspace_bytes(M, N, K)
+    assert 16384 + least < stated
+    inp = I.make_linear(7900 + K + N, M, K, N, m_max=64)
+    packed = B.pack_from_numpy(inp)
+    cols = sample_columns(np.random.default_rng(K + N), N, min(24, N // 8))
+    y32, _, _ = R.w4a16_gemm(inp.x, *column_subproblem(inp, cols), 128, want64=False)
+    xd = torch.from_numpy(inp.x).to(DEV)
+
+    def call(ws):
+        y = torch.full((M + 2, N), SENTINEL, dtype=torch.float16, device=DEV)
+        B.w4a16_gemm(xd, packed, y, M, N, K, 128, ws)
+        torch.cuda.synchronize()
+        out = y.cpu().numpy()
+        assert (out[M:] == np.float16(SENTINEL)).all()
+        check_gemm(out[:M, cols], y32, f"M={M} K={K} N={N}")
+        return out
+
+    call(B.new_workspace(16384 + least))
+    if least:
+        with pytest.raises(B.W4A16Error):
+            call(B.new_workspace(16384 + least)[:16384 + least - 1])
+    else:
+        call(None)
+    assert np.array_equal(call(B.new_workspace(stated)).view(np.uint16), call(B.new_workspace(4 * stated)).view(np.uint16))
