@@ -1604,7 +1604,7 @@ static bool flat_variant_exists(int tw, int nw, int ng)
     Z(4, 8, 1, 1) Z(3, 8, 1, 2) Z(3, 8, 1, 1) Z(4, 4, 1, 1) Z(3, 4, 2, 1) Z(2, 4, 2, 1) Z(2, 8, 2, 1) Z(2, 4, 3, 1) Z(4, 4, 2, 1) Z(3, 4, 1, 1) \
     Z(2, 2, 3, 2) Z(3, 2, 3, 1) Z(2, 2, 3, 1) Z(4, 2, 2, 1) Z(3, 2, 2, 1) Z(2, 2, 2, 1)
 
-static bool variant_exists(int mt, int tw, int nw, int depth, int ks = 0)
+static constexpr bool variant_exists(int mt, int tw, int nw, int depth, int ks = 0)
 {
 #define Z(MT_, TW_, KS_, D_) if (ks == KS_ && mt == MT_ && tw == TW_ && depth == D_) return true;
     if (ks > 0) {
@@ -1621,6 +1621,18 @@ static bool variant_exists(int mt, int tw, int nw, int depth, int ks = 0)
     return false;
 }
 
+// the same of the K-split kernels (and nw == 1) for one group in flight, as a table: the rules below ask for every call
+struct SplitVariants { bool v[4][9][17] = {}; };   // [row tiles - 1][tiles per wavefront][wavefronts]
+static constexpr SplitVariants split_variants()
+{
+    SplitVariants r;
+    for (int mt = 1; mt <= 4; ++mt)
+        for (int tw = 2; tw <= 8; tw *= 2)
+            for (int nw = 1; nw <= 16; nw = nw == 1 ? 4 : nw * 2) r.v[mt - 1][tw][nw] = variant_exists(mt, tw, nw, 1);
+    return r;
+}
+constexpr SplitVariants kSplitVariants = split_variants();
+
 // Shapes without a measured row.  Two least-squares fits give the time of a plan in microseconds from its launch shape,
 // over weights that come from HBM: 2477 plans of 92 calls (M = 1 .. 16) and 3039 of 132 (M = 20 .. 64) on 32 shapes,
 // K = 640 .. 28672, N = 1000 .. 32000.  The plan with the least time lies 2 to 3 % behind the best measured one in the mean.
@@ -1628,36 +1640,68 @@ static bool variant_exists(int mt, int tw, int nw, int depth, int ks = 0)
 // pass (4096 x 12288 at 32 rows: 288 workgroups 19.0 us, 192 workgroups 13.4), and a second kernel or a last arriver costs 2 to 3 us,
 // so one K split on fewer compute units is often ahead (18944 -> 3584 at one row: 280 workgroups 17.2 us, 224 11.5).
 // (8 wavefronts fill half a compute unit's slots, and with these kernels' registers one such workgroup at a time runs on it.)
-static float plan_time(const Plan &p, int M, int N, int K, int &passes)
-{
-    const int groups = K / kGroup, tiles = pad_cols(N) / 16, mt = (M + 15) / 16;
-    const int S = p.S;
-    const float stream = (float)tiles * 16.f * (float)K * 0.52e-6f / 7.f;   // us at 7 TB/s
-    const float partials = (float)M * (float)N * (float)S * 1e-6f;
-    const bool last_arriver = S > 1 && p.fused, two_kernels = S > 1 && !p.fused;
-    float t;
-    if (p.ks == 0) {   // wavefronts that split K
-        const int workgroups = tiles / p.tw * S, gw = (groups + S * p.nw - 1) / (S * p.nw);   // groups of a wavefront
-        const float tw = (float)p.tw, g = (float)gw, fill = (float)(workgroups * p.nw) / 2048.f;
-        t = 2.66f + g * (0.53f + 0.007f * tw - fill * (0.0135f + 0.006f * tw)) + 0.728f * stream + 0.231f * tw + (p.nw == 8 ? 0.368f : 0.f);
-        if (M > 8) t += 0.543f + tw * (0.0146f * g - 0.048f);
-        if (last_arriver) t += 1.13f + (float)S * (0.22f + 0.0037f * tw);
-        if (two_kernels) t += 1.54f + 0.0825f * (float)S + 2.77f * partials;
-        passes = (workgroups * p.nw + 8 * 272 - 1) / (8 * 272);
-    } else {   // column quarters times K sets
-        const int workgroups = (tiles / p.tw + 3) / 4 * S, steps = (groups + S * p.ks - 1) / (S * p.ks);
-        const bool four = p.tw == 4, three = p.ks == 3;
-        const float m = (float)mt, fill = (float)workgroups / 256.f;
-        const float step = 0.388f + 0.134f * m + (four ? 0.183f + 0.064f * m : 0.f) + (three ? 0.052f + 0.073f * m : 0.f) -
-                           (p.depth == 2 ? 0.052f : 0.f) + fill * (float)p.ks * (four ? 0.127f : 0.042f);
-        t = 2.70f + (float)steps * step + 0.303f * stream + 0.614f * m + (four ? 1.165f + 0.225f * m : 0.f) + (three ? 0.42f : 0.f) +
-            (p.depth == 2 ? 0.58f : 0.f);
-        if (last_arriver) t += 2.f + (float)S * (0.076f * m * (float)p.tw - 0.049f);
-        if (two_kernels) t += 1.15f + 0.124f * (float)S + 2.07f * partials;
-        passes = (workgroups + 255) / 256;
+// Every call of such a shape pays for this on the host, so the fits are kept as three sums: what does not depend on the K splits,
+// worked out once per launch shape; the walk along K; and what the splits cost.
+struct PlanTimes {
+    float stream, m, rows_cols;   // time of the weight at 7 TB/s; row tiles; M * N in millions
+    int M, groups, tiles;
+    PlanTimes(int M_, int N, int K) : M(M_), groups(K / kGroup), tiles(pad_cols(N) / 16)
+    {
+        stream = (float)tiles * 16.f * (float)K * 0.52e-6f / 7.f;
+        m = (float)((M + 15) / 16);
+        rows_cols = (float)M * (float)N * 1e-6f;
     }
-    return passes > 1 ? t * (1.f + 0.5f * (float)(passes - 1)) : t;
-}
+};
+struct ShapeTime {
+    int units, ways;   // workgroups per K split, wavefronts (or K sets) that share a K range
+    bool k_sets;
+    float base, group, per_fill, fill_one, last, last_split, second, second_split;
+    ShapeTime(const PlanTimes &c, int tw_, int nw, int depth, int ks)
+    {
+        const float tw = (float)tw_;
+        k_sets = ks > 0;
+        if (!k_sets) {   // wavefronts that split K
+            const bool many = c.M > 8;
+            units = c.tiles / tw_;
+            ways = nw;
+            base = 2.66f + 0.728f * c.stream + 0.231f * tw + (nw == 8 ? 0.368f : 0.f) + (many ? 0.543f - 0.048f * tw : 0.f);
+            group = 0.53f + 0.007f * tw + (many ? 0.0146f * tw : 0.f);
+            per_fill = -(0.0135f + 0.006f * tw);
+            fill_one = (float)nw / 2048.f;
+            last = 1.13f, last_split = 0.22f + 0.0037f * tw;
+            second = 1.54f, second_split = 0.0825f + 2.77f * c.rows_cols;
+        } else {   // column quarters times K sets
+            const bool four = tw_ == 4, three = ks == 3;
+            units = (c.tiles / tw_ + 3) / 4;
+            ways = ks;
+            base = 2.70f + 0.303f * c.stream + 0.614f * c.m + (four ? 1.165f + 0.225f * c.m : 0.f) + (three ? 0.42f : 0.f) + (depth == 2 ? 0.58f : 0.f);
+            group = 0.388f + 0.134f * c.m + (four ? 0.183f + 0.064f * c.m : 0.f) + (three ? 0.052f + 0.073f * c.m : 0.f) - (depth == 2 ? 0.052f : 0.f);
+            per_fill = (float)ks * (four ? 0.127f : 0.042f);
+            fill_one = 1.f / 256.f;
+            last = 2.f, last_split = 0.076f * c.m * tw - 0.049f;
+            second = 1.15f, second_split = 0.124f + 2.07f * c.rows_cols;
+        }
+    }
+    // without what the splits cost
+    float walk(const PlanTimes &c, int S) const { return base + longest(c, S) * (group + crowding(S)); }
+    // no less than this up to `most` splits: the longest walk is shortest there, and a crowding that helps helps most there
+    float least_walk(const PlanTimes &c, int most) const
+    {
+        const float help = crowding(most);
+        return base + longest(c, most) * (group + (help < 0.f ? help : 0.f));
+    }
+    float longest(const PlanTimes &c, int S) const   // groups of the longest walk, rounded up; a float division is the faster one
+    {
+        const float walk = (float)c.groups / (float)(S * ways);
+        const int down = (int)walk;
+        return (float)(down + ((float)down < walk ? 1 : 0));
+    }
+    float crowding(int S) const { return per_fill * (fill_one * (float)(units * S)); }
+    float last_arriver(int S) const { return last + last_split * (float)S; }
+    float second_kernel(int S) const { return second + second_split * (float)S; }
+    float split_cost(int S) const { return last_arriver(S) < second_kernel(S) ? last_arriver(S) : second_kernel(S); }   // grows with S
+    int passes(int S) const { return k_sets ? (units * S + 255) / 256 : (units * S * ways + 8 * 272 - 1) / (8 * 272); }
+};
 
 static size_t partial_bytes(int mt, int nblocks, const Plan &pl, int groups);
 
@@ -1665,35 +1709,59 @@ static size_t partial_bytes(int mt, int nblocks, const Plan &pl, int groups);
 // twentieth where the plain plan itself takes more than one.  On the fitted calls no pick is slower than the plain plan and the
 // mean gain is 12 %; on 116 other shapes and row counts 13 %, up to 1.8 times (5120 -> 13000 at 37 rows 25.9 -> 17.6 us,
 // 12288 x 12288 at one row 25.2 -> 17.0, at 64 rows 47.5 -> 33).
+struct RuleShape { int tw, nw, depth, ks, slots; };   // slots: workgroups that run at once
+constexpr RuleShape kRuleShapes[] = {
+    {2, 4, 1, 0, 512}, {4, 4, 1, 0, 512}, {8, 4, 1, 0, 512}, {2, 8, 1, 0, 256}, {4, 8, 1, 0, 256}, {8, 8, 1, 0, 256},   // one row tile
+    {2, 0, 1, 2, 256}, {2, 0, 2, 2, 256}, {2, 0, 1, 3, 256}, {2, 0, 2, 3, 256}, {4, 0, 1, 2, 256}, {4, 0, 2, 2, 256}, {4, 0, 1, 3, 256}};
+constexpr int kRuleShapeCount = sizeof(kRuleShapes) / sizeof(kRuleShapes[0]);
+struct RuleShapes {   // of a number of row tiles
+    int count = 0;
+    RuleShape v[kRuleShapeCount] = {};
+};
+static constexpr RuleShapes rule_shapes(int mt)
+{
+    RuleShapes r;
+    for (const RuleShape &v : kRuleShapes) {
+        if ((mt == 1) != (v.ks == 0) || !variant_exists(mt, v.tw, v.nw, v.depth, v.ks)) continue;
+        if (mt > 2 && v.depth == 2 && (v.tw != 2 || v.ks != 2)) continue;   // not among the measured ones
+        r.v[r.count++] = v;
+    }
+    return r;
+}
+constexpr RuleShapes kRuleShapesOf[4] = {rule_shapes(1), rule_shapes(2), rule_shapes(3), rule_shapes(4)};
+
 static Plan predicted_plan(const Plan &plain, int M, int N, int K)
 {
     // what the caller's workspace and the built-in scratch have to hold does not grow beyond the latter
     constexpr size_t kRoom = (size_t)32 << 20;
-    const int groups = K / kGroup, nblocks = pad_cols(N) / kBlockCols, tiles = nblocks * kTiles, mt = (M + 15) / 16;
+    const int groups = K / kGroup, nblocks = pad_cols(N) / kBlockCols, mt = (M + 15) / 16;
     if (partial_bytes(mt, nblocks, plain, groups) > kRoom) return plain;
+    const PlanTimes call(M, N, K);
     Plan best = plain;
-    int passes;
-    float least = plan_time(plain, M, N, K, passes);
-    least *= passes > 1 ? 0.95f : 0.87f;
-    static const struct { int tw, nw, depth, ks; } kShapes[] = {
-        {2, 4, 1, 0}, {4, 4, 1, 0}, {8, 4, 1, 0}, {2, 8, 1, 0}, {4, 8, 1, 0}, {8, 8, 1, 0},                              // one row tile
-        {2, 0, 1, 2}, {2, 0, 2, 2}, {2, 0, 1, 3}, {2, 0, 2, 3}, {4, 0, 1, 2}, {4, 0, 2, 2}, {4, 0, 1, 3}};               // more
-    for (const auto &v : kShapes) {
-        if ((mt == 1) != (v.ks == 0) || !variant_exists(mt, v.tw, v.nw, v.depth, v.ks)) continue;
+    float least;
+    {
+        const ShapeTime t(call, plain.tw, plain.nw, plain.depth, plain.ks);
+        const int passes = t.passes(plain.S);
+        least = t.walk(call, plain.S) + (plain.S == 1 ? 0.f : plain.fused ? t.last_arriver(plain.S) : t.second_kernel(plain.S));
+        least *= passes > 1 ? 0.95f * (1.f + 0.5f * (float)(passes - 1)) : 0.87f;
+    }
+    const RuleShapes &shapes = kRuleShapesOf[mt - 1];
+    for (int k = 0; k < shapes.count; ++k) {
+        const RuleShape &v = shapes.v[k];
         if (v.ks > 0 && staged_steps(v.tw, v.depth) && K > kStagedMaxK) continue;
-        if (mt > 2 && v.depth == 2 && (v.tw != 2 || v.ks != 2)) continue;   // not among the measured ones
-        const int units = v.ks ? (tiles / v.tw + 3) / 4 : tiles / v.tw, ways = v.ks ? v.ks : v.nw;
-        int most = (v.ks ? 256 : 2048 / v.nw) / units;
-        most = most > 16 ? 16 : most;
-        most = most > groups / ways ? groups / ways : most;
+        const ShapeTime t(call, v.tw, v.nw, v.depth, v.ks);
+        const int fit = (int)((float)v.slots / (float)t.units), deep = (int)((float)groups / (float)t.ways);
+        int most = fit < 16 ? fit : 16;
+        most = most > deep ? deep : most;
+        if (most < 1 || t.least_walk(call, most) >= least) continue;
         const int splits[5] = {1, 2, most / 2, most * 3 / 4, most};
         for (int i = 0; i < 5; ++i) {
-            if (splits[i] < 1 || splits[i] > most || (i > 1 && splits[i] <= splits[i - 1])) continue;
-            for (int fused = 0; fused < (splits[i] > 1 ? 2 : 1); ++fused) {
-                const Plan p = {v.tw, v.nw, v.depth, splits[i], splits[i] > 1 ? fused : plain.fused, v.ks, 0};
-                const float t = plan_time(p, M, N, K, passes);
-                if (t < least && partial_bytes(mt, nblocks, p, groups) <= kRoom) least = t, best = p;
-            }
+            const int S = splits[i];
+            if (S < 1 || S > most || (i > 1 && S <= splits[i - 1])) continue;
+            if (i == 1 && t.least_walk(call, most) + t.split_cost(2) >= least) break;   // nor does any other split
+            const float sum = t.walk(call, S) + (S > 1 ? t.split_cost(S) : 0.f);   // one pass: S is at most what the chip holds
+            const Plan p = {v.tw, v.nw, v.depth, S, S > 1 ? t.last_arriver(S) < t.second_kernel(S) : plain.fused, v.ks, 0};
+            if (sum < least && partial_bytes(mt, nblocks, p, groups) <= kRoom) least = sum, best = p;
         }
     }
     return best;
@@ -1728,11 +1796,16 @@ static Plan choose_plan(int M, int N, int K, bool least = false)
                 if (p.fused_reduce != 2) pl.fused = p.fused_reduce;
                 return pl;
             }
+        const auto take_row = [&](const TunedRow &r) {
+            if (r.N != N || r.K != K || r.mt != row_bucket(M) || !variant_exists(mt, r.tw, r.nw, r.depth, r.ks)) return false;
+            best = {r.tw, r.nw, r.depth, r.S, r.fused, r.ks, 0};
+            return true;
+        };
         for (const TunedRow &r : kTuned)
-            if (r.N == N && r.K == K && r.mt == row_bucket(M) && variant_exists(mt, r.tw, r.nw, r.depth, r.ks))
-                best = {r.tw, r.nw, r.depth, r.S, r.fused, r.ks, 0};
-        for (const TunedRow &r : kTunedLeast)
-            if (least && r.N == N && r.K == K && r.mt == row_bucket(M)) best = {r.tw, r.nw, r.depth, r.S, r.fused, r.ks, 0};
+            if (take_row(r)) break;
+        if (least)
+            for (const TunedRow &r : kTunedLeast)
+                if (take_row(r)) break;
     }
     const bool by_rule = free_choice && best.tw == 0;   // no measured row
     if (p.k_sets > 0) {   // forced: the high-occupancy column-split variant
@@ -1756,25 +1829,33 @@ static Plan choose_plan(int M, int N, int K, bool least = false)
     if (best.tw == 0) {
         const int forced_s = p.split_k > 0 ? (p.split_k < groups ? p.split_k : groups) : 0;
         double best_cost = 1e30;
-        for (int tw = 8; tw >= 2; tw >>= 1) {
+        for (int lg_tw = 3; lg_tw >= 1; --lg_tw) {
+            const int tw = 1 << lg_tw;
             if (p.tiles_per_wave > 0 && tw != p.tiles_per_wave) continue;
-            for (int nw = 1; nw <= 16; nw = (nw == 1 ? 4 : nw << 1)) {
+            for (int lg_nw = 0; lg_nw <= 4; lg_nw += lg_nw == 0 ? 2 : 1) {   // shifts: integer divisions were most of the time of this rule
+                const int nw = 1 << lg_nw;
                 if (p.waves_per_wg > 0 ? nw != p.waves_per_wg : (nw == 16 || nw == 1)) continue;
+                const int units = nw == 1 ? ((tiles >> lg_tw) + 3) / 4 : tiles >> lg_tw;   // workgroups per K split
+                int cap = groups >> (lg_nw + 1) > 0 ? groups >> (lg_nw + 1) : 1;   // two groups per wavefront (sharing a K range) at least
+                if (cap > 16) cap = 16;
                 for (int depth = 1; depth <= 4; depth <<= 1) {
                     if (p.prefetch_depth > 0 ? depth != p.prefetch_depth : depth != 1) continue;
-                    if (!variant_exists(mt, tw, nw, depth)) continue;
-                    const int units = nw == 1 ? (tiles / tw + 3) / 4 : tiles / tw;   // workgroups per K split
-                    const int kways = nw == 1 ? 1 : nw;                        // wavefronts sharing a K range
-                    int cap = groups / (2 * kways) > 0 ? groups / (2 * kways) : 1;   // two groups per wavefront at least
-                    if (cap > 16) cap = 16;
-                    for (int s = forced_s ? forced_s : 1; s <= (forced_s ? forced_s : cap); ++s) {
+                    if (depth == 1 ? !kSplitVariants.v[mt - 1][tw][nw] : !variant_exists(mt, tw, nw, depth)) continue;
+                    // largest split first: once the chip is too empty for the first term alone, smaller ones are worse still
+                    for (int s = forced_s ? forced_s : cap; s >= (forced_s ? forced_s : 1); --s) {
                         const double fill = (double)units * s / 256.0;         // workgroups per compute unit
+                        // the terms below, none of them negative, reordered (hence the allowance for rounding)
+                        const double room = best_cost + 1e-9 - 0.05 * mt * ((8 >> lg_tw) - 1);
+                        if (1.5 > (room + 1.5) * fill) break;                   // 1.5 (1 / fill - 1) > room
+                        if (0.06 * mt * (s - 1) + 0.25 * (fill - 1) > room || 1.5 > (room - 0.06 * mt * (s - 1) + 1.5) * fill) continue;
                         double cost = fill >= 1 ? 0.25 * (fill - 1) : 1.5 * (1 / fill - 1);
                         cost += 0.06 * mt * (s - 1);                            // partial-sum round trip
-                        cost += 0.05 * mt * (8 / tw - 1);                       // x-fragment reuse
+                        cost += 0.05 * mt * ((8 >> lg_tw) - 1);                 // x-fragment reuse
                         cost += (mt > 1 && nw > 4) ? 0.3 : 0.0;                 // registers: big tiles want 4 wavefronts
                         cost += (mt == 1 && nw == 4 && units * s < 384) ? 0.3 : 0.0;
-                        if (groups % (s * kways) != 0) cost += 0.2;            // uneven work per wavefront
+                        if (cost >= best_cost) continue;
+                        const int even = (int)((float)groups / (float)(s << lg_nw));   // exact where it matters: a multiple divides exactly
+                        if (even * (s << lg_nw) != groups) cost += 0.2;        // uneven work per wavefront
                         if (cost < best_cost) { best_cost = cost; best = {tw, nw, depth, s, mt == 1, 0, 0}; }
                     }
                 }
@@ -1996,17 +2077,34 @@ size_t w4a16_workspace_bytes(int M_max, int N, int K, int G)
     return kTicketBytes + need;
 }
 
-static int gemm_entry(const void *x, const void *packed, const Out &out, int M, int N, int K, int G, void *workspace,
-                      size_t workspace_bytes, void *stream)
+static int check_gemm(const void *x, const void *packed, const void *y, int M, int N, int K, int G)
 {
-    int rc = check_weight_shape(N, K, G);
+    const int rc = check_weight_shape(N, K, G);
     if (rc != W4A16_OK) return rc;
     if (M < 1) return W4A16_EINVAL;
     if (M > W4A16_MAX_M) return W4A16_EUNSUP;
-    if (!x || !packed || !out.y) return W4A16_ENULL;
-    if (misaligned(x) || misaligned(packed) || misaligned(out.y) || workspace_misaligned(workspace)) return W4A16_EALIGN;
+    if (!x || !packed || !y) return W4A16_ENULL;
+    return misaligned(x) || misaligned(packed) || misaligned(y) ? W4A16_EALIGN : W4A16_OK;
+}
+
+static int run_plan(Plan pl, const void *x, const void *packed, const Out &out, int M, int N, int K, void *workspace, void *stream)
+{
     const int nblocks = pad_cols(N) / kBlockCols;
-    const int mt = (M + 15) / 16;
+    // one ticket per column unit: only the last-arriver sums use them
+    const bool wants_tickets = pl.S == 0 || (pl.S > 1 && pl.fused && pl.nw != 1);
+    if (wants_tickets && nblocks * kTiles / pl.tw > kMaxTickets) {
+        if (pl.S == 0) return W4A16_EUNSUP;   // the even split has no two-kernel form
+        pl.fused = 0;                         // same K split, summed by the second kernel
+    }
+    return dispatch((M + 15) / 16, pl, x, packed, out, M, N, K, workspace, (hipStream_t)stream);
+}
+
+static int gemm_entry(const void *x, const void *packed, const Out &out, int M, int N, int K, int G, void *workspace,
+                      size_t workspace_bytes, void *stream)
+{
+    const int rc = check_gemm(x, packed, out.y, M, N, K, G);
+    if (rc != W4A16_OK) return rc;
+    if (workspace_misaligned(workspace)) return W4A16_EALIGN;
     Plan pl = choose_plan(M, N, K);
     if (pl.tw == 0) return W4A16_EUNSUP;
     const size_t room = workspace && workspace_bytes > kTicketBytes ? workspace_bytes - kTicketBytes : 0;
@@ -2014,13 +2112,7 @@ static int gemm_entry(const void *x, const void *packed, const Out &out, int M, 
         pl = choose_plan(M, N, K, true);
         if (plan_need(pl, M, N, K) > room) return W4A16_EWORKSPACE;
     }
-    // one ticket per column unit: only the last-arriver sums use them
-    const bool wants_tickets = pl.S == 0 || (pl.S > 1 && pl.fused && pl.nw != 1);
-    if (wants_tickets && nblocks * kTiles / pl.tw > kMaxTickets) {
-        if (pl.S == 0) return W4A16_EUNSUP;   // the even split has no two-kernel form
-        pl.fused = 0;                         // same K split, summed by the second kernel
-    }
-    return dispatch(mt, pl, x, packed, out, M, N, K, workspace, (hipStream_t)stream);
+    return run_plan(pl, x, packed, out, M, N, K, workspace, stream);
 }
 
 // ---- w4a16_gemm for callers that cannot allocate a workspace ---------------------------------------
@@ -2048,12 +2140,8 @@ static int static_scratch(void **ptr)
 
 int w4a16_gemm_static(const void *x, const void *packed, void *y, int M, int N, int K, int G, void *stream)
 {
-    int rc = check_weight_shape(N, K, G);
+    int rc = check_gemm(x, packed, y, M, N, K, G);
     if (rc != W4A16_OK) return rc;
-    if (M < 1) return W4A16_EINVAL;
-    if (M > W4A16_MAX_M) return W4A16_EUNSUP;
-    if (!x || !packed || !y) return W4A16_ENULL;
-    if (misaligned(x) || misaligned(packed) || misaligned(y)) return W4A16_EALIGN;
     const Plan pl = choose_plan(M, N, K);
     if (pl.tw == 0) return W4A16_EUNSUP;
     if (plan_need(pl, M, N, K) > kStaticScratchPartials) return W4A16_EWORKSPACE;   // this shape needs more than the built-in scratch holds
@@ -2064,7 +2152,7 @@ int w4a16_gemm_static(const void *x, const void *packed, void *y, int M, int N, 
     // not: they are cleared here (a fill kernel, so the call can be captured in a graph) whenever they are used.
     if (pl.S == 0 || (pl.S > 1 && pl.fused && pl.nw != 1))
         if ((rc = w4a16_workspace_init(ws, kStaticScratchBytes, stream)) != W4A16_OK) return rc;
-    return gemm_entry(x, packed, Out{(_Float16 *)y, nullptr, kEpiNone}, M, N, K, G, ws, kStaticScratchBytes, stream);
+    return run_plan(pl, x, packed, Out{(_Float16 *)y, nullptr, kEpiNone}, M, N, K, ws, stream);
 }
 
 int w4a16_plan_describe(int M, int N, int K, int G, int *out)
