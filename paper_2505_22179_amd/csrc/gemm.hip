@@ -1237,6 +1237,7 @@ __device__ __forceinline__ void cs_segment(const _Float16 *__restrict__ x, const
         constexpr int kStepLoads = TW + 1 + (SYM ? 0 : 1);   // code, scale and zero-point loads of a step
         if (mine > 0) copy_x(0, 0);
         if (mine > 1) copy_x(1, 1);
+        __builtin_amdgcn_sched_barrier(0);   // x before the codes: the wait below counts on it
 #pragma unroll
         for (int d = 0; d < DEPTH; ++d)
             if (d < mine) {
@@ -1246,8 +1247,9 @@ __device__ __forceinline__ void cs_segment(const _Float16 *__restrict__ x, const
                 for (int t = 0; t < TW; ++t)
                     w[d][t] = stream_quad(recs, code_off + (uint32_t)(t * 1024), rec);
             }
-        if (mine >= DEPTH) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(DEPTH * kStepLoads) : "memory");   // the x tiles, not the codes
+        if (mine >= DEPTH) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(DEPTH * kStepLoads) : "memory");   // the x tiles
         else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        // (the compiler waits for everything at this one barrier, the first codes too; at those of the steady loop it adds nothing)
         __syncthreads();
         if (mine > 0) {
 #pragma unroll

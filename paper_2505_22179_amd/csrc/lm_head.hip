@@ -140,8 +140,8 @@ __global__ __launch_bounds__(256) void lm_head_logits_kernel(const _Float16 *__r
 // Logits of more than 16 rows.  There the x fragments, not the weights, filled the load path of the kernel above: every
 // wavefront fetched its own (sixteen rows x 64 bytes a load, the costliest pattern for a compute unit's address path,
 // as many loads as for the weights).  Here the NW wavefronts of a workgroup walk k together on TWL tiles each and
-// share the x tile of a macro step through LDS: whole cache lines, global -> LDS directly, two steps ahead into three
-// buffers, one barrier per step.  The tile is kept as MTL * 4 blocks of 1 KB, block (mt, jp, h) = rows 16 mt + 8 h .. + 7
+// share the x tile of a macro step through LDS: whole cache lines, global -> LDS directly, requested two steps ahead into
+// three buffers (and waited for one step later, see below), one barrier per step.  The tile is kept as MTL * 4 blocks of 1 KB, block (mt, jp, h) = rows 16 mt + 8 h .. + 7
 // times the 128 bytes of blocks 2 jp and 2 jp + 1 of the step; the eight 16-byte chunks of a row sit at
 // chunk ^ (4 h + row / 2), which spreads a fragment read over all LDS banks.  Workgroups start their k walk at
 // different steps, as above.  What bounds it is the weight stream: V = 128256, 60 rows, K = 8192: 475 -> 330 us for the whole
@@ -209,6 +209,7 @@ __global__ __launch_bounds__(64 * NW, 2) void lm_head_logits_shared_kernel(const
         for (int mt = 0; mt < MTL; ++mt) acc[t][mt] = (float4v){0.f, 0.f, 0.f, 0.f};
     copy_x(0, 0);
     if (steps > 1) copy_x(1, 1);
+    __builtin_amdgcn_sched_barrier(0);   // the counted waits below rely on the order of these requests, here and in step()
 #pragma unroll
     for (int d = 0; d < DEPTH; ++d)
         if (d < steps)   // uniform
@@ -220,6 +221,7 @@ __global__ __launch_bounds__(64 * NW, 2) void lm_head_logits_shared_kernel(const
     auto step = [&](int s, int slot, bool more_w, bool more_x) {
         __syncthreads();
         if (more_x) copy_x(s + 2, b_free);
+        __builtin_amdgcn_sched_barrier(0);   // x before the weights of this step: kNewer counts on it
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             u32x4 xf[MTL];
@@ -241,7 +243,10 @@ __global__ __launch_bounds__(64 * NW, 2) void lm_head_logits_shared_kernel(const
     };
     // A step's barrier says that its x tile is complete, so every wavefront first waits for its own share of it.  Newer
     // than that share are, from the third step on, the weights requested in the two steps before and one x share; in
-    // the first two steps at least the DEPTH steps of weights the walk starts with.
+    // the first two steps at least the DEPTH steps of weights the walk starts with.  These counts are the least that is
+    // needed.  What runs is stricter: __syncthreads is a fence of the workgroup, and the compiler waits there for every copy into
+    // LDS that it sees under way, vmcnt(0) at the first step of a trip of the loop and vmcnt(4 TWL) at the others, so
+    // at most one step of weights stays in flight across a barrier.
     constexpr int kStepLoads = 4 * TWL, kNewer = 2 * kStepLoads + MTL * 4 / NW;
     static_assert(kNewer < 64 && DEPTH * kStepLoads < 64, "the wait counter has six bits");
     constexpr int kAhead = DEPTH > 2 ? DEPTH : 2;   // how far the requests of a step reach
