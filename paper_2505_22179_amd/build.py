@@ -27,7 +27,7 @@ def stale() -> bool:
     if not os.path.exists(LIB):
         return True
     t = os.path.getmtime(LIB)
-    deps = sources() + glob.glob(os.path.join(CSRC, "*.h")) + glob.glob(os.path.join(INCLUDE, "*.h"))
+    deps = sources() + [f for d, ext in ((CSRC, "*.h"), (CSRC, "*.inc"), (INCLUDE, "*.h")) for f in glob.glob(os.path.join(d, ext))]
     return any(os.path.getmtime(d) > t for d in deps)
 
 

@@ -88,14 +88,14 @@ def candidates(N: int, K: int, M: int):
                 for depth in (1, 2):
                     for S in (1, 2, 3, 4, 5, 6, 8, 10, 12, 16):
                         wgs = ((N // 16) // tw + 3) // 4 * S
-                        if wgs < 160 or wgs > 2048 or S * ks * 2 > K // G:
+                        if wgs < 128 or wgs > 2048 or S * ks * 2 > K // G:
                             continue
                         for fused in ((0,) if S == 1 else (0, 1)):
                             yield (tw, 0, depth, S, fused, ks, 0)
     for tw in (8, 4, 2):
         for nw in (1, 4, 8, 16):   # 1 = column-split workgroup sharing x through LDS
             for depth in (1, 2, 4):
-                for S, fused in ((1, 1), (2, 1), (2, 0), (3, 0), (4, 1), (4, 0), (6, 0), (8, 0)):
+                for S, fused in ((1, 1), (2, 1), (2, 0), (3, 1), (3, 0), (4, 1), (4, 0), (6, 0), (8, 0)):
                     units = (N // 16) // tw
                     waves = units * S * (nw if nw > 1 else 1)
                     if waves < 768 or waves > 16384 or S * max(nw, 2) > K // G or (nw == 1 and fused == 1 and S > 1):
