@@ -354,6 +354,11 @@ int w4a16_plan_describe(int M, int N, int K, int G, int *out);
  * workspace gets too.  Host only: touches no GPU.  Errors as tree_verify_attn's size and workspace checks. */
 int tree_verify_attn_plan_describe(int M, int P, int Hq, int Hkv, int D, size_t workspace_bytes, int *out);
 
+/* The logits kernel lm_head_topk would run with the current knobs.  out receives 3 ints: [0] 1 if the wavefronts of a
+ * workgroup share x through LDS, 0 if each fetches its own, [1] wavefronts per workgroup, [2] vocabulary tiles per
+ * wavefront.  Host only: touches no GPU.  Errors as lm_head_topk's shape checks. */
+int lm_head_plan_describe(int M, int V, int K, int *out);
+
 /* Measurement aid, not part of the method: enqueues a kernel that only reads the first
  * bytes - bytes % 16 bytes of `buf` with 16-byte streaming loads (one 32 KB chunk per workgroup)
  * and writes nothing, except -- practically never -- one 32-bit word to `sink` (4-byte aligned, device)

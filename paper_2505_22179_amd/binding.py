@@ -18,7 +18,7 @@ EXPORTS = (
     "w4a16_gemm", "w4a16_gemm_fused", "w4a16_gemm_rope", "w4a16_pack_heads", "w4a16_pack_gate_up", "w4a16_read_probe", "tree_verify_attn_workspace_bytes",
     "tree_verify_attn", "tree_accept", "rms_norm", "rope_append", "lm_head_workspace_bytes", "lm_head_topk",
     "lm_head_packed_bytes", "lm_head_pack", "w4a16_decoder_layer", "w4a16_plan_describe", "w4a16_gemm_static", "w4a16_weight_is_symmetric",
-    "tree_verify_attn_plan_describe",
+    "tree_verify_attn_plan_describe", "lm_head_plan_describe",
 )
 
 EPI_NONE, EPI_RESIDUAL, EPI_SILU_MUL = 0, 1, 2
@@ -93,6 +93,7 @@ def load() -> ctypes.CDLL:
     L.lm_head_pack.argtypes = [vp, vp, i, i, vp]
     L.lm_head_workspace_bytes.restype = sz
     L.lm_head_workspace_bytes.argtypes = [i, i, i, i]
+    L.lm_head_plan_describe.argtypes = [i, i, i, ctypes.POINTER(ctypes.c_int)]
     L.lm_head_topk.argtypes = [vp, vp, i, i, i, i, vp, vp, vp, vp, sz, vp]
     _lib = L
     return L
@@ -250,6 +251,13 @@ def lm_head_topk(x, packed, M: int, V: int, K: int, top_k: int, logits, top_idx,
     nbytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     _check(load().lm_head_topk(_ptr(x), _ptr(packed), M, V, K, top_k, _ptr(logits), _ptr(top_idx), _ptr(top_logprob),
                                _ptr(workspace), nbytes, _stream()), "lm_head_topk")
+
+
+def lm_head_plan_describe(M: int, V: int, K: int) -> tuple:
+    """(x shared through LDS, wavefronts per workgroup, tiles per wavefront); host only"""
+    out = (ctypes.c_int * 3)()
+    _check(load().lm_head_plan_describe(M, V, K, out), "lm_head_plan_describe")
+    return tuple(out)
 
 
 def w4a16_read_probe(buf, nbytes: int, sink) -> None:

@@ -578,6 +578,19 @@ size_t lm_head_workspace_bytes(int M, int V, int K, int top_k)
     return slots * 2 * sizeof(float) + slots * top_k * (sizeof(float) + sizeof(int)) + 256;
 }
 
+int lm_head_plan_describe(int M, int V, int K, int *out)
+{
+    if (!out) return W4A16_ENULL;
+    const int rc = check_lm_head(M, V, K, 1);
+    if (rc != W4A16_OK) return rc;
+    const LmPlan plan = lm_plan(M, (V + 15) / 16, K);
+    if (plan.nw == 0) return W4A16_EUNSUP;
+    out[0] = plan.shared;
+    out[1] = plan.nw;
+    out[2] = plan.twl;
+    return W4A16_OK;
+}
+
 int lm_head_topk(const void *x, const void *packed, int M, int V, int K, int top_k, float *logits, int32_t *top_idx,
                  float *top_logprob, void *workspace, size_t workspace_bytes, void *stream)
 {

@@ -119,6 +119,15 @@ def test_plan_describe():
         B.w4a16_set_param("waves_per_wg", 0)
 
 
+def test_lm_head_plan_describe():
+    lib, out = B.load(), (ctypes.c_int * 3)()
+    assert lib.lm_head_plan_describe(10, 128256, 4096, None) == -2
+    assert lib.lm_head_plan_describe(0, 128256, 4096, out) == -1
+    assert lib.lm_head_plan_describe(65, 128256, 4096, out) == -4
+    assert B.lm_head_plan_describe(1, 128256, 4096) == (0, 4, 1) and B.lm_head_plan_describe(10, 128256, 4096) == (0, 4, 2)
+    assert B.lm_head_plan_describe(60, 128256, 8192)[0] == 1
+
+
 def test_product_never_imports_the_oracle():
     pkg = os.path.join(ROOT, "paper_2505_22179_amd")
     bad = re.compile(r"^\s*(from|import)\s+oracle\b|liboracle|w4a16_oracle|#include\s+\"[^\"]*oracle", re.M)

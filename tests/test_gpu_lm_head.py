@@ -87,15 +87,28 @@ def test_lm_head_parity(M, K, V, top_k):
                                    (64, 128, 66000), (17, 2048, 40000), (64, 1152, 66000)])
 def test_lm_head_shared_rows(M, K, V):
     """more than 16 rows share x through LDS: walks shorter than the pipeline (1 to 5 steps), tiles that do not fill the
-    last workgroup, vocabularies that are no multiple of 4 (scalar stores), both kernels and every number of tiles per
-    workgroup of the size rule (fp32 sums: the tolerance of check())"""
+    last workgroup, vocabularies that are no multiple of 4 (scalar stores), every number of tiles per workgroup, and what
+    the size rule picks (fp32 sums: the tolerance of check())"""
     x, W = I.make_lm_head(9900 + M + K + V, M, K, V)
     try:
         for tiles_per_wave in (0, 1, 2, 4):
             B.w4a16_set_param("lm_tiles", tiles_per_wave)
+            assert tiles_per_wave == 0 or B.lm_head_plan_describe(M, V, K) == (1, 8, tiles_per_wave)
             check(x, W, 3, f"M={M} K={K} V={V} tiles per wavefront {tiles_per_wave}")
     finally:
         B.w4a16_set_param("lm_tiles", 0)
+
+
+@pytest.mark.parametrize("M,K,V", [(64, 2048, 49501), (32, 2048, 33001), (48, 1024, 34000),   # an even number of k steps
+                                   (17, 1152, 34000), (48, 896, 33001),                       # an odd one
+                                   (50, 2 ** 20 + 128, 70)])                                  # beyond the 32-bit offsets of the other
+def test_lm_head_private_rows(M, K, V):
+    """more than 16 rows in the kernel whose wavefronts fetch their own x, where the size rule keeps it: two, three and
+    four row tiles, whole and partial rings of k steps"""
+    assert B.lm_head_plan_describe(M, V, K) == (0, 4, 4)
+    x, W = I.make_lm_head(9950 + M + V, M, K, V, w_std=0.02 if K < 10000 else 0.001)
+    print(f"lm_head private rows M={M} K={K} V={V}", flush=True)
+    check(x, W, 3, f"M={M} K={K} V={V}")
 
 
 def test_lm_head_full_vocabulary():
