@@ -1044,8 +1044,10 @@ __device__ __forceinline__ void compute_group_lean(const u32x4 (&a)[MT][4], Quan
 // the products of the tile before it.  An x fragment is read from LDS once per group and lives for one step (two in
 // registers), x itself travels global -> LDS without passing through registers, and loads address through buffer
 // descriptors (no 64-bit lane addresses): that pays for the partial sums of all tiles and, with two tiles, for a second group
-// of codes in flight.  What bounds it at 64 rows is the power budget -- 2.35 GHz while the same kernel only streams
-// or only expands, 1.75 GHz with products and stream together -- so what helps is less work beside the products:
+// of codes in flight.  What bounds it at 64 rows (70B gate_up, stamps inside the kernel): expansion and products alone cost a SIMD 449
+// cycles per tile and group, 48.5 us at 2.37 GHz -- they share its issue port; the loads beside them add 63 cycles, and the power that all
+// of it draws lowers the clock to 2.04 GHz (1.77 on another card): 64.3 us.  The stream alone takes 43.7 us, with the expansion
+// beside it 45.1.  So what helps is less issue beside the products:
 // sixteen LDS reads of x and their waits at the head of every group, and the copies of x through registers, are gone.
 // Against the tile-by-tile form above, on weights that come from HBM: 70B gate_up 76.2 -> 72.8 us at 64 rows, 64.6 -> 62.0
 // at 48, 52.2 -> 51.4 at 32; 70B down at 64 rows 45.5 -> 42.8, 8B gate_up at 60 rows 24.8 -> 23.7.
@@ -1146,7 +1148,7 @@ __device__ __forceinline__ void compute_group_staged(u32x4 (&a)[kFragRing][MT], 
 // tiles; wavefront (kset, colq) = (index / 4, index % 4) works on the TW tiles of column quarter
 // colq and on every KS-th quantisation group starting at kset, so KS wavefronts share each SIMD.
 // Per step the workgroup parks the x fragments of KS consecutive groups in LDS (operand order,
-// double-buffered, one barrier per step); the KS partial sums of a column meet in LDS at the end.
+// two buffers, three in the staged form; one barrier per step); the KS partial sums of a column meet in LDS at the end.
 // One (column unit, group range) segment of the kernel below: groups g_begin .. g_end-1 of workgroup
 // unit wg_unit.  nslots == 1: the segment is the unit's whole K and its sums are stored.  Otherwise it
 // is contributor `slot` of `nslots` (ascending group ranges) and its sums go to the workspace, slot
@@ -1163,7 +1165,7 @@ __device__ __forceinline__ void cs_segment(const _Float16 *__restrict__ x, const
     constexpr int R = 4 * TW * MT;                 // accumulator registers per lane
     constexpr int E4 = R * 16;                     // float4 results per wavefront
     constexpr int kBufQuads = KS * MT * 4 * 64;    // 16-byte fragments of one step's x tiles
-    u32x4 *xa = reinterpret_cast<u32x4 *>(lds4);   // [2][KS][MT*4][64]
+    u32x4 *xa = reinterpret_cast<u32x4 *>(lds4);   // [2, staged 3][KS][MT*4][64]
     float4v *out4 = lds4;                          // [4*KS wavefronts][E4], reuses the x tiles after the loop
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);

@@ -144,8 +144,9 @@ __global__ __launch_bounds__(256) void lm_head_logits_kernel(const _Float16 *__r
 // three buffers (and waited for one step later, see below), one barrier per step.  The tile is kept as MTL * 4 blocks of 1 KB, block (mt, jp, h) = rows 16 mt + 8 h .. + 7
 // times the 128 bytes of blocks 2 jp and 2 jp + 1 of the step; the eight 16-byte chunks of a row sit at
 // chunk ^ (4 h + row / 2), which spreads a fragment read over all LDS banks.  Workgroups start their k walk at
-// different steps, as above.  What bounds it is the weight stream: V = 128256, 60 rows, K = 8192: 475 -> 330 us for the whole
-// call (6.6 TB/s of weights in this kernel), K = 4096: 249 -> 184; 24 rows, K = 8192: 359 -> 330, K = 4096: 185 -> 175.
+// different steps, as above.  What bounds it is the weight stream where it is long (V = 128256, K = 8192, 60 rows: 6.6 TB/s of weights);
+// shorter walks also wait for their first tiles and at the barriers.  Whole call, top 1, V = 128256, against the kernel
+// above: 60 rows, K = 8192 476 -> 333 us, K = 4096 250 -> 185; 24 rows, K = 8192 358 -> 328, K = 4096 183 -> 177.
 constexpr int kLmSharedMaxK = 1 << 20;   // its descriptors and offsets are 32-bit (M * K * 2 and TWL * K * 32 bytes); wider heads take the kernel above
 template <int MTL, int NW, int TWL, int DEPTH>
 __global__ __launch_bounds__(64 * NW, 2) void lm_head_logits_shared_kernel(const _Float16 *__restrict__ x,
@@ -506,14 +507,14 @@ __global__ __launch_bounds__(kLmThreads) void lm_head_merge_kernel(const float *
 // the hidden-state rows differ (K = 4096: M = 16 240 -> 194 us with two); a single row is a broadcast and runs best with one.
 // More rows share x through LDS.  A workgroup then takes T = 4, 8, 16 or 32 tiles and a compute unit works on about one at a
 // time, so the call takes about rounds x T: the T with the least of it, where a smaller T also shares x less
-// (V = 128256, where 8, 16 and 32 tie at a multiple of 256 workgroups: 204 / 194 / 175 us at 24 rows, K = 4096).  With T by this
-// rule against four tiles per wavefront throughout: V = 4000 101 -> 32 us, 32000 110 -> 62, 50000 117 -> 82 (60 rows, K = 4096).
+// (V = 128256, where 8, 16 and 32 tie at a multiple of 256 workgroups: 204 / 192 / 177 us at 24 rows, K = 4096).  With T by this
+// rule against 32 throughout: V = 4000 104 -> 32 us, 32000 113 -> 62, 50000 120 -> 82 (60 rows, K = 4096).
 // Short walks amortise the fill of the pipeline over too few steps: up to K = 1024 at most eight tiles (V = 128256, 60 rows:
-// 85 us with 32, 72 with 8, 73 in the kernel above), and with fewer rows the kernel above, whose wavefronts need no barrier, stays
-// ahead beyond one such round (V = 128256: K = 1024 55 against 62 us at 24 rows, 62 against 68 at 40; K = 2048 94 against 95 at
+// 84 us with 32, 71 with 8, 73 in the kernel above), and with fewer rows the kernel above, whose wavefronts need no barrier, stays
+// ahead beyond one such round (V = 128256: K = 1024 55 against 63 us at 24 rows, 62 against 67 at 40; K = 2048 95 against 97 at
 // 24).  It also does where 16 tiles fill the chip and K is a power of two, so that all tiles of a workgroup ask the same memory
-// channels at any moment (V = 64000: K = 4096 91 against 99 us at 24 rows, K = 2048 57 against 72 at 40 and 68 against 70 at 60;
-// but K = 3840 89 against 84 at 24 rows, and K = 4096 104 against 100 at 40).
+// channels at any moment (V = 64000: K = 4096 91 against 101 us at 24 rows, K = 2048 57 against 68 at 40 and 68 against 70 at 60;
+// but K = 3840 90 against 84 at 24 rows, and K = 4096 103 against 100 at 40).  (All: whole call, top 1, two weight copies in turn.)
 struct LmPlan { bool shared; int nw, twl; };
 static LmPlan lm_plan(int M, int tiles, int K)
 {
