@@ -318,7 +318,8 @@ int lm_head_topk(const void *x, const void *packed, int M, int V, int K, int top
  * wavefront owns that many quantisation groups and requests all of their weights up front; needs
  * K / 128 == split_k * waves_per_wg * flat_groups); a combination that is not compiled, or that
  * does not fit the shape, makes w4a16_gemm return W4A16_EUNSUP,
- * "attn_splits" (0 = by size, else the number of key ranges per row tile in tree_verify_attn, at most 32),
+ * "attn_splits" (0 = by size, else the number of key ranges per row tile in tree_verify_attn, at most 32 and
+ * as many as the stated workspace holds),
  * "attn_pack" (how the rows of a KV group are cut into row tiles in tree_verify_attn: 0 = by size;
  * 1 = one tile per query head always; 2 = the whole group in one tile whenever it fits 64 rows; 3 = the whole group cut
  * evenly into as few tiles as 64 rows allow; 10 + d = exactly d heads per tile
