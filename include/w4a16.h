@@ -277,7 +277,8 @@ size_t lm_head_packed_bytes(int V, int K);
  * `packed` receives lm_head_packed_bytes(V, K) bytes. */
 int lm_head_pack(const void *W, void *packed, int V, int K, void *stream);
 
-/* Scratch lm_head_topk needs for these sizes (per-chunk softmax statistics and top-k candidates). */
+/* Scratch lm_head_topk wants for these sizes: softmax statistics of the logits in groups of 64 to 512 tokens.  Less is accepted,
+ * down to ceil(V / 512) * M * (8 + 8 * top_k) + 256 bytes, where it may cost a pass over the logits. */
 size_t lm_head_workspace_bytes(int M, int V, int K, int top_k);
 
 /* Draft-side language-model head with log-softmax and top-k (paper section 2.1: the draft model uses
@@ -292,7 +293,8 @@ size_t lm_head_workspace_bytes(int M, int V, int K, int top_k);
  *            logprob = logit - log(sum_v exp(logit[m, v]))
  * x, packed, logits, workspace 16-byte aligned; top_idx, top_logprob 4-byte aligned.  Requires
  * K % 128 == 0, 1 <= top_k <= min(V, 64), V <= 262144 and ceil(V / 512) * top_k <= 8192.  `workspace` holds
- * lm_head_workspace_bytes(M, V, K, top_k) bytes and needs no initialisation.  Deterministic. */
+ * lm_head_workspace_bytes(M, V, K, top_k) bytes and needs no initialisation.  Deterministic.  A -inf or NaN logit wins no place
+ * (a list that runs short ends in token 0x7FFFFFFF, log-probability -inf); a NaN or +inf makes the row's log-probabilities NaN. */
 int lm_head_topk(const void *x, const void *packed, int M, int V, int K, int top_k, float *logits, int32_t *top_idx,
                  float *top_logprob, void *workspace, size_t workspace_bytes, void *stream);
 

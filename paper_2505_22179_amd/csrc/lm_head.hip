@@ -12,7 +12,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kLmDepth = 4;        // macro steps of weights in flight per wavefront
 constexpr int kLmStepK = 128;      // k per macro step: 256 contiguous bytes of every weight row
-constexpr int kLmChunk = 512;      // logits per wavefront of the top-k pass
+constexpr int kLmChunk = 512;      // logits per wavefront of the statistics pass (small workspaces)
 constexpr int kLmThreads = 256;
 constexpr int kLmMaxTopK = 64;
 
@@ -37,6 +37,55 @@ __global__ void lm_head_pack_kernel(const _Float16 *__restrict__ W, u32x4 *__res
     packed[idx] = piece;
 }
 
+// Statistics of the logits a workgroup has just produced, one entry per row and workgroup (a granule of NW * TWL * 16
+// tokens): the largest logit and the sum of exp(logit - largest).  With them the softmax needs no pass of its own over the logits, and
+// the top tokens of a row are known to lie in the granules with the largest maxima.  A granule without a finite logit
+// sums relative to 0; a NaN never is a maximum and makes the sum a NaN.
+struct LmStat {
+    float max, sum;
+};
+constexpr float kNegInf = -__builtin_inff();
+__device__ __forceinline__ float sum_base(float max) { return max == kNegInf ? 0.f : max; }
+
+template <int TWL, int MTL, int NW>
+__device__ __forceinline__ void store_stats(const float4v (&acc)[TWL][MTL], LmStat (*part)[MTL * 16], LmStat *__restrict__ stats, int tile0, int V, int M)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int r = lane >> 4, c = lane & 15;
+#pragma unroll
+    for (int mt = 0; mt < MTL; ++mt) {
+        float v[TWL][4], mx = kNegInf, se = 0.f;
+#pragma unroll
+        for (int t = 0; t < TWL; ++t)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {   // tokens past the vocabulary (padding, and tiles past the end) count for nothing
+                v[t][i] = (tile0 + t) * 16 + 4 * r + i < V ? acc[t][mt][i] : kNegInf;
+                mx = fmaxf(mx, v[t][i]);
+            }
+        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        const float base = sum_base(mx);
+#pragma unroll
+        for (int t = 0; t < TWL; ++t)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) se += __expf(v[t][i] - base);
+        se += __shfl_xor(se, 16, 64);
+        se += __shfl_xor(se, 32, 64);
+        if (r == 0) part[wave][mt * 16 + c] = {mx, se};
+    }
+    __syncthreads();
+    const int row = threadIdx.x;
+    if (row < M) {   // M <= 16 MTL <= the workgroup's threads
+        float mx = kNegInf, se = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) mx = fmaxf(mx, part[w][row].max);
+        const float base = sum_base(mx);
+#pragma unroll
+        for (int w = 0; w < NW; ++w) se += part[w][row].sum * __expf(part[w][row].max - base);
+        stats[(size_t)row * gridDim.x + blockIdx.x] = {mx, se};
+    }
+}
+
 // Logits.  A wavefront owns one vocabulary tile (16 tokens = the rows of the MFMA result, the up to 16
 // hidden-state rows its columns) and streams the tile's K / 32 blocks with a ring of kLmDepth macro
 // steps (4 blocks = 4 KB each) in flight; the x fragments (at most 16 x K fp16, L2-resident) are
@@ -47,13 +96,15 @@ __global__ void lm_head_pack_kernel(const _Float16 *__restrict__ W, u32x4 *__res
 template <bool EVEN, int TWL, int MTL, int DEPTH>
 __global__ __launch_bounds__(256) void lm_head_logits_kernel(const _Float16 *__restrict__ x,
                                                              const u32x4 *__restrict__ packed,
-                                                             float *__restrict__ logits, int M, int V, int K, int tiles)
+                                                             float *__restrict__ logits, LmStat *__restrict__ stats, int M, int V,
+                                                             int K, int tiles)
 {
+    __shared__ LmStat part[4][MTL * 16];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane >> 4, c = lane & 15;
     const int tile0 = (blockIdx.x * 4 + wave) * TWL;   // TWL consecutive tiles share every x fragment
-    if (tile0 >= tiles) return;   // no barrier in this kernel
+    // a wavefront past the last tile repeats it: its logits are not stored, but it takes part in the statistics' barrier
     const int steps = K / kLmStepK;
     const u32x4 *wp[TWL];
 #pragma unroll
@@ -63,7 +114,7 @@ __global__ __launch_bounds__(256) void lm_head_logits_kernel(const _Float16 *__r
 #pragma unroll
     for (int mt = 0; mt < MTL; ++mt) xp[mt] = reinterpret_cast<const u32x4 *>(x + (size_t)min(mt * 16 + c, M - 1) * K + 8 * r);
     u32x4 w[DEPTH][TWL][4], xf[DEPTH][MTL][4];
-    const int rot = (tile0 / TWL) % steps;
+    const int rot = (min(tile0, tiles - 1) / TWL) % steps;
     auto load = [&](int s, int slot) {
         int sr = s + rot;              // uniform
         sr = sr >= steps ? sr - steps : sr;
@@ -135,6 +186,7 @@ __global__ __launch_bounds__(256) void lm_head_logits_kernel(const _Float16 *__r
                 }
             }
         }
+    if (stats) store_stats<TWL, MTL, 4>(acc, part, stats, tile0, V, M);   // uniform
 }
 
 // Logits of more than 16 rows.  There the x fragments, not the weights, filled the load path of the kernel above: every
@@ -151,7 +203,8 @@ constexpr int kLmSharedMaxK = 1 << 20;   // its descriptors and offsets are 32-b
 template <int MTL, int NW, int TWL, int DEPTH>
 __global__ __launch_bounds__(64 * NW, 2) void lm_head_logits_shared_kernel(const _Float16 *__restrict__ x,
                                                                                     const u32x4 *__restrict__ packed,
-                                                                                    float *__restrict__ logits, int M, int V,
+                                                                                    float *__restrict__ logits,
+                                                                                    LmStat *__restrict__ stats, int M, int V,
                                                                                     int K, int tiles)
 {
     constexpr int kTileQuads = MTL * 4 * 64;   // 16-byte pieces of one step's x tile
@@ -285,6 +338,9 @@ __global__ __launch_bounds__(64 * NW, 2) void lm_head_logits_shared_kernel(const
                 }
             }
         }
+    // b_now is the buffer after the last tile's: nothing was copied to it, and its readers have passed the last step's barrier
+    static_assert(NW * MTL * 16 * sizeof(LmStat) <= sizeof(xa[0]), "the statistics of the wavefronts fit a buffer");
+    if (stats) store_stats<TWL, MTL, NW>(acc, reinterpret_cast<LmStat(*)[MTL * 16]>(xa[b_now]), stats, tile0, V, M);   // uniform
 }
 
 // (value, token) pairs ordered by value, equal values by ascending token
@@ -295,7 +351,7 @@ struct Cand {
 // (bitwise operators on purpose: no short-circuit branches in the scan loops)
 __device__ __forceinline__ bool better(const Cand &a, const Cand &b) { return (a.val > b.val) | ((a.val == b.val) & (a.idx < b.idx)); }
 
-// Wavefront-wide maximum / minimum, returned to every lane, on the data-parallel-primitive path of the
+// Wavefront-wide maximum, returned to every lane, on the data-parallel-primitive path of the
 // vector ALU (no LDS round trips): quad butterflies, rotations inside each row of 16 lanes, then the
 // four row results are read into scalars.
 template <int CTRL>
@@ -303,7 +359,7 @@ __device__ __forceinline__ int dpp_move(int v)
 {
     return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xF, 0xF, false);
 }
-constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E, kRowRor4 = 0x124, kRowRor8 = 0x128;
+constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E, kRowRor4 = 0x124, kRowRor8 = 0x128, kWaveShr1 = 0x138;
 
 __device__ __forceinline__ float wave_max(float v)
 {
@@ -319,23 +375,14 @@ __device__ __forceinline__ float wave_max(float v)
     return fmaxf(fmaxf(a, b), fmaxf(c, d));
 }
 
-__device__ __forceinline__ int wave_min(int v)
+__device__ __forceinline__ float lane_value(float v, int lane)   // lane uniform
 {
-    v = min(v, dpp_move<kQuadXor1>(v));
-    v = min(v, dpp_move<kQuadXor2>(v));
-    v = min(v, dpp_move<kRowRor4>(v));
-    v = min(v, dpp_move<kRowRor8>(v));
-    return min(min(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
-               min(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
 }
-
-// best pair of the wavefront, returned to every lane: the largest value, and among the lanes that
-// hold it the smallest token
-__device__ __forceinline__ Cand wave_best(Cand mine)
+// set bits of a ballot below this lane
+__device__ __forceinline__ int lanes_below(uint64_t which)
 {
-    const float vmax = wave_max(mine.val);
-    const int imin = wave_min(mine.val == vmax ? mine.idx : 0x7FFFFFFF);
-    return {vmax, imin};
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(which >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)which, 0));
 }
 
 // butterfly sum over the wavefront (fixed order), returned to every lane
@@ -346,160 +393,192 @@ __device__ __forceinline__ float wave_sum(float v)
     return v;
 }
 
-constexpr float kNegInf = -__builtin_inff();
 constexpr int kNoToken = 0x7FFFFFFF;
 
-// Pass 1 over the logits: one WAVEFRONT per chunk of 512 logits of one row (no barriers: the top_k
-// rounds are shuffles only).  Per chunk: maximum, sum of exp(l - max) and the chunk's top_k
-// (value, token) pairs, largest first.  Lane l holds logits l, l + 64, ... of the chunk.
-__global__ __launch_bounds__(kLmThreads) void lm_head_chunk_kernel(const float *__restrict__ logits, int V, int top_k,
-                                                                   int chunks, float *__restrict__ chunk_max,
-                                                                   float *__restrict__ chunk_sum,
-                                                                   float *__restrict__ cand_val, int *__restrict__ cand_idx)
+// The statistics as a pass over the logits, for workspaces that hold one entry per 512 tokens only: one wavefront per chunk of
+// 512 logits of one row.
+__global__ __launch_bounds__(kLmThreads) void lm_head_stats_kernel(const float *__restrict__ logits, LmStat *__restrict__ stats, int V, int chunks)
 {
     constexpr int kPerLane = kLmChunk / 64;
-    fetch_arguments_together(logits, V, top_k, chunks, chunk_max, chunk_sum, cand_val, cand_idx);
     const int lane = threadIdx.x & 63;
     const int chunk = blockIdx.x * (kLmThreads / 64) + (threadIdx.x >> 6), m = blockIdx.y;
     if (chunk >= chunks) return;
     const float *row = logits + (size_t)m * V;
     const int base = chunk * kLmChunk + lane;
-    float val[kPerLane];
+    float val[kPerLane], mx = kNegInf, se = 0.f;
 #pragma unroll
-    for (int i = 0; i < kPerLane; ++i) val[i] = base + 64 * i < V ? row[base + 64 * i] : kNegInf;
-    // a lane's tokens ascend with i, so a strict comparison keeps the lowest token among equal values;
-    // retired and padding entries are -inf and never win
-    auto lane_best = [&]() {
-        Cand b = {kNegInf, kNoToken};
+    for (int i = 0; i < kPerLane; ++i) {
+        val[i] = base + 64 * i < V ? row[base + 64 * i] : kNegInf;
+        mx = fmaxf(mx, val[i]);
+    }
+    mx = wave_max(mx);
+    const float from = sum_base(mx);
 #pragma unroll
-        for (int i = 0; i < kPerLane; ++i) {
-            const bool win = val[i] > b.val;
-            b.val = win ? val[i] : b.val;
-            b.idx = win ? base + 64 * i : b.idx;
-        }
-        return b;
-    };
-    Cand mine = lane_best();
-    Cand best = wave_best(mine);
-    const float mx = best.val;   // every chunk holds at least one token
-    float se = 0.f;
-#pragma unroll
-    for (int i = 0; i < kPerLane; ++i) se += __expf(val[i] - mx);   // exp(-inf) = 0 for the padding
+    for (int i = 0; i < kPerLane; ++i) se += __expf(val[i] - from);
     se = wave_sum(se);
-    const size_t slot = (size_t)m * chunks + chunk;
-    if (lane == 0) {
-        chunk_max[slot] = mx;
-        chunk_sum[slot] = se;
-    }
-    for (int round = 0; round < top_k; ++round) {
-        if (round > 0) best = wave_best(mine);
-        if (lane == 0) {
-            cand_val[slot * top_k + round] = best.val;
-            cand_idx[slot * top_k + round] = best.idx;
-        }
-        if (best.idx == mine.idx && best.idx != kNoToken) {   // the owner retires the winner and looks again
-#pragma unroll
-            for (int i = 0; i < kPerLane; ++i) val[i] = best.idx == base + 64 * i ? kNegInf : val[i];
-            mine = lane_best();
-        }
-    }
+    if (lane == 0) stats[(size_t)m * chunks + chunk] = {mx, se};
 }
 
-// Pass 2: one wavefront per row merges the chunks: log of the sum of exponentials, then a k-way merge of
-// the chunks' candidate lists (each already sorted, largest first), which sit in LDS: lane l owns the
-// lists of chunks l, l + 64, ... and keeps their current heads in registers; per round the best head of
-// the wavefront is emitted and its owner advances that list.
-constexpr int kLmListsPerLane = 8;            // chunks <= 512
-constexpr int kLmMaxCandidates = 8192;        // chunks * top_k, 64 KB of LDS
-__global__ __launch_bounds__(kLmThreads) void lm_head_merge_kernel(const float *__restrict__ chunk_max,
-                                                           const float *__restrict__ chunk_sum,
-                                                           const float *__restrict__ cand_val,
-                                                           const int *__restrict__ cand_idx, int chunks, int top_k,
-                                                           int32_t *__restrict__ top_idx, float *__restrict__ top_logprob)
+// The best pairs seen so far, best first: lane l holds the l-th.
+struct Best {
+    Cand c = {kNegInf, kNoToken};
+    // takes in the pairs of the lanes that offer one; `worst`: lane of the pair that a new one has to beat
+    __device__ __forceinline__ void offer(Cand mine, bool offers, int worst)
+    {
+        const int lane = threadIdx.x & 63;
+        for (;;) {
+            const Cand last = {lane_value(c.val, worst), __builtin_amdgcn_readlane(c.idx, worst)};
+            const uint64_t todo = __ballot(offers && better(mine, last));
+            if (todo == 0) return;   // uniform; every round below withdraws one offer
+            const int from = __builtin_ctzll(todo);
+            const Cand cand = {lane_value(mine.val, from), __builtin_amdgcn_readlane(mine.idx, from)};
+            const int place = __popcll(__ballot(better(c, cand)));   // the better ones are the first lanes
+            const float up_val = __builtin_bit_cast(float, dpp_move<kWaveShr1>(__builtin_bit_cast(int, c.val)));
+            const int up_idx = dpp_move<kWaveShr1>(c.idx);
+            c.val = lane < place ? c.val : lane == place ? cand.val : up_val;
+            c.idx = lane < place ? c.idx : lane == place ? cand.idx : up_idx;
+            offers = offers && lane != from;
+        }
+    }
+};
+
+// Log of the sum of exponentials and the top tokens of a row, one workgroup per row.
+//   1. The row's granules are dealt to the lanes.  The k-th largest of a wavefront's lane maxima is a value that k tokens
+//      reach, and so is the least of the four wavefronts' (k / 4)-th largest: the row's k best tokens reach the larger of them all, the bound.
+//   2. Only granules whose maximum reaches the bound are read again, and only their tokens that reach it are kept: k to
+//      about 2 k of them where values differ.
+//   3. A thread per kept token counts the better ones: its place.  (More than a list holds, with many equal logits
+//      or more places than granules: the wavefronts keep their k best while they read the granules a second time, and the first merges them.)
+// Nothing in the usual path runs k times in a row.  A round trip to memory for the statistics, one for the logits: latency bounds it.
+// The two passes this replaces (the k best of every 512 logits, then a merge of those lists) read all logits again:
+// top 10 of 10 x 128256 8.3 + 9.6 -> 7.8 us, top 1 of 60 x 128256 8.3 + 4.7 -> 4.8; whole calls 172.3 -> 164.0 and 348 -> 341 (K = 4096, 8192),
+// top 10 of 5 x 5000 (K = 2048) 26.2 -> 17.9, top 32 of 64 x 128256 271 -> 203.
+constexpr int kLmKept = kLmThreads;       // tokens the lists hold, and the third step ranks
+constexpr int kLmMaxPerLane = 16;         // 262144 tokens in granules of 64: 4096 of them over 256 lanes
+constexpr int kLmAhead = 16;              // logits in flight per lane
+template <int PER>
+__global__ __launch_bounds__(kLmThreads) void lm_head_merge_kernel(const float *__restrict__ logits, const LmStat *__restrict__ stats, int V,
+                                                                   int granules, int granule, int top_k, int32_t *__restrict__ top_idx,
+                                                                   float *__restrict__ top_logprob)
 {
-    extern __shared__ float lds_f[];
-    fetch_arguments_together(chunk_max, chunk_sum, cand_val, cand_idx, chunks, top_k, top_idx, top_logprob);
-    const int m = blockIdx.x, lane = threadIdx.x & 63;
-    const int total = chunks * top_k;
-    float *lval = lds_f;
-    int *lidx = reinterpret_cast<int *>(lds_f + total);
-    // the first wavefront's share of the chunk maxima and sums, requested together with the lists
-    float cmax[kLmListsPerLane], csum[kLmListsPerLane];
+    constexpr int kWaves = kLmThreads / 64;
+    __shared__ float wave_alone[kWaves], wave_shared[kWaves];
+    __shared__ LmStat wave_stat[kWaves];
+    __shared__ int wave_kept[kWaves];
+    __shared__ Cand kept[kWaves][kLmKept];
+    __shared__ int chosen[kWaves][PER * 64];
+    fetch_arguments_together(logits, stats, V, granules, granule, top_k, top_idx, top_logprob);
+    const int m = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const float *const row = logits + (size_t)m * V;
+    LmStat st[PER];
 #pragma unroll
-    for (int h = 0; h < kLmListsPerLane; ++h) {
-        const int ch = lane + 64 * h, chc = ch < chunks ? ch : chunks - 1;   // clamped address, value discarded:
-        const float a = chunk_max[(size_t)m * chunks + chc];                 // no branch around the load
-        const float b = chunk_sum[(size_t)m * chunks + chc];
-        cmax[h] = ch < chunks ? a : kNegInf;
-        csum[h] = ch < chunks ? b : 0.f;
+    for (int i = 0; i < PER; ++i) st[i] = stats[(size_t)m * granules + min(tid + kLmThreads * i, granules - 1)];   // lanes past the end drop theirs
+    float lane_mx = kNegInf;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        if (tid + kLmThreads * i >= granules) st[i] = {kNegInf, 0.f};
+        lane_mx = fmaxf(lane_mx, st[i].max);
     }
-    {   // all four wavefronts stage the lists, every load of a thread in flight at once: whether a round of
-        // loads happens is a uniform decision and a lane past the end reads the last entry (and drops it), so
-        // no load sits under a per-lane condition, which would be compiled as a branch with a wait of its own
-        constexpr int kPer = kLmMaxCandidates / kLmThreads;
-        const int rounds = (total + kLmThreads - 1) / kLmThreads;
-        float sv[kPer];
-        int si[kPer];
-#pragma unroll
-        for (int i = 0; i < kPer; ++i) {
-            if (i < rounds) {
-                const int e = threadIdx.x + kLmThreads * i, ec = e < total ? e : total - 1;
-                sv[i] = cand_val[(size_t)m * total + ec];
-                si[i] = cand_idx[(size_t)m * total + ec];
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < kPer; ++i) {
-            const int e = threadIdx.x + kLmThreads * i;
-            if (i < rounds && e < total) {
-                lval[e] = sv[i];
-                lidx[e] = si[i];
-            }
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x >= 64) return;   // the merge itself is one wavefront's work
-    float mx = kNegInf;
-#pragma unroll
-    for (int h = 0; h < kLmListsPerLane; ++h) mx = fmaxf(mx, cmax[h]);
-    mx = wave_max(mx);
+    const float wave_mx = wave_max(lane_mx);
     float se = 0.f;
 #pragma unroll
-    for (int h = 0; h < kLmListsPerLane; ++h) se += csum[h] * __expf(cmax[h] - mx);   // absent chunks: 0 * exp(-inf) = 0
+    for (int i = 0; i < PER; ++i) se += st[i].sum * __expf(st[i].max - sum_base(wave_mx));   // absent ones: 0 * exp(-inf) = 0
     se = wave_sum(se);
+    float alone = wave_mx, shared = wave_mx;   // values that k, and k / 4, of this wavefront's lanes reach
+    if (top_k > 1) {   // uniform
+        int larger = 0;
+#pragma unroll
+        for (int l = 0; l < 64; ++l) larger += lane_value(lane_mx, l) > lane_mx ? 1 : 0;
+        alone = -wave_max(larger < top_k ? -lane_mx : kNegInf);   // the least of the lanes that fewer than k surpass
+        shared = -wave_max(larger < (top_k + kWaves - 1) / kWaves ? -lane_mx : kNegInf);
+    }
+    if (lane == 0) {
+        wave_stat[wave] = {wave_mx, se};
+        wave_alone[wave] = alone;
+        wave_shared[wave] = shared;
+    }
+    __syncthreads();
+    float mx = kNegInf;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+        alone = fmaxf(alone, wave_alone[w]);
+        shared = fminf(shared, wave_shared[w]);
+        mx = fmaxf(mx, wave_stat[w].max);
+    }
+    const float bound = top_k > 1 ? fmaxf(alone, shared) : mx;
+    se = 0.f;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) se += wave_stat[w].sum * __expf(wave_stat[w].max - sum_base(mx));
     const float lse = mx + __logf(se);
-    Cand head[kLmListsPerLane];
-    int ptr[kLmListsPerLane];
+
+    // this wavefront's granules that reach the bound, as pieces of 64 tokens
+    const auto counts = [&](float v) { return v >= bound && v > kNegInf; };
+    int found = 0;
 #pragma unroll
-    for (int h = 0; h < kLmListsPerLane; ++h) {
-        const int ch = lane + 64 * h;
-        ptr[h] = 0;
-        head[h] = ch < chunks ? Cand{lval[ch * top_k], lidx[ch * top_k]} : Cand{kNegInf, kNoToken};
+    for (int i = 0; i < PER; ++i) {
+        const uint64_t which = __ballot(counts(st[i].max));
+        if (counts(st[i].max)) chosen[wave][found + lanes_below(which)] = tid + kLmThreads * i;
+        found += __popcll(which);
     }
-    for (int round = 0; round < top_k; ++round) {
-        Cand mine = {kNegInf, kNoToken};
+    const int shift = 31 - __builtin_clz((unsigned)granule) - 6;   // granules are 64, 128, 256 or 512 tokens
+    const int pieces = found << shift;
+    // goes through them: take(logit, token) once per piece, lane by lane
+    const auto each_piece = [&](auto take) {
+        for (int p0 = 0; p0 < pieces; p0 += kLmAhead) {
+            float l[kLmAhead];
+            int token[kLmAhead];
 #pragma unroll
-        for (int h = 0; h < kLmListsPerLane; ++h) {
-            const bool win = better(head[h], mine);
-            mine.val = win ? head[h].val : mine.val;
-            mine.idx = win ? head[h].idx : mine.idx;
-        }
-        const Cand best = wave_best(mine);
-        if (lane == 0) {
-            top_idx[m * top_k + round] = best.idx;
-            top_logprob[m * top_k + round] = best.val - lse;
-        }
-        if (best.idx == mine.idx && best.idx != kNoToken) {   // the owner advances the list the winner came from
-#pragma unroll
-            for (int h = 0; h < kLmListsPerLane; ++h) {
-                if (head[h].idx == best.idx) {
-                    ++ptr[h];
-                    const int e = (lane + 64 * h) * top_k + ptr[h];
-                    head[h] = ptr[h] < top_k ? Cand{lval[e], lidx[e]} : Cand{kNegInf, kNoToken};
-                }
+            for (int i = 0; i < kLmAhead; ++i) {   // a piece past the last repeats it and is not looked at
+                const int p = min(p0 + i, pieces - 1);
+                token[i] = chosen[wave][p >> shift] * granule + (p & ((1 << shift) - 1)) * 64 + lane;
+                l[i] = row[min(token[i], V - 1)];
             }
+#pragma unroll
+            for (int i = 0; i < kLmAhead; ++i)
+                if (p0 + i < pieces) take(token[i] < V ? l[i] : kNegInf, token[i]);   // uniform
         }
+    };
+    int keeps = 0;
+    each_piece([&](float l, int token) {
+        const uint64_t which = __ballot(counts(l));
+        const int place = keeps + lanes_below(which);
+        if (counts(l) && place < kLmKept) kept[wave][place] = {l, token};
+        keeps += __popcll(which);
+    });
+    if (lane == 0) wave_kept[wave] = keeps;
+    __syncthreads();
+    int total = 0, w_mine = 0, at = tid;   // the tid-th kept token is entry `at` of list w_mine
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+        const int n = wave_kept[w];
+        total += n;
+        if (w_mine == w && at >= n && w + 1 < kWaves) at -= n, ++w_mine;
     }
+    const auto store = [&](int place, Cand c) {
+        top_idx[m * top_k + place] = c.idx;
+        top_logprob[m * top_k + place] = c.val - lse;
+    };
+    if (total <= kLmKept) {   // uniform
+        if (tid < top_k && tid >= total) store(tid, {kNegInf, kNoToken});   // fewer tokens than that have a logit
+        if (wave * 64 >= total) return;
+        const Cand mine = tid < total ? kept[w_mine][at] : Cand{kNegInf, kNoToken};
+        int place = 0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w)
+#pragma unroll 8
+            for (int j = 0; j < wave_kept[w]; ++j) place += better(kept[w][j], mine) ? 1 : 0;
+        if (tid < total && place < top_k) store(place, mine);
+        return;
+    }
+    Best top;
+    each_piece([&](float l, int token) { top.offer({l, token}, counts(l), top_k - 1); });
+    __syncthreads();   // everybody has left the lists
+    kept[wave][lane] = top.c;
+    __syncthreads();
+    if (wave != 0) return;
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w) top.offer(kept[w][lane], lane < top_k && kept[w][lane].idx != kNoToken, top_k - 1);
+    if (lane < top_k) store(lane, top.c);
 }
 
 // Which logits kernel, how many wavefronts share a workgroup and how many vocabulary tiles each takes.
@@ -539,13 +618,21 @@ static LmPlan lm_plan(int M, int tiles, int K)
 }
 
 static int lm_chunks(int V) { return (V + kLmChunk - 1) / kLmChunk; }
+constexpr int kLmMaxChunks = 512, kLmMaxCandidates = 8192;   // chunks, chunks * top_k: the sizes that are served
+
+// Least accepted workspace.  It always holds the statistics of the chunks.
+static size_t lm_least_bytes(int M, int V, int top_k)
+{
+    const size_t slots = (size_t)M * lm_chunks(V);
+    return slots * 2 * sizeof(float) + slots * top_k * (sizeof(float) + sizeof(int)) + 256;
+}
 
 static int check_lm_head(int M, int V, int K, int top_k)
 {
     if (M < 1 || V < 1 || K < 1 || top_k < 1 || top_k > V) return W4A16_EINVAL;
     if (K % kLmStepK != 0) return W4A16_EINVAL;
     if (M > W4A16_MAX_M || top_k > kLmMaxTopK) return W4A16_EUNSUP;
-    if (lm_chunks(V) > 64 * kLmListsPerLane || (long long)lm_chunks(V) * top_k > kLmMaxCandidates) return W4A16_EUNSUP;
+    if (lm_chunks(V) > kLmMaxChunks || (long long)lm_chunks(V) * top_k > kLmMaxCandidates) return W4A16_EUNSUP;
     return W4A16_OK;
 }
 
@@ -575,8 +662,8 @@ int lm_head_pack(const void *W, void *packed, int V, int K, void *stream)
 size_t lm_head_workspace_bytes(int M, int V, int K, int top_k)
 {
     if (check_lm_head(M, V, K, top_k) != W4A16_OK) return 0;
-    const size_t slots = (size_t)M * lm_chunks(V);
-    return slots * 2 * sizeof(float) + slots * top_k * (sizeof(float) + sizeof(int)) + 256;
+    const size_t least = lm_least_bytes(M, V, top_k), finest = (size_t)M * ((V + 63) / 64) * sizeof(LmStat);   // the smallest granules
+    return finest > least ? finest : least;
 }
 
 int lm_head_plan_describe(int M, int V, int K, int *out)
@@ -600,30 +687,22 @@ int lm_head_topk(const void *x, const void *packed, int M, int V, int K, int top
     if (!x || !packed || !logits || !top_idx || !top_logprob) return W4A16_ENULL;
     if (misaligned(x) || misaligned(packed) || misaligned(logits) || misaligned(workspace)) return W4A16_EALIGN;
     if ((reinterpret_cast<uintptr_t>(top_idx) | reinterpret_cast<uintptr_t>(top_logprob)) & 3u) return W4A16_EALIGN;
-    if (!workspace || workspace_bytes < lm_head_workspace_bytes(M, V, K, top_k)) return W4A16_EWORKSPACE;
-    const int tiles = (V + 15) / 16, chunks = lm_chunks(V);
-    const size_t slots = (size_t)M * chunks;
-    float *chunk_max = reinterpret_cast<float *>(workspace);
-    float *chunk_sum = chunk_max + slots;
-    float *cand_val = chunk_sum + slots;
-    int *cand_idx = reinterpret_cast<int *>(cand_val + slots * top_k);
-    static bool lds_ok = false;   // LDS above 48 KB needs an opt-in, once
-    if (!lds_ok) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(&lm_head_merge_kernel),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, kLmMaxCandidates * 8) != hipSuccess)
-            return W4A16_EHIP;
-        lds_ok = true;
-    }
+    if (!workspace || workspace_bytes < lm_least_bytes(M, V, top_k)) return W4A16_EWORKSPACE;
+    const int tiles = (V + 15) / 16;
     hipStream_t s = (hipStream_t)stream;
     const int mtl = (M + 15) / 16;
     const LmPlan plan = lm_plan(M, tiles, K);
     if (plan.nw == 0) return W4A16_EUNSUP;
     const dim3 grid((unsigned)((tiles + plan.nw * plan.twl - 1) / (plan.nw * plan.twl)));
+    // the logits kernel leaves its statistics; a workspace below the stated size may have room for coarser ones only, which then take a pass
+    const bool fine = workspace_bytes >= (size_t)M * grid.x * sizeof(LmStat);
+    const int granule = fine ? plan.nw * plan.twl * 16 : kLmChunk, granules = fine ? (int)grid.x : lm_chunks(V);
+    LmStat *const all_stats = reinterpret_cast<LmStat *>(workspace), *const stats = fine ? all_stats : nullptr;
     if (plan.shared) {
 #define W4_LM_SHARED(MTL_, NW_, TWL_, D_)                                                                               \
     if (mtl == MTL_ && plan.nw == NW_ && plan.twl == TWL_)                                                              \
         hipLaunchKernelGGL((lm_head_logits_shared_kernel<MTL_, NW_, TWL_, D_>), grid, dim3(64 * NW_), 0, s,             \
-                           (const _Float16 *)x, (const u32x4 *)packed, logits, M, V, K, tiles)
+                           (const _Float16 *)x, (const u32x4 *)packed, logits, stats, M, V, K, tiles)
         W4_LM_SHARED(2, 4, 1, 4); W4_LM_SHARED(2, 8, 1, 4); W4_LM_SHARED(2, 8, 2, 2); W4_LM_SHARED(2, 8, 4, 2);
         W4_LM_SHARED(3, 4, 1, 4); W4_LM_SHARED(3, 8, 1, 4); W4_LM_SHARED(3, 8, 2, 2); W4_LM_SHARED(3, 8, 4, 2);
         W4_LM_SHARED(4, 4, 1, 4); W4_LM_SHARED(4, 8, 1, 4); W4_LM_SHARED(4, 8, 2, 2); W4_LM_SHARED(4, 8, 4, 2);
@@ -635,10 +714,10 @@ int lm_head_topk(const void *x, const void *packed, int M, int V, int K, int top
     do {                                                                                                                \
         if (even)                                                                                                       \
             hipLaunchKernelGGL((lm_head_logits_kernel<true, TWL_, MTL_, DEPTH_>), grid, dim3(256), 0, s,                \
-                               (const _Float16 *)x, (const u32x4 *)packed, logits, M, V, K, tiles);                     \
+                               (const _Float16 *)x, (const u32x4 *)packed, logits, stats, M, V, K, tiles);                     \
         else                                                                                                            \
             hipLaunchKernelGGL((lm_head_logits_kernel<false, TWL_, MTL_, DEPTH_>), grid, dim3(256), 0, s,               \
-                               (const _Float16 *)x, (const u32x4 *)packed, logits, M, V, K, tiles);                     \
+                               (const _Float16 *)x, (const u32x4 *)packed, logits, stats, M, V, K, tiles);                     \
     } while (0)
         if (mtl == 1 && plan.twl == 1) W4_LM_LAUNCH(1, 1, kLmDepth);
         else if (mtl == 1) W4_LM_LAUNCH(2, 1, kLmDepth);
@@ -647,11 +726,17 @@ int lm_head_topk(const void *x, const void *packed, int M, int V, int K, int top
         else W4_LM_LAUNCH(4, 4, 2);
 #undef W4_LM_LAUNCH
     }
-    hipLaunchKernelGGL(lm_head_chunk_kernel, dim3((unsigned)((chunks + kLmThreads / 64 - 1) / (kLmThreads / 64)), (unsigned)M), dim3(kLmThreads), 0, s,
-                       (const float *)logits, V, top_k, chunks, chunk_max, chunk_sum, cand_val, cand_idx);
-    hipLaunchKernelGGL(lm_head_merge_kernel, dim3((unsigned)M), dim3(kLmThreads), (size_t)chunks * top_k * 8, s, (const float *)chunk_max,
-                       (const float *)chunk_sum, (const float *)cand_val, (const int *)cand_idx, chunks, top_k, top_idx,
-                       top_logprob);
+    if (!fine)
+        hipLaunchKernelGGL(lm_head_stats_kernel, dim3((unsigned)((granules + kLmThreads / 64 - 1) / (kLmThreads / 64)), (unsigned)M), dim3(kLmThreads), 0, s,
+                           (const float *)logits, all_stats, V, granules);
+#define W4_LM_MERGE(PER_)                                                                                                \
+    hipLaunchKernelGGL(lm_head_merge_kernel<PER_>, dim3((unsigned)M), dim3(kLmThreads), 0, s, (const float *)logits,           \
+                       (const LmStat *)all_stats, V, granules, granule, top_k, top_idx, top_logprob)
+    const int per_lane = (granules + kLmThreads - 1) / kLmThreads;
+    if (per_lane <= 1) W4_LM_MERGE(1);
+    else if (per_lane <= 4) W4_LM_MERGE(4);
+    else W4_LM_MERGE(kLmMaxPerLane);
+#undef W4_LM_MERGE
     return launch_status();
 }
 

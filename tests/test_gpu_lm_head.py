@@ -136,3 +136,62 @@ def test_determinism():
     b = run(x, W, 10)
     for u, v in zip(a, b):
         assert np.array_equal(u, v)
+
+
+@pytest.mark.parametrize("M,K,V,top_k", [(3, 128, 40000, 16), (33, 128, 40001, 64), (1, 128, 70, 64)])
+def test_equal_logits_beyond_the_lists(M, K, V, top_k):
+    """all logits equal, so every token reaches the bound and the lists of the merge overflow: the first tokens win"""
+    L, Ix, P = run(np.zeros((M, K), np.float16), I.make_lm_head(9960, 1, K, V)[1], top_k)
+    assert (Ix == np.arange(top_k)).all() and (L == 0).all()
+    assert np.abs(P + np.log(V)).max() <= 2e-3
+
+
+@pytest.mark.parametrize("M,K,V,top_k", [(4, 128, 65001, 64), (2, 256, 128256, 32), (40, 128, 3000, 64), (5, 128, 255, 16)])
+def test_many_top_tokens(M, K, V, top_k):
+    """k from a few lanes' worth to as many as a wavefront has: both ways of picking the kept tokens"""
+    x, W = I.make_lm_head(9970 + V, M, K, V)
+    check(x, W, top_k, f"M={M} K={K} V={V} k={top_k}")
+
+
+@pytest.mark.parametrize("M", [2, 20])
+def test_infinite_and_nan_logits(M):
+    """-inf logits (whole granules of them) take no part in sum and order, fewer finite ones than top_k leave the rest of the
+    list empty, and a NaN makes the row's log-probabilities NaN but wins no place"""
+    K, V, top_k = 128, 3000, 8
+    x, W = I.make_lm_head(9980, M, K, V)
+    x[:, 0] = 1
+    W[512:1700, 0] = -np.inf
+    ref = x.astype(np.float64) @ W.astype(np.float64).T
+    order = np.argsort(-ref, axis=1, kind="stable")[:, :top_k]
+    lse = np.log(np.exp(ref).sum(axis=1))
+    _, Ix, P = run(x, W, top_k)
+    assert (np.take_along_axis(ref, Ix, 1) >= np.take_along_axis(ref, order, 1) - 2 * TOL).all()
+    assert np.abs(P - (np.take_along_axis(ref, Ix, 1) - lse[:, None])).max() <= 2e-3
+    W[5:, 0] = -np.inf
+    _, Ix, P = run(x, W, top_k)
+    assert (np.sort(Ix[:, :5], axis=1) == np.arange(5)).all() and (Ix[:, 5:] == 0x7FFFFFFF).all() and np.isneginf(P[:, 5:]).all()
+    W[2999, 0] = np.nan
+    _, Ix, P = run(x, W, top_k)
+    assert (np.sort(Ix[:, :5], axis=1) == np.arange(5)).all() and np.isnan(P).all()
+
+
+@pytest.mark.parametrize("M,K,V,top_k", [(1, 256, 5000, 1), (30, 256, 5001, 2)])
+def test_workspace_below_the_stated_size(M, K, V, top_k):
+    """the least accepted workspace (statistics and candidates of 512-token chunks) gives the same tokens through a pass over
+    the logits; anything below is refused"""
+    x, W = I.make_lm_head(9990, M, K, V)
+    L, Ix, P = run(x, W, top_k)
+    chunks = -(-V // 512)
+    least = M * chunks * (8 + 8 * top_k) + 256
+    assert least < B.lm_head_workspace_bytes(M, V, K, top_k)
+    xd, Wraw = torch.from_numpy(x).to(DEV), torch.from_numpy(W).to(DEV)
+    Wd = torch.empty(B.lm_head_packed_bytes(V, K), dtype=torch.uint8, device=DEV)
+    B.lm_head_pack(Wraw, Wd, V, K)
+    logits = torch.empty(M, V, device=DEV)
+    idx, lp = torch.empty(M, top_k, dtype=torch.int32, device=DEV), torch.empty(M, top_k, device=DEV)
+    ws = torch.zeros(least + 64, dtype=torch.uint8, device=DEV)
+    B.lm_head_topk(xd, Wd, M, V, K, top_k, logits, idx, lp, ws[:least])
+    assert np.array_equal(logits.cpu().numpy(), L) and np.array_equal(idx.cpu().numpy(), Ix) and (ws[least:] == 0).all()
+    assert np.abs(lp.cpu().numpy() - P).max() <= 1e-5   # the sum of exponentials in other groups
+    with pytest.raises(B.W4A16Error):
+        B.lm_head_topk(xd, Wd, M, V, K, top_k, logits, idx, lp, ws[:least - 16])
