@@ -1468,6 +1468,135 @@ __device__ __forceinline__ void cs_segment(const _Float16 *__restrict__ x, const
     }
 }
 
+// K-split workgroups of more than one row tile.  The eight wavefronts work on the same TW column tiles, each on its own
+// quantisation groups, as in gemm_kernel; but x fragments fetched straight from L2 (sixteen rows times 64 bytes a load) would occupy the
+// load path longer than the weights, so a wavefront copies the x tile of its next group into LDS of its own, whole cache
+// lines, global -> LDS directly, while it computes on the current one, whose fragments it holds in registers.  No wavefront waits
+// for another before the sums meet at the end, and K needs no split across workgroups where the columns alone fill the chip.
+// What bounds it: for short walks the latencies of launch, first loads and epilogue (one group per wavefront: 3.6 us); for long ones
+// the x tile, 16 KB per wavefront and group at 64 rows, which four column quarters would share (70B down at 64 rows: 46 us against 42.5
+// of the column-split kernel, gate_up 93 against 73).  So it takes the shapes in between; us, column-split or K-split kernel before -> now: 8B q/k/v
+// 10.0 -> 8.9 at 32 rows and 13.2 -> 11.3 at 64, 70B o_proj 21.0 -> 16.7 at 60, 8B down 13.4 -> 10.8 at 30 and 19.2 -> 16.0 at 60,
+// 5120 -> 13000 at 37 16.9 -> 14.2, 1024 -> 2624 at 48 7.4 -> 4.0.  Not better: two or four groups of codes in flight (the larger
+// loop costs more than the latency it hides), the copies of x spread over the tiles instead of issued together.
+constexpr int kXWaves = 8;
+template <int MT, int TW, bool SYM>
+__global__ __launch_bounds__(kXWaves * 64) void gemm_x_kernel(
+    const _Float16 *__restrict__ x, const uint8_t *__restrict__ packed, const Out y,
+    float *__restrict__ partial, uint32_t *__restrict__ tickets, int M, int N, int K, int groups, int S, int fused,
+    int gq, int grem)
+{
+    extern __shared__ float4v lds4[];
+    __shared__ uint32_t ticket_sh;
+    constexpr int NW = kXWaves;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane >> 4, c = lane & 15;
+    const int unit = blockIdx.y, ks = blockIdx.x;   // grid = (S, units)
+    const int nb = (unit * TW) >> 3, t0 = (unit * TW) & 7;
+    const KRange kr = k_range(ks, gq, grem);
+    const int g0 = kr.begin + wave < kr.end ? kr.begin + wave : kr.begin;
+    const int n_w = kr.begin + wave < kr.end ? (kr.end - g0 + NW - 1) / NW : 0;
+
+    // The x tile of a group: MT * 4 blocks of 1 KB, block (mt, jp, h) = rows 16 mt + 8 h .. + 7 times the 128 bytes of k steps
+    // 2 jp and 2 jp + 1, chunks swizzled (the layout cs_segment describes).  rows >= M repeat row M - 1
+    uint32_t xoff[MT][2];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int row8 = lane >> 3, row = mt * 16 + h * 8 + row8;
+            xoff[mt][h] = ((uint32_t)(row < M ? row : M - 1) * (uint32_t)K + (uint32_t)(((lane & 7) ^ (4 * h + (row8 >> 1))) * 8)) * 2;
+        }
+    uint32_t xfrag[2];
+    {
+        const int h = c >> 3, row8 = c & 7, sw = 4 * h + (row8 >> 1);
+        xfrag[0] = (uint32_t)(h * 1024 + (row8 * 8 + (r ^ sw)) * 16);
+        xfrag[1] = (uint32_t)(h * 1024 + (row8 * 8 + ((4 + r) ^ sw)) * 16);
+    }
+    uint8_t *const xtile = reinterpret_cast<uint8_t *>(lds4) + wave * (MT * 4096);
+    const Stretch xs = stretch(x + (size_t)g0 * kGroup, (uint32_t)(((size_t)M * K - (size_t)g0 * kGroup) * 2));
+    const Stretch recs = stretch(packed + record_offset(nb, g0, groups), (uint32_t)(groups - g0) * kRecordBytes);
+    const uint32_t code_off = (uint32_t)(t0 * 1024 + lane * 16);
+    const uint32_t scale_off = (uint32_t)(kScalesOff + c * 16 + t0 * 2), zero_off = (uint32_t)(kZerosOff + c * 4);
+    auto copy_x = [&](int i) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+                quad_to_lds(xs, xtile + (mt * 4 + b) * 1024, xoff[mt][b & 1], (uint32_t)i * (NW * kGroup * 2) + (uint32_t)(b >> 1) * 128);
+    };
+    u32x4 a[MT][4];
+    auto read_x = [&]() {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+                a[mt][j] = *reinterpret_cast<const u32x4 *>(xtile + (mt * 2 + (j >> 1)) * 2048 + xfrag[j & 1]);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the copies that follow overwrite the tile
+    };
+    constexpr int kGroupLoads = TW + 1 + (SYM ? 0 : 1);
+    const DequantConsts magic = dequant_consts();
+    float4v acc[TW][MT];
+#pragma unroll
+    for (int t = 0; t < TW; ++t)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) acc[t][mt] = (float4v){0.f, 0.f, 0.f, 0.f};
+    u32x4 w[TW];
+    StagedQuant<TW> qw;
+    auto load_codes = [&](uint32_t rec, int t) { w[t] = stream_quad(recs, code_off + (uint32_t)(t * 1024), rec); };
+    auto compute = [&](int next, bool refill) {   // the codes of group `next` take the place of this group's
+        const StagedQuant<TW> q = qw;
+        const uint32_t zbits = q.z >> (4 * t0), rec = (uint32_t)next * (NW * kRecordBytes);
+        if (refill) load_quant<TW, SYM>(qw, recs, rec, scale_off, zero_off);
+#pragma unroll
+        for (int t = 0; t < TW; ++t) {
+            const uint32_t z = (zbits >> (4 * t)) & 0xFu, zz = z | (z << 16);
+            const half2v zneg = as_h2(SYM ? kSymZneg : (zz | 0xE400E400u));              // -(1024 + z)
+            const half2v zneg16 = as_h2(SYM ? kSymZneg16 : ((zz << 4) | 0xD400D400u));   // -(64 + z)
+            float4v part[MT];
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) part[mt] = (float4v){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const half8v b = dequant8(w[t][j], zneg, zneg16, magic);
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+                    part[mt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8v, a[mt][j]), b, part[mt], 0, 0, 0);
+            }
+            if (refill) load_codes(rec, t);
+            const uint32_t s2 = q.s[t >> 1];
+            const float s = (float)__builtin_bit_cast(_Float16, (uint16_t)((t & 1) ? (s2 >> 16) : (s2 & 0xFFFFu)));
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) acc[t][mt] += s * part[mt];
+            __builtin_amdgcn_sched_barrier(0);   // tiles stay apart, as in compute_group_lean
+        }
+    };
+    // At the head of a group its x tile is older than the loads of its codes, the newest ones: a count says when it has landed.
+    auto next_x = [&]() {
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kGroupLoads) : "memory");
+        read_x();
+    };
+    if (n_w > 0) {   // uniform
+        copy_x(0);
+        __builtin_amdgcn_sched_barrier(0);   // x before the codes, here and below
+        load_quant<TW, SYM>(qw, recs, 0, scale_off, zero_off);
+#pragma unroll
+        for (int t = 0; t < TW; ++t) load_codes(0, t);
+        __builtin_amdgcn_sched_barrier(0);
+        for (int i = 0; i + 1 < n_w; ++i) {
+            next_x();
+            copy_x(i + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            compute(i + 1, true);
+        }
+        next_x();
+        compute(0, false);
+    }
+    __syncthreads();   // the x tiles are dead
+    finish_unit<MT, TW, NW>(acc, lds4, ticket_sh, y, partial, tickets, M, N, S, fused, unit, ks, nb, t0, tid, lane, wave);
+}
+
 // Two ways to share the work.  Classic (per == 0): grid = (S, workgroup units), workgroup (ks, u) takes
 // K split ks of unit u.  Even split (per > 0): the (unit, group) pairs, unit-major, are dealt out in
 // runs of `per` to a 1-D grid, so every workgroup gets the same number of groups even when the units
@@ -1554,6 +1683,7 @@ struct Plan {
                  // (4*ks wavefronts per workgroup; nw is then 0)
     int ng;      // 0, or the groups per wavefront of the all-loads-up-front variant (M <= 4 only;
                  // K / 128 == S * nw * ng exactly)
+    size_t room = 0;   // bytes of partial sums below which the call is refused, although this plan may need fewer (gemm_entry)
 };
 
 // measured rows are keyed by a row bucket: 0 for M <= 8 (plain decoding and sequence verification), else
@@ -1594,7 +1724,8 @@ static bool flat_variant_exists(int tw, int nw, int ng)
 #define W4_VARIANTS(X)                                                                              \
     W4_VARIANTS_SMALL(X, 1) W4_VARIANTS_SMALL(X, 2) W4_VARIANTS_SMALL(X, 3) W4_VARIANTS_SMALL(X, 4) \
     X(1, 2, 8, 1) X(1, 2, 8, 2) X(1, 2, 8, 4) X(1, 4, 4, 4) X(1, 4, 8, 1) X(1, 4, 8, 2)                         \
-    X(1, 8, 8, 1) X(1, 8, 8, 2) X(2, 2, 8, 1) X(2, 2, 8, 2) X(2, 4, 8, 1)
+    X(1, 8, 8, 1) X(1, 8, 8, 2)                                                                     \
+    X(2, 2, 8, 1) X(2, 4, 8, 1) X(2, 8, 8, 1) X(3, 2, 8, 1) X(3, 4, 8, 1) X(4, 2, 8, 1) X(4, 4, 8, 1)
 
 // column-split variant (nw == 0): Y(MT, TW, DEPTH)
 #define W4_NS_VARIANTS(Y)                                                                           \
@@ -1637,9 +1768,9 @@ static constexpr SplitVariants split_variants()
 }
 constexpr SplitVariants kSplitVariants = split_variants();
 
-// Shapes without a measured row.  Two least-squares fits give the time of a plan in microseconds from its launch shape,
+// Shapes without a measured row.  Least-squares fits give the time of a plan in microseconds from its launch shape,
 // over weights that come from HBM: 2477 plans of 92 calls (M = 1 .. 16) and 3039 of 132 (M = 20 .. 64) on 32 shapes,
-// K = 640 .. 28672, N = 1000 .. 32000.  The plan with the least time lies 2 to 3 % behind the best measured one in the mean.
+// K = 640 .. 28672, N = 1000 .. 32000; and 1638 plans of 240 calls of the kernel whose wavefronts have x tiles of their own, N up to 57344.  The plan with the least time lies 2 to 3 % behind the best measured one in the mean.
 // What the formulas know and the plain rule below does not: a workgroup more than the chip holds at once costs a whole second
 // pass (4096 x 12288 at 32 rows: 288 workgroups 19.0 us, 192 workgroups 13.4), and a second kernel or a last arriver costs 2 to 3 us,
 // so one K split on fewer compute units is often ahead (18944 -> 3584 at one row: 280 workgroups 17.2 us, 224 11.5).
@@ -1658,13 +1789,24 @@ struct PlanTimes {
 };
 struct ShapeTime {
     int units, ways;   // workgroups per K split, wavefronts (or K sets) that share a K range
-    bool k_sets;
+    bool k_sets, own_x;
     float base, group, per_fill, fill_one, last, last_split, second, second_split;
     ShapeTime(const PlanTimes &c, int tw_, int nw, int depth, int ks)
     {
         const float tw = (float)tw_;
         k_sets = ks > 0;
-        if (!k_sets) {   // wavefronts that split K
+        own_x = !k_sets && c.M > 16;
+        if (own_x) {   // wavefronts that split K, each with an x tile of its own
+            const float m_tw = c.m * tw;
+            units = c.tiles / tw_;
+            ways = kXWaves;
+            base = 3.333f + 1.622f * c.stream - 0.591f * c.m - 0.277f * tw + 0.237f * m_tw;
+            group = 0.368f + 0.114f * c.m + 0.008f * tw + 0.081f * m_tw;
+            per_fill = -1.281f + 0.559f * c.m - 0.158f * m_tw;
+            fill_one = 1.f / 256.f;
+            last = 1.572f - 0.032f * m_tw, last_split = 0.079f + 0.017f * m_tw;
+            second = 1.505f, second_split = 0.198f + 2.468f * c.rows_cols;
+        } else if (!k_sets) {   // wavefronts that split K
             const bool many = c.M > 8;
             units = c.tiles / tw_;
             ways = nw;
@@ -1704,7 +1846,7 @@ struct ShapeTime {
     float last_arriver(int S) const { return last + last_split * (float)S; }
     float second_kernel(int S) const { return second + second_split * (float)S; }
     float split_cost(int S) const { return last_arriver(S) < second_kernel(S) ? last_arriver(S) : second_kernel(S); }   // grows with S
-    int passes(int S) const { return k_sets ? (units * S + 255) / 256 : (units * S * ways + 8 * 272 - 1) / (8 * 272); }
+    int passes(int S) const { return k_sets || own_x ? (units * S + 255) / 256 : (units * S * ways + 8 * 272 - 1) / (8 * 272); }
 };
 
 static size_t partial_bytes(int mt, int nblocks, const Plan &pl, int groups);
@@ -1717,6 +1859,8 @@ struct RuleShape { int tw, nw, depth, ks, slots; };   // slots: workgroups that 
 constexpr RuleShape kRuleShapes[] = {
     {2, 4, 1, 0, 512}, {4, 4, 1, 0, 512}, {8, 4, 1, 0, 512}, {2, 8, 1, 0, 256}, {4, 8, 1, 0, 256}, {8, 8, 1, 0, 256},   // one row tile
     {2, 0, 1, 2, 256}, {2, 0, 2, 2, 256}, {2, 0, 1, 3, 256}, {2, 0, 2, 3, 256}, {4, 0, 1, 2, 256}, {4, 0, 2, 2, 256}, {4, 0, 1, 3, 256}};
+constexpr int kComputeUnits = 256;
+constexpr int kOwnXTiles[] = {2, 4, 8};   // tiles per wavefront of the kernel whose wavefronts have x tiles of their own
 constexpr int kRuleShapeCount = sizeof(kRuleShapes) / sizeof(kRuleShapes[0]);
 struct RuleShapes {   // of a number of row tiles
     int count = 0;
@@ -1734,7 +1878,7 @@ static constexpr RuleShapes rule_shapes(int mt)
 }
 constexpr RuleShapes kRuleShapesOf[4] = {rule_shapes(1), rule_shapes(2), rule_shapes(3), rule_shapes(4)};
 
-static Plan predicted_plan(const Plan &plain, int M, int N, int K)
+static Plan predicted_plan(const Plan &plain, int M, int N, int K, bool own_x)
 {
     // what the caller's workspace and the built-in scratch have to hold does not grow beyond the latter
     constexpr size_t kRoom = (size_t)32 << 20;
@@ -1742,11 +1886,12 @@ static Plan predicted_plan(const Plan &plain, int M, int N, int K)
     if (partial_bytes(mt, nblocks, plain, groups) > kRoom) return plain;
     const PlanTimes call(M, N, K);
     Plan best = plain;
-    float least;
+    float least, best_time;
     {
         const ShapeTime t(call, plain.tw, plain.nw, plain.depth, plain.ks);
         const int passes = t.passes(plain.S);
         least = t.walk(call, plain.S) + (plain.S == 1 ? 0.f : plain.fused ? t.last_arriver(plain.S) : t.second_kernel(plain.S));
+        best_time = least * (1.f + 0.5f * (float)(passes - 1));
         least *= passes > 1 ? 0.95f * (1.f + 0.5f * (float)(passes - 1)) : 0.87f;
     }
     const RuleShapes &shapes = kRuleShapesOf[mt - 1];
@@ -1765,6 +1910,26 @@ static Plan predicted_plan(const Plan &plain, int M, int N, int K)
             if (i == 1 && t.least_walk(call, most) + t.split_cost(2) >= least) break;   // nor does any other split
             const float sum = t.walk(call, S) + (S > 1 ? t.split_cost(S) : 0.f);   // one pass: S is at most what the chip holds
             const Plan p = {v.tw, v.nw, v.depth, S, S > 1 ? t.last_arriver(S) < t.second_kernel(S) : plain.fused, v.ks, 0};
+            if (sum < least && partial_bytes(mt, nblocks, p, groups) <= kRoom) least = best_time = sum, best = p;
+        }
+    }
+    if (mt == 1 || !own_x || K > kStagedMaxK) return best;
+    // Wavefronts with x tiles of their own, where they promise a fourteenth less still: in one pass, and with half a group per
+    // wavefront at least.  On 240 random shapes and row counts 1.24 times faster in the mean and 1.4 % slower at worst than without them.
+    least = 0.93f * best_time;
+    const size_t plain_bytes = partial_bytes(mt, nblocks, plain, groups), best_bytes = partial_bytes(mt, nblocks, best, groups);
+    const size_t room = plain_bytes < best_bytes ? plain_bytes : best_bytes;
+    for (const int tw : kOwnXTiles) {
+        if (!variant_exists(mt, tw, kXWaves, 1)) continue;
+        const ShapeTime t(call, tw, kXWaves, 1, 0);
+        const int fit = kComputeUnits / t.units, deep = groups / (kXWaves / 2);
+        const int most = fit < 1 ? 0 : deep < 1 ? 1 : deep < fit ? (deep < 16 ? deep : 16) : (fit < 16 ? fit : 16);
+        const int splits[5] = {1, 2, most / 2, most * 3 / 4, most};
+        for (int i = 0; i < 5; ++i) {
+            const int S = splits[i];
+            if (S < 1 || S > most || (i > 1 && S <= splits[i - 1])) continue;
+            const float sum = t.walk(call, S) + (S > 1 ? t.split_cost(S) : 0.f);
+            const Plan p = {tw, kXWaves, 1, S, S == 1 || t.last_arriver(S) < t.second_kernel(S), 0, 0, room};
             if (sum < least && partial_bytes(mt, nblocks, p, groups) <= kRoom) least = sum, best = p;
         }
     }
@@ -1776,10 +1941,13 @@ static Plan predicted_plan(const Plan &plain, int M, int N, int K)
 // K splits across workgroups as that allows (each costs an fp32 partial round trip that grows
 // with M), and as many tiles per wavefront as that allows (each x fragment is reused per tile).
 // Any knob set through w4a16_set_param overrides the corresponding field.
-// `least`: the plan of a call whose workspace does not hold this one, i.e. is smaller than the stated size.  It is the plain rule's,
-// which may ask for less; without it such calls, accepted as long as the plain rule served them, would be refused.
-static Plan choose_plan(int M, int N, int K, bool least = false)
+// `no_own_x`, then `least`: the plans of a call whose workspace does not hold the one before, i.e. is smaller than the stated size.  The last is
+// the plain rule's, which may ask for less; without them such calls, accepted as long as these served them, would be refused.
+// And what they could not serve stays refused (Plan::room).
+enum class Choice { preferred, no_own_x, least };
+static Plan choose_plan(int M, int N, int K, Choice choice = Choice::preferred)
 {
+    const bool least = choice == Choice::least;
     const Params &p = params();
     const int mt = (M + 15) / 16;
     const int groups = K / kGroup, tiles = pad_cols(N) / 16;
@@ -1866,14 +2034,14 @@ static Plan choose_plan(int M, int N, int K, bool least = false)
             }
         }
     }
-    if (by_rule && best.tw != 0 && !least) best = predicted_plan(best, M, N, K);
+    if (by_rule && best.tw != 0 && !least) best = predicted_plan(best, M, N, K, choice == Choice::preferred);
+    if (mt > 1 && best.nw == kXWaves && K > kStagedMaxK) best.tw = 0;   // forced by knobs: its offsets are 32-bit too
     if (p.fused_reduce != 2) best.fused = p.fused_reduce;
     return best;   // tw == 0: the knobs name a variant that is not compiled
 }
 
 // Even split of the column-split kernel's (workgroup unit, group) pairs over the compute units:
 // run length, number of runs (= workgroups) and the largest number of runs that touch one unit.
-constexpr int kComputeUnits = 256;
 struct EvenSplit { int per, runs, max_slots; };
 static EvenSplit even_split(int wg_units, int groups)
 {
@@ -1909,10 +2077,16 @@ static int launch_sym(const void *x, const void *packed, const Out &y, int M, in
                       void *workspace, hipStream_t stream)
 {
     static bool lds_ok = false;   // LDS above 64 KB needs an opt-in, once per kernel
-    const size_t lds_bytes = (size_t)NW * 4 * TW * MT * 64 * sizeof(float);
+    constexpr bool kOwnX = MT > 1 && NW == kXWaves;
+    auto *const kernel = [] {
+        if constexpr (kOwnX) return &gemm_x_kernel<MT, TW, SYM>;
+        else return &gemm_kernel<MT, TW, NW, DEPTH, SYM>;
+    }();
+    const size_t sum_bytes = (size_t)NW * 4 * TW * MT * 64 * sizeof(float), x_bytes = kOwnX ? (size_t)NW * MT * 4096 : 0;
+    const size_t lds_bytes = sum_bytes > x_bytes ? sum_bytes : x_bytes;
     if (lds_bytes > 160 * 1024) return W4A16_EUNSUP;
     if (!lds_ok && lds_bytes > 48 * 1024) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_kernel<MT, TW, NW, DEPTH, SYM>),
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes) != hipSuccess)
             return W4A16_EHIP;
         lds_ok = true;
@@ -1921,7 +2095,7 @@ static int launch_sym(const void *x, const void *packed, const Out &y, int M, in
     const int units = nblocks * kTiles / TW;
     uint32_t *tickets = reinterpret_cast<uint32_t *>(workspace);
     float *partial = reinterpret_cast<float *>(reinterpret_cast<uint8_t *>(workspace) + kTicketBytes);
-    hipLaunchKernelGGL((gemm_kernel<MT, TW, NW, DEPTH, SYM>), dim3((unsigned)S, (unsigned)units), dim3(NW * 64), lds_bytes,
+    hipLaunchKernelGGL(kernel, dim3((unsigned)S, (unsigned)units), dim3(NW * 64), lds_bytes,
                        stream, (const _Float16 *)x, (const uint8_t *)packed, y, partial, tickets, M, N,
                        K, groups, S, fused, groups / S, groups % S);
     if (S > 1 && !fused)
@@ -2074,9 +2248,11 @@ size_t w4a16_workspace_bytes(int M_max, int N, int K, int G)
     const int nblocks = pad_cols(N) / kBlockCols;
     size_t need = 0;
     for (int m = 1; m <= M_max; ++m) {   // the plan depends on M only through a few thresholds: cheap enough
-        const Plan pl = choose_plan(m, N, K);
-        size_t b = pl.tw ? partial_bytes((m + 15) / 16, nblocks, pl, K / kGroup) : 0;
-        if (b > need) need = b;
+        for (const Choice choice : {Choice::preferred, Choice::no_own_x}) {
+            const Plan pl = choose_plan(m, N, K, choice);
+            size_t b = pl.tw ? partial_bytes((m + 15) / 16, nblocks, pl, K / kGroup) : 0;
+            if (b > need) need = b;
+        }
     }
     return kTicketBytes + need;
 }
@@ -2112,8 +2288,9 @@ static int gemm_entry(const void *x, const void *packed, const Out &out, int M, 
     Plan pl = choose_plan(M, N, K);
     if (pl.tw == 0) return W4A16_EUNSUP;
     const size_t room = workspace && workspace_bytes > kTicketBytes ? workspace_bytes - kTicketBytes : 0;
-    if (plan_need(pl, M, N, K) > room) {
-        pl = choose_plan(M, N, K, true);
+    if (plan_need(pl, M, N, K) > room || pl.room > room) {
+        pl = choose_plan(M, N, K, Choice::no_own_x);
+        if (plan_need(pl, M, N, K) > room) pl = choose_plan(M, N, K, Choice::least);
         if (plan_need(pl, M, N, K) > room) return W4A16_EWORKSPACE;
     }
     return run_plan(pl, x, packed, out, M, N, K, workspace, stream);

@@ -112,6 +112,27 @@ def test_parity_wide_workgroups(M, K, N, big_ws):
         assert np.array_equal(run_gemm(ex, ex_packed, big_ws).view(np.uint16), ex16.view(np.uint16)), variant
 
 
+@pytest.mark.parametrize("M,K,N", [(17, 128, 8), (32, 640, 264), (33, 1024, 136), (48, 1152, 1000), (49, 2176, 128), (64, 3200, 520), (24, 14336, 256)])
+def test_parity_own_x_tiles(M, K, N, big_ws):
+    """more than one row tile, eight wavefronts that split K and keep an x tile each: fewer groups than wavefronts, one group
+    each, one or two wavefronts with one more, splits across workgroups that leave some without a group, partial row tiles"""
+    print(f"gemm parity (own x tiles) M={M} K={K} N={N}", flush=True)
+    inp = I.make_linear(5700 + M + K + N, M, K, N)
+    packed = B.pack_from_numpy(inp)
+    y32, _, _ = R.w4a16_gemm(inp.x, inp.qweight, inp.scales, inp.qzeros, 128, want64=False)
+    ex = I.make_linear(5750 + M, M, K, N, x_kind="small_int", scale_kind="pow2")
+    ex_packed = B.pack_from_numpy(ex)
+    _, _, ex16 = R.w4a16_gemm(ex.x, ex.qweight, ex.scales, ex.qzeros, 128, want64=False)
+    for tw in (2, 4) + ((8,) if M <= 32 else ()):
+        for split in (1, 2, 3, 5):
+            for fused in ((0, 1) if split > 1 else (0,)):
+                set_variant(tw, 8, 1, split, fused)
+                what = f"M={M} K={K} N={N} (tw, split, fused)={(tw, split, fused)}"
+                assert B.w4a16_plan_describe(M, N, K, 128)[:5] == (0, (M + 15) // 16, tw, 8, 1)
+                check_gemm(run_gemm(inp, packed, big_ws), y32, what)
+                assert np.array_equal(run_gemm(ex, ex_packed, big_ws).view(np.uint16), ex16.view(np.uint16)), what
+
+
 # high-occupancy column-split workgroups, M > 16 only: (tiles_per_wave, k_sets, prefetch_depth, split_k)
 VARIANTS_CS = [(2, 1, 2, 1), (2, 2, 2, 1), (2, 2, 2, 3), (4, 1, 2, 1), (4, 1, 2, 2), (4, 2, 2, 1),
                (2, 3, 1, 3), (2, 3, 1, 1), (2, 3, 2, 1), (4, 3, 1, 2), (2, 2, 1, 3), (4, 2, 1, 2), (4, 1, 1, 1), (8, 1, 1, 1)]
