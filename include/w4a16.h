@@ -324,9 +324,10 @@ int lm_head_topk(const void *x, const void *packed, int M, int V, int K, int top
  * as many as the stated workspace holds),
  * "attn_pack" (how the rows of a KV group are cut into row tiles in tree_verify_attn: 0 = by size;
  * 1 = one tile per query head always; 2 = the whole group in one tile whenever it fits 64 rows; 3 = the whole group cut
- * evenly into as few tiles as 64 rows allow; 10 + d = exactly d heads per tile
+ * evenly into as few tiles as 64 rows allow; 4 = as 32 rows allow; 10 + d = exactly d heads per tile
  * where d divides the group and the tile fits 64 rows, else one), "attn_row_tiles" (which kernel of
- * tree_verify_attn runs: 0 = the one that shares K and V tiles through LDS; the older one, kept for comparison:
+ * tree_verify_attn runs: 0 = by the height of a row tile, the one that shares K and V tiles through LDS or, up to 32 rows, the one
+ * whose wavefronts bring their own; the older one, kept for comparison:
  * 2 = a wavefront carries 32 query rows, in two row groups for taller tiles; 4 = 64 rows, one wavefront
  * per SIMD), "attn_fused_merge" (how the key ranges of a
  * row tile are merged: 2 = by the last of its workgroups to finish, 1 = by a second kernel, 0 = by size, the former while

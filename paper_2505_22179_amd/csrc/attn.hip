@@ -7,9 +7,10 @@
 // transposed (the contraction there runs over keys while V is stored with the head dimension
 // contiguous).  Key ranges of different workgroups are combined in range order, by the last
 // workgroup of a tile to finish or by a second small kernel, so the result does not depend on
-// scheduling.  Two kernels: tree_attn_shared_kernel, which every call runs by default (eight
-// wavefronts, K and V tiles brought to LDS once per workgroup and shared), and the older
-// tree_attn_kernel (every wavefront fetches its own K fragments and V rows), kept selectable.
+// scheduling.  Three kernels: tree_attn_shared_kernel (eight wavefronts, K and V tiles brought to LDS once
+// per workgroup and shared) for row tiles of 33 .. 64 rows, tree_attn_wave_kernel (each wavefront brings its own tiles and
+// walks without barriers) for shorter ones, and the older tree_attn_kernel (every wavefront fetches its own K fragments
+// and V rows), kept selectable.
 #include <type_traits>
 
 #include "internal.h"
@@ -60,6 +61,14 @@ __device__ __forceinline__ float row_group_max(float v)
     asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
     a = max_of_two(a, b);
     b = a;
+    asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+    return max_of_two(a, b);
+}
+
+// maximum over the lanes l and l ^ 32, returned to both
+__device__ __forceinline__ float half_wave_max(float v)
+{
+    float a = v, b = v;
     asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
     return max_of_two(a, b);
 }
@@ -578,7 +587,7 @@ __global__ __launch_bounds__(64 * kSharedWaves) void tree_attn_shared_kernel(
     // after the transfers below have been requested
     __shared__ uint64_t row_bits[kRowsPad];
     const bool reaches_draft = b1 * kKeyBlock > P;   // uniform over the workgroup
-    uint8_t mask_byte[8];
+    uint32_t mask_byte[8] = {};
     if (reaches_draft) {
         const int mcol = min(lane, M - 1);
 #pragma unroll
@@ -631,6 +640,7 @@ __global__ __launch_bounds__(64 * kSharedWaves) void tree_attn_shared_kernel(
     if (reaches_draft) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
+            asm volatile("" : "+v"(mask_byte[i]));   // keeps the comparison, and with it the wait for the byte, from being done before the transfers
             const uint64_t bits = __ballot(mask_byte[i] != 0 && wave * 8 + i < M && lane < M);
             if (lane == i) row_bits[wave * 8 + i] = bits;
         }
@@ -833,6 +843,291 @@ __global__ __launch_bounds__(64 * kSharedWaves) void tree_attn_shared_kernel(
     merge_tile(unit_o, unit_ml, out, tid, 64 * kSharedWaves, tile, nsplit);
 }
 
+// ---- Row tiles of at most 32 rows: wavefronts with K and V tiles of their own --------------------------
+// With so few rows half of the wavefronts above would carry padding.  Here each of the eight wavefronts carries all 32 rows of
+// the tile and takes key steps of its own, wave, wave + 8, ... of the range.  It shares no K or V tile, so it brings them itself
+// (direct global -> LDS transfers into 16 KB of its own: the next step's K as soon as this step's scores are done, its V after
+// the products) and meets the others only at the end: no barrier in the walk, and one wavefront's softmax runs beside another's products.
+// 32x32x16 steps leave a lane with sixteen scores of ONE query row (column lane % 32; keys 8 a + 4 h + b, h = lane / 32), again the
+// operand of O^T += V^T . P^T as they stand, and two lanes share a row.  Chunks of K, V and Q rows are permuted as above.
+// What bounds it: at short prefixes the chain launch, first tiles, exchange, merge (5.5 us with one step); at long ones
+// the transfers, 16 KB per step and 32 rows.  Against the kernel above, same split, us: prefix 2048, 64/8 heads, M = 1 9.1 -> 8.3, M = 8 11.2 -> 9.8;
+// 32/8 heads, M = 30 11.8 -> 10.7; prefix 16000, 64/8 heads, M = 1 19.2 -> 17.5.  A form with 64 rows per wavefront (250 registers) lost
+// to the kernel above (15.7 against 16.6 us at M = 60, prefix 2048; even at prefix 8000): the exchange doubles.
+constexpr int kWaveBytes = 2 * kTileBytes;
+constexpr int kWaveQ = kSharedWaves * kWaveBytes;                              // Q tile behind the K and V tiles
+constexpr int kWaveState = kSharedWaves * kExWave;                             // after the walk: [row][wavefront] (max, sum) behind the exchange rows,
+constexpr int kWaveRows = 32;
+constexpr int kWaveWeights = kWaveState + kWaveRows * kSharedWaves * 8;        // [row][wavefront] (weight, weighted sum)
+constexpr int kWaveEnd = kWaveWeights + kWaveRows * kSharedWaves * 8;
+constexpr int kWaveLds = kWaveQ + kWaveRows * kHeadDim * 2 > kWaveEnd ? kWaveQ + kWaveRows * kHeadDim * 2 : kWaveEnd;
+typedef float float16v __attribute__((ext_vector_type(16)));
+typedef float float2v __attribute__((ext_vector_type(2)));
+
+// the transposing read of four key rows at lds_addr + OFFSET and the four that lie eight rows further on
+template <int OFFSET>
+__device__ __forceinline__ void read_transposed_rows(short4v &lo, short4v &hi, uint32_t lds_addr)
+{
+    asm volatile("ds_read_b64_tr_b16 %0, %2 offset:%3\n\tds_read_b64_tr_b16 %1, %2 offset:%4"
+                 : "=&v"(lo), "=&v"(hi)
+                 : "v"(lds_addr), "n"(OFFSET), "n"(OFFSET + 8 * 256));
+}
+// returns once at most N LDS operations of this wavefront are still under way; the pair awaited cannot be used above it
+template <int N>
+__device__ __forceinline__ void wait_transposed(short4v &lo, short4v &hi)
+{
+    asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(lo), "+v"(hi) : "n"(N));
+}
+
+__global__ __launch_bounds__(64 * kSharedWaves) void tree_attn_wave_kernel(
+    const _Float16 *__restrict__ q, const _Float16 *__restrict__ k, const _Float16 *__restrict__ v,
+    const uint8_t *__restrict__ mask, _Float16 *__restrict__ out, float *__restrict__ part_o,
+    float *__restrict__ part_ml, uint32_t *__restrict__ tickets, int M, int P, int Hq, int Hkv,
+    int group, float scale_log2e, int nsplit, int bq, int brem, int tile_rows, int tiles_per_kv, int fused)
+{
+    extern __shared__ float4v smem4[];
+    uint8_t *lds = reinterpret_cast<uint8_t *>(smem4);
+    const unsigned grid = gridDim.x;
+    fetch_arguments_together(q, k, v, mask, out, part_o, part_ml, tickets, M, P, Hq, Hkv, group, scale_log2e, nsplit, bq, brem, tile_rows,
+                             tiles_per_kv, fused, grid);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int h = lane >> 5, c = lane & 31;
+    int lid = blockIdx.x;   // workgroups of one KV head on one XCD (see tree_attn_kernel)
+    if ((grid & 7) == 0) lid = (blockIdx.x & 7) * (grid >> 3) + (blockIdx.x >> 3);
+    const int unit = lid / nsplit, sp = lid % nsplit;
+    const RowTile tile(unit, M, Hq, group, tile_rows, tiles_per_kv);
+    const int kvh = tile.kvh, R = tile.rows;
+    const int T = P + M;
+    const int b0 = sp * bq + (sp < brem ? sp : brem), b1 = b0 + bq + (sp < brem ? 1 : 0);
+    const size_t kv_row_bytes = (size_t)Hkv * kHeadDim * 2;
+    auto locate = [&](int rho, int &qrow) {   // tile row -> its query row and the element offset of its (query row, head) in q and out
+        int head;
+        tile.locate(rho, qrow, head);
+        return (uint32_t)(qrow * Hq + head) * kHeadDim;
+    };
+    // tree mask of the draft keys as in tree_attn_shared_kernel: bytes requested first, words made of them later
+    __shared__ uint64_t row_bits[kRowsPad];
+    const bool reaches_draft = b1 * kKeyBlock > P;   // uniform over the workgroup
+    uint32_t mask_byte[8] = {};
+    if (reaches_draft) {
+        const int mcol = min(lane, M - 1);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) mask_byte[i] = mask[(size_t)min(wave * 8 + i, M - 1) * M + mcol];
+    }
+    // transfers: lane l of transfer i fills bytes 16 (l % 16) .. of tile row 4 i + l / 16
+    const int trow = lane >> 4, tchunk = lane & 15;
+    uint8_t *const ktile = lds + wave * kWaveBytes, *const vtile = ktile + kTileBytes, *const qtile = lds + kWaveQ;
+    {
+        const int rho = 4 * wave + trow;
+        int qrow;
+        const uint32_t elem = locate(rho, qrow);
+        row_to_lds(reinterpret_cast<const uint8_t *>(q) + (size_t)elem * 2 + ((tchunk ^ (rho & 7)) << 4), qtile + wave * 1024);
+    }
+    const uint8_t *const k_src = reinterpret_cast<const uint8_t *>(k) + (size_t)kvh * kHeadDim * 2;
+    const uint8_t *const v_src = reinterpret_cast<const uint8_t *>(v) + (size_t)kvh * kHeadDim * 2;
+    uint32_t lane_k[2], lane_v[2];   // the chunk permutation depends on the transfer's parity only
+#pragma unroll
+    for (int par = 0; par < 2; ++par) {
+        const int key = 4 * par + trow;
+        lane_k[par] = (uint32_t)trow * (uint32_t)kv_row_bytes + (uint32_t)((tchunk ^ (key & 7)) << 4);
+        lane_v[par] = (uint32_t)trow * (uint32_t)kv_row_bytes + (uint32_t)((tchunk ^ ((2 * key) & 15)) << 4);
+    }
+    auto request = [&](int step, const uint8_t *src, const uint32_t (&lane_src)[2], int twice, uint8_t *dst) {
+        const int key0 = step * kKeyBlock;
+        if (key0 + kKeyBlock <= T) {   // uniform
+            const uint8_t *from = src + (size_t)key0 * kv_row_bytes;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) row_to_lds(from + (size_t)(4 * i) * kv_row_bytes + lane_src[i & 1], dst + i * 1024);
+        } else {   // the last step of all: rows beyond the last key repeat it (they are masked out below)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int key = 4 * i + trow, swz = twice ? (2 * key) & 15 : key & 7;
+                row_to_lds(src + (size_t)min(key0 + key, T - 1) * kv_row_bytes + ((tchunk ^ swz) << 4), dst + i * 1024);
+            }
+        }
+    };
+    int step = b0 + wave;
+    if (step < b1) {   // uniform over the wavefront
+        request(step, k_src, lane_k, 0, ktile);
+        request(step, v_src, lane_v, 1, vtile);
+    }
+    if (reaches_draft) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            asm volatile("" : "+v"(mask_byte[i]));   // keeps the comparison, and with it the wait for the byte, from being done before the transfers
+            const uint64_t bits = __ballot(mask_byte[i] != 0 && wave * 8 + i < M && lane < M);
+            if (lane == i) row_bits[wave * 8 + i] = bits;
+        }
+    }
+    // everybody's part of the Q tile has landed (it is older than the sixteen transfers of K and V), and the mask words
+    if (step < b1) asm volatile("s_waitcnt vmcnt(16) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+
+    const uint32_t frag = (uint32_t)(c * 256 + ((h ^ (c & 7)) << 4));   // fragment j of K or Q: chunk (2 j + h) ^ (row % 8)
+    half8v qf[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) qf[j] = *reinterpret_cast<const half8v *>(qtile + (frag ^ (j << 5)));
+    uint64_t mbits = 0;
+    if (reaches_draft) {
+        int qrow;
+        locate(c, qrow);
+        mbits = row_bits[qrow];
+    }
+    // V: lane s of 16-lane block b points at key row 4 (b / 2) + s / 4 (and 8 further on), elements 32 dt + 16 (b % 2) + 4 (s % 4) ..
+    const int vkey = 4 * h + ((lane & 15) >> 2);
+    const uint32_t vbase = lds_address(vtile), vfrag = vkey * 256 + (((2 * ((lane >> 4) & 1) + ((lane >> 1) & 1)) ^ (2 * vkey)) << 4) + 8 * (lane & 1);
+    float16v o[4];
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o[dt][i] = 0.f;
+    float m_run = kLowest, l_run = 0.f;   // l_run: this lane's share (its keys) of the row's sum
+
+    while (step < b1) {   // uniform over the wavefront; no barrier inside
+        const int next = step + kSharedWaves, key0 = step * kKeyBlock;
+        const bool more = next < b1;
+        asm volatile("s_waitcnt vmcnt(8)" ::: "memory");   // K of this step; its V is newer
+        float16v sc;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sc[i] = 0.f;
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            sc = __builtin_amdgcn_mfma_f32_32x32x16_f16(*reinterpret_cast<const half8v *>(ktile + (frag ^ (j << 5))), qf[j], sc, 0, 0, 0);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the K tile has been read
+        if (more) request(next, k_src, lane_k, 0, ktile);
+        half8v pb[2];
+        const bool prefix_only = key0 + kKeyBlock <= P;   // uniform: committed keys, all visible
+        float s[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[i] = sc[i];   // key 8 (i / 4) + 4 h + i % 4 of the step
+        if (!prefix_only) {   // the visibility window of tree_attn_shared_kernel
+            const int first = key0 - P;
+            const uint64_t window = first >= 0 ? mbits >> first : (mbits << -first) | ((1ull << -first) - 1);
+            const uint32_t mine = (uint32_t)window >> (4 * h);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) s[i] = ((mine >> (8 * (i >> 2) + (i & 3))) & 1u) ? s[i] : -__builtin_inff();
+        }
+        // the scale is positive (checked by the host): the largest raw score is the largest scaled one
+        const float m_a = max_of_three(max_of_three(s[0], s[1], s[2]), max_of_three(s[3], s[4], s[5]), max_of_three(s[6], s[7], s[8]));
+        const float m_b = max_of_three(max_of_three(s[9], s[10], s[11]), max_of_three(s[12], s[13], s[14]), s[15]);
+        const float m_new = max_of_two(m_run, half_wave_max(max_of_two(m_a, m_b)) * scale_log2e);
+        const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+        float psum[4];
+#pragma unroll
+        for (int i = 0; i < 16; i += 4) {
+            float p[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i + e], scale_log2e, -m_new));
+                pb[i >> 3][(i & 7) + e] = (_Float16)p[e];
+            }
+            psum[i >> 2] = (p[0] + p[1]) + (p[2] + p[3]);
+        }
+        l_run = l_run * alpha + ((psum[0] + psum[1]) + (psum[2] + psum[3]));
+        m_run = m_new;
+        if (__any(alpha != 1.0f)) {
+#pragma unroll
+            for (int dt = 0; dt < 4; ++dt) o[dt] *= alpha;
+        }
+        if (more) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");   // V of this step; the next K is newer
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        // V^T fragments (dt, u), two ahead of the products that use them: slots 8 h .. 8 h + 3 are keys 16 u + 4 h .., slots
+        // 8 h + 4 .. those eight further on -- the keys whose probabilities this lane's column holds
+        short4v lo[8], hi[8];
+        auto read_v = [&](auto f) {
+            constexpr int F = decltype(f)::value;
+            read_transposed_rows<(F & 1) * 16 * 256>(lo[F], hi[F], vbase + (vfrag ^ ((F >> 1) << 6)));
+        };
+        auto product = [&](auto f) {
+            constexpr int F = decltype(f)::value;
+            if constexpr (F + 2 < 8) read_v(std::integral_constant<int, F + 2>{});
+            wait_transposed<F + 2 < 8 ? 4 : F + 1 < 8 ? 2 : 0>(lo[F], hi[F]);
+            typedef short short8v __attribute__((ext_vector_type(8)));
+            const short8v both = __builtin_shufflevector(lo[F], hi[F], 0, 1, 2, 3, 4, 5, 6, 7);
+            const half8v va = __builtin_bit_cast(half8v, both);
+            o[F >> 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(va, pb[F & 1], o[F >> 1], 0, 0, 0);
+        };
+        read_v(std::integral_constant<int, 0>{});
+        read_v(std::integral_constant<int, 1>{});
+        product(std::integral_constant<int, 0>{});
+        product(std::integral_constant<int, 1>{});
+        product(std::integral_constant<int, 2>{});
+        product(std::integral_constant<int, 3>{});
+        product(std::integral_constant<int, 4>{});
+        product(std::integral_constant<int, 5>{});
+        product(std::integral_constant<int, 6>{});
+        product(std::integral_constant<int, 7>{});
+        if (more) request(next, v_src, lane_v, 1, vtile);
+        step = next;
+    }
+
+    // The states of the eight wavefronts meet in LDS; the weights are worked out once per (row, wavefront)
+    l_run += __shfl_xor(l_run, 32, 64);
+    __syncthreads();   // every wavefront has left the K, V and Q tiles
+    uint8_t *const mine = lds + wave * kExWave;
+    float2v *const state = reinterpret_cast<float2v *>(lds + kWaveState), *const weights = reinterpret_cast<float2v *>(lds + kWaveWeights);
+    if (h == 0) state[c * kSharedWaves + wave] = (float2v){m_run, l_run};
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+            *reinterpret_cast<float4v *>(mine + c * kExRow + (8 * dt + 2 * a + h) * 16) =
+                (float4v){o[dt][4 * a], o[dt][4 * a + 1], o[dt][4 * a + 2], o[dt][4 * a + 3]};
+    __syncthreads();
+    auto row_max = [&](int row) {
+        float m_all = kLowest;
+#pragma unroll
+        for (int w = 0; w < kSharedWaves; ++w) m_all = fmaxf(m_all, state[row * kSharedWaves + w][0]);
+        return m_all;
+    };
+    if (tid < kWaveRows * kSharedWaves) {
+        const float2v me = state[tid];
+        const float wgt = __builtin_amdgcn_exp2f(me[0] - row_max(tid / kSharedWaves));
+        weights[tid] = (float2v){wgt, wgt * me[1]};
+    }
+    __syncthreads();
+    const bool last = nsplit == 1;
+    const PartialBuffer unit_o = partial_buffer(part_o + (size_t)unit * nsplit * kRowsPad * kHeadDim);
+    const PartialBuffer unit_ml = partial_buffer(part_ml + (size_t)unit * nsplit * kRowsPad * 2);
+#pragma unroll
+    for (int it = 0; it < 2; ++it) {   // thread t: four consecutive outputs of a row, 32 threads per row
+        const int item = tid + it * (64 * kSharedWaves);
+        const int rho = item >> 5, quad = item & 31;
+        float4v val = {0.f, 0.f, 0.f, 0.f};
+        float l_all = 0.f;
+#pragma unroll
+        for (int w = 0; w < kSharedWaves; ++w) {
+            const float2v wl = weights[rho * kSharedWaves + w];
+            l_all += wl[1];
+            val += wl[0] * *reinterpret_cast<const float4v *>(lds + w * kExWave + rho * kExRow + quad * 16);
+        }
+        if (rho >= R) continue;
+        if (last) {
+            val *= 1.f / l_all;
+            typedef _Float16 half4v __attribute__((ext_vector_type(4)));
+            half4v hv = {(_Float16)val[0], (_Float16)val[1], (_Float16)val[2], (_Float16)val[3]};
+            int qrow;
+            *reinterpret_cast<half4v *>(out + locate(rho, qrow) + quad * 4) = hv;
+        } else {   // written through to memory in either mode (see tree_attn_shared_kernel)
+            store_partial(unit_o, (sp * kRowsPad + rho) * (kHeadDim / 4) + quad, val);
+            if (quad == 0) {
+                store_partial_f32(unit_ml, (sp * kRowsPad + rho) * 2, row_max(rho));
+                store_partial_f32(unit_ml, (sp * kRowsPad + rho) * 2 + 1, l_all);
+            }
+        }
+    }
+    if (last || !fused) return;   // uniform over the grid
+    __shared__ uint32_t ticket_sh;   // last-arriver merge of the tile's key ranges, as in tree_attn_kernel
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid == 0) ticket_sh = __hip_atomic_fetch_add(&tickets[unit], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (ticket_sh != (uint32_t)(nsplit - 1)) return;
+    if (tid == 0) __hip_atomic_store(&tickets[unit], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    merge_tile(unit_o, unit_ml, out, tid, 64 * kSharedWaves, tile, nsplit);
+}
+
 // merge of the key ranges: one thread per four consecutive output elements, ranges in order;
 // NS = compiled upper bound of the number of ranges (all loads of a thread are issued at once)
 template <int NS>
@@ -978,9 +1273,9 @@ static int heads_per_tile(int M, int Hq, int Hkv, int knob)
 }
 
 // the whole group cut evenly into as few tiles as 64 rows allow; a tile may end inside a head
-static void even_tiles(int pairs, int &tile_rows, int &tiles_per_kv)
+static void even_tiles(int pairs, int most, int &tile_rows, int &tiles_per_kv)
 {
-    const int n = (pairs + kRowsPad - 1) / kRowsPad;
+    const int n = (pairs + most - 1) / most;
     tile_rows = (pairs + n - 1) / n;
     tiles_per_kv = (pairs + tile_rows - 1) / tile_rows;
 }
@@ -997,8 +1292,8 @@ static AttnPlan plain_plan(int M, int P, int Hq, int Hkv, int pack, int splits, 
 {
     const int group = Hq / Hkv, steps = key_steps(M, P);
     AttnPlan p;
-    if (pack == 3) {
-        even_tiles(group * M, p.tile_rows, p.tiles_per_kv);
+    if (pack == 3 || pack == 4) {
+        even_tiles(group * M, pack == 3 ? kRowsPad : kRowsPad / 2, p.tile_rows, p.tiles_per_kv);
     } else {
         const int d = heads_per_tile(M, Hq, Hkv, pack);
         p.tile_rows = d * M;
@@ -1013,63 +1308,31 @@ static AttnPlan plain_plan(int M, int P, int Hq, int Hkv, int pack, int splits, 
     return p;
 }
 
-// Time of a plan in microseconds, up to errors of some ten percent: a least-squares fit to 2663 measured plans (64/8, 32/8,
-// 16/2 and 8/8 heads, M = 1 .. 60, prefixes of 100 .. 16000, every tiling, 1 .. 32 ranges, both merges).  A workgroup's key steps
-// cost more when the chip is full and with short tiles; a fused merge costs one memory round trip per pass of the last
-// workgroup over its rows, the second kernel its launch.
+// Time of a plan in microseconds, up to errors of some six percent: least-squares fits to 5700 measured plans of 165 calls (64/8,
+// 40/8, 32/8, 16/2, 12/2 and 8/8 heads, M = 1 .. 64, prefixes of 16 .. 20000, every tiling, 1 .. 32 ranges, both merges), one for each
+// of the two kernels.  A workgroup's walk costs per round of its key wavefronts and per step (its transfers), more when the chip is full; a fused
+// merge costs by the last workgroup's rows and ranges, the second kernel its launch.
 static float plan_time(const AttnPlan &p, int M, int P, int Hkv)
 {
-    const int units = Hkv * p.tiles_per_kv, groups = units * p.ranges;
-    const float steps4 = 0.25f * (float)((key_steps(M, P) + p.ranges - 1) / p.ranges), fill = (float)(groups < 256 ? groups : 256) / 256.f;
-    float t = 5.1f + (float)((groups + 255) / 256) * steps4 * (1.4f + fill * (p.tile_rows > 32 ? 0.38f : 0.54f)) + 0.0235f * (float)p.tile_rows;
-    if (p.ranges > 1 && p.fused) {
-        const int per_pass = p.ranges <= 4 ? 64 : p.ranges <= 8 ? 32 : 16;   // rows
-        t += 0.95f + 0.25f * (float)((p.tile_rows + per_pass - 1) / per_pass) + 0.06f * (float)p.ranges + 0.006f * (float)(p.tile_rows * p.ranges);
-    } else if (p.ranges > 1) {
-        t += 2.f + 0.00006f * (float)(groups * p.tile_rows) + 0.08f * (float)p.ranges + (p.ranges > 16 ? 0.3f : 0.f);
+    const int units = Hkv * p.tiles_per_kv, groups = units * p.ranges, passes = (groups + 255) / 256;
+    const int steps = (key_steps(M, P) + p.ranges - 1) / p.ranges;
+    const float fill = (float)(groups < 256 ? groups : 256) / 256.f, rows = (float)p.tile_rows, ranges = (float)p.ranges;
+    const bool beyond_l2 = (float)(P + M) * (Hkv > 8 ? (float)Hkv / 8.f : 1.f) > 5860.f;   // 3 MB of K and V per XCD
+    const float far = beyond_l2 ? fill * (float)steps : 0.f;
+    if (p.tile_rows <= kWaveRows) {
+        const float rounds = (float)((steps + 7) / 8);
+        const float t = 5.225f + 0.028f * rows + (float)passes * (0.1672f * rounds * fill + 0.1562f * (float)steps + (steps > 8 ? 0.435f : 0.f) + 0.0487f * far);
+        if (p.ranges > 1) return t + (p.fused ? 1.297f + 0.0557f * ranges + 0.0058f * rows * ranges : 2.715f + 0.00002f * (float)groups * rows + 0.042f * ranges);
+        return steps > 8 ? t + 0.4f : t;   // the fit's error for one range of a few rounds: 40/8 heads, M = 2, nine steps 7.5 us, in five ranges 7.2
     }
-    return t;
-}
-
-// The plain plan, unless another one promises a tenth (and a microsecond) less: d heads per tile or even tiles, with one, two or four ranges or
-// as many as fill the chip (or half of it).  At long prefixes that is full tiles, which read K and V least often and
-// waste no rows, and up to 32 ranges; at short ones a single range and no merge; and where the plain plan's rounding up
-// makes more workgroups than compute units (40/8 heads: 280), as many as there are.  Over 360 other calls (also 12/2 and 40/8
-// heads, prefixes of 40 .. 32000) 13 % faster in the mean than the plain plan, at worst 3 % slower: P = 16000, 64/8 heads: M = 4 34.3 -> 21.8 us, M = 16 36.9 -> 25.7,
-// M = 24 39.2 -> 32.9, M = 40 61.9 -> 47.3; 32/8 heads: M = 8 34.6 -> 21.7, M = 24 36.6 -> 25.0; P = 100, 64/8 heads: M = 32 11.1 -> 8.1,
-// M = 60 11.3 -> 8.8; at prefix 2048 the plain plan stays for 64/8 and 32/8 heads.
-static AttnPlan plan_by_size(const AttnPlan &plain, int M, int P, int Hq, int Hkv)
-{
-    const int group = Hq / Hkv, steps = key_steps(M, P);
-    AttnPlan best = plain;
-    const float plain_time = plan_time(plain, M, P, Hkv);
-    float least = plain_time - (plain_time > 10.f ? 0.1f * plain_time : 1.f);
-    for (int d = 0; d <= group; ++d) {
-        AttnPlan p = {d * M, 0, 1, 0};
-        if (d == 0) {
-            even_tiles(group * M, p.tile_rows, p.tiles_per_kv);
-        } else {
-            if (group % d != 0 || M * d > kRowsPad) continue;
-            p.tiles_per_kv = group / d;
-        }
-        const int units = Hkv * p.tiles_per_kv;
-        int most = steps < kMaxRanges ? steps : kMaxRanges;
-        most = most > kChipTiles / units ? kChipTiles / units : most;
-        const int choices[5] = {1, 2, 4, most / 2, most};
-        for (int i = 0; i < 5; ++i) {
-            p.ranges = choices[i];
-            if (p.ranges < 1 || p.ranges > most || (i > 2 && p.ranges <= 4)) continue;
-            for (p.fused = 0; p.fused < (p.ranges > 1 ? 2 : 1); ++p.fused) {
-                const float t = plan_time(p, M, P, Hkv);
-                if (t < least) least = t, best = p;
-            }
-        }
-    }
-    return best;
+    const float rounds = (float)((steps + 3) / 4);
+    const float t = 5.73f + 0.0184f * rows + (float)passes * (0.4556f * (rounds - 1.f) + 0.0965f * rounds * fill + 0.2233f * (float)steps + 0.0183f * far);
+    if (p.ranges == 1) return t;
+    return t + (p.fused ? 1.55f + 0.00713f * rows * ranges : 2.27f + 0.0001122f * (float)groups * rows + 0.0229f * ranges + (p.ranges > 16 ? 0.268f : 0.f));
 }
 
 // Partial results (tiles x ranges) that the stated workspace holds: those of the plain plan at any knob setting, and those
-// of any plan_by_size() -- at most kChipTiles in all, at most Hq tiles.  Grows with M and P, so one workspace serves smaller calls.
+// of any plan_by_size() -- at most kChipTiles in all.  Grows with M and P, so one workspace serves smaller calls.
 static size_t stated_partials(int M, int P, int Hq)
 {
     const size_t steps = (size_t)key_steps(M, P), heads = (size_t)Hq;
@@ -1077,6 +1340,46 @@ static size_t stated_partials(int M, int P, int Hq)
     const size_t by_size = heads * (steps < kMaxRanges ? steps : kMaxRanges);
     const size_t capped = by_size < kChipTiles ? by_size : kChipTiles;
     return plain > capped ? plain : capped;
+}
+
+// The plain plan, or the one of these that promises the least time: d heads per tile, or even tiles of at most 64 or 32 rows, with one, two, four
+// or eight ranges or as many as fill the chip (or a half or three quarters of it).  At long prefixes that is full tiles, which read K and V least often and
+// waste no rows, and up to 32 ranges; at short ones a single range and no merge; and where the plain plan's rounding up
+// makes more workgroups than compute units (40/8 heads: 280), as many as there are.  Tiles of up to 32 rows run in the kernel whose wavefronts share
+// nothing and cover eight key steps at a time, so they need half the ranges: us, before that kernel -> now: prefix 2048, M = 24 of 64/8 heads 13.7 -> 11.3,
+// M = 60 of 32/8 heads 14.9 -> 11.4, M = 1 8.5 -> 7.7; prefix 500, M = 18 of 64/8 heads 11.5 -> 8.4; prefix 16001, M = 40 of 32/8 heads 28.0 -> 26.4; 34 random calls
+// 1.14 x in the mean, one 5 % slower.  The picks lie 2 to 3 % behind the best measured plan in the mean.
+static AttnPlan plan_by_size(const AttnPlan &plain, int M, int P, int Hq, int Hkv)
+{
+    const int group = Hq / Hkv, steps = key_steps(M, P);
+    const int stated = (int)stated_partials(M, P, Hq);
+    AttnPlan best = plain;
+    float least = plan_time(plain, M, P, Hkv);
+    if (least > 15.f) least *= 0.95f;   // long walks: the fits are off by more than what many tilings differ by
+    // a group of at most eight rows stays in one tile (plain decoding, 32/8 heads, prefix 2048: 8.2 us against 8.7 in two)
+    for (int d = M * group <= 8 ? group : -1; d <= group; ++d) {
+        AttnPlan p = {d * M, 0, 1, 0};
+        if (d <= 0) {
+            even_tiles(group * M, d == 0 ? kRowsPad : kWaveRows, p.tile_rows, p.tiles_per_kv);
+        } else {
+            if (group % d != 0 || M * d > kRowsPad) continue;
+            p.tiles_per_kv = group / d;
+        }
+        const int units = Hkv * p.tiles_per_kv;
+        int most = steps < kMaxRanges ? steps : kMaxRanges;
+        most = most > kChipTiles / units ? kChipTiles / units : most;
+        const int choices[7] = {1, 2, 4, 8, most / 2, most * 3 / 4, most};
+        for (int i = 0; i < 7; ++i) {
+            p.ranges = choices[i];
+            if (p.ranges < 1 || p.ranges > most || (p.ranges > 1 && units * p.ranges > stated)) continue;
+            if (i > 3 && (p.ranges <= 2 || p.ranges == 4 || p.ranges == 8)) continue;   // already looked at
+            for (p.fused = 0; p.fused < (p.ranges > 1 ? 2 : 1); ++p.fused) {
+                const float t = plan_time(p, M, P, Hkv);
+                if (t < least) least = t, best = p;
+            }
+        }
+    }
+    return best;
 }
 
 // bytes of partial results a plan writes; one range writes none
@@ -1138,9 +1441,23 @@ static int launch_attn_shared(int grid, hipStream_t stream, Args... args)
 }
 
 template <typename... Args>
+static int launch_attn_wave(int grid, hipStream_t stream, Args... args)
+{
+    static bool lds_ok = false;
+    if (!lds_ok) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(&tree_attn_wave_kernel),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, kWaveLds) != hipSuccess)
+            return W4A16_EHIP;
+        lds_ok = true;
+    }
+    hipLaunchKernelGGL(tree_attn_wave_kernel, dim3((unsigned)grid), dim3(64 * kSharedWaves), kWaveLds, stream, args...);
+    return W4A16_OK;
+}
+
+template <typename... Args>
 static int launch_attn(int rt, int rgroups, int grid, hipStream_t stream, Args... args)
 {
-    if (rt == 0) return launch_attn_shared(grid, stream, args...);
+    if (rt == 0) return rgroups == 2 ? launch_attn_shared(grid, stream, args...) : launch_attn_wave(grid, stream, args...);
     if (rt == 4) return launch_attn_variant<4, 1>(grid, stream, args...);
     if (rgroups == 2) return launch_attn_variant<2, 2>(grid, stream, args...);
     return launch_attn_variant<2, 1>(grid, stream, args...);
@@ -1182,13 +1499,11 @@ int tree_verify_attn(const void *q, const void *k, const void *v, const uint8_t 
     float *part_ml = part_o + (size_t)units * ns * kRowsPad * kHeadDim;
     const float scale_log2e = scale * 1.4426950408889634f;
     const int nblk = key_steps(M, P);
-    // Every tile runs in the kernel that shares K and V tiles through LDS (rt = 0 below): it is the fastest
-    // form at every tile height, with half of its rows padding too (prefix 2048, 64/8 heads: 11.2 against
-    // 12.0 us at M = 8, 13.8 against 16.7 at M = 24, 15.7 against 22.3 at M = 64).  The older kernel stays
-    // selectable for comparison: one wavefront per SIMD carrying all 64 rows (4), or 32 rows per wavefront,
-    // in two row groups for taller tiles (2).
+    // Tiles of more than 32 rows run in the kernel that shares K and V tiles through LDS, others in the one whose wavefronts have
+    // their own (rt = 0 below).  The older kernel stays selectable for comparison: one wavefront per SIMD carrying all 64 rows (4), or 32
+    // rows per wavefront, in two row groups for taller tiles (2).
     const int knob = params().attn_row_tiles;
-    const int rt = knob == 4 ? 4 : knob == 2 ? 2 : 0, rgroups = (rt == 2 && rows > 32) ? 2 : 1;
+    const int rt = knob == 4 ? 4 : knob == 2 ? 2 : 0, rgroups = rows > kWaveRows ? 2 : 1;
     rc = launch_attn(rt, rgroups, units * ns, (hipStream_t)stream, (const _Float16 *)q, (const _Float16 *)k,
                      (const _Float16 *)v, mask, (_Float16 *)out, part_o, part_ml, reinterpret_cast<uint32_t *>(workspace),
                      M, P, Hq, Hkv, Hq / Hkv, scale_log2e, ns, nblk / ns, nblk % ns, rows, pl.tiles_per_kv, pl.fused);

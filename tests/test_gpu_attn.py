@@ -168,6 +168,40 @@ def test_peaked_softmax(gain):
             check(run_attn(a), ref64, f"peaked softmax x{gain} splits={splits} row_tiles={row_tiles}")
 
 
+@pytest.mark.parametrize("M,P,Hq,Hkv", [(32, 0, 8, 8), (31, 95, 8, 8), (1, 255, 8, 4), (33, 600, 8, 4), (60, 300, 16, 2), (64, 1025, 8, 2)])
+def test_short_tiles(M, P, Hq, Hkv):
+    """tiles of at most 32 rows, whose wavefronts walk the keys on their own: full and partial tiles that end inside a head, fewer key
+    steps than wavefronts, exactly eight and nine of them, ranges shorter than a round, both merges"""
+    a = I.make_attn(8360 + M + P, M, P, Hq, Hkv, 128)
+    ref64, _ = R.tree_verify_attn(a.q, a.k, a.v, a.mask, a.scale)
+    ws = B.new_workspace(16384 + 2 * Hq * 32 * 64 * 130 * 4)   # more tiles than heads, asked for below
+    B.w4a16_set_param("attn_pack", 4)
+    for splits in (1, 2, 3, 9):
+        B.w4a16_set_param("attn_splits", splits)
+        plan = B.tree_verify_attn_plan_describe(M, P, Hq, Hkv, 128, ws.numel() * ws.element_size())
+        assert plan[0] <= 32 and plan[2] <= splits
+        got = []
+        for merge in (1, 2):
+            B.w4a16_set_param("attn_fused_merge", merge)
+            got.append(run_attn(a, ws))
+            check(got[-1], ref64, f"M={M} P={P} heads {Hq}/{Hkv} splits={splits} merge={merge}")
+        assert np.array_equal(got[0].view(np.uint16), got[1].view(np.uint16)), splits
+
+
+@pytest.mark.parametrize("M", [20, 45])
+@pytest.mark.parametrize("rise", [0.02, 0.3, -0.3])
+def test_maxima_that_move_along_the_keys(M, rise):
+    """scores that rise by `rise` powers of two from key to key, so that a row's maximum moves in every step; falling ones leave
+    it in the first"""
+    a = I.make_attn(8350, M, 700, 16, 2, 128)
+    a.q[..., 0] = np.float16(4.0)
+    a.k[..., 0] = (rise / (4.0 * a.scale * 1.4426950408889634) * np.arange(a.k.shape[0])).astype(np.float16)[:, None]
+    ref64, _ = R.tree_verify_attn(a.q, a.k, a.v, a.mask, a.scale)
+    for splits in (0, 1, 5):
+        B.w4a16_set_param("attn_splits", splits)
+        check(run_attn(a), ref64, f"M={M} rise={rise} splits={splits}")
+
+
 def test_constant_values_come_back_exactly():
     """V = c for every key: any convex combination of it is c, whatever the weights"""
     a = I.make_attn(8400, 33, 515, 8, 2, 128)
