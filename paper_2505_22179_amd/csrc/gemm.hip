@@ -1468,7 +1468,7 @@ __device__ __forceinline__ void cs_segment(const _Float16 *__restrict__ x, const
     }
 }
 
-// K-split workgroups of more than one row tile.  The eight wavefronts work on the same TW column tiles, each on its own
+// K-split workgroups with x through LDS.  The eight wavefronts work on the same TW column tiles, each on its own
 // quantisation groups, as in gemm_kernel; but x fragments fetched straight from L2 (sixteen rows times 64 bytes a load) would occupy the
 // load path longer than the weights, so a wavefront copies the x tile of its next group into LDS of its own, whole cache
 // lines, global -> LDS directly, while it computes on the current one, whose fragments it holds in registers.  No wavefront waits
@@ -1489,6 +1489,7 @@ __global__ __launch_bounds__(kXWaves * 64) void gemm_x_kernel(
     extern __shared__ float4v lds4[];
     __shared__ uint32_t ticket_sh;
     constexpr int NW = kXWaves;
+    constexpr bool kOff = kOffsetCodes && MT == 1;   // offset-code arithmetic for a single row tile
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane >> 4, c = lane & 15;
@@ -1549,6 +1550,9 @@ __global__ __launch_bounds__(kXWaves * 64) void gemm_x_kernel(
         const StagedQuant<TW> q = qw;
         const uint32_t zbits = q.z >> (4 * t0), rec = (uint32_t)next * (NW * kRecordBytes);
         if (refill) load_quant<TW, SYM>(qw, recs, rec, scale_off, zero_off);
+        float4v negc[MT], xsum[MT];
+        if constexpr (kOff && SYM) group_sums_symmetric<MT>(a, negc);
+        else if constexpr (kOff) group_sums<MT>(a, negc, xsum);
 #pragma unroll
         for (int t = 0; t < TW; ++t) {
             const uint32_t z = (zbits >> (4 * t)) & 0xFu, zz = z | (z << 16);
@@ -1556,10 +1560,10 @@ __global__ __launch_bounds__(kXWaves * 64) void gemm_x_kernel(
             const half2v zneg16 = as_h2(SYM ? kSymZneg16 : ((zz << 4) | 0xD400D400u));   // -(64 + z)
             float4v part[MT];
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) part[mt] = (float4v){0.f, 0.f, 0.f, 0.f};
+            for (int mt = 0; mt < MT; ++mt) part[mt] = kOff ? negc[mt] : (float4v){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const half8v b = dequant8(w[t][j], zneg, zneg16, magic);
+                const half8v b = kOff ? offset8(w[t][j], magic) : dequant8(w[t][j], zneg, zneg16, magic);
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt)
                     part[mt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8v, a[mt][j]), b, part[mt], 0, 0, 0);
@@ -1567,8 +1571,16 @@ __global__ __launch_bounds__(kXWaves * 64) void gemm_x_kernel(
             if (refill) load_codes(rec, t);
             const uint32_t s2 = q.s[t >> 1];
             const float s = (float)__builtin_bit_cast(_Float16, (uint16_t)((t & 1) ? (s2 >> 16) : (s2 & 0xFFFFu)));
+            // (all four rows without a branch, also for M = 1: behind one, the compiler lets the next tile's codes be written to the
+            // registers of the rows nobody reads while the matrix instruction that fills them is still under way)
+            if constexpr (kOff && SYM) {
+                fold_symmetric(acc[t][0], part[0], s, true);
+            } else if constexpr (kOff) {
+                fold_offset(acc[t][0], part[0], xsum[0], s, (float)z, true);
+            } else {
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) acc[t][mt] += s * part[mt];
+                for (int mt = 0; mt < MT; ++mt) acc[t][mt] += s * part[mt];
+            }
             __builtin_amdgcn_sched_barrier(0);   // tiles stay apart, as in compute_group_lean
         }
     };
@@ -1770,7 +1782,7 @@ constexpr SplitVariants kSplitVariants = split_variants();
 
 // Shapes without a measured row.  Least-squares fits give the time of a plan in microseconds from its launch shape,
 // over weights that come from HBM: 2477 plans of 92 calls (M = 1 .. 16) and 3039 of 132 (M = 20 .. 64) on 32 shapes,
-// K = 640 .. 28672, N = 1000 .. 32000; and 1638 plans of 240 calls of the kernel whose wavefronts have x tiles of their own, N up to 57344.  The plan with the least time lies 2 to 3 % behind the best measured one in the mean.
+// K = 640 .. 28672, N = 1000 .. 32000; and 1638 plans of 240 calls (and 1426 of 130 with 5 .. 16 rows) of the kernel whose wavefronts have x tiles of their own, N up to 57344.  The plan with the least time lies 2 to 3 % behind the best measured one in the mean.
 // What the formulas know and the plain rule below does not: a workgroup more than the chip holds at once costs a whole second
 // pass (4096 x 12288 at 32 rows: 288 workgroups 19.0 us, 192 workgroups 13.4), and a second kernel or a last arriver costs 2 to 3 us,
 // so one K split on fewer compute units is often ahead (18944 -> 3584 at one row: 280 workgroups 17.2 us, 224 11.5).
@@ -1795,8 +1807,18 @@ struct ShapeTime {
     {
         const float tw = (float)tw_;
         k_sets = ks > 0;
-        own_x = !k_sets && c.M > 16;
-        if (own_x) {   // wavefronts that split K, each with an x tile of its own
+        // (up to four rows the two kernels differ little, see own_x_tiles; the fit knows single passes over the chip only)
+        own_x = !k_sets && (c.M > 16 || (c.M > 4 && nw == kXWaves && c.tiles / tw_ <= 256));
+        if (own_x && c.M <= 16) {   // wavefronts that split K, each with an x tile of its own: one row tile
+            units = c.tiles / tw_;
+            ways = kXWaves;
+            base = 2.229f + 0.3136f * c.stream + 0.0453f * tw + 0.0051f * (float)c.M;
+            group = 0.3875f + 0.1346f * tw;
+            per_fill = 0.f;
+            fill_one = 1.f / 256.f;
+            last = 1.404f, last_split = 0.1524f;
+            second = 1.825f, second_split = 0.1051f + 1.46f * c.rows_cols;
+        } else if (own_x) {   // the same with more
             const float m_tw = c.m * tw;
             units = c.tiles / tw_;
             ways = kXWaves;
@@ -2070,26 +2092,39 @@ static size_t plan_need(const Plan &pl, int M, int N, int K)
     return pl.S != 1 ? partial_bytes((M + 15) / 16, pad_cols(N) / kBlockCols, pl, K / kGroup) : 0;
 }
 
+// Which K-split kernel runs with eight wavefronts: the one whose wavefronts copy x tiles into LDS of their own, or the one that fetches fragments
+// from L2.  With one row tile a fragment load costs the load path four times what a copy of whole lines does, unless the rows are few
+// (lanes of rows that do not exist ask for the last one's lines): up to four rows the two differ by 3 % either way (3072 -> 4000 at one row
+// 4.3 us against 4.5 with copies, 70B down 21.5 against 21.7), but with eight tiles per wavefront and no split, or walks of eight groups, the copies are never
+// behind (at one row 4096 -> 28672 12.0 -> 11.4).
+// From five rows on they are ahead everywhere: 16 rows: 3072 -> 4000 6.1 -> 4.8, 5120 -> 13000 10.9 -> 9.7, 4096 -> 28672 13.5 -> 12.3, 70B down 23.5 -> 22.7.
+static bool own_x_tiles(int M, int K, int S, int tw, int nw, int depth)
+{
+    if (nw != kXWaves || depth != 1) return false;
+    return M > 16 || (K <= kStagedMaxK && (M > 4 || (tw == 8 && S == 1) || K / kGroup >= 8 * kXWaves * S));
+}
+
 // symmetric-weight instantiations exist for the K-split and the high-occupancy column-split kernels; the other
 // two families (and any call without the caller's word for it) read the zero-points, which is always correct
 template <int MT, int TW, int NW, int DEPTH, bool SYM>
 static int launch_sym(const void *x, const void *packed, const Out &y, int M, int N, int K, int S, int fused,
                       void *workspace, hipStream_t stream)
 {
-    static bool lds_ok = false;   // LDS above 64 KB needs an opt-in, once per kernel
-    constexpr bool kOwnX = MT > 1 && NW == kXWaves;
-    auto *const kernel = [] {
-        if constexpr (kOwnX) return &gemm_x_kernel<MT, TW, SYM>;
-        else return &gemm_kernel<MT, TW, NW, DEPTH, SYM>;
+    static bool lds_ok[2] = {false, false};   // LDS above 64 KB needs an opt-in, once per kernel
+    const bool own = own_x_tiles(M, K, S, TW, NW, DEPTH);
+    auto *const kernel = [&] {
+        if constexpr (NW != kXWaves || DEPTH != 1) return &gemm_kernel<MT, TW, NW, DEPTH, SYM>;
+        else if constexpr (MT > 1) return &gemm_x_kernel<MT, TW, SYM>;
+        else return own ? &gemm_x_kernel<MT, TW, SYM> : &gemm_kernel<MT, TW, NW, DEPTH, SYM>;
     }();
-    const size_t sum_bytes = (size_t)NW * 4 * TW * MT * 64 * sizeof(float), x_bytes = kOwnX ? (size_t)NW * MT * 4096 : 0;
+    const size_t sum_bytes = (size_t)NW * 4 * TW * MT * 64 * sizeof(float), x_bytes = own ? (size_t)NW * MT * 4096 : 0;
     const size_t lds_bytes = sum_bytes > x_bytes ? sum_bytes : x_bytes;
     if (lds_bytes > 160 * 1024) return W4A16_EUNSUP;
-    if (!lds_ok && lds_bytes > 48 * 1024) {
+    if (!lds_ok[own] && lds_bytes > 48 * 1024) {
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes) != hipSuccess)
             return W4A16_EHIP;
-        lds_ok = true;
+        lds_ok[own] = true;
     }
     const int groups = K / kGroup, nblocks = pad_cols(N) / kBlockCols;
     const int units = nblocks * kTiles / TW;

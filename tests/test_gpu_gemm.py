@@ -112,9 +112,9 @@ def test_parity_wide_workgroups(M, K, N, big_ws):
         assert np.array_equal(run_gemm(ex, ex_packed, big_ws).view(np.uint16), ex16.view(np.uint16)), variant
 
 
-@pytest.mark.parametrize("M,K,N", [(17, 128, 8), (32, 640, 264), (33, 1024, 136), (48, 1152, 1000), (49, 2176, 128), (64, 3200, 520), (24, 14336, 256)])
+@pytest.mark.parametrize("M,K,N", [(1, 1152, 136), (4, 640, 264), (2, 8192, 136), (5, 128, 8), (8, 2176, 1000), (16, 3200, 128), (17, 128, 8), (32, 640, 264), (33, 1024, 136), (48, 1152, 1000), (49, 2176, 128), (64, 3200, 520), (24, 14336, 256)])
 def test_parity_own_x_tiles(M, K, N, big_ws):
-    """more than one row tile, eight wavefronts that split K and keep an x tile each: fewer groups than wavefronts, one group
+    """eight wavefronts that split K and keep an x tile each (up to four rows with eight unsplit column tiles or a long walk only): fewer groups than wavefronts, one group
     each, one or two wavefronts with one more, splits across workgroups that leave some without a group, partial row tiles"""
     print(f"gemm parity (own x tiles) M={M} K={K} N={N}", flush=True)
     inp = I.make_linear(5700 + M + K + N, M, K, N)
