@@ -220,26 +220,20 @@ __device__ __forceinline__ void group_sums_symmetric(const u32x4 (&a)[MT][4], fl
     }
 }
 
-__device__ __forceinline__ void fold_symmetric(float4v &acc, const float4v &part, float s, bool more_rows)
+// Both folds take all four rows of a register quad, also for M = 1, and without a branch.  Behind a branch that skips the rows nobody
+// reads, the compiler counts the skipped instructions as wait states on the path that skips them too, and lets the next tile's codes be
+// written to those rows' registers while the matrix instruction that fills them is still under way: wrong results at M = 1, seen once.
+__device__ __forceinline__ void fold_symmetric(float4v &acc, const float4v &part, float s)
 {
-    acc[0] += s * part[0];
-    if (more_rows) {   // uniform: M > 1
-        asm volatile("");   // keeps this a branch, as in fold_offset
 #pragma unroll
-        for (int i = 1; i < 4; ++i) acc[i] += s * part[i];
-    }
+    for (int i = 0; i < 4; ++i) acc[i] += s * part[i];
 }
 
-// acc += s (part - z X) for the rows that exist: register i of a lane is row 4 * (lane / 16) + i
-__device__ __forceinline__ void fold_offset(float4v &acc, const float4v &part, const float4v &xs, float s, float zf,
-                                            bool more_rows)
+// acc += s (part - z X): register i of a lane is row 4 * (lane / 16) + i
+__device__ __forceinline__ void fold_offset(float4v &acc, const float4v &part, const float4v &xs, float s, float zf)
 {
-    acc[0] += s * (part[0] - zf * xs[0]);
-    if (more_rows) {   // uniform: M > 1
-        asm volatile("");   // keeps this a branch: if-converted, M = 1 would pay for all four rows
 #pragma unroll
-        for (int i = 1; i < 4; ++i) acc[i] += s * (part[i] - zf * xs[i]);
-    }
+    for (int i = 0; i < 4; ++i) acc[i] += s * (part[i] - zf * xs[i]);
 }
 
 // One quantisation group for this wavefront's TW column tiles, software-pipelined over tiles:
@@ -253,8 +247,7 @@ template <int MT, int TW, bool ALWAYS_REFILL, bool OFF = false, bool SYM = false
 __device__ __forceinline__ void compute_group(u32x4 (&a)[MT][4], const QuantWords &f, const QuantWords &fn,
                                               u32x4 (&w)[TW], u32x4 (&wn)[TW], half8v (&bc)[4],
                                               float4v (&acc)[TW][MT], const uint8_t *refill_rec, bool refill,
-                                              bool next_group, int t0, int lane, const DequantConsts &magic,
-                                              bool more_rows = true)
+                                              bool next_group, int t0, int lane, const DequantConsts &magic)
 {
     const TileQuant<TW> q = tile_quant<TW>(f, t0);
     const TileQuant<TW> qn = tile_quant<TW>(fn, t0);
@@ -290,11 +283,11 @@ __device__ __forceinline__ void compute_group(u32x4 (&a)[MT][4], const QuantWord
         float s = (float)sh;
         if constexpr (OFF && SYM) {
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) fold_symmetric(acc[t][mt], part[mt], s, more_rows);
+            for (int mt = 0; mt < MT; ++mt) fold_symmetric(acc[t][mt], part[mt], s);
         } else if constexpr (OFF) {
             const float zf = (float)((q.zbits >> (4 * t)) & 0xFu);
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) fold_offset(acc[t][mt], part[mt], xs[mt], s, zf, more_rows);
+            for (int mt = 0; mt < MT; ++mt) fold_offset(acc[t][mt], part[mt], xs[mt], s, zf);
         } else {
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) acc[t][mt] += s * part[mt];
@@ -715,7 +708,7 @@ __global__ __launch_bounds__(NW * 64, min_waves_per_simd(MT, TW, NW, DEPTH)) voi
             load_operands<MT, SYM>((u & 1) ? fa : fb, recw + (size_t)(gi + 1) * kStep, xp, g0 + (gi + 1) * NW, c);
             compute_group<MT, TW, true, kOff, SYM>(((u & 1) ? fb : fa).a, ((u & 1) ? fb : fa).q, ((u & 1) ? fa : fb).q,
                                               w[u % DEPTH], w[(u + 1) % DEPTH], bc, acc,
-                                              recw + (size_t)(gi + DEPTH) * kStep, true, true, t0, lane, magic, M > 1);
+                                              recw + (size_t)(gi + DEPTH) * kStep, true, true, t0, lane, magic);
         }
     }
     // drain: at most U + DEPTH - 1 groups left; ring position and fragment buffer stay static
@@ -728,7 +721,7 @@ __global__ __launch_bounds__(NW * 64, min_waves_per_simd(MT, TW, NW, DEPTH)) voi
             compute_group<MT, TW, false, kOff, SYM>(((u & 1) ? fb : fa).a, ((u & 1) ? fb : fa).q, ((u & 1) ? fa : fb).q,
                                                w[u % DEPTH], w[(u + 1) % DEPTH], bc, acc,
                                                recw + (size_t)(gi + DEPTH) * kStep, gi + DEPTH < n_w, gi + 1 < n_w, t0,
-                                               lane, magic, M > 1);
+                                               lane, magic);
         }
     }
 
@@ -818,7 +811,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_flat_kernel(
             uint32_t s2 = q.sw[t >> 1];
             _Float16 sh = __builtin_bit_cast(_Float16, (uint16_t)((t & 1) ? (s2 >> 16) : (s2 & 0xFFFFu)));
             if constexpr (kOffsetCodes)
-                fold_offset(acc[t][0], part, xsum[0], (float)sh, (float)((q.zbits >> (4 * t)) & 0xFu), M > 1);
+                fold_offset(acc[t][0], part, xsum[0], (float)sh, (float)((q.zbits >> (4 * t)) & 0xFu));
             else
                 acc[t][0] += (float)sh * part;
         }
@@ -1571,12 +1564,10 @@ __global__ __launch_bounds__(kXWaves * 64) void gemm_x_kernel(
             if (refill) load_codes(rec, t);
             const uint32_t s2 = q.s[t >> 1];
             const float s = (float)__builtin_bit_cast(_Float16, (uint16_t)((t & 1) ? (s2 >> 16) : (s2 & 0xFFFFu)));
-            // (all four rows without a branch, also for M = 1: behind one, the compiler lets the next tile's codes be written to the
-            // registers of the rows nobody reads while the matrix instruction that fills them is still under way)
             if constexpr (kOff && SYM) {
-                fold_symmetric(acc[t][0], part[0], s, true);
+                fold_symmetric(acc[t][0], part[0], s);
             } else if constexpr (kOff) {
-                fold_offset(acc[t][0], part[0], xsum[0], s, (float)z, true);
+                fold_offset(acc[t][0], part[0], xsum[0], s, (float)z);
             } else {
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt) acc[t][mt] += s * part[mt];
