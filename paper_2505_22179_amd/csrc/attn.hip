@@ -20,6 +20,7 @@ namespace w4 {
 
 typedef _Float16 half8v __attribute__((ext_vector_type(8)));
 typedef float float4v __attribute__((ext_vector_type(4)));
+typedef float float16v __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
@@ -35,6 +36,7 @@ constexpr int kChipTiles = 256;  // tiles x ranges of the plans that are picked 
 
 // v_max3_f32 and v_max_f32 as they stand: fmaxf chains are compiled with a canonicalising v_max x, x per
 // operand, which doubles the instruction count of a row maximum; no score here is a NaN.
+// The compiler adds no wait states before inline assembly: results of matrix instructions pass through settled() first.
 __device__ __forceinline__ float max_of_three(float a, float b, float c)
 {
     float d;
@@ -48,6 +50,14 @@ __device__ __forceinline__ float max_of_two(float a, float b)
     asm("v_max_f32 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
     return d;
 }
+
+// Wait states until the results of matrix instructions that were just issued may be read: eight after a 16x16x32 step,
+// twelve after a 32x32x16 one (passes + 4).  In straight code, so that they lie on every path from the products to the first read.
+__device__ __forceinline__ void settled(float4v &a, float4v &b, float4v &c, float4v &d)
+{
+    asm volatile("s_nop 7" : "+v"(a), "+v"(b), "+v"(c), "+v"(d));
+}
+__device__ __forceinline__ void settled(float16v &a) { asm volatile("s_nop 7\n\ts_nop 3" : "+v"(a)); }
 
 // Maximum over the four lanes l, l ^ 16, l ^ 32, l ^ 48 (the lanes that share a query row), returned to
 // all four.  v_permlane16_swap exchanges the odd 16-lane rows of its first operand with the even rows of
@@ -708,6 +718,7 @@ __global__ __launch_bounds__(64 * kSharedWaves) void tree_attn_shared_kernel(
                     sb[rt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fb, qf[rt][j], sb[rt], 0, 0, 0);
                 }
             }
+            settled(sa[0], sb[0], sa[1], sb[1]);
             const bool prefix_only = key0 + kKeyBlock <= P;   // uniform: committed keys, all visible
 #pragma unroll
             for (int rt = 0; rt < 2; ++rt) {
@@ -861,7 +872,6 @@ constexpr int kWaveRows = 32;
 constexpr int kWaveWeights = kWaveState + kWaveRows * kSharedWaves * 8;        // [row][wavefront] (weight, weighted sum)
 constexpr int kWaveEnd = kWaveWeights + kWaveRows * kSharedWaves * 8;
 constexpr int kWaveLds = kWaveQ + kWaveRows * kHeadDim * 2 > kWaveEnd ? kWaveQ + kWaveRows * kHeadDim * 2 : kWaveEnd;
-typedef float float16v __attribute__((ext_vector_type(16)));
 typedef float float2v __attribute__((ext_vector_type(2)));
 
 // the transposing read of four key rows at lds_addr + OFFSET and the four that lie eight rows further on
@@ -996,6 +1006,7 @@ __global__ __launch_bounds__(64 * kSharedWaves) void tree_attn_wave_kernel(
             sc = __builtin_amdgcn_mfma_f32_32x32x16_f16(*reinterpret_cast<const half8v *>(ktile + (frag ^ (j << 5))), qf[j], sc, 0, 0, 0);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the K tile has been read
         if (more) request(next, k_src, lane_k, 0, ktile);
+        settled(sc);
         half8v pb[2];
         const bool prefix_only = key0 + kKeyBlock <= P;   // uniform: committed keys, all visible
         float s[16];

@@ -138,7 +138,7 @@ def found(tmp_path_factory):
     return out, matrix
 
 
-@pytest.mark.parametrize("kernels", ["gemm_", "lm_head_"])
+@pytest.mark.parametrize("kernels", ["gemm_", "tree_attn_", "lm_head_"])
 def test_no_result_of_a_matrix_instruction_is_touched_too_early(found, kernels):
     bad, matrix = found
     assert sum(n for kernel, n in matrix.items() if kernels in kernel) > 100   # the listing was understood
