@@ -1,6 +1,8 @@
 // lm_head_topk: the draft model's fp16 language-model head (a GEMV-shaped fp16 x fp16 product over a
 // vocabulary-sized weight, HBM-bound), the log-softmax of its logits and their top-k.  Contract in
 // include/w4a16.h.
+#include <type_traits>
+
 #include "internal.h"
 #include "devscope.h"
 
@@ -447,11 +449,16 @@ struct Best {
 //      reach, and so is the least of the four wavefronts' (k / 4)-th largest: the row's k best tokens reach the larger of them all, the bound.
 //   2. Only granules whose maximum reaches the bound are read again, and only their tokens that reach it are kept: k to
 //      about 2 k of them where values differ.
-//   3. A thread per kept token counts the better ones: its place.  (More than a list holds, with many equal logits
-//      or more places than granules: the wavefronts keep their k best while they read the granules a second time, and the first merges them.)
+//   3. A thread per kept token counts the better ones: its place.
+// Many equal logits (rows of zeros), logits in order, or more places than granules bring more tokens to the bound than the lists
+// hold.  Of granules that just reach it a wavefront reads only its first k, and where the bound is the largest logit of all it keeps
+// only its first k tokens.  Else the logits that were read raise the bound in the way of step 1, and a second reading keeps the tokens that reach
+// the new one, of ties the first k.  Where that is still too many, the wavefronts keep their k best in a third reading and the first merges
+// them.  us, whole call, without these steps (third reading at once) and with them: 1 x 128256 (K = 1024), top 1, rows of zeros 167.5 -> 43.6,
+// 10 x 128256 (K = 4096), top 10, the same 289.9 -> 165.5, 4 x 65000 (K = 1024), top 64, rising logits 595 -> 44 (random ones 33 before and now).
 // Nothing in the usual path runs k times in a row.  A round trip to memory for the statistics, one for the logits: latency bounds it.
 // The two passes this replaces (the k best of every 512 logits, then a merge of those lists) read all logits again:
-// top 10 of 10 x 128256 8.3 + 9.6 -> 7.8 us, top 1 of 60 x 128256 8.3 + 4.7 -> 4.8; whole calls 172.3 -> 164.0 and 348 -> 341 (K = 4096, 8192),
+// top 10 of 10 x 128256 8.3 + 9.6 -> 7.8 us, top 1 of 60 x 128256 8.3 + 4.7 -> 4.8; whole calls 174.0 -> 165.6 and 337.7 -> 328.9 (K = 4096, 8192),
 // top 10 of 5 x 5000 (K = 2048) 26.2 -> 17.9, top 32 of 64 x 128256 271 -> 203.
 constexpr int kLmKept = kLmThreads;       // tokens the lists hold, and the third step ranks
 constexpr int kLmMaxPerLane = 16;         // 262144 tokens in granules of 64: 4096 of them over 256 lanes
@@ -484,41 +491,55 @@ __global__ __launch_bounds__(kLmThreads) void lm_head_merge_kernel(const float *
 #pragma unroll
     for (int i = 0; i < PER; ++i) se += st[i].sum * __expf(st[i].max - sum_base(wave_mx));   // absent ones: 0 * exp(-inf) = 0
     se = wave_sum(se);
-    float alone = wave_mx, shared = wave_mx;   // values that k, and k / 4, of this wavefront's lanes reach
-    if (top_k > 1) {   // uniform
-        int larger = 0;
+    // values that k, and k / 4, of this wavefront's lanes reach with theirs
+    const auto store_reached = [&](float lane_max) {
+        float alone = kNegInf, shared = kNegInf;
+        if (top_k > 1) {   // uniform
+            int larger = 0;
 #pragma unroll
-        for (int l = 0; l < 64; ++l) larger += lane_value(lane_mx, l) > lane_mx ? 1 : 0;
-        alone = -wave_max(larger < top_k ? -lane_mx : kNegInf);   // the least of the lanes that fewer than k surpass
-        shared = -wave_max(larger < (top_k + kWaves - 1) / kWaves ? -lane_mx : kNegInf);
-    }
-    if (lane == 0) {
-        wave_stat[wave] = {wave_mx, se};
-        wave_alone[wave] = alone;
-        wave_shared[wave] = shared;
-    }
+            for (int l = 0; l < 64; ++l) larger += lane_value(lane_max, l) > lane_max ? 1 : 0;
+            alone = -wave_max(larger < top_k ? -lane_max : kNegInf);   // the least of the lanes that fewer than k surpass
+            shared = -wave_max(larger < (top_k + kWaves - 1) / kWaves ? -lane_max : kNegInf);
+        }
+        if (lane == 0) {
+            wave_alone[wave] = alone;
+            wave_shared[wave] = shared;
+        }
+    };
+    const auto reached = [&]() {
+        float alone = kNegInf, shared = wave_shared[0];
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            alone = fmaxf(alone, wave_alone[w]);
+            shared = fminf(shared, wave_shared[w]);
+        }
+        return fmaxf(alone, shared);
+    };
+    store_reached(lane_mx);
+    if (lane == 0) wave_stat[wave] = {wave_mx, se};
     __syncthreads();
     float mx = kNegInf;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-        alone = fmaxf(alone, wave_alone[w]);
-        shared = fminf(shared, wave_shared[w]);
-        mx = fmaxf(mx, wave_stat[w].max);
-    }
-    const float bound = top_k > 1 ? fmaxf(alone, shared) : mx;
+    for (int w = 0; w < kWaves; ++w) mx = fmaxf(mx, wave_stat[w].max);
+    float bound = top_k > 1 ? reached() : mx;
     se = 0.f;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) se += wave_stat[w].sum * __expf(wave_stat[w].max - sum_base(mx));
     const float lse = mx + __logf(se);
 
-    // this wavefront's granules that reach the bound, as pieces of 64 tokens
-    const auto counts = [&](float v) { return v >= bound && v > kNegInf; };
-    int found = 0;
+    // this wavefront's granules that reach the bound, as pieces of 64 tokens; of those that just reach it the first k, which hold k tokens
+    // that do
+    const auto reaches = [&](float v) { return v >= bound && v > kNegInf; };
+    int found = 0, level = 0;
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-        const uint64_t which = __ballot(counts(st[i].max));
-        if (counts(st[i].max)) chosen[wave][found + lanes_below(which)] = tid + kLmThreads * i;
+        const bool just = reaches(st[i].max) && st[i].max == bound;
+        const uint64_t which_just = __ballot(just);
+        const bool take = reaches(st[i].max) && (!just || level + lanes_below(which_just) < top_k);
+        const uint64_t which = __ballot(take);
+        if (take) chosen[wave][found + lanes_below(which)] = tid + kLmThreads * i;
         found += __popcll(which);
+        level += __popcll(which_just);
     }
     const int shift = 31 - __builtin_clz((unsigned)granule) - 6;   // granules are 64, 128, 256 or 512 tokens
     const int pieces = found << shift;
@@ -538,21 +559,42 @@ __global__ __launch_bounds__(kLmThreads) void lm_head_merge_kernel(const float *
                 if (p0 + i < pieces) take(token[i] < V ? l[i] : kNegInf, token[i]);   // uniform
         }
     };
-    int keeps = 0;
-    each_piece([&](float l, int token) {
-        const uint64_t which = __ballot(counts(l));
-        const int place = keeps + lanes_below(which);
-        if (counts(l) && place < kLmKept) kept[wave][place] = {l, token};
-        keeps += __popcll(which);
-    });
-    if (lane == 0) wave_kept[wave] = keeps;
-    __syncthreads();
-    int total = 0, w_mine = 0, at = tid;   // the tid-th kept token is entry `at` of list w_mine
+    int total, w_mine, at;   // the tid-th kept token is entry `at` of list w_mine
+    float seen = kNegInf;    // the largest logit that this lane has read
+    const int limit = bound == mx ? top_k : kLmKept;   // all tokens at the bound are equal: the first k of a wavefront will do
+    // keeps the tokens that reach the bound; with `cut_ties` only the first k of this wavefront's that just reach it
+    const auto collect = [&](auto cut_ties) {
+        int keeps = 0, level = 0;
+        each_piece([&](float l, int token) {
+            bool keep = reaches(l);
+            if constexpr (decltype(cut_ties)::value) {
+                const uint64_t just = __ballot(keep && l == bound);
+                keep = keep && (l > bound || level + lanes_below(just) < top_k);
+                level += __popcll(just);
+            } else {
+                seen = fmaxf(seen, l);
+            }
+            const uint64_t which = __ballot(keep);
+            const int place = keeps + lanes_below(which);
+            if (keep && place < limit) kept[wave][place] = {l, token};
+            keeps += __popcll(which);
+        });
+        if (lane == 0) wave_kept[wave] = limit < kLmKept ? min(keeps, limit) : keeps;   // more than a list holds: not enough of a bound
+        __syncthreads();
+        total = 0, w_mine = 0, at = tid;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-        const int n = wave_kept[w];
-        total += n;
-        if (w_mine == w && at >= n && w + 1 < kWaves) at -= n, ++w_mine;
+        for (int w = 0; w < kWaves; ++w) {
+            const int n = wave_kept[w];
+            total += n;
+            if (w_mine == w && at >= n && w + 1 < kWaves) at -= n, ++w_mine;
+        }
+    };
+    collect(std::false_type{});
+    if (total > kLmKept) {   // uniform
+        store_reached(seen);
+        __syncthreads();   // everybody has read the counts
+        bound = fmaxf(bound, reached());
+        collect(std::true_type{});
     }
     const auto store = [&](int place, Cand c) {
         top_idx[m * top_k + place] = c.idx;
@@ -571,7 +613,7 @@ __global__ __launch_bounds__(kLmThreads) void lm_head_merge_kernel(const float *
         return;
     }
     Best top;
-    each_piece([&](float l, int token) { top.offer({l, token}, counts(l), top_k - 1); });
+    each_piece([&](float l, int token) { top.offer({l, token}, reaches(l), top_k - 1); });
     __syncthreads();   // everybody has left the lists
     kept[wave][lane] = top.c;
     __syncthreads();

@@ -140,10 +140,63 @@ def test_determinism():
 
 @pytest.mark.parametrize("M,K,V,top_k", [(3, 128, 40000, 16), (33, 128, 40001, 64), (1, 128, 70, 64)])
 def test_equal_logits_beyond_the_lists(M, K, V, top_k):
-    """all logits equal, so every token reaches the bound and the lists of the merge overflow: the first tokens win"""
+    """all logits equal, so every token reaches the bound, more than the lists of the merge hold: the first tokens win"""
     L, Ix, P = run(np.zeros((M, K), np.float16), I.make_lm_head(9960, 1, K, V)[1], top_k)
     assert (Ix == np.arange(top_k)).all() and (L == 0).all()
     assert np.abs(P + np.log(V)).max() <= 2e-3
+
+
+def weights_in_order(kind, K, V):
+    """a vocabulary whose first weight column, and with it the logits of the rows below, takes a certain order"""
+    v = np.arange(V)
+    column = {"rising": v / V * 8, "falling": -v / V * 8, "three levels": v * 7 % 3, "zero": 0 * v,
+              "a low one per 64": np.where(v % 64 == 0, -9, v % 1021 / 128)}[kind]
+    W = np.zeros((V, K), np.float16)
+    W[:, 0] = column
+    return W
+
+
+@pytest.mark.parametrize("kind", ["rising", "falling", "three levels", "a low one per 64"])
+@pytest.mark.parametrize("M,K,V,top_k", [(3, 128, 40000, 16), (33, 128, 40001, 64), (1, 128, 4480, 64), (2, 128, 500, 8), (2, 128, 128256, 2)])
+def test_orders_along_the_vocabulary(M, K, V, top_k, kind):
+    """many more tokens at or above the first bound than the lists hold: it is raised from the logits read (rising ones), ties are cut
+    off (levels), or neither helps and the wavefronts keep their best (one lane of 64 with low logits only, fewer than four wavefronts with granules)"""
+    W = weights_in_order(kind, K, V)
+    x = np.zeros((M, K), np.float16)
+    x[:, 0] = 0.5 ** (np.arange(M) % 3)
+    L, Ix, _ = run(x, W, top_k)
+    exact = x[:, :1].astype(np.float32) * W[:, 0].astype(np.float32)
+    assert np.array_equal(L, exact)
+    assert np.array_equal(Ix, np.argsort(-exact, axis=1, kind="stable")[:, :top_k])
+
+
+@pytest.mark.parametrize("M,K,V,top_k,kind", [(1, 128, 128256, 1, "zero"), (10, 128, 128256, 10, "zero"), (4, 128, 65000, 64, "rising"), (5, 128, 5000, 10, "three levels")])
+def test_no_order_is_slow(M, K, V, top_k, kind):
+    """rows of equal logits (padding rows of zeros) and ordered ones take about as long as random ones.  Before ties were cut
+    off and the bound was raised, 4 to 18 times as long; the limit of twice leaves room for a third reading of the logits"""
+    def usec(x, W):
+        xd, Wraw = torch.from_numpy(x).to(DEV), torch.from_numpy(W).to(DEV)
+        Wd = torch.empty(B.lm_head_packed_bytes(V, K), dtype=torch.uint8, device=DEV)
+        B.lm_head_pack(Wraw, Wd, V, K)
+        logits = torch.empty(M, V, device=DEV)
+        idx, lp = torch.empty(M, top_k, dtype=torch.int32, device=DEV), torch.empty(M, top_k, device=DEV)
+        ws = torch.empty(B.lm_head_workspace_bytes(M, V, K, top_k), dtype=torch.uint8, device=DEV)
+        best = 1e9
+        for _ in range(5):
+            begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            begin.record()
+            for _ in range(50):
+                B.lm_head_topk(xd, Wd, M, V, K, top_k, logits, idx, lp, ws)
+            end.record()
+            end.synchronize()
+            best = min(best, begin.elapsed_time(end) * 20)
+        return best
+    x, W = I.make_lm_head(9965, M, K, V)
+    one = np.zeros((M, K), np.float16)
+    one[:, 0] = 1
+    usual, ordered = usec(x, W), usec(one, weights_in_order(kind, K, V))
+    print(f"lm_head M={M} V={V} k={top_k}: random {usual:.1f} us, {kind} {ordered:.1f} us", flush=True)
+    assert ordered <= 2 * usual
 
 
 @pytest.mark.parametrize("M,K,V,top_k", [(4, 128, 65001, 64), (2, 256, 128256, 32), (40, 128, 3000, 64), (5, 128, 255, 16)])
