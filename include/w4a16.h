@@ -294,7 +294,8 @@ size_t lm_head_workspace_bytes(int M, int V, int K, int top_k);
  * x, packed, logits, workspace 16-byte aligned; top_idx, top_logprob 4-byte aligned.  Requires
  * K % 128 == 0, 1 <= top_k <= min(V, 64), V <= 262144 and ceil(V / 512) * top_k <= 8192.  `workspace` holds
  * lm_head_workspace_bytes(M, V, K, top_k) bytes and needs no initialisation.  Deterministic.  A -inf or NaN logit wins no place
- * (a list that runs short ends in token 0x7FFFFFFF, log-probability -inf); a NaN or +inf makes the row's log-probabilities NaN. */
+ * (a list that runs short ends in token 0x7FFFFFFF, log-probability -inf); a NaN, a +inf or a row of nothing but -inf makes the row's
+ * log-probabilities NaN. */
 int lm_head_topk(const void *x, const void *packed, int M, int V, int K, int top_k, float *logits, int32_t *top_idx,
                  float *top_logprob, void *workspace, size_t workspace_bytes, void *stream);
 

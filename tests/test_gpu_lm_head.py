@@ -228,6 +228,16 @@ def test_infinite_and_nan_logits(M):
     assert (np.sort(Ix[:, :5], axis=1) == np.arange(5)).all() and np.isnan(P).all()
 
 
+@pytest.mark.parametrize("M", [1, 20])
+def test_rows_without_a_finite_logit(M):
+    """the logarithm of their sum of exponentials does not exist: no token, and NaN as in any log-softmax"""
+    K, V, top_k = 128, 1500, 4
+    x, W = np.zeros((M, K), np.float16), np.zeros((V, K), np.float16)
+    x[:, 0], W[:, 0] = 1, -np.inf
+    L, Ix, P = run(x, W, top_k)
+    assert np.isneginf(L).all() and (Ix == 0x7FFFFFFF).all() and np.isnan(P).all()
+
+
 @pytest.mark.parametrize("M,K,V,top_k", [(1, 256, 5000, 1), (30, 256, 5001, 2)])
 def test_workspace_below_the_stated_size(M, K, V, top_k):
     """the least accepted workspace (statistics and candidates of 512-token chunks) gives the same tokens through a pass over
