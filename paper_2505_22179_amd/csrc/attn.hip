@@ -1291,6 +1291,18 @@ static void even_tiles(int pairs, int most, int &tile_rows, int &tiles_per_kv)
     tiles_per_kv = (pairs + tile_rows - 1) / tile_rows;
 }
 
+// Partial results (tiles x ranges) that the stated workspace holds: those of the plain plan with up to one tile per query head, and those
+// of any plan_by_size() -- at most kChipTiles in all.  Grows with M and P, so one workspace serves smaller calls.  Tiles of at most 32 rows may
+// be twice as many as query heads: the plain plan then takes no more ranges than fit.
+static size_t stated_partials(int M, int P, int Hq)
+{
+    const size_t steps = (size_t)key_steps(M, P), heads = (size_t)Hq;
+    const size_t plain = heads * (steps < kMaxSplits ? steps : kMaxSplits);
+    const size_t by_size = heads * (steps < kMaxRanges ? steps : kMaxRanges);
+    const size_t capped = by_size < kChipTiles ? by_size : kChipTiles;
+    return plain > capped ? plain : capped;
+}
+
 // The plain plan, and what the knobs make of it.  The key ranges of a tile are merged by the last of its workgroups to
 // finish, or by a second kernel.  Fused saves a launch and the wait for it, but one workgroup then reads all the partials
 // of its tile (rows x ranges x 512 B), which pays while they are few.  Measured break-even points, prefix 2048: about 160
@@ -1313,6 +1325,10 @@ static AttnPlan plain_plan(int M, int P, int Hq, int Hkv, int pack, int splits, 
     const int units = Hkv * p.tiles_per_kv;
     int want = splits > 0 ? splits : (256 + units - 1) / units;   // about one workgroup per compute unit
     want = want > steps ? steps : want;
+    if (pack == 4) {
+        const int fit = (int)(stated_partials(M, P, Hq) / (size_t)units);   // one at least: more than Hq tiles have more than 32 rows and so two key steps
+        most_ranges = most_ranges < fit ? most_ranges : fit;
+    }
     p.ranges = want > most_ranges ? most_ranges : want < 1 ? 1 : want;
     const int row_ranges = p.tile_rows * p.ranges;
     p.fused = p.ranges > 1 && row_ranges <= (p.ranges <= 4 ? 160 : (p.ranges <= 8 && p.tile_rows == M) ? 512 : 256);
@@ -1340,17 +1356,6 @@ static float plan_time(const AttnPlan &p, int M, int P, int Hkv)
     const float t = 5.73f + 0.0184f * rows + (float)passes * (0.4556f * (rounds - 1.f) + 0.0965f * rounds * fill + 0.2233f * (float)steps + 0.0183f * far);
     if (p.ranges == 1) return t;
     return t + (p.fused ? 1.55f + 0.00713f * rows * ranges : 2.27f + 0.0001122f * (float)groups * rows + 0.0229f * ranges + (p.ranges > 16 ? 0.268f : 0.f));
-}
-
-// Partial results (tiles x ranges) that the stated workspace holds: those of the plain plan at any knob setting, and those
-// of any plan_by_size() -- at most kChipTiles in all.  Grows with M and P, so one workspace serves smaller calls.
-static size_t stated_partials(int M, int P, int Hq)
-{
-    const size_t steps = (size_t)key_steps(M, P), heads = (size_t)Hq;
-    const size_t plain = heads * (steps < kMaxSplits ? steps : kMaxSplits);
-    const size_t by_size = heads * (steps < kMaxRanges ? steps : kMaxRanges);
-    const size_t capped = by_size < kChipTiles ? by_size : kChipTiles;
-    return plain > capped ? plain : capped;
 }
 
 // The plain plan, or the one of these that promises the least time: d heads per tile, or even tiles of at most 64 or 32 rows, with one, two, four
@@ -1419,6 +1424,7 @@ static AttnPlan attn_plan(int M, int P, int Hq, int Hkv, size_t room)
     }
     if (plan_bytes(best, Hkv) > room) best = plain;
     if (pr.attn_fused_merge != 0) best.fused = best.ranges > 1 && pr.attn_fused_merge == 2;
+    if (Hkv * best.tiles_per_kv > kMaxTickets) best.fused = 0;   // a ticket per tile
     return best;
 }
 

@@ -75,6 +75,28 @@ def test_the_stated_size_serves_smaller_calls_and_never_shrank():
                     assert B.tree_verify_attn_workspace_bytes(m, p, Hq, Hkv, 128) <= stated
 
 
+@pytest.fixture
+def knobs():
+    yield B.w4a16_set_param
+    for name in ("attn_pack", "attn_splits", "attn_fused_merge"):
+        B.w4a16_set_param(name, 0)
+
+
+@pytest.mark.parametrize("splits,merge", [(0, 0), (2, 0), (9, 2), (32, 2)])
+@pytest.mark.parametrize("pack", [1, 2, 3, 4, 14])
+def test_the_stated_size_serves_every_way_of_cutting_tiles(knobs, pack, splits, merge):
+    """no more partial results than it holds, and a ticket for every tile that the last of its workgroups merges"""
+    knobs("attn_pack", pack)
+    knobs("attn_splits", splits)
+    knobs("attn_fused_merge", merge)
+    for M, P, Hq, Hkv in list(calls())[::3] + [(M, P, Hq, Hkv) for Hq, Hkv in ((4096, 512), (4096, 4096)) for M in (1, 33, 64) for P in (0, 300, 5000)]:
+        stated = B.tree_verify_attn_workspace_bytes(M, P, Hq, Hkv, 128)
+        rows, tiles, ranges, fused, _ = B.tree_verify_attn_plan_describe(M, P, Hq, Hkv, 128, stated)
+        assert ranges == 1 or TICKETS + Hkv * tiles * ranges * PARTIAL <= stated, (M, P, Hq, Hkv)
+        assert not fused or Hkv * tiles <= TICKETS // 4, (M, P, Hq, Hkv)
+        assert 1 <= rows <= (32 if pack == 4 else 64) and (tiles - 1) * rows < Hq // Hkv * M <= tiles * rows
+
+
 def test_describe_rejects_what_the_call_rejects():
     for args, code in (((0, 10, 8, 8, 128), -1), ((1, -1, 8, 8, 128), -1), ((65, 10, 8, 8, 128), -4), ((1, 10, 8, 8, 64), -4),
                        ((1, 10, 64, 4, 128), -4), ((1, 10, 64, 7, 128), -1)):

@@ -188,6 +188,17 @@ def test_short_tiles(M, P, Hq, Hkv):
         assert np.array_equal(got[0].view(np.uint16), got[1].view(np.uint16)), splits
 
 
+@pytest.mark.parametrize("M,P,Hq,Hkv", [(64, 300, 8, 1), (60, 300, 16, 2), (33, 600, 8, 4)])
+def test_short_tiles_in_the_stated_workspace(M, P, Hq, Hkv):
+    """more tiles than query heads, with as many key ranges as the stated workspace holds"""
+    a = I.make_attn(8370 + M + P, M, P, Hq, Hkv, 128)
+    ref64, _ = R.tree_verify_attn(a.q, a.k, a.v, a.mask, a.scale)
+    B.w4a16_set_param("attn_pack", 4)
+    for splits in (0, 16):
+        B.w4a16_set_param("attn_splits", splits)
+        check(run_attn(a), ref64, f"M={M} P={P} heads {Hq}/{Hkv} splits={splits}")
+
+
 @pytest.mark.parametrize("M", [20, 45])
 @pytest.mark.parametrize("rise", [0.02, 0.3, -0.3])
 def test_maxima_that_move_along_the_keys(M, rise):
