@@ -1728,7 +1728,7 @@ static bool flat_variant_exists(int tw, int nw, int ng)
     W4_VARIANTS_SMALL(X, 1) W4_VARIANTS_SMALL(X, 2) W4_VARIANTS_SMALL(X, 3) W4_VARIANTS_SMALL(X, 4) \
     X(1, 2, 8, 1) X(1, 2, 8, 2) X(1, 2, 8, 4) X(1, 4, 4, 4) X(1, 4, 8, 1) X(1, 4, 8, 2)                         \
     X(1, 8, 8, 1) X(1, 8, 8, 2)                                                                     \
-    X(2, 2, 8, 1) X(2, 4, 8, 1) X(2, 8, 8, 1) X(3, 2, 8, 1) X(3, 4, 8, 1) X(4, 2, 8, 1) X(4, 4, 8, 1)
+    X(2, 2, 8, 1) X(2, 2, 8, 2) X(2, 4, 8, 1) X(2, 8, 8, 1) X(3, 2, 8, 1) X(3, 4, 8, 1) X(4, 2, 8, 1) X(4, 4, 8, 1)
 
 // column-split variant (nw == 0): Y(MT, TW, DEPTH)
 #define W4_NS_VARIANTS(Y)                                                                           \
@@ -1891,6 +1891,14 @@ static constexpr RuleShapes rule_shapes(int mt)
 }
 constexpr RuleShapes kRuleShapesOf[4] = {rule_shapes(1), rule_shapes(2), rule_shapes(3), rule_shapes(4)};
 
+// Eight wavefronts and more than one row tile: beyond the 32-bit offsets of gemm_x_kernel the one that fetches x from L2 runs, in the forms
+// that were compiled before there was another
+static constexpr bool fetched_x_variant(int mt, int tw) { return mt == 1 || (mt == 2 && tw <= 4); }
+static bool reaches_all_of_k(int mt, int tw, int nw, int K)
+{
+    return K <= kStagedMaxK || nw != kXWaves || fetched_x_variant(mt, tw);
+}
+
 static Plan predicted_plan(const Plan &plain, int M, int N, int K, bool own_x)
 {
     // what the caller's workspace and the built-in scratch have to hold does not grow beyond the latter
@@ -2026,6 +2034,7 @@ static Plan choose_plan(int M, int N, int K, Choice choice = Choice::preferred)
                 for (int depth = 1; depth <= 4; depth <<= 1) {
                     if (p.prefetch_depth > 0 ? depth != p.prefetch_depth : depth != 1) continue;
                     if (depth == 1 ? !kSplitVariants.v[mt - 1][tw][nw] : !variant_exists(mt, tw, nw, depth)) continue;
+                    if (!reaches_all_of_k(mt, tw, nw, K)) continue;
                     // largest split first: once the chip is too empty for the first term alone, smaller ones are worse still
                     for (int s = forced_s ? forced_s : cap; s >= (forced_s ? forced_s : 1); --s) {
                         const double fill = (double)units * s / 256.0;         // workgroups per compute unit
@@ -2048,7 +2057,6 @@ static Plan choose_plan(int M, int N, int K, Choice choice = Choice::preferred)
         }
     }
     if (by_rule && best.tw != 0 && !least) best = predicted_plan(best, M, N, K, choice == Choice::preferred);
-    if (mt > 1 && best.nw == kXWaves && K > kStagedMaxK) best.tw = 0;   // forced by knobs: its offsets are 32-bit too
     if (p.fused_reduce != 2) best.fused = p.fused_reduce;
     return best;   // tw == 0: the knobs name a variant that is not compiled
 }
@@ -2092,7 +2100,7 @@ static size_t plan_need(const Plan &pl, int M, int N, int K)
 static bool own_x_tiles(int M, int K, int S, int tw, int nw, int depth)
 {
     if (nw != kXWaves || depth != 1) return false;
-    return M > 16 || (K <= kStagedMaxK && (M > 4 || (tw == 8 && S == 1) || K / kGroup >= 8 * kXWaves * S));
+    return K <= kStagedMaxK && (M > 4 || (tw == 8 && S == 1) || K / kGroup >= 8 * kXWaves * S);
 }
 
 // symmetric-weight instantiations exist for the K-split and the high-occupancy column-split kernels; the other
@@ -2105,9 +2113,10 @@ static int launch_sym(const void *x, const void *packed, const Out &y, int M, in
     const bool own = own_x_tiles(M, K, S, TW, NW, DEPTH);
     auto *const kernel = [&] {
         if constexpr (NW != kXWaves || DEPTH != 1) return &gemm_kernel<MT, TW, NW, DEPTH, SYM>;
-        else if constexpr (MT > 1) return &gemm_x_kernel<MT, TW, SYM>;
+        else if constexpr (!fetched_x_variant(MT, TW)) return &gemm_x_kernel<MT, TW, SYM>;
         else return own ? &gemm_x_kernel<MT, TW, SYM> : &gemm_kernel<MT, TW, NW, DEPTH, SYM>;
     }();
+    if (!own && NW == kXWaves && DEPTH == 1 && !fetched_x_variant(MT, TW)) return W4A16_EUNSUP;   // no plan asks for it
     const size_t sum_bytes = (size_t)NW * 4 * TW * MT * 64 * sizeof(float), x_bytes = own ? (size_t)NW * MT * 4096 : 0;
     const size_t lds_bytes = sum_bytes > x_bytes ? sum_bytes : x_bytes;
     if (lds_bytes > 160 * 1024) return W4A16_EUNSUP;

@@ -133,6 +133,50 @@ def test_parity_own_x_tiles(M, K, N, big_ws):
                 assert np.array_equal(run_gemm(ex, ex_packed, big_ws).view(np.uint16), ex16.view(np.uint16)), what
 
 
+# eight wavefronts that fetch x from L2 with two row tiles: two groups of codes in flight, or contractions of 2 ** 25 and more
+VARIANTS_FETCHED_X = [(2, 8, 2, 1, 1), (2, 8, 2, 3, 0), (2, 8, 2, 2, 1)]
+
+
+@pytest.mark.parametrize("M,K,N", [(17, 128, 8), (32, 2176, 264), (24, 5120, 136)])
+def test_parity_fetched_x(M, K, N, big_ws):
+    print(f"gemm parity (fetched x) M={M} K={K} N={N}", flush=True)
+    inp = I.make_linear(5800 + M + K + N, M, K, N)
+    packed = B.pack_from_numpy(inp)
+    y32, _, _ = R.w4a16_gemm(inp.x, inp.qweight, inp.scales, inp.qzeros, 128, want64=False)
+    for variant in VARIANTS_FETCHED_X:
+        set_variant(*variant)
+        assert B.w4a16_plan_describe(M, N, K, 128)[:5] == (0, 2, 2, 8, 2)
+        check_gemm(run_gemm(inp, packed, big_ws), y32, f"M={M} K={K} N={N} variant={variant}")
+
+
+def test_eight_wavefronts_beyond_32_bit_offsets(big_ws):
+    """17 rows of 2 ** 25 elements: x zero but for some single ones all along K, all scales one, so the sums are whole numbers"""
+    M, K, N = 17, 2 ** 25, 8
+    g = torch.Generator(device=DEV).manual_seed(5900)
+    records = torch.randint(0, 256, (K // 128, 8512), dtype=torch.uint8, device=DEV, generator=g)
+    records[:, 8192:8448] = torch.ones(128, dtype=torch.float16, device=DEV).view(torch.uint8)
+    x = torch.zeros(M, K, dtype=torch.float16, device=DEV)
+    want = np.zeros((M, N))
+    rng = np.random.default_rng(5901)
+    for k in sorted({0, K - 1, *rng.integers(0, K, 60).tolist()}):
+        record = records[k // 128].cpu().numpy()
+        j, r, p = k % 128 // 32, k % 32 // 8, k % 8
+        ones = rng.integers(-1, 2, M)
+        x[:, k] = torch.from_numpy(ones).to(DEV, torch.float16)
+        for n in range(N):
+            word = int(record[(16 * r + n) * 16 + 4 * j:][:4].view(np.uint32)[0])
+            zero = int(record[8448 + 4 * n]) & 15
+            want[:, n] += ones * ((word >> 4 * ((p >> 1) + 4 * (p & 1)) & 15) - zero)
+    assert np.abs(want).max() < 2048
+    for tw, depth in ((2, 1), (4, 1), (2, 2)):
+        for split in (1, 3):
+            set_variant(tw, 8, depth, split, 1)
+            assert B.w4a16_plan_describe(M, N, K, 128)[:5] == (0, 2, tw, 8, depth)
+            y = torch.full((M, N), 7.0, dtype=torch.float16, device=DEV)
+            B.w4a16_gemm(x, records, y, M, N, K, 128, big_ws)
+            assert np.array_equal(y.cpu().numpy(), want), (tw, depth, split)
+
+
 # high-occupancy column-split workgroups, M > 16 only: (tiles_per_wave, k_sets, prefetch_depth, split_k)
 VARIANTS_CS = [(2, 1, 2, 1), (2, 2, 2, 1), (2, 2, 2, 3), (4, 1, 2, 1), (4, 1, 2, 2), (4, 2, 2, 1),
                (2, 3, 1, 3), (2, 3, 1, 1), (2, 3, 2, 1), (4, 3, 1, 2), (2, 2, 1, 3), (4, 2, 1, 2), (4, 1, 1, 1), (8, 1, 1, 1)]

@@ -199,6 +199,24 @@ def test_longest_contractions_stay_off_the_staged_kernels():
             B.w4a16_set_param(name, 0)
 
 
+@pytest.mark.parametrize("tw,depth,accepted", [(2, 1, (17, 32)), (4, 1, (17, 32)), (2, 2, (17, 32)), (0, 1, (17, 32)), (0, 0, (17, 32)), (0, 2, (17, 32)), (8, 1, ()), (4, 2, ())])
+def test_eight_wavefronts_serve_the_longest_contractions_too(tw, depth, accepted):
+    """by the knobs, with two row tiles; the kernel whose wavefronts copy x has 32-bit offsets, the one that fetches it does not"""
+    knobs = (("waves_per_wg", 8), ("tiles_per_wave", tw), ("prefetch_depth", depth))
+    out = (ctypes.c_int * 8)()
+    for name, value in knobs:
+        B.w4a16_set_param(name, value)
+    try:
+        for K in (2 ** 25, 2 ** 26):
+            for M in (17, 32, 33, 64):
+                code = B.load().w4a16_plan_describe(M, 1280, K, 128, out)
+                assert code == (0 if M in accepted else -4), (M, K)
+                assert code or out[3] == 8
+    finally:
+        for name, _ in knobs:
+            B.w4a16_set_param(name, 0)
+
+
 def test_planning_by_rule_is_cheap():
     """every call plans anew, and small calls are bound by the host: the rule for shapes without a measured row may cost
     some tenths of a microsecond over a table row (at most 0.45 where it was measured; loops over every candidate took 1.2)"""
