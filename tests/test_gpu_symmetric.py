@@ -46,22 +46,24 @@ def run(inp, packed, ws, epi=B.EPI_NONE, residual=None, M=None):
     return out[:M]
 
 
-# kernel families that have a symmetric instantiation: K-split workgroups (any M) and the column-split kernel with
-# interleaved K sets (M > 16); {} is the library's own plan
+# kernel families that have a symmetric instantiation: K-split workgroups (any M; among them eight wavefronts with x tiles of their
+# own) and the column-split kernel with interleaved K sets (M > 16); {} is the library's own plan
 def families(M):
     fam = [{}, dict(tiles_per_wave=8, waves_per_wg=4, prefetch_depth=1, split_k=1), dict(tiles_per_wave=2, waves_per_wg=4, prefetch_depth=2, split_k=3, fused_reduce=1),
            dict(tiles_per_wave=4, waves_per_wg=4, prefetch_depth=2, split_k=2, fused_reduce=0)]
     if M <= 16:
-        fam += [dict(tiles_per_wave=4, waves_per_wg=8, prefetch_depth=1, split_k=1), dict(tiles_per_wave=2, waves_per_wg=8, prefetch_depth=2, split_k=2, fused_reduce=1)]
+        fam += [dict(tiles_per_wave=4, waves_per_wg=8, prefetch_depth=1, split_k=1), dict(tiles_per_wave=2, waves_per_wg=8, prefetch_depth=2, split_k=2, fused_reduce=1),
+                dict(tiles_per_wave=8, waves_per_wg=8, prefetch_depth=1, split_k=1)]
     if M > 16:
         fam += [dict(tiles_per_wave=2, k_sets=2, prefetch_depth=1, split_k=1), dict(tiles_per_wave=4, k_sets=1, prefetch_depth=2, split_k=2),
                 dict(tiles_per_wave=2, k_sets=2, prefetch_depth=2, split_k=3, fused_reduce=1)]
+        fam += [dict(tiles_per_wave=tw, waves_per_wg=8, prefetch_depth=1, split_k=tw // 2, fused_reduce=1) for tw in ((2, 4, 8) if M <= 32 else (2, 4))]
     if 16 < M <= 48:
         fam += [dict(tiles_per_wave=2, k_sets=3, prefetch_depth=1, split_k=3, fused_reduce=1)]
     return fam
 
 
-CASES = [(1, 4096, 544), (5, 2048, 256), (8, 1536, 992), (16, 1024, 256), (17, 2048, 288), (40, 1536, 1312), (64, 2048, 1024), (60, 4096, 160)]   # N % 32 == 0: the gate needs it
+CASES = [(1, 4096, 544), (4, 1152, 288), (5, 2048, 256), (8, 1536, 992), (16, 1024, 256), (17, 2048, 288), (40, 1536, 1312), (64, 2048, 1024), (60, 4096, 160)]   # N % 32 == 0: the gate needs it
 
 
 @pytest.mark.parametrize("M,K,N", CASES)
