@@ -548,12 +548,12 @@ __device__ __forceinline__ void read_transposed_pair(short4v &lo, short4v &hi, u
                  : "=&v"(lo), "=&v"(hi)
                  : "v"(lds_addr), "n"(OFFSET), "n"(OFFSET + 16 * 256));
 }
-// returns once at most N LDS operations of this wavefront (the N most recent) are still under way; `first` is
-// the first result of the oldest pair still awaited, so that its use cannot be moved above the wait
+// returns once at most N LDS operations of this wavefront (the N most recent) are still under way; lo and hi are the
+// oldest pair still awaited, so that no use of it, not even a copy, can be moved above the wait
 template <int N>
-__device__ __forceinline__ void wait_lds_reads(short4v &first)
+__device__ __forceinline__ void wait_lds_reads(short4v &lo, short4v &hi)
 {
-    asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(first) : "n"(N));
+    asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(lo), "+v"(hi) : "n"(N));
 }
 // lane l's 16 bytes at src land at lds_base + 16 l (lds_base wavefront-uniform); counted by vmcnt
 __device__ __forceinline__ void row_to_lds(const uint8_t *src, uint8_t *lds_base)
@@ -764,11 +764,11 @@ __global__ __launch_bounds__(64 * kSharedWaves) void tree_attn_shared_kernel(
         for (int dt = 0; dt < 8; ++dt) {
             if (dt + 2 < 8) read_transposed_pair<BUF * kStepBytes>(lo[dt + 2], hi[dt + 2], vfrag[dt + 2]);
             if (dt + 2 < 8)
-                wait_lds_reads<4>(lo[dt]);
+                wait_lds_reads<4>(lo[dt], hi[dt]);
             else if (dt + 1 < 8)
-                wait_lds_reads<2>(lo[dt]);
+                wait_lds_reads<2>(lo[dt], hi[dt]);
             else
-                wait_lds_reads<0>(lo[dt]);
+                wait_lds_reads<0>(lo[dt], hi[dt]);
             typedef short short8v __attribute__((ext_vector_type(8)));
             const short8v both = __builtin_shufflevector(lo[dt], hi[dt], 0, 1, 2, 3, 4, 5, 6, 7);
             const half8v va = __builtin_bit_cast(half8v, both);
@@ -882,12 +882,6 @@ __device__ __forceinline__ void read_transposed_rows(short4v &lo, short4v &hi, u
                  : "=&v"(lo), "=&v"(hi)
                  : "v"(lds_addr), "n"(OFFSET), "n"(OFFSET + 8 * 256));
 }
-// returns once at most N LDS operations of this wavefront are still under way; the pair awaited cannot be used above it
-template <int N>
-__device__ __forceinline__ void wait_transposed(short4v &lo, short4v &hi)
-{
-    asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(lo), "+v"(hi) : "n"(N));
-}
 
 __global__ __launch_bounds__(64 * kSharedWaves) void tree_attn_wave_kernel(
     const _Float16 *__restrict__ q, const _Float16 *__restrict__ k, const _Float16 *__restrict__ v,
@@ -958,10 +952,13 @@ __global__ __launch_bounds__(64 * kSharedWaves) void tree_attn_wave_kernel(
         }
     };
     int step = b0 + wave;
+    __builtin_amdgcn_sched_barrier(0);   // Q before K before V: the waits below count on it
     if (step < b1) {   // uniform over the wavefront
         request(step, k_src, lane_k, 0, ktile);
+        __builtin_amdgcn_sched_barrier(0);
         request(step, v_src, lane_v, 1, vtile);
     }
+    __builtin_amdgcn_sched_barrier(0);
     if (reaches_draft) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
@@ -970,7 +967,9 @@ __global__ __launch_bounds__(64 * kSharedWaves) void tree_attn_wave_kernel(
             if (lane == i) row_bits[wave * 8 + i] = bits;
         }
     }
-    // everybody's part of the Q tile has landed (it is older than the sixteen transfers of K and V), and the mask words
+    // everybody's part of the Q tile has landed (it is older than the sixteen transfers of K and V), and the mask words.  As compiled, the first step
+    // waits for its V tile all the same: the compiler cannot count across these waits, so it waits for every transfer where the mask
+    // bytes are used, and in all workgroups once more ahead of the loop, where the registers of those bytes are taken for the sums.
     if (step < b1) asm volatile("s_waitcnt vmcnt(16) lgkmcnt(0)\n\ts_barrier" ::: "memory");
     else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 
@@ -1053,7 +1052,7 @@ __global__ __launch_bounds__(64 * kSharedWaves) void tree_attn_wave_kernel(
         auto product = [&](auto f) {
             constexpr int F = decltype(f)::value;
             if constexpr (F + 2 < 8) read_v(std::integral_constant<int, F + 2>{});
-            wait_transposed<F + 2 < 8 ? 4 : F + 1 < 8 ? 2 : 0>(lo[F], hi[F]);
+            wait_lds_reads<F + 2 < 8 ? 4 : F + 1 < 8 ? 2 : 0>(lo[F], hi[F]);
             typedef short short8v __attribute__((ext_vector_type(8)));
             const short8v both = __builtin_shufflevector(lo[F], hi[F], 0, 1, 2, 3, 4, 5, 6, 7);
             const half8v va = __builtin_bit_cast(half8v, both);

@@ -1576,6 +1576,8 @@ __global__ __launch_bounds__(kXWaves * 64) void gemm_x_kernel(
         }
     };
     // At the head of a group its x tile is older than the loads of its codes, the newest ones: a count says when it has landed.
+    // (As compiled, the forms with two or four tiles and zero-points wait for all loads ahead of the loop: the last group is peeled off, its codes
+    // live in other registers than the loop's, and the first group's are copied.  There the second group's x copies start late.)
     auto next_x = [&]() {
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kGroupLoads) : "memory");
         read_x();
