@@ -51,11 +51,15 @@ __device__ __forceinline__ float max_of_two(float a, float b)
     return d;
 }
 
-// Wait states until the results of matrix instructions that were just issued may be read: eight after a 16x16x32 step,
-// twelve after a 32x32x16 one (passes + 4).  In straight code, so that they lie on every path from the products to the first read.
-__device__ __forceinline__ void settled(float4v &a, float4v &b, float4v &c, float4v &d)
+// Wait states until results of matrix instructions that were just issued may be read: passes + 4, that is eight after a 16x16x32 step and twelve
+// after a 32x32x16 one.  settled<N>() adds N of them and keeps reads of its operands behind it; the steps and other
+// instructions in between make up the rest, on every path from the products to the first read.
+template <int N>
+__device__ __forceinline__ void settled(float4v &a, float4v &b)
 {
-    asm volatile("s_nop 7" : "+v"(a), "+v"(b), "+v"(c), "+v"(d));
+    static_assert(N >= 0 && N <= 8, "one s_nop");
+    if constexpr (N == 0) asm volatile("" : "+v"(a), "+v"(b));
+    else asm volatile("s_nop %2" : "+v"(a), "+v"(b) : "n"(N - 1));
 }
 __device__ __forceinline__ void settled(float16v &a) { asm volatile("s_nop 7\n\ts_nop 3" : "+v"(a)); }
 
@@ -718,10 +722,11 @@ __global__ __launch_bounds__(64 * kSharedWaves) void tree_attn_shared_kernel(
                     sb[rt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fb, qf[rt][j], sb[rt], 0, 0, 0);
                 }
             }
-            settled(sa[0], sb[0], sa[1], sb[1]);
             const bool prefix_only = key0 + kKeyBlock <= P;   // uniform: committed keys, all visible
 #pragma unroll
             for (int rt = 0; rt < 2; ++rt) {
+                if (rt == 0) settled<6>(sa[0], sb[0]);   // two more steps were issued after theirs
+                else settled<0>(sa[1], sb[1]);           // the first row tile's maximum lies in between
                 float s[8];
 #pragma unroll
                 for (int i = 0; i < 8; ++i) s[i] = (i < 4) ? sa[rt][i & 3] : sb[rt][i & 3];
