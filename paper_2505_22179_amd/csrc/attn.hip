@@ -98,13 +98,13 @@ struct RowTile {
     int rows;     // valid rows
     int index;    // number of the tile in its KV head
     bool whole;   // one query head per tile: no division
-    __device__ __forceinline__ RowTile(int unit, int M_, int Hq_, int group_, int tile_rows, int tiles_per_kv)
+    __device__ __forceinline__ RowTile(int kvh_, int index_, int M_, int Hq_, int group_, int tile_rows)
     {
         M = M_;
         Hq = Hq_;
         group = group_;
-        kvh = unit / tiles_per_kv;
-        index = unit - kvh * tiles_per_kv;
+        kvh = kvh_;
+        index = index_;
         first = index * tile_rows;
         rows = min(tile_rows, group * M - first);
         whole = tile_rows == M;
@@ -118,6 +118,27 @@ struct RowTile {
         head = kvh * group + j;
     }
 };
+
+// The row tile and the key range of a workgroup.  Workgroups go to the eight XCDs in turn; numbered so that each XCD gets a run of
+// consecutive numbers, and the tiles of one KV head and one range next to each other, an XCD reads few keys, and its L2 brings them
+// in once for all their tiles.  Any grid, each pair once.  Before, a grid that eight does not divide kept the order of launch, and its XCDs all read all keys; and
+// the ranges of a tile stood together, so that with fewer KV heads than XCDs each XCD read most keys of a head.  us: 28/4 heads, M = 28, prefix
+// 11477 31.1 -> 18.7, M = 8, prefix 3404 14.4 -> 10.0; 24/3 heads, M = 36, prefix 21792 43.3 -> 25.6; 20/5 heads, M = 52, prefix 3695 17.7 -> 12.9.
+struct Share {
+    int kvh, tile, range;   // KV head, row tile in it, key range
+    // by_tiles, by_ranges: divider() of tiles_per_kv and nsplit -- the divisions stand before the first address, where nothing hides them
+    __device__ __forceinline__ Share(unsigned block, unsigned grid, int nsplit, int tiles_per_kv, uint32_t by_tiles, uint32_t by_ranges)
+    {
+        const unsigned xcd = block & 7u;
+        const unsigned number = xcd * (grid >> 3) + min(xcd, grid & 7u) + (block >> 3);
+        const unsigned rest = __umulhi(2 * number, by_tiles);
+        tile = (int)(number - rest * (unsigned)tiles_per_kv);
+        kvh = (int)__umulhi(2 * rest, by_ranges);
+        range = (int)rest - kvh * nsplit;
+    }
+};
+// n / d == umulhi(2 n, divider(d)) while n d < 2^31: the factor exceeds 2^31 / d by less than one, n times that stays below 2^31 / d
+static uint32_t divider(int d) { return (uint32_t)(((1u << 31) + (unsigned)d - 1) / (unsigned)d); }
 
 // Merge of the key ranges of one tile by the workgroup that finished last (fused mode): NS = compiled
 // upper bound of the number of ranges, IT = items a thread handles at once (all their loads are issued
@@ -227,7 +248,7 @@ __global__ __launch_bounds__(256 * RG) void tree_attn_kernel(
     if ((grid & 7) == 0) lid = (blockIdx.x & 7) * (grid >> 3) + (blockIdx.x >> 3);
     // Tiles that hold the rows of several query heads of a KV group read K and V once for all of them.
     const int unit = lid / nsplit, sp = lid % nsplit;
-    const RowTile tile(unit, M, Hq, group, tile_rows, tiles_per_kv);
+    const RowTile tile(unit / tiles_per_kv, unit % tiles_per_kv, M, Hq, group, tile_rows);
     const int kvh = tile.kvh, R = tile.rows;
     const int T = P + M;
     // key steps of this split: bq = nblk / nsplit each, the first brem = nblk % nsplit one more (host-computed)
@@ -565,26 +586,25 @@ __device__ __forceinline__ void row_to_lds(const uint8_t *src, uint8_t *lds_base
     __builtin_amdgcn_global_load_lds((global_void *)src, (lds_void *)lds_base, 16, 0, 0);
 }
 
+// (The arguments fill two lines of the scalar cache, here and in the next kernel.  A third, for gridDim, costs every call 0.06 us.)
 __global__ __launch_bounds__(64 * kSharedWaves) void tree_attn_shared_kernel(
-    const _Float16 *__restrict__ q, const _Float16 *__restrict__ k, const _Float16 *__restrict__ v,
+    uint32_t by_tiles, uint32_t by_ranges, const _Float16 *__restrict__ q, const _Float16 *__restrict__ k, const _Float16 *__restrict__ v,
     const uint8_t *__restrict__ mask, _Float16 *__restrict__ out, float *__restrict__ part_o,
     float *__restrict__ part_ml, uint32_t *__restrict__ tickets, int M, int P, int Hq, int Hkv,
     int group, float scale_log2e, int nsplit, int bq, int brem, int tile_rows, int tiles_per_kv, int fused)
 {
     extern __shared__ float4v smem4[];
     uint8_t *lds = reinterpret_cast<uint8_t *>(smem4);
-    const unsigned grid = gridDim.x;
-    fetch_arguments_together(q, k, v, mask, out, part_o, part_ml, tickets, M, P, Hq, Hkv, group, scale_log2e, nsplit, bq, brem, tile_rows,
-                             tiles_per_kv, fused, grid);
+    fetch_arguments_together(by_tiles, by_ranges, q, k, v, mask, out, part_o, part_ml, tickets, M, P, Hq, Hkv, group, scale_log2e, nsplit, bq, brem, tile_rows,
+                             tiles_per_kv, fused);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kw = wave >> 1, rh = wave & 1;   // key wavefront, row half
     const int r = lane >> 4, c = lane & 15;
-    int lid = blockIdx.x;   // workgroups of one KV head on one XCD (see tree_attn_kernel)
-    if ((grid & 7) == 0) lid = (blockIdx.x & 7) * (grid >> 3) + (blockIdx.x >> 3);
-    const int unit = lid / nsplit, sp = lid % nsplit;
-    const RowTile tile(unit, M, Hq, group, tile_rows, tiles_per_kv);
-    const int kvh = tile.kvh, R = tile.rows;
+    const Share share(blockIdx.x, (unsigned)(Hkv * tiles_per_kv * nsplit), nsplit, tiles_per_kv, by_tiles, by_ranges);
+    const int kvh = share.kvh, unit = kvh * tiles_per_kv + share.tile, sp = share.range;
+    const RowTile tile(kvh, share.tile, M, Hq, group, tile_rows);
+    const int R = tile.rows;
     const int T = P + M;
     const int b0 = sp * bq + (sp < brem ? sp : brem), b1 = b0 + bq + (sp < brem ? 1 : 0);
     const int rounds = (b1 - b0 + 3) >> 2;
@@ -889,24 +909,22 @@ __device__ __forceinline__ void read_transposed_rows(short4v &lo, short4v &hi, u
 }
 
 __global__ __launch_bounds__(64 * kSharedWaves) void tree_attn_wave_kernel(
-    const _Float16 *__restrict__ q, const _Float16 *__restrict__ k, const _Float16 *__restrict__ v,
+    uint32_t by_tiles, uint32_t by_ranges, const _Float16 *__restrict__ q, const _Float16 *__restrict__ k, const _Float16 *__restrict__ v,
     const uint8_t *__restrict__ mask, _Float16 *__restrict__ out, float *__restrict__ part_o,
     float *__restrict__ part_ml, uint32_t *__restrict__ tickets, int M, int P, int Hq, int Hkv,
     int group, float scale_log2e, int nsplit, int bq, int brem, int tile_rows, int tiles_per_kv, int fused)
 {
     extern __shared__ float4v smem4[];
     uint8_t *lds = reinterpret_cast<uint8_t *>(smem4);
-    const unsigned grid = gridDim.x;
-    fetch_arguments_together(q, k, v, mask, out, part_o, part_ml, tickets, M, P, Hq, Hkv, group, scale_log2e, nsplit, bq, brem, tile_rows,
-                             tiles_per_kv, fused, grid);
+    fetch_arguments_together(by_tiles, by_ranges, q, k, v, mask, out, part_o, part_ml, tickets, M, P, Hq, Hkv, group, scale_log2e, nsplit, bq, brem, tile_rows,
+                             tiles_per_kv, fused);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int h = lane >> 5, c = lane & 31;
-    int lid = blockIdx.x;   // workgroups of one KV head on one XCD (see tree_attn_kernel)
-    if ((grid & 7) == 0) lid = (blockIdx.x & 7) * (grid >> 3) + (blockIdx.x >> 3);
-    const int unit = lid / nsplit, sp = lid % nsplit;
-    const RowTile tile(unit, M, Hq, group, tile_rows, tiles_per_kv);
-    const int kvh = tile.kvh, R = tile.rows;
+    const Share share(blockIdx.x, (unsigned)(Hkv * tiles_per_kv * nsplit), nsplit, tiles_per_kv, by_tiles, by_ranges);
+    const int kvh = share.kvh, unit = kvh * tiles_per_kv + share.tile, sp = share.range;
+    const RowTile tile(kvh, share.tile, M, Hq, group, tile_rows);
+    const int R = tile.rows;
     const int T = P + M;
     const int b0 = sp * bq + (sp < brem ? sp : brem), b1 = b0 + bq + (sp < brem ? 1 : 0);
     const size_t kv_row_bytes = (size_t)Hkv * kHeadDim * 2;
@@ -1476,9 +1494,9 @@ static int launch_attn_wave(int grid, hipStream_t stream, Args... args)
 }
 
 template <typename... Args>
-static int launch_attn(int rt, int rgroups, int grid, hipStream_t stream, Args... args)
+static int launch_attn(int rt, int rgroups, int grid, hipStream_t stream, uint32_t by_tiles, uint32_t by_ranges, Args... args)
 {
-    if (rt == 0) return rgroups == 2 ? launch_attn_shared(grid, stream, args...) : launch_attn_wave(grid, stream, args...);
+    if (rt == 0) return rgroups == 2 ? launch_attn_shared(grid, stream, by_tiles, by_ranges, args...) : launch_attn_wave(grid, stream, by_tiles, by_ranges, args...);
     if (rt == 4) return launch_attn_variant<4, 1>(grid, stream, args...);
     if (rgroups == 2) return launch_attn_variant<2, 2>(grid, stream, args...);
     return launch_attn_variant<2, 1>(grid, stream, args...);
@@ -1525,7 +1543,7 @@ int tree_verify_attn(const void *q, const void *k, const void *v, const uint8_t 
     // rows per wavefront, in two row groups for taller tiles (2).
     const int knob = params().attn_row_tiles;
     const int rt = knob == 4 ? 4 : knob == 2 ? 2 : 0, rgroups = rows > kWaveRows ? 2 : 1;
-    rc = launch_attn(rt, rgroups, units * ns, (hipStream_t)stream, (const _Float16 *)q, (const _Float16 *)k,
+    rc = launch_attn(rt, rgroups, units * ns, (hipStream_t)stream, divider(pl.tiles_per_kv), divider(ns), (const _Float16 *)q, (const _Float16 *)k,
                      (const _Float16 *)v, mask, (_Float16 *)out, part_o, part_ml, reinterpret_cast<uint32_t *>(workspace),
                      M, P, Hq, Hkv, Hq / Hkv, scale_log2e, ns, nblk / ns, nblk % ns, rows, pl.tiles_per_kv, pl.fused);
     if (rc != W4A16_OK) return rc;
