@@ -127,20 +127,29 @@ def test_the_walk_finds_what_a_branch_goes_round():
 def found(tmp_path_factory):
     if not shutil.which(OBJDUMP):
         pytest.skip("no llvm-objdump")
-    path, out, matrix = tmp_path_factory.mktemp("code") / "object", [], {}
+    path, out, matrix, order = tmp_path_factory.mktemp("code") / "object", [], {}, {}
     for obj in code_objects(build.build(force=False)):
         path.write_bytes(obj)
         bad, code = violations(subprocess.run([OBJDUMP, "-d", str(path)], capture_output=True, text=True, check=True).stdout.splitlines())
         out += bad
-        for name, kernel in zip(code.name, code.kernel):
+        for name, operands, kernel in zip(code.name, code.operands, code.kernel):
             if name.startswith("v_mfma"):
                 matrix[kernel] = matrix.get(kernel, 0) + 1
-    return out, matrix
+            if "tree_attn_merge" in kernel and (name.startswith("global_load") or "vmcnt" in operands):
+                order.setdefault(kernel, []).append("load" if "load" in name else "wait")
+    return out, matrix, order
 
 
 @pytest.mark.parametrize("kernels", ["gemm_", "tree_attn_", "lm_head_"])
 def test_no_result_of_a_matrix_instruction_is_touched_too_early(found, kernels):
-    bad, matrix = found
+    bad, matrix, _ = found
     assert sum(n for kernel, n in matrix.items() if kernels in kernel) > 100   # the listing was understood
     bad = [b for b in bad if kernels in b.split(":")[0]]
     assert not bad, f"{len(bad)}:\n" + "\n".join(bad[:40])
+
+
+@pytest.mark.parametrize("ranges", [4, 8])
+def test_the_merge_asks_for_all_partial_results_before_it_waits(found, ranges):
+    """two loads per key range; one memory round trip, not one per range"""
+    order, = (o for kernel, o in found[2].items() if f"tree_attn_merge_kernelILi{ranges}E" in kernel)
+    assert order[:2 * ranges] == ["load"] * (2 * ranges) and "load" not in order[2 * ranges:]
