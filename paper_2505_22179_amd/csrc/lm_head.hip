@@ -477,13 +477,17 @@ __global__ __launch_bounds__(kLmThreads) void lm_head_merge_kernel(const float *
     fetch_arguments_together(logits, stats, V, granules, granule, top_k, top_idx, top_logprob);
     const int m = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const float *const row = logits + (size_t)m * V;
+    // This lane's granules.  Up to 64 stay with the first wavefront, which then knows the k-th largest maximum of all -- if there are k.  Otherwise
+    // and up to 256 they are dealt in turn, so that each wavefront gives its share of the bound and of the reading: us, whole call, top 64 of
+    // 10 x 22794 (K = 128) 70 -> 17.5, of 5 x 3808 53 -> 14.6.  More fill all lanes in either order, and this one reads the statistics in whole lines.
+    const int first = PER == 1 && (granules > 64 || top_k > granules) ? lane * kWaves + wave : tid;
     LmStat st[PER];
 #pragma unroll
-    for (int i = 0; i < PER; ++i) st[i] = stats[(size_t)m * granules + min(tid + kLmThreads * i, granules - 1)];   // lanes past the end drop theirs
+    for (int i = 0; i < PER; ++i) st[i] = stats[(size_t)m * granules + min(first + kLmThreads * i, granules - 1)];   // lanes past the end drop theirs
     float lane_mx = kNegInf;
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-        if (tid + kLmThreads * i >= granules) st[i] = {kNegInf, 0.f};
+        if (first + kLmThreads * i >= granules) st[i] = {kNegInf, 0.f};
         lane_mx = fmaxf(lane_mx, st[i].max);
     }
     const float wave_mx = wave_max(lane_mx);
@@ -530,16 +534,26 @@ __global__ __launch_bounds__(kLmThreads) void lm_head_merge_kernel(const float *
     // this wavefront's granules that reach the bound, as pieces of 64 tokens; of those that just reach it the first k, which hold k tokens
     // that do
     const auto reaches = [&](float v) { return v >= bound && v > kNegInf; };
-    int found = 0, level = 0;
+    int found = 0;
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-        const bool just = reaches(st[i].max) && st[i].max == bound;
-        const uint64_t which_just = __ballot(just);
-        const bool take = reaches(st[i].max) && (!just || level + lanes_below(which_just) < top_k);
-        const uint64_t which = __ballot(take);
-        if (take) chosen[wave][found + lanes_below(which)] = tid + kLmThreads * i;
+        const uint64_t which = __ballot(reaches(st[i].max));
+        if (reaches(st[i].max)) chosen[wave][found + lanes_below(which)] = first + kLmThreads * i;
         found += __popcll(which);
-        level += __popcll(which_just);
+    }
+    if (found > top_k) {   // uniform: once more, without those that are too many
+        int level = 0;
+        found = 0;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const bool just = reaches(st[i].max) && st[i].max == bound;
+            const uint64_t which_just = __ballot(just);
+            const bool take = reaches(st[i].max) && (!just || level + lanes_below(which_just) < top_k);
+            const uint64_t which = __ballot(take);
+            if (take) chosen[wave][found + lanes_below(which)] = first + kLmThreads * i;
+            found += __popcll(which);
+            level += __popcll(which_just);
+        }
     }
     const int shift = 31 - __builtin_clz((unsigned)granule) - 6;   // granules are 64, 128, 256 or 512 tokens
     const int pieces = found << shift;
