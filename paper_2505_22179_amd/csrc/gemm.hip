@@ -1775,7 +1775,8 @@ constexpr SplitVariants kSplitVariants = split_variants();
 
 // Shapes without a measured row.  Least-squares fits give the time of a plan in microseconds from its launch shape,
 // over weights that come from HBM: 2477 plans of 92 calls (M = 1 .. 16) and 3039 of 132 (M = 20 .. 64) on 32 shapes,
-// K = 640 .. 28672, N = 1000 .. 32000; and 1638 plans of 240 calls (and 1426 of 130 with 5 .. 16 rows) of the kernel whose wavefronts have x tiles of their own, N up to 57344.  The plan with the least time lies 2 to 3 % behind the best measured one in the mean.
+// K = 640 .. 28672, N = 1000 .. 32000; and 1638 plans of 240 calls (and 1426 of 130 with 5 .. 16 rows) of the kernel whose wavefronts
+// have x tiles of their own, N up to 57344.  The plan with the least time lies 1 to 3 % behind the best measured one in the mean.
 // What the formulas know and the plain rule below does not: a workgroup more than the chip holds at once costs a whole second
 // pass (4096 x 12288 at 32 rows: 288 workgroups 19.0 us, 192 workgroups 13.4), and a second kernel or a last arriver costs 2 to 3 us,
 // so one K split on fewer compute units is often ahead (18944 -> 3584 at one row: 280 workgroups 17.2 us, 224 11.5).
@@ -1810,6 +1811,7 @@ struct ShapeTime {
             per_fill = 0.f;
             fill_one = 1.f / 256.f;
             last = 1.404f, last_split = 0.1524f;
+            if (tw_ == 2) last = 1.175f, last_split = 0.204f;   // 680 pairs of plans that differ in this alone: with 12 splits 0.6 us behind the second kernel
             second = 1.825f, second_split = 0.1051f + 1.46f * c.rows_cols;
         } else if (own_x) {   // the same with more
             const float m_tw = c.m * tw;
@@ -1867,7 +1869,8 @@ struct ShapeTime {
 static size_t partial_bytes(int mt, int nblocks, const Plan &pl, int groups);
 
 // The plain rule's plan, unless the fits promise an eighth less from one that runs in a single pass over the chip -- a
-// twentieth where the plain plan itself takes more than one.  On the fitted calls no pick is slower than the plain plan and the
+// twentieth where the plain plan itself takes more than one, or its wavefronts have x tiles of their own, whose fit errs less (23424 -> 632 at
+// 12 rows 9.1 us with an eighth, 7.6 with a twentieth).  On the fitted calls no pick is slower than the plain plan and the
 // mean gain is 12 %; on 116 other shapes and row counts 13 %, up to 1.8 times (5120 -> 13000 at 37 rows 25.9 -> 17.6 us,
 // 12288 x 12288 at one row 25.2 -> 17.0, at 64 rows 47.5 -> 33).
 struct RuleShape { int tw, nw, depth, ks, slots; };   // slots: workgroups that run at once
@@ -1901,6 +1904,16 @@ static bool reaches_all_of_k(int mt, int tw, int nw, int K)
     return K <= kStagedMaxK || nw != kXWaves || fetched_x_variant(mt, tw);
 }
 
+// What the fit of that kernel does not know.  A wavefront has nothing to do while there are fewer groups than wavefronts, and one with many tiles works on
+// them one by one: 128 -> 28176 at 21 rows 4.4 us in another kernel, 5.3 with eight tiles; 128 -> 13344 at 37 rows 4.4 and 4.75 with four.  And eight tiles
+// (17 .. 32 rows, unsplit for wide weights) pay with one full round of groups, or from nearly three on: 896 -> 18512 at 27 rows 7.45 and 7.1, 3456 -> 25688
+// at 20 rows 18.4 and 17.0, but 2688 -> 17648 at 18 rows 11.55 and 12.45, 2048 -> 27456 at 24 rows 10.55 and 11.1.
+static bool enough_groups(int mt, int tw, int groups)
+{
+    if (tw == 8) return groups >= 3 * kXWaves - 1 || groups == kXWaves || groups == kXWaves - 1;
+    return tw == 2 || groups > 1 || mt == 2;
+}
+
 static Plan predicted_plan(const Plan &plain, int M, int N, int K, bool own_x)
 {
     // what the caller's workspace and the built-in scratch have to hold does not grow beyond the latter
@@ -1915,7 +1928,7 @@ static Plan predicted_plan(const Plan &plain, int M, int N, int K, bool own_x)
         const int passes = t.passes(plain.S);
         least = t.walk(call, plain.S) + (plain.S == 1 ? 0.f : plain.fused ? t.last_arriver(plain.S) : t.second_kernel(plain.S));
         best_time = least * (1.f + 0.5f * (float)(passes - 1));
-        least *= passes > 1 ? 0.95f * (1.f + 0.5f * (float)(passes - 1)) : 0.87f;
+        least *= passes > 1 ? 0.95f * (1.f + 0.5f * (float)(passes - 1)) : t.own_x ? 0.95f : 0.87f;
     }
     const RuleShapes &shapes = kRuleShapesOf[mt - 1];
     for (int k = 0; k < shapes.count; ++k) {
@@ -1938,12 +1951,13 @@ static Plan predicted_plan(const Plan &plain, int M, int N, int K, bool own_x)
     }
     if (mt == 1 || !own_x || K > kStagedMaxK) return best;
     // Wavefronts with x tiles of their own, where they promise a fourteenth less still: in one pass, and with half a group per
-    // wavefront at least.  On 240 random shapes and row counts 1.24 times faster in the mean and 1.4 % slower at worst than without them.
+    // wavefront at least.  On 2212 random calls whose plan they change 1.35 times
+    // faster in the mean than without them, two more than 3 % slower and none more than 6 %.
     least = 0.93f * best_time;
     const size_t plain_bytes = partial_bytes(mt, nblocks, plain, groups), best_bytes = partial_bytes(mt, nblocks, best, groups);
     const size_t room = plain_bytes < best_bytes ? plain_bytes : best_bytes;
     for (const int tw : kOwnXTiles) {
-        if (!variant_exists(mt, tw, kXWaves, 1)) continue;
+        if (!variant_exists(mt, tw, kXWaves, 1) || !enough_groups(mt, tw, groups)) continue;
         const ShapeTime t(call, tw, kXWaves, 1, 0);
         const int fit = kComputeUnits / t.units, deep = groups / (kXWaves / 2);
         const int most = fit < 1 ? 0 : deep < 1 ? 1 : deep < fit ? (deep < 16 ? deep : 16) : (fit < 16 ? fit : 16);

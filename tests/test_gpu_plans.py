@@ -217,6 +217,20 @@ def test_eight_wavefronts_serve_the_longest_contractions_too(tw, depth, accepted
             B.w4a16_set_param(name, 0)
 
 
+def test_few_groups_get_narrow_tiles():
+    """wavefronts with x tiles of their own: no four tiles on a single group beyond 32 rows, no eight on fewer than seven, nor on one round and a bit"""
+    own_x = 0
+    for M in (17, 24, 32, 33, 48, 64):
+        for groups in list(range(1, 26)) + [40, 80]:
+            for N in (504, 2000, 5000, 9000, 13000, 18000, 24000, 28000, 32000):
+                family, mt, tw, nw, *_ = B.w4a16_plan_describe(M, N, 128 * groups)
+                if family == 0 and nw == 8:
+                    own_x += 1
+                    assert tw < 8 or groups in (7, 8) or groups >= 23, (M, groups, N)
+                    assert tw < 4 or groups > 1 or mt == 2, (M, groups, N)
+    assert own_x > 300
+
+
 def test_planning_by_rule_is_cheap():
     """every call plans anew, and small calls are bound by the host: the rule for shapes without a measured row may cost
     some tenths of a microsecond over a table row (at most 0.45 where it was measured; loops over every candidate took 1.2)"""
