@@ -1383,13 +1383,15 @@ static float plan_time(const AttnPlan &p, int M, int P, int Hkv)
     const int units = Hkv * p.tiles_per_kv, groups = units * p.ranges, passes = (groups + 255) / 256;
     const int steps = (key_steps(M, P) + p.ranges - 1) / p.ranges;
     const float fill = (float)(groups < 256 ? groups : 256) / 256.f, rows = (float)p.tile_rows, ranges = (float)p.ranges;
-    const bool beyond_l2 = (float)(P + M) * (Hkv > 8 ? (float)Hkv / 8.f : 1.f) > 5860.f;   // 3 MB of K and V per XCD
+    const bool beyond_l2 = (float)(P + M) * (Hkv > 8 ? (float)Hkv / 8.f : 1.f) > 5860.f;   // 3 MB of K and V per XCD (fewer than eight KV heads leave an XCD less)
     const float far = beyond_l2 ? fill * (float)steps : 0.f;
     if (p.tile_rows <= kWaveRows) {
         const float rounds = (float)((steps + 7) / 8);
         const float t = 5.225f + 0.028f * rows + (float)passes * (0.1672f * rounds * fill + 0.1562f * (float)steps + (steps > 8 ? 0.435f : 0.f) + 0.0487f * far);
         if (p.ranges > 1) return t + (p.fused ? 1.297f + 0.0557f * ranges + 0.0058f * rows * ranges : 2.715f + 0.00002f * (float)groups * rows + 0.042f * ranges);
-        return steps > 8 ? t + 0.4f : t;   // the fit's error for one range of a few rounds: 40/8 heads, M = 2, nine steps 7.5 us, in five ranges 7.2
+        // the fit's error for one range of a few rounds: 40/8 heads, M = 2, nine steps 7.5 us, in three ranges 7.3.  With it the picks of nine head counts and prefixes of
+        // 200 .. 760 are within 5 % of the best, but for 128/16 heads at 16 rows (two ranges 8.7, one 7.8)
+        return steps > 8 ? t + 0.4f : t;
     }
     const float rounds = (float)((steps + 3) / 4);
     const float t = 5.73f + 0.0184f * rows + (float)passes * (0.4556f * (rounds - 1.f) + 0.0965f * rounds * fill + 0.2233f * (float)steps + 0.0183f * far);
@@ -1402,8 +1404,8 @@ static float plan_time(const AttnPlan &p, int M, int P, int Hkv)
 // waste no rows, and up to 32 ranges; at short ones a single range and no merge; and where the plain plan's rounding up
 // makes more workgroups than compute units (40/8 heads: 280), as many as there are.  Tiles of up to 32 rows run in the kernel whose wavefronts share
 // nothing and cover eight key steps at a time, so they need half the ranges: us, before that kernel -> now: prefix 2048, M = 24 of 64/8 heads 13.7 -> 11.3,
-// M = 60 of 32/8 heads 14.9 -> 11.4, M = 1 8.5 -> 7.7; prefix 500, M = 18 of 64/8 heads 11.5 -> 8.4; prefix 16001, M = 40 of 32/8 heads 28.0 -> 26.4; 34 random calls
-// 1.14 x in the mean, one 5 % slower.  The picks lie 2 to 3 % behind the best measured plan in the mean.
+// M = 60 of 32/8 heads 14.9 -> 11.4, M = 1 8.5 -> 7.7; prefix 500, M = 18 of 64/8 heads 11.5 -> 8.4; prefix 16001, M = 40 of 32/8 heads 27.1 -> 25.0; 975 random
+// calls of twelve head counts 0.86 to 0.90 of the time before, four of them 6 to 9 % more.  The picks lie 2 to 3 % behind the best measured plan in the mean.
 static AttnPlan plan_by_size(const AttnPlan &plain, int M, int P, int Hq, int Hkv)
 {
     const int group = Hq / Hkv, steps = key_steps(M, P);
@@ -1411,7 +1413,8 @@ static AttnPlan plan_by_size(const AttnPlan &plain, int M, int P, int Hq, int Hk
     AttnPlan best = plain;
     float least = plan_time(plain, M, P, Hkv);
     if (least > 15.f) least *= 0.95f;   // long walks: the fits are off by more than what many tilings differ by
-    // a group of at most eight rows stays in one tile (plain decoding, 32/8 heads, prefix 2048: 8.2 us against 8.7 in two)
+    // A group of at most eight rows stays in one tile.  Eight head counts, prefixes 60 .. 20000, against the best split of the group: ahead from prefix 1000 on with
+    // eight KV heads (32/8, prefix 2048: 8.0 us against 8.4), elsewhere within 0.2 us; with two KV heads 0.2 to 1 us behind at prefixes of 300 to 12000
     for (int d = M * group <= 8 ? group : -1; d <= group; ++d) {
         AttnPlan p = {d * M, 0, 1, 0};
         if (d <= 0) {

@@ -1470,7 +1470,7 @@ __device__ __forceinline__ void cs_segment(const _Float16 *__restrict__ x, const
 // the x tile, 16 KB per wavefront and group at 64 rows, which four column quarters would share (70B down at 64 rows: 46 us against 42.5
 // of the column-split kernel, gate_up 93 against 73).  So it takes the shapes in between; us, column-split or K-split kernel before -> now: 8B q/k/v
 // 10.0 -> 8.9 at 32 rows and 13.2 -> 11.3 at 64, 70B o_proj 21.0 -> 16.7 at 60, 8B down 13.4 -> 10.8 at 30 and 19.2 -> 16.0 at 60,
-// 5120 -> 13000 at 37 16.9 -> 14.2, 1024 -> 2624 at 48 7.4 -> 4.0.  Not better: two or four groups of codes in flight (the larger
+// 5120 -> 13000 at 37 16.5 -> 14.8, 1024 -> 2624 at 48 7.4 -> 4.0.  Not better: two or four groups of codes in flight (the larger
 // loop costs more than the latency it hides), the copies of x spread over the tiles instead of issued together.
 constexpr int kXWaves = 8;
 template <int MT, int TW, bool SYM>
@@ -1723,7 +1723,7 @@ static bool flat_variant_exists(int tw, int nw, int ng)
     return false;
 }
 
-// the kernel variants that are compiled: X(MT, TW, NW, DEPTH)
+// the kernel variants that are compiled: X(MT, TW, NW, DEPTH); eight wavefronts with a depth of two or four are asked for by knobs only
 #define W4_VARIANTS_SMALL(X, MT)                                                                    \
     X(MT, 2, 4, 1) X(MT, 2, 4, 2) X(MT, 2, 4, 4) X(MT, 4, 4, 1) X(MT, 4, 4, 2) X(MT, 8, 4, 1) X(MT, 8, 4, 2)
 #define W4_VARIANTS(X)                                                                              \
@@ -2112,7 +2112,7 @@ static size_t plan_need(const Plan &pl, int M, int N, int K)
 // (lanes of rows that do not exist ask for the last one's lines): up to four rows the two differ by 3 % either way (3072 -> 4000 at one row
 // 4.3 us against 4.5 with copies, 70B down 21.5 against 21.7), but with eight tiles per wavefront and no split, or walks of eight groups, the copies are never
 // behind (at one row 4096 -> 28672 12.0 -> 11.4).
-// From five rows on they are ahead everywhere: 16 rows: 3072 -> 4000 6.1 -> 4.8, 5120 -> 13000 10.9 -> 9.7, 4096 -> 28672 13.5 -> 12.3, 70B down 23.5 -> 22.7.
+// From five rows on they are ahead, or level (70B q/k/v within 2 % either way): 16 rows: 3072 -> 4000 6.1 -> 4.8, 5120 -> 13000 10.9 -> 9.7, 4096 -> 28672 13.5 -> 12.3, 70B down 23.5 -> 22.7.
 static bool own_x_tiles(int M, int K, int S, int tw, int nw, int depth)
 {
     if (nw != kXWaves || depth != 1) return false;
