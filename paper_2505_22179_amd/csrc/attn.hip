@@ -1404,15 +1404,15 @@ static float plan_time(const AttnPlan &p, int M, int P, int Hkv)
 // waste no rows, and up to 32 ranges; at short ones a single range and no merge; and where the plain plan's rounding up
 // makes more workgroups than compute units (40/8 heads: 280), as many as there are.  Tiles of up to 32 rows run in the kernel whose wavefronts share
 // nothing and cover eight key steps at a time, so they need half the ranges: us, before that kernel -> now: prefix 2048, M = 24 of 64/8 heads 13.7 -> 11.3,
-// M = 60 of 32/8 heads 14.9 -> 11.4, M = 1 8.5 -> 7.7; prefix 500, M = 18 of 64/8 heads 11.5 -> 8.4; prefix 16001, M = 40 of 32/8 heads 27.1 -> 25.0; 975 random
-// calls of twelve head counts 0.86 to 0.90 of the time before, four of them 6 to 9 % more.  The picks lie 2 to 3 % behind the best measured plan in the mean.
+// M = 60 of 32/8 heads 14.9 -> 11.4, M = 1 8.5 -> 7.7; prefix 500, M = 18 of 64/8 heads 11.5 -> 8.4; prefix 16001, M = 40 of 32/8 heads 27.1 -> 25.0; 1025 random
+// calls of sixteen head counts 0.87 to 0.89 of the time before, one of them 9 % more, no other 5 %.  (Nothing speaks for the plain plan as such: with a twentieth's
+// allowance on long walks 39 of these calls took 2 to 3 % more.)  The picks lie 2 to 3 % behind the best measured plan in the mean.
 static AttnPlan plan_by_size(const AttnPlan &plain, int M, int P, int Hq, int Hkv)
 {
     const int group = Hq / Hkv, steps = key_steps(M, P);
     const int stated = (int)stated_partials(M, P, Hq);
     AttnPlan best = plain;
     float least = plan_time(plain, M, P, Hkv);
-    if (least > 15.f) least *= 0.95f;   // long walks: the fits are off by more than what many tilings differ by
     // A group of at most eight rows stays in one tile.  Eight head counts, prefixes 60 .. 20000, against the best split of the group: ahead from prefix 1000 on with
     // eight KV heads (32/8, prefix 2048: 8.0 us against 8.4), elsewhere within 0.2 us; with two KV heads 0.2 to 1 us behind at prefixes of 300 to 12000
     for (int d = M * group <= 8 ? group : -1; d <= group; ++d) {
