@@ -15,6 +15,7 @@
 // do not depend on scheduling.
 #include "internal.h"
 #include "devscope.h"
+#include <type_traits>
 
 namespace w4 {
 
@@ -1602,6 +1603,164 @@ __global__ __launch_bounds__(kXWaves * 64) void gemm_x_kernel(
     finish_unit<MT, TW, NW>(acc, lds4, ticket_sh, y, partial, tickets, M, N, S, fused, unit, ks, nb, t0, tid, lane, wave);
 }
 
+// The linears that follow a norm, for at most kFlatMaxRows rows: y = rms_norm(h, gamma) . W without a kernel for the norm.  At one row
+// a norm of its own costs 3.2 us, nearly all of it launch and round trips; here every workgroup works the norm of the whole rows out
+// again, 8 - 16 KB a row from L2, while its first codes are on their way (h and gamma are requested ahead of them, so that waiting for h
+// never waits for weights).  The arithmetic and its order are those of rms_norm_kernel, slot by slot: slot i of a thread stands for that
+// kernel's thread tid + kThreads * i, which holds one 16-byte chunk of a row (K <= 8192).  The rows, rounded to fp16, are parked in LDS
+// and the walk reads its first MFMA operands there.  DEPTH groups of codes are in flight per wavefront, and every wavefront has at least
+// DEPTH groups (checked by the host): with DEPTH == the number of groups this is the all-loads-up-front walk.
+// Whole layer (two norms), us, with norms of their own -> now, prefix 1000: 8B one row 49.3 -> 45.3, two 48.9 -> 45.2, four 49.9 -> 48.4; 70B one row
+// 101.7 -> 96.9, four 105.6 -> 104.8; hidden 2048, one row 37.3 -> 33.5, four 38.1 -> 36.5.  Forms for one, two and four rows are compiled: the
+// rows' arithmetic stands ahead of the first product, and what four rows cost over one (about 1 us a norm) is the gain that shrinks; with more rows, or
+// the 128 KB of sixteen, it would be gone.  Two groups of eight tiles in flight: the 8B layer 45.4 -> 45.5, the 70B layer 97.6 -> 98.9, so one.
+constexpr int kNormedMaxK = 8192;
+template <int TW, int NW, int DEPTH, int ROWS, bool SYM>
+__global__ __launch_bounds__(NW * 64) void gemm_normed_kernel(
+    const _Float16 *__restrict__ h, const uint8_t *__restrict__ packed, int M, int N, int K, int groups, int S, int fused,
+    int gq, int grem, const _Float16 *__restrict__ gamma, float eps, const Out y, float *__restrict__ partial,
+    uint32_t *__restrict__ tickets)
+{
+    extern __shared__ float4v lds4[];
+    __shared__ uint32_t ticket_sh;
+    constexpr int kThreads = NW * 64, kNormWaves = 16, kSlots = kNormWaves / NW;
+    __shared__ __attribute__((aligned(16))) float wave_sum[ROWS][kNormWaves];
+    fetch_arguments_together(h, packed, M, N, K, groups, S, fused, gq, grem, gamma, eps);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane >> 4, c = lane & 15;
+    const int unit = blockIdx.y, ks = blockIdx.x;   // grid = (S, units)
+    const int nb = (unit * TW) >> 3, t0 = (unit * TW) & 7;
+    const KRange kr = k_range(ks, gq, grem);
+    const int g0 = kr.begin + wave;
+    const int n_w = (kr.end - g0 + NW - 1) / NW;    // >= DEPTH
+
+    // 1. the rows and the norm weights
+    const int chunks = K >> 3;
+    half8v hv[ROWS][kSlots], gv[kSlots];
+#pragma unroll
+    for (int i = 0; i < kSlots; ++i) {
+        const int ch = min(tid + kThreads * i, chunks - 1);
+#pragma unroll
+        for (int m = 0; m < ROWS; ++m) hv[m][i] = *reinterpret_cast<const half8v *>(h + (size_t)(m < M ? m : M - 1) * K + ch * 8);
+        gv[i] = *reinterpret_cast<const half8v *>(gamma + ch * 8);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // 2. the first codes
+    const Stretch recs = stretch(packed + record_offset(nb, g0, groups), (uint32_t)(groups - g0) * kRecordBytes);
+    const uint32_t code_off = (uint32_t)(t0 * 1024 + lane * 16);
+    const uint32_t scale_off = (uint32_t)(kScalesOff + c * 16 + t0 * 2), zero_off = (uint32_t)(kZerosOff + c * 4);
+    u32x4 w[DEPTH][TW];
+    StagedQuant<TW> qw[DEPTH];
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) {
+        const uint32_t rec = (uint32_t)d * (NW * kRecordBytes);
+        load_quant<TW, SYM>(qw[d], recs, rec, scale_off, zero_off);
+#pragma unroll
+        for (int t = 0; t < TW; ++t) w[d][t] = stream_quad(recs, code_off + (uint32_t)(t * 1024), rec);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // 3. the norm
+    float ss[ROWS][kSlots];
+#pragma unroll
+    for (int i = 0; i < kSlots; ++i)
+#pragma unroll
+        for (int m = 0; m < ROWS; ++m) {
+            float v = 0.f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v = fmaf((float)hv[m][i][e], (float)hv[m][i][e], v);
+            ss[m][i] = tid + kThreads * i < chunks ? v : 0.f;
+        }
+    const auto add_rotated = [&](auto amount) {   // adds the value `amount` lanes on in the row of sixteen
+#pragma unroll
+        for (int i = 0; i < kSlots; ++i)
+#pragma unroll
+            for (int m = 0; m < ROWS; ++m)
+                ss[m][i] += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, ss[m][i]), 0x120 + decltype(amount)::value, 0xF, 0xF, false));
+    };
+#pragma unroll
+    for (int off = 32; off > 8; off >>= 1)
+#pragma unroll
+        for (int i = 0; i < kSlots; ++i)
+#pragma unroll
+            for (int m = 0; m < ROWS; ++m) ss[m][i] += __shfl_xor(ss[m][i], off, 64);
+    // within sixteen lanes a rotation stands for the butterfly: lanes that differ in bits already summed over hold equal values
+    add_rotated(std::integral_constant<int, 8>{});
+    add_rotated(std::integral_constant<int, 4>{});
+    add_rotated(std::integral_constant<int, 2>{});
+    add_rotated(std::integral_constant<int, 1>{});
+    if (lane == 0)
+#pragma unroll
+        for (int i = 0; i < kSlots; ++i)
+#pragma unroll
+            for (int m = 0; m < ROWS; ++m) wave_sum[m][wave + NW * i] = ss[m][i];
+    __syncthreads();
+    u32x4 *const xs = reinterpret_cast<u32x4 *>(lds4);
+    const int stride16 = chunks + 1;   // one 16-byte word of padding per row
+#pragma unroll
+    for (int m = 0; m < ROWS; ++m) {
+        float total = 0.f;
+#pragma unroll
+        for (int v = 0; v < kNormWaves; v += 4) {
+            const float4v four = *reinterpret_cast<const float4v *>(&wave_sum[m][v]);
+            total = (((total + four[0]) + four[1]) + four[2]) + four[3];
+        }
+        const float scale = 1.0f / sqrtf(total / (float)K + eps);
+#pragma unroll
+        for (int i = 0; i < kSlots; ++i) {
+            half8v o;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) o[e] = (_Float16)((float)hv[m][i][e] * scale * (float)gv[i][e]);
+            const int ch = tid + kThreads * i;
+            if (ch < chunks && m < M) xs[m * stride16 + ch] = __builtin_bit_cast(u32x4, o);
+        }
+    }
+    __syncthreads();
+
+    // 4. the walk
+    const DequantConsts magic = dequant_consts();
+    float4v acc[TW][1];
+#pragma unroll
+    for (int t = 0; t < TW; ++t) acc[t][0] = (float4v){0.f, 0.f, 0.f, 0.f};
+    const u32x4 *const xrow = xs + (c < M ? c : M - 1) * stride16 + r;
+    const auto compute = [&](int i, u32x4 (&wd)[TW], StagedQuant<TW> &qd, bool refill) {   // group i; group i + DEPTH takes its codes' place
+        u32x4 a[1][4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) a[0][j] = xrow[(g0 + NW * i) * 16 + j * 4];
+        const StagedQuant<TW> q = qd;
+        const uint32_t zbits = q.z >> (4 * t0), rec = (uint32_t)(i + DEPTH) * (NW * kRecordBytes);
+        if (refill) load_quant<TW, SYM>(qd, recs, rec, scale_off, zero_off);
+        float4v negc[1], xsum[1];
+        if constexpr (SYM) group_sums_symmetric<1>(a, negc);
+        else group_sums<1>(a, negc, xsum);
+#pragma unroll
+        for (int t = 0; t < TW; ++t) {
+            half8v b[4];
+            offset_tile(b, wd[t], magic);
+            float4v part = negc[0];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                part = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8v, a[0][j]), b[j], part, 0, 0, 0);
+            if (refill) wd[t] = stream_quad(recs, code_off + (uint32_t)(t * 1024), rec);
+            const uint32_t s2 = q.s[t >> 1];
+            const float sc = (float)__builtin_bit_cast(_Float16, (uint16_t)((t & 1) ? (s2 >> 16) : (s2 & 0xFFFFu)));
+            if constexpr (SYM) fold_symmetric(acc[t][0], part, sc);
+            else fold_offset(acc[t][0], part, xsum[0], sc, (float)((zbits >> (4 * t)) & 0xFu));
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    int i = 0;
+    for (; i + 2 * DEPTH <= n_w; i += DEPTH) {   // every group here has a successor DEPTH groups on
+#pragma unroll
+        for (int u = 0; u < DEPTH; ++u) compute(i + u, w[u], qw[u], true);
+    }
+#pragma unroll
+    for (int u = 0; u < 2 * DEPTH - 1; ++u)
+        if (i + u < n_w) compute(i + u, w[u % DEPTH], qw[u % DEPTH], i + u + DEPTH < n_w);   // uniform
+    __syncthreads();   // the rows are dead: the epilogue reuses their LDS
+    finish_unit<1, TW, NW>(acc, lds4, ticket_sh, y, partial, tickets, M, N, S, fused, unit, ks, nb, t0, tid, lane, wave);
+}
+
 // Two ways to share the work.  Classic (per == 0): grid = (S, workgroup units), workgroup (ks, u) takes
 // K split ks of unit u.  Even split (per > 0): the (unit, group) pairs, unit-major, are dealt out in
 // runs of `per` to a 1-D grid, so every workgroup gets the same number of groups even when the units
@@ -2287,6 +2446,64 @@ static int dispatch(int mt, const Plan &pl, const void *x, const void *packed, c
     return W4A16_EUNSUP;
 }
 
+// ---- linears behind a norm (gemm_normed) ------------------------------------------------------------
+// The K-split shapes compiled with the norm of their rows in front: {tiles per wavefront, wavefronts, groups in flight}.  The walk of a plan
+// is kept (tiles, wavefronts, K splits, and with them the order of all sums), so the results are those of the two kernels bit for bit.
+template <int TW, int NW, int DEPTH, int ROWS, bool SYM>
+static int launch_normed(const void *h, const void *gamma, float eps, const void *packed, const Out &y, int M, int N, int K, const Plan &pl,
+                         void *workspace, hipStream_t stream)
+{
+    static bool lds_ok = false;
+    const auto lds_for = [](int rows, int k) {
+        const size_t x_bytes = (size_t)rows * (k / 8 + 1) * 16, sum_bytes = (size_t)NW * 4 * TW * 64 * sizeof(float);
+        return x_bytes > sum_bytes ? x_bytes : sum_bytes;
+    };
+    if (!lds_ok && lds_for(ROWS, kNormedMaxK) > 48 * 1024) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_normed_kernel<TW, NW, DEPTH, ROWS, SYM>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_for(ROWS, kNormedMaxK)) != hipSuccess)
+            return W4A16_EHIP;
+        lds_ok = true;
+    }
+    const int groups = K / kGroup, units = pad_cols(N) / 16 / TW, S = pl.S;
+    uint32_t *tickets = reinterpret_cast<uint32_t *>(workspace);
+    float *partial = reinterpret_cast<float *>(reinterpret_cast<uint8_t *>(workspace) + kTicketBytes);
+    hipLaunchKernelGGL((gemm_normed_kernel<TW, NW, DEPTH, ROWS, SYM>), dim3((unsigned)S, (unsigned)units), dim3(NW * 64), lds_for(M, K), stream,
+                       (const _Float16 *)h, (const uint8_t *)packed, M, N, K, groups, S, pl.fused, groups / S, groups % S,
+                       (const _Float16 *)gamma, eps, y, partial, tickets);
+    if (S > 1 && !pl.fused)
+        hipLaunchKernelGGL((splitk_reduce_kernel<1, TW>), dim3((unsigned)units), dim3(kReduceThreads), 0, stream,
+                           (const float *)partial, y, M, N, S);
+    return launch_status();
+}
+
+// W4A16_EUNSUP: no such form of this plan
+static int dispatch_normed(const void *h, const void *gamma, float eps, const void *packed, const Out &y, int M, int N, int K, Plan pl,
+                           void *workspace, hipStream_t stream)
+{
+    if (M > kFlatMaxRows || K > kNormedMaxK || pl.S < 1 || pl.ks > 0 || (pl.nw != 8 && pl.nw != 4)) return W4A16_EUNSUP;
+    const int least = K / kGroup / pl.S / pl.nw;   // groups of the wavefront that has fewest
+    if (least < 1) return W4A16_EUNSUP;
+#define N1(TW_, NW_, D_, ROWS_, SYM_) return launch_normed<TW_, NW_, D_, ROWS_, SYM_>(h, gamma, eps, packed, y, M, N, K, pl, workspace, stream)
+#define N2(TW_, NW_, D_)                                                                       \
+    do {                                                                                       \
+        if (y.sym && M == 1) N1(TW_, NW_, D_, 1, true);                                        \
+        if (y.sym && M == 2) N1(TW_, NW_, D_, 2, true);                                        \
+        if (y.sym) N1(TW_, NW_, D_, kFlatMaxRows, true);                                       \
+        if (M == 1) N1(TW_, NW_, D_, 1, false);                                                \
+        if (M == 2) N1(TW_, NW_, D_, 2, false);                                                \
+        N1(TW_, NW_, D_, kFlatMaxRows, false);                                                 \
+    } while (0)
+    if (pl.tw == 2 && pl.nw == 8 && least >= 4) N2(2, 8, 4);
+    if (pl.tw == 2 && pl.nw == 8) N2(2, 8, 1);
+    if (pl.tw == 4 && pl.nw == 8 && least >= 2) N2(4, 8, 2);
+    if (pl.tw == 4 && pl.nw == 8) N2(4, 8, 1);
+    if (pl.tw == 8 && pl.nw == 8) N2(8, 8, 1);
+    if (pl.tw == 8 && pl.nw == 4) N2(8, 4, 1);
+#undef N2
+#undef N1
+    return W4A16_EUNSUP;
+}
+
 }  // namespace w4
 
 using namespace w4;
@@ -2318,7 +2535,15 @@ static int check_gemm(const void *x, const void *packed, const void *y, int M, i
     return misaligned(x) || misaligned(packed) || misaligned(y) ? W4A16_EALIGN : W4A16_OK;
 }
 
-static int run_plan(Plan pl, const void *x, const void *packed, const Out &out, int M, int N, int K, void *workspace, void *stream)
+// rows still to be normed: the linear's input is rms_norm(x, gamma), which goes to `scratch` where it does not stay inside the kernel
+struct Norm {
+    const void *gamma;
+    float eps;
+    void *scratch;
+};
+
+static int run_plan(Plan pl, const void *x, const void *packed, const Out &out, int M, int N, int K, void *workspace, void *stream,
+                    const Norm *norm = nullptr)
 {
     const int nblocks = pad_cols(N) / kBlockCols;
     // one ticket per column unit: only the last-arriver sums use them
@@ -2327,11 +2552,17 @@ static int run_plan(Plan pl, const void *x, const void *packed, const Out &out, 
         if (pl.S == 0) return W4A16_EUNSUP;   // the even split has no two-kernel form
         pl.fused = 0;                         // same K split, summed by the second kernel
     }
+    if (norm) {
+        int rc = dispatch_normed(x, norm->gamma, norm->eps, packed, out, M, N, K, pl, workspace, (hipStream_t)stream);
+        if (rc != W4A16_EUNSUP) return rc;
+        if ((rc = rms_norm(x, norm->gamma, norm->scratch, M, K, norm->eps, stream)) != W4A16_OK) return rc;
+        x = norm->scratch;
+    }
     return dispatch((M + 15) / 16, pl, x, packed, out, M, N, K, workspace, (hipStream_t)stream);
 }
 
 static int gemm_entry(const void *x, const void *packed, const Out &out, int M, int N, int K, int G, void *workspace,
-                      size_t workspace_bytes, void *stream)
+                      size_t workspace_bytes, void *stream, const Norm *norm = nullptr)
 {
     const int rc = check_gemm(x, packed, out.y, M, N, K, G);
     if (rc != W4A16_OK) return rc;
@@ -2344,7 +2575,7 @@ static int gemm_entry(const void *x, const void *packed, const Out &out, int M, 
         if (plan_need(pl, M, N, K) > room) pl = choose_plan(M, N, K, Choice::least);
         if (plan_need(pl, M, N, K) > room) return W4A16_EWORKSPACE;
     }
-    return run_plan(pl, x, packed, out, M, N, K, workspace, stream);
+    return run_plan(pl, x, packed, out, M, N, K, workspace, stream, norm);
 }
 
 // ---- w4a16_gemm for callers that cannot allocate a workspace ---------------------------------------
@@ -2409,8 +2640,8 @@ int w4a16_gemm(const void *x, const void *packed, void *y, int M, int N, int K, 
     return gemm_entry(x, packed, Out{(_Float16 *)y, nullptr, kEpiNone}, M, N, K, G, workspace, workspace_bytes, stream);
 }
 
-int w4a16_gemm_fused(const void *x, const void *packed, void *y, int M, int N, int K, int G, int epilogue,
-                     const void *residual, void *workspace, size_t workspace_bytes, void *stream)
+static int gemm_fused(const void *x, const void *packed, void *y, int M, int N, int K, int G, int epilogue,
+                      const void *residual, void *workspace, size_t workspace_bytes, void *stream, const Norm *norm)
 {
     const int sym = (epilogue & W4A16_SYMMETRIC) ? 1 : 0;
     epilogue &= ~W4A16_SYMMETRIC;
@@ -2427,23 +2658,18 @@ int w4a16_gemm_fused(const void *x, const void *packed, void *y, int M, int N, i
                   "public and internal epilogue codes agree");
     Out out = {(_Float16 *)y, (const _Float16 *)residual, epilogue};
     out.sym = sym;
-    return gemm_entry(x, packed, out, M, N, K, G, workspace, workspace_bytes, stream);
+    return gemm_entry(x, packed, out, M, N, K, G, workspace, workspace_bytes, stream, norm);
 }
 
-
-int w4a16_gemm_rope(const void *x, const void *packed, int M, int K, int G, const int32_t *pos, const float *cos_table,
-                    const float *sin_table, int n_pos, void *q, void *k_cache, void *v_cache, int P, int Hq, int Hkv, int D,
-                    void *workspace, size_t workspace_bytes, void *stream)
+int w4a16_gemm_fused(const void *x, const void *packed, void *y, int M, int N, int K, int G, int epilogue,
+                     const void *residual, void *workspace, size_t workspace_bytes, void *stream)
 {
-    return w4::gemm_rope(x, packed, M, K, G, pos, cos_table, sin_table, n_pos, q, k_cache, v_cache, P, Hq, Hkv, D, workspace,
-                         workspace_bytes, stream, 0);
+    return gemm_fused(x, packed, y, M, N, K, G, epilogue, residual, workspace, workspace_bytes, stream, nullptr);
 }
 
-}  // extern "C"
-
-int w4::gemm_rope(const void *x, const void *packed, int M, int K, int G, const int32_t *pos, const float *cos_table,
-                  const float *sin_table, int n_pos, void *q, void *k_cache, void *v_cache, int P, int Hq, int Hkv, int D,
-                  void *workspace, size_t workspace_bytes, void *stream, int symmetric)
+static int gemm_rope(const void *x, const void *packed, int M, int K, int G, const int32_t *pos, const float *cos_table,
+                     const float *sin_table, int n_pos, void *q, void *k_cache, void *v_cache, int P, int Hq, int Hkv, int D,
+                     void *workspace, size_t workspace_bytes, void *stream, int symmetric, const Norm *norm)
 {
     if (P < 0 || Hq < 1 || Hkv < 1 || D < 32 || D % 32 != 0 || n_pos < 1) return W4A16_EINVAL;
     if ((long long)(Hq + 2 * Hkv) * D > 0x7fffffff) return W4A16_EUNSUP;
@@ -2454,5 +2680,33 @@ int w4::gemm_rope(const void *x, const void *packed, int M, int K, int G, const 
     Out out = {(_Float16 *)q, nullptr, kEpiRope,
                {pos, cos_table, sin_table, (_Float16 *)q, (_Float16 *)k_cache, (_Float16 *)v_cache, n_pos, P, Hq, Hkv, D}};
     out.sym = symmetric ? 1 : 0;
-    return gemm_entry(x, packed, out, M, (Hq + 2 * Hkv) * D, K, G, workspace, workspace_bytes, stream);
+    return gemm_entry(x, packed, out, M, (Hq + 2 * Hkv) * D, K, G, workspace, workspace_bytes, stream, norm);
+}
+
+int w4a16_gemm_rope(const void *x, const void *packed, int M, int K, int G, const int32_t *pos, const float *cos_table,
+                    const float *sin_table, int n_pos, void *q, void *k_cache, void *v_cache, int P, int Hq, int Hkv, int D,
+                    void *workspace, size_t workspace_bytes, void *stream)
+{
+    return gemm_rope(x, packed, M, K, G, pos, cos_table, sin_table, n_pos, q, k_cache, v_cache, P, Hq, Hkv, D, workspace,
+                     workspace_bytes, stream, 0, nullptr);
+}
+
+}  // extern "C"
+
+int w4::gemm_fused_normed(const void *h, const void *gamma, float eps, void *norm, const void *packed, void *y, int M, int N, int K,
+                          int epilogue, void *workspace, size_t workspace_bytes, void *stream)
+{
+    const Norm n = {gamma, eps, norm};
+    const int rc = check_rms_norm(h, gamma, norm, M, K, eps);
+    return rc != W4A16_OK ? rc : gemm_fused(h, packed, y, M, N, K, kGroup, epilogue, nullptr, workspace, workspace_bytes, stream, &n);
+}
+
+int w4::gemm_rope_normed(const void *h, const void *gamma, float eps, void *norm, const void *packed, int M, int K, const int32_t *pos,
+                         const float *cos_table, const float *sin_table, int n_pos, void *q, void *k_cache, void *v_cache, int P, int Hq,
+                         int Hkv, int D, void *workspace, size_t workspace_bytes, void *stream, int symmetric)
+{
+    const Norm n = {gamma, eps, norm};
+    const int rc = check_rms_norm(h, gamma, norm, M, K, eps);
+    return rc != W4A16_OK ? rc : gemm_rope(h, packed, M, K, kGroup, pos, cos_table, sin_table, n_pos, q, k_cache, v_cache, P, Hq, Hkv, D,
+                                           workspace, workspace_bytes, stream, symmetric, &n);
 }

@@ -63,10 +63,16 @@ struct Params {
 };
 Params &params();
 
-// w4a16_gemm_rope with the caller's word that the weight is symmetric (the exported entry point passes 0)
-int gemm_rope(const void *x, const void *packed, int M, int K, int G, const int32_t *pos, const float *cos_table,
-              const float *sin_table, int n_pos, void *q, void *k_cache, void *v_cache, int P, int Hq, int Hkv, int D,
-              void *workspace, size_t workspace_bytes, void *stream, int symmetric);
+// argument checks of rms_norm
+int check_rms_norm(const void *x, const void *gamma, const void *y, int M, int K, float eps);
+
+// rms_norm of h into `norm`, then w4a16_gemm_fused (no residual), or w4a16_gemm_rope with the caller's word that the weight is symmetric;
+// where the linear can work the norm out itself (few rows) `norm` is not written
+int gemm_fused_normed(const void *h, const void *gamma, float eps, void *norm, const void *packed, void *y, int M, int N, int K,
+                      int epilogue, void *workspace, size_t workspace_bytes, void *stream);
+int gemm_rope_normed(const void *h, const void *gamma, float eps, void *norm, const void *packed, int M, int K, const int32_t *pos,
+                     const float *cos_table, const float *sin_table, int n_pos, void *q, void *k_cache, void *v_cache, int P, int Hq,
+                     int Hkv, int D, void *workspace, size_t workspace_bytes, void *stream, int symmetric);
 
 // number of 256-byte-aligned bytes reserved for tickets at the start of a workspace
 constexpr size_t kTicketBytes = 16384;   // 4096 tickets

@@ -156,6 +156,15 @@ __global__ __launch_bounds__(kRopeThreads) void rope_append_kernel(
     }
 }
 
+int check_rms_norm(const void *x, const void *gamma, const void *y, int M, int K, float eps)
+{
+    if (M < 1 || K < 8 || K % 8 != 0 || !(eps >= 0.f)) return W4A16_EINVAL;
+    if (M > 65535) return W4A16_EUNSUP;
+    if (K > kNormThreads * kNormChunks * 8) return W4A16_EUNSUP;
+    if (!x || !gamma || !y) return W4A16_ENULL;
+    return misaligned(x) || misaligned(gamma) || misaligned(y) ? W4A16_EALIGN : W4A16_OK;
+}
+
 }  // namespace w4
 
 using namespace w4;
@@ -164,11 +173,8 @@ extern "C" {
 
 int rms_norm(const void *x, const void *gamma, void *y, int M, int K, float eps, void *stream)
 {
-    if (M < 1 || K < 8 || K % 8 != 0 || !(eps >= 0.f)) return W4A16_EINVAL;
-    if (M > 65535) return W4A16_EUNSUP;
-    if (K > kNormThreads * kNormChunks * 8) return W4A16_EUNSUP;
-    if (!x || !gamma || !y) return W4A16_ENULL;
-    if (misaligned(x) || misaligned(gamma) || misaligned(y)) return W4A16_EALIGN;
+    const int rc = check_rms_norm(x, gamma, y, M, K, eps);
+    if (rc != W4A16_OK) return rc;
     hipLaunchKernelGGL(rms_norm_kernel, dim3((unsigned)M), dim3(kNormThreads), 0, (hipStream_t)stream,
                        (const _Float16 *)x, (const _Float16 *)gamma, (_Float16 *)y, K, eps);
     return launch_status();
@@ -210,14 +216,13 @@ extern "C" int w4a16_decoder_layer(const w4a16_layer_weights *w, void *h, int M,
     const int sym = w->symmetric ? W4A16_SYMMETRIC : 0;
     int rc;
     // attention block: h += Wo . attn(rope(Wqkv . norm(h)))
-    if ((rc = rms_norm(h, w->norm1_gamma, s->norm, M, H, w->eps, stream)) != W4A16_OK) return rc;
-    if (w->qkv_heads_packed) {   // projection, rotary embedding and K/V append in one kernel
-        if ((rc = w4::gemm_rope(s->norm, w->qkv_packed, M, H, kGroup, pos, cos_table, sin_table, n_pos, s->q, k_cache, v_cache,
-                                P, Hq, Hkv, D, s->gemm_workspace, s->gemm_workspace_bytes, stream, w->symmetric)) != W4A16_OK)
+    if (w->qkv_heads_packed) {   // projection, rotary embedding and K/V append in one kernel (at few rows the norm too)
+        if ((rc = gemm_rope_normed(h, w->norm1_gamma, w->eps, s->norm, w->qkv_packed, M, H, pos, cos_table, sin_table, n_pos, s->q, k_cache,
+                                   v_cache, P, Hq, Hkv, D, s->gemm_workspace, s->gemm_workspace_bytes, stream, w->symmetric)) != W4A16_OK)
             return rc;
     } else {
-        if ((rc = w4a16_gemm_fused(s->norm, w->qkv_packed, s->qkv, M, Nqkv, H, kGroup, W4A16_EPI_NONE | sym, nullptr,
-                                   s->gemm_workspace, s->gemm_workspace_bytes, stream)) != W4A16_OK)
+        if ((rc = gemm_fused_normed(h, w->norm1_gamma, w->eps, s->norm, w->qkv_packed, s->qkv, M, Nqkv, H, W4A16_EPI_NONE | sym,
+                                    s->gemm_workspace, s->gemm_workspace_bytes, stream)) != W4A16_OK)
             return rc;
         if ((rc = rope_append(s->qkv, pos, cos_table, sin_table, n_pos, s->q, k_cache, v_cache, M, P, Hq, Hkv, D, stream)) !=
             W4A16_OK)
@@ -230,9 +235,8 @@ extern "C" int w4a16_decoder_layer(const w4a16_layer_weights *w, void *h, int M,
                                s->gemm_workspace_bytes, stream)) != W4A16_OK)
         return rc;
     // feed-forward block: h += Wdown . (silu(Wgate . n) * (Wup . n)),  n = norm(h)
-    if ((rc = rms_norm(h, w->norm2_gamma, s->norm, M, H, w->eps, stream)) != W4A16_OK) return rc;
-    if ((rc = w4a16_gemm_fused(s->norm, w->gate_up_packed, s->act, M, 2 * F, H, kGroup, W4A16_EPI_SILU_MUL | sym, nullptr,
-                               s->gemm_workspace, s->gemm_workspace_bytes, stream)) != W4A16_OK)
+    if ((rc = gemm_fused_normed(h, w->norm2_gamma, w->eps, s->norm, w->gate_up_packed, s->act, M, 2 * F, H, W4A16_EPI_SILU_MUL | sym,
+                                s->gemm_workspace, s->gemm_workspace_bytes, stream)) != W4A16_OK)
         return rc;
     return w4a16_gemm_fused(s->act, w->down_packed, h, M, H, F, kGroup, W4A16_EPI_RESIDUAL | sym, h, s->gemm_workspace,
                             s->gemm_workspace_bytes, stream);

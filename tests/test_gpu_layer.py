@@ -553,3 +553,58 @@ def test_fused_epilogues_full_size_sampled_columns(M):
     qw, sc, qz = column_subproblem(inp, cols)
     want, _ = R.w4a16_gemm_residual(inp.x, qw, sc, qz, res[:, cols])
     check_gemm(got[:, cols], want, f"down + residual, M={M}")
+
+
+# ---- linears that work the norm of few rows out themselves -------------------------------------------
+# (hidden, tiles per wavefront, wavefronts, K splits) of the forms compiled with the norm in front, one and several groups in flight,
+# ragged walks among them (9, 21 and 33 groups), the longest row, and a row beyond it, which takes the two kernels
+
+NORMED = [(1152, 2, 8, 1), (4224, 2, 8, 1), (8192, 2, 8, 1), (1024, 4, 8, 1), (2688, 4, 8, 1), (1152, 8, 8, 1), (8192, 8, 8, 3), (640, 8, 4, 1),
+          (4096, 8, 4, 2), (8320, 8, 8, 1)]
+
+
+@pytest.mark.parametrize("H,tw,nw,split", NORMED)
+@pytest.mark.parametrize("symmetric", [False, True])
+def test_layer_of_few_rows_is_its_steps_bit_for_bit(H, tw, nw, split, symmetric, big_ws):
+    P, Hq, Hkv, D, F = 40, 2, 1, 128, 384
+    N = (Hq + 2 * Hkv) * D
+    lin = [I.make_linear(9400 + i, 1, K, N_) for i, (K, N_) in enumerate(((H, N), (Hq * D, H), (H, 2 * F), (F, H)))]
+    if symmetric:
+        for inp in lin:
+            inp.qzeros[...] = np.uint32(0x88888888).astype(inp.qzeros.dtype)
+    heads = not symmetric   # w4a16_gemm_rope itself does not take the symmetric form
+    packed = [B.pack_from_numpy(lin[0], head_dim=D if heads else 0), B.pack_from_numpy(lin[1]), B.pack_from_numpy(lin[2], gate_up=True),
+              B.pack_from_numpy(lin[3])]
+    code = B.SYMMETRIC if symmetric else 0
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+    f16 = lambda *shape: torch.empty(shape, dtype=torch.float16, device=DEV)
+    g1, g2 = dev(I.make_gamma(9411, H)), dev(I.make_gamma(9412, H))
+    cos, sin = (dev(t) for t in I.make_rope_tables(P + 16, D))
+    for M in (1, 2, 3, 4, 5):
+        print(f"   H={H} tw={tw} nw={nw} split={split} M={M}", flush=True)
+        rng = np.random.default_rng(9420 + M)
+        h0 = dev(I.make_hidden(9430 + M, M, H))
+        pos, mask = dev(np.arange(P, P + M, dtype=np.int32)), dev(np.tril(np.ones((M, M), dtype=np.uint8)))
+        kc, vc = (dev(rng.standard_normal((P + M, Hkv, D), dtype=np.float32).astype(np.float16)) for _ in range(2))
+        bufs = [f16(M, H), f16(M, N), f16(M, Hq, D), f16(M, Hq, D), f16(M, F)]
+        aws = B.new_workspace(B.tree_verify_attn_workspace_bytes(M, P, Hq, Hkv, D))
+        set_knobs(tw=tw, nw=nw, depth=1, split=split)
+        h, k, v = h0.clone(), kc.clone(), vc.clone()
+        weights = B.layer_weights(*packed, g1, g2, H, Hq, Hkv, D, F, 1e-5, qkv_heads_packed=heads, symmetric=symmetric)
+        B.w4a16_decoder_layer(weights, h, M, P, pos, cos, sin, P + 16, mask, k, v, B.layer_scratch(*bufs, big_ws, aws))
+        norm, qkv, q, att, act = bufs
+        h2, k2, v2 = h0.clone(), kc.clone(), vc.clone()
+        B.rms_norm(h2, g1, norm, M, H, 1e-5)
+        if heads:
+            B.w4a16_gemm_rope(norm, packed[0], M, H, 128, pos, cos, sin, P + 16, q, k2, v2, P, Hq, Hkv, D, big_ws)
+        else:
+            B.w4a16_gemm_fused(norm, packed[0], qkv, M, N, H, 128, code, None, big_ws)
+            B.rope_append(qkv, pos, cos, sin, P + 16, q, k2, v2, M, P, Hq, Hkv, D)
+        B.tree_verify_attn(q, k2, v2, mask, att, M, P, Hq, Hkv, D, 1.0 / np.sqrt(D), aws)
+        B.w4a16_gemm_fused(att.view(M, Hq * D), packed[1], h2, M, H, Hq * D, 128, B.EPI_RESIDUAL | code, h2, big_ws)
+        B.rms_norm(h2, g2, norm, M, H, 1e-5)
+        B.w4a16_gemm_fused(norm, packed[2], act, M, 2 * F, H, 128, B.EPI_SILU_MUL | code, None, big_ws)
+        B.w4a16_gemm_fused(act, packed[3], h2, M, H, F, 128, B.EPI_RESIDUAL | code, h2, big_ws)
+        torch.cuda.synchronize()
+        for a, b, what in ((h, h2, "h"), (k, k2, "k"), (v, v2, "v")):
+            assert torch.equal(a.view(torch.int16), b.view(torch.int16)), f"{what}, M={M}"
