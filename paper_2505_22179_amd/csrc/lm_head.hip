@@ -49,10 +49,11 @@ struct LmStat {
 constexpr float kNegInf = -__builtin_inff();
 __device__ __forceinline__ float sum_base(float max) { return max == kNegInf ? 0.f : max; }
 
-template <int TWL, int MTL, int NW>
-__device__ __forceinline__ void store_stats(const float4v (&acc)[TWL][MTL], LmStat (*part)[MTL * 16], LmStat *__restrict__ stats, int tile0, int V, int M)
+// a wavefront's part, and the workgroup's from those of NW wavefronts
+template <int TWL, int MTL>
+__device__ __forceinline__ void wave_stats(const float4v (&acc)[TWL][MTL], LmStat (&part)[MTL * 16], int tile0, int V)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63;
     const int r = lane >> 4, c = lane & 15;
 #pragma unroll
     for (int mt = 0; mt < MTL; ++mt) {
@@ -73,11 +74,15 @@ __device__ __forceinline__ void store_stats(const float4v (&acc)[TWL][MTL], LmSt
             for (int i = 0; i < 4; ++i) se += __expf(v[t][i] - base);
         se += __shfl_xor(se, 16, 64);
         se += __shfl_xor(se, 32, 64);
-        if (r == 0) part[wave][mt * 16 + c] = {mx, se};
+        if (r == 0) part[mt * 16 + c] = {mx, se};
     }
+}
+template <int ROWS, int NW>
+__device__ __forceinline__ void store_stats(const LmStat (*part)[ROWS], LmStat *__restrict__ stats, int M)
+{
     __syncthreads();
     const int row = threadIdx.x;
-    if (row < M) {   // M <= 16 MTL <= the workgroup's threads
+    if (row < M) {   // M <= ROWS <= the workgroup's threads
         float mx = kNegInf, se = 0.f;
 #pragma unroll
         for (int w = 0; w < NW; ++w) mx = fmaxf(mx, part[w][row].max);
@@ -188,7 +193,131 @@ __global__ __launch_bounds__(256) void lm_head_logits_kernel(const _Float16 *__r
                 }
             }
         }
-    if (stats) store_stats<TWL, MTL, 4>(acc, part, stats, tile0, V, M);   // uniform
+    if (stats) {   // uniform
+        wave_stats<TWL, MTL>(acc, part[wave], tile0, V);
+        store_stats<MTL * 16, 4>(part, stats, M);
+    }
+}
+
+// Logits where the vocabulary is too small to fill the chip with wavefronts of whole walks.  A workgroup takes four tiles (64 tokens, the least
+// granule) with kLmKeptSets wavefronts on each, which deal the macro steps out among them and meet in LDS, in order.  The hidden-state rows are copied
+// to LDS before the walk, whole cache lines straight there, in as few phases as LDS holds their x tiles in, so the walk asks for weights only: in the
+// kernel above x fragments are as many loads as weights, sixteen rows x 64 bytes each, and a wavefront's walk is a chain of K / 512 round
+// trips; in the kernel below a step has a barrier.  Block (step, jp, hb) of 1 KB holds rows 8 hb .. + 7 times the 128 bytes of blocks 2 jp and 2 jp + 1 of the
+// step, chunks swizzled as there.  HB = 1: at most eight rows, for which the lanes of rows 8 .. 15 read the first eight again (never stored).
+// What bounds it: what one compute unit takes in (some 35 - 50 B/ns here) while V / 64 of them work, then launch, the x copies and the finishing
+// kernel.  Whole call, top 8, us, before -> now: 16 rows, V = 4000, K = 2048 22.8 -> 13.6, 5120 48.0 -> 22.2, 8192 69.0 -> 29.9; V = 16000, K = 3200 38.5 -> 24.8;
+// 6 rows, V = 10000, K = 1408 16.9 -> 12.9; 4 rows, V = 4000, K = 8192 31.9 -> 27.8; 40 rows, V = 5000, K = 8192 49.5 -> 39.7, K = 2048 18.8 -> 17.1.
+constexpr int kLmKeptSets = 4, kLmKeptWaves = 4 * kLmKeptSets;
+constexpr int kLmKeptLds = 144 * 1024;   // x tiles that fit beside the statistics
+template <int HB, int DEPTH>
+__global__ __launch_bounds__(64 * kLmKeptWaves) void lm_head_logits_kept_kernel(const _Float16 *__restrict__ x, const u32x4 *__restrict__ packed,
+                                                                                float *__restrict__ logits, LmStat *__restrict__ stats, int M, int V,
+                                                                                int K, int tiles, int phases, int phase_q, int phase_rem)
+{
+    constexpr int MTL = (HB + 1) / 2;
+    extern __shared__ u32x4 xt[];   // [step of the phase][jp][hb][64]; afterwards the sums
+    __shared__ LmStat part[4][MTL * 16];
+    fetch_arguments_together(x, packed, logits, stats, M, V, K, tiles, phases, phase_q, phase_rem);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r = lane >> 4, c = lane & 15;
+    const int t = wave & 3, set = wave >> 2;
+    const int tile0 = blockIdx.x * 4 + t;   // a wavefront past the last tile repeats it; its logits are not stored
+    const Stretch xs = stretch(x, (uint32_t)M * (uint32_t)K * 2);
+    const Stretch ws = stretch(packed + (size_t)min(tile0, tiles - 1) * (K / 32) * 64, (uint32_t)K * 32);
+    const auto xoff = [&](int hb) {   // byte offset of what this lane copies of block hb
+        const int row8 = lane >> 3, row = min(hb * 8 + row8, M - 1);
+        return ((uint32_t)row * (uint32_t)K + (uint32_t)(((lane & 7) ^ (4 * (hb & 1) + (row8 >> 1))) * 8)) * 2;
+    };
+    const uint32_t lane_off = (uint32_t)lane * 16;
+    uint32_t xfrag[2];
+    {
+        const int h = HB == 1 ? 0 : c >> 3, row8 = c & 7, sw = 4 * h + (row8 >> 1);
+        xfrag[0] = (uint32_t)(h * 64 + row8 * 8 + (r ^ sw));
+        xfrag[1] = (uint32_t)(h * 64 + row8 * 8 + ((4 + r) ^ sw));
+    }
+    float4v acc[1][MTL];
+#pragma unroll
+    for (int mt = 0; mt < MTL; ++mt) acc[0][mt] = (float4v){0.f, 0.f, 0.f, 0.f};
+    u32x4 w[DEPTH][4];
+    for (int ph = 0; ph < phases; ++ph) {   // as many steps at a time as LDS holds x tiles of; uniform over the grid
+        const int begin = ph * phase_q + min(ph, phase_rem), steps = phase_q + (ph < phase_rem ? 1 : 0);
+        const int mine = (steps - set + kLmKeptSets - 1) / kLmKeptSets;   // >= DEPTH (checked by the host)
+        if (ph > 0) __syncthreads();   // everybody has left the last phase's x tiles
+        const uint32_t own = xoff(wave % HB);
+        for (int b = wave; b < steps * 2 * HB; b += kLmKeptWaves)   // b = (step * 2 + jp) * HB + hb
+            quad_to_lds(xs, xt + b * 64, kLmKeptWaves % HB == 0 ? own : xoff(b % HB), (uint32_t)(begin * 2 + b / HB) * 128);
+        __builtin_amdgcn_sched_barrier(0);   // x before the weights: the wait below counts on it
+        // tiles lie K * 32 bytes apart: each workgroup starts its walk at another step (see above)
+        const int rot = (int)(blockIdx.x % (unsigned)mine);
+        const auto step_of = [&](int i) {   // uniform, i < 2 * mine - rot
+            const int k = i + rot;
+            return (uint32_t)(set + kLmKeptSets * (k >= mine ? k - mine : k));
+        };
+        const auto load = [&](int i, int slot) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) w[slot][j] = stream_quad(ws, lane_off + (uint32_t)j * 1024, ((uint32_t)begin + step_of(i)) * 4096);
+        };
+        const auto compute = [&](int i, int slot) {
+            const u32x4 *const tile = xt + step_of(i) * (2 * HB * 64);
+            u32x4 xf[MTL][4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int mt = 0; mt < MTL; ++mt) xf[mt][j] = tile[((j >> 1) * HB + 2 * mt) * 64 + xfrag[j & 1]];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int mt = 0; mt < MTL; ++mt)
+                    acc[0][mt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8v, w[slot][j]), __builtin_bit_cast(half8v, xf[mt][j]),
+                                                                        acc[0][mt], 0, 0, 0);
+        };
+#pragma unroll
+        for (int u = 0; u < DEPTH; ++u) load(u, u);
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(4 * DEPTH) : "memory");   // everybody's x has landed
+        int i = 0;
+        for (; i + 2 * DEPTH <= mine; i += DEPTH) {   // uniform over the wavefront; no barrier inside
+#pragma unroll
+            for (int u = 0; u < DEPTH; ++u) {
+                compute(i + u, u);
+                load(i + u + DEPTH, u);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 2 * DEPTH - 1; ++u)
+            if (i + u < mine) {   // uniform
+                compute(i + u, u % DEPTH);
+                if (i + u + DEPTH < mine) load(i + u + DEPTH, u % DEPTH);
+            }
+    }
+    // the sets of a tile meet, in order
+    __syncthreads();   // everybody has left the x tiles
+    float4v *const sums = reinterpret_cast<float4v *>(xt);
+    if (set > 0)
+#pragma unroll
+        for (int mt = 0; mt < MTL; ++mt) sums[(wave * MTL + mt) * 64 + lane] = acc[0][mt];
+    __syncthreads();
+    if (set == 0) {
+#pragma unroll
+        for (int mt = 0; mt < MTL; ++mt) {
+#pragma unroll
+            for (int q = 1; q < kLmKeptSets; ++q) acc[0][mt] += sums[((q * 4 + t) * MTL + mt) * 64 + lane];
+            const int v0 = tile0 * 16 + 4 * r, row = mt * 16 + c;
+            if (row < M && tile0 < tiles) {
+                float *dst = logits + (size_t)row * V + v0;
+                if ((V & 3) == 0 && v0 + 3 < V) {
+                    *reinterpret_cast<float4v *>(dst) = acc[0][mt];
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (v0 + e < V) dst[e] = acc[0][mt][e];
+                }
+            }
+        }
+        if (stats) wave_stats<1, MTL>(acc, part[t], tile0, V);   // uniform
+    }
+    if (stats) store_stats<MTL * 16, 4>(part, stats, M);   // uniform
 }
 
 // Logits of more than 16 rows.  There the x fragments, not the weights, filled the load path of the kernel above: every
@@ -342,7 +471,11 @@ __global__ __launch_bounds__(64 * NW, 2) void lm_head_logits_shared_kernel(const
         }
     // b_now is the buffer after the last tile's: nothing was copied to it, and its readers have passed the last step's barrier
     static_assert(NW * MTL * 16 * sizeof(LmStat) <= sizeof(xa[0]), "the statistics of the wavefronts fit a buffer");
-    if (stats) store_stats<TWL, MTL, NW>(acc, reinterpret_cast<LmStat(*)[MTL * 16]>(xa[b_now]), stats, tile0, V, M);   // uniform
+    if (stats) {   // uniform
+        LmStat(*const part)[MTL * 16] = reinterpret_cast<LmStat(*)[MTL * 16]>(xa[b_now]);
+        wave_stats<TWL, MTL>(acc, part[wave], tile0, V);
+        store_stats<MTL * 16, NW>(part, stats, M);
+    }
 }
 
 // (value, token) pairs ordered by value, equal values by ascending token
@@ -650,11 +783,30 @@ __global__ __launch_bounds__(kLmThreads) void lm_head_merge_kernel(const float *
 // 24).  It also does where 16 tiles fill the chip and K is a power of two, so that all tiles of a workgroup ask the same memory
 // channels at any moment (V = 64000: K = 4096 91 against 101 us at 24 rows, K = 2048 57 against 68 at 40 and 68 against 70 at 60;
 // but K = 3840 90 against 84 at 24 rows, and K = 4096 103 against 100 at 40).  (All: whole call, top 1, two weight copies in turn.)
-struct LmPlan { bool shared; int nw, twl; };
+struct LmPlan { bool shared; int nw, twl; bool kept = false; };   // kept: the kernel that keeps x in LDS; nw * twl tiles to a workgroup there too
+// Small vocabularies go to the kernel whose workgroups keep x in LDS, four tiles each: up to one workgroup per compute unit with 5 to 16 rows
+// (beyond, a second pass over the chip costs more than is saved: 24000 tokens, K = 4096, 16 rows 49.0 against 51.1 us, 32000 51.7 against 60.5); up to
+// 160 of them with more rows, which the kernel with shared x tiles serves better by then (16000 tokens, K = 2048, 60 rows 24.3 against 25.9; 10000
+// tokens 21.4 against 20.7); up to 64 with four rows or fewer, whose x is little to fetch either way (16000 tokens, K = 4096, one row 27.4 against 33.6; 4000
+// tokens, K = 5120 21.6 against 20.5).  Its walk goes in phases, the fewest whose x tiles fit LDS, each with two or four steps for every wavefront at least;
+// with few rows two were no gain (K = 1024, 10000 tokens, two rows 11.5 against 11.7).
+struct LmKept { int hb, depth, phases, q, rem; size_t lds; };
+static LmKept lm_kept(int M, int K)
+{
+    const int hb = M <= 8 ? 1 : 2 * ((M + 15) / 16), steps = K / kLmStepK, tile = hb * 2048, most = kLmKeptLds / tile;
+    const int phases = (steps + most - 1) / most, q = steps / phases, rem = steps % phases;
+    const int depth = q >= 4 * kLmKeptSets ? 4 : q >= 2 * kLmKeptSets ? 2 : 0;
+    const size_t x_bytes = (size_t)(q + (rem > 0)) * tile, sum_bytes = (size_t)kLmKeptWaves * ((hb + 1) / 2) * 1024;
+    return {hb, depth, phases, q, rem, x_bytes > sum_bytes ? x_bytes : sum_bytes};
+}
 static LmPlan lm_plan(int M, int tiles, int K)
 {
     const int knob = params().lm_tiles;
     if (knob > 0 && knob != 1 && knob != 2 && !(knob == 4 && M > 16)) return {false, 0, 0};   // not compiled
+    if (knob == 0 && K <= kLmSharedMaxK && (tiles + 3) / 4 <= (M > 16 ? 160 : M > 4 ? 256 : 64)) {
+        const LmKept walk = lm_kept(M, K);
+        if (walk.depth > 0 && (M > 4 || walk.depth == 4)) return {false, 4, 1, true};
+    }
     if (M <= 16) return {false, 4, knob > 0 ? knob : (M <= 4 ? 1 : 2)};
     if (K > kLmSharedMaxK) return {false, 4, 4};
     if (knob > 0) return {true, 8, knob};
@@ -729,8 +881,8 @@ int lm_head_plan_describe(int M, int V, int K, int *out)
     if (rc != W4A16_OK) return rc;
     const LmPlan plan = lm_plan(M, (V + 15) / 16, K);
     if (plan.nw == 0) return W4A16_EUNSUP;
-    out[0] = plan.shared;
-    out[1] = plan.nw;
+    out[0] = plan.shared || plan.kept;
+    out[1] = plan.kept ? kLmKeptWaves : plan.nw;
     out[2] = plan.twl;
     return W4A16_OK;
 }
@@ -763,6 +915,24 @@ int lm_head_topk(const void *x, const void *packed, int M, int V, int K, int top
         W4_LM_SHARED(3, 4, 1, 4); W4_LM_SHARED(3, 8, 1, 4); W4_LM_SHARED(3, 8, 2, 2); W4_LM_SHARED(3, 8, 4, 2);
         W4_LM_SHARED(4, 4, 1, 4); W4_LM_SHARED(4, 8, 1, 4); W4_LM_SHARED(4, 8, 2, 2); W4_LM_SHARED(4, 8, 4, 2);
 #undef W4_LM_SHARED
+    } else if (plan.kept) {
+        const LmKept walk = lm_kept(M, K);
+        static bool lds_ok[9][2] = {};
+#define W4_LM_KEPT(HB_, D_)                                                                                                                \
+    if (walk.hb == HB_ && walk.depth == D_) {                                                                                              \
+        const auto kernel = &lm_head_logits_kept_kernel<HB_, D_>;                                                                          \
+        bool &ok = lds_ok[HB_][D_ == 4];                                                                                                   \
+        if (!ok && walk.lds > 48 * 1024) {                                                                                                 \
+            if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kLmKeptLds) != hipSuccess) \
+                return W4A16_EHIP;                                                                                                         \
+            ok = true;                                                                                                                     \
+        }                                                                                                                                  \
+        hipLaunchKernelGGL(kernel, grid, dim3(64 * kLmKeptWaves), walk.lds, s, (const _Float16 *)x, (const u32x4 *)packed, logits, stats,  \
+                           M, V, K, tiles, walk.phases, walk.q, walk.rem);                                                                 \
+    }
+        W4_LM_KEPT(1, 2) W4_LM_KEPT(2, 2) W4_LM_KEPT(4, 2) W4_LM_KEPT(6, 2) W4_LM_KEPT(8, 2)
+        W4_LM_KEPT(1, 4) W4_LM_KEPT(2, 4) W4_LM_KEPT(4, 4) W4_LM_KEPT(6, 4) W4_LM_KEPT(8, 4)
+#undef W4_LM_KEPT
     } else {
         const int depth = mtl > 1 ? 2 : kLmDepth;
         const bool even = (K / kLmStepK) % depth == 0;

@@ -111,6 +111,27 @@ def test_lm_head_private_rows(M, K, V):
     check(x, W, 3, f"M={M} K={K} V={V}")
 
 
+@pytest.mark.parametrize("M,K,V", [(1, 2048, 16), (4, 2176, 4096), (2, 8192, 1001),          # up to four rows: walks of sixteen steps and more
+                                   (5, 1024, 70), (8, 1152, 16384), (7, 9344, 333),          # one block of eight rows; K = 9344: two phases
+                                   (9, 1024, 2049), (16, 4608, 5003), (13, 4736, 130),       # two blocks; 36 steps fit LDS, 37 do not
+                                   (17, 1024, 10240), (32, 2304, 1002), (24, 8192, 515),     # two row tiles, phases of sixteen steps and more
+                                   (33, 1536, 64), (48, 2176, 3001), (64, 1152, 9999), (64, 8192, 1000)])
+def test_lm_head_kept_rows(M, K, V):
+    """small vocabularies: x kept in LDS, the walk dealt to four sets of wavefronts, in one phase or several, with steps that the sets do not
+    share evenly, workgroups with fewer than four tiles and vocabularies that are no multiple of 4"""
+    assert B.lm_head_plan_describe(M, V, K) == (1, 16, 1)
+    x, W = I.make_lm_head(9970 + M + K + V, M, K, V)
+    print(f"lm_head kept rows M={M} K={K} V={V}", flush=True)
+    check(x, W, min(5, V), f"M={M} K={K} V={V}")
+
+
+def test_lm_head_kept_rows_end_where_the_rule_says():
+    for M, K, V, kept in ((4, 2048, 4096, True), (4, 2048, 4097, False), (4, 1920, 4096, False), (5, 1024, 16384, True), (16, 1024, 16385, False),
+                          (16, 896, 5000, False), (17, 1024, 10240, True), (17, 1024, 10241, False), (64, 2048, 10240, True),
+                          (60, 3584, 5000, False)):   # 28 steps are four phases of seven: less than two for each set
+        assert (B.lm_head_plan_describe(M, V, K) == (1, 16, 1)) == kept, (M, K, V)
+
+
 def test_lm_head_full_vocabulary():
     """the benchmark's configuration: Llama-3 vocabulary, hidden size 4096, ten beams, top 10"""
     M, K, V, top_k = 10, 4096, 128256, 10
