@@ -1582,25 +1582,35 @@ __global__ __launch_bounds__(kXWaves * 64) void gemm_x_kernel(
         }
     };
     // At the head of a group its x tile is older than the loads of its codes, the newest ones: a count says when it has landed.
-    // (As compiled, the forms with two or four tiles and zero-points wait for all loads ahead of the loop: the last group is peeled off, its codes
-    // live in other registers than the loop's, and the first group's are copied.  There the second group's x copies start late.)
     auto next_x = [&]() {
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kGroupLoads) : "memory");
         read_x();
     };
-    if (n_w > 0) {   // uniform
+    const auto start = [&]() {
         copy_x(0);
         __builtin_amdgcn_sched_barrier(0);   // x before the codes, here and below
         load_quant<TW, SYM>(qw, recs, 0, scale_off, zero_off);
 #pragma unroll
         for (int t = 0; t < TW; ++t) load_codes(0, t);
         __builtin_amdgcn_sched_barrier(0);
-        for (int i = 0; i + 1 < n_w; ++i) {
+    };
+    // Entered with a group to go, the loop takes the first codes in the registers they were requested in; entered with perhaps none, the compiler gave the
+    // last group's codes other registers, copied the first ones and waited for every load to do so, ahead of the loop, so that the second group's x copies
+    // started late.  us, before -> now: 5120 -> 13000 at 37 rows 14.97 -> 14.67, 4096 -> 28672 at 14 14.65 -> 13.79, 14336 -> 4096 at 6 9.96 -> 9.55, 1536 -> 9344
+    // at 51 7.71 -> 7.24, 8B gate_up at one row 12.50 -> 12.06; walks of one or two groups with two tiles 0.99 ... 1.05 times as fast.
+    if (n_w > 1) {   // uniform
+        start();
+        int i = 1;
+        do {
             next_x();
-            copy_x(i + 1);
+            copy_x(i);
             __builtin_amdgcn_sched_barrier(0);
-            compute(i + 1, true);
-        }
+            compute(i, true);
+        } while (++i < n_w);
+        next_x();
+        compute(0, false);
+    } else if (n_w == 1) {
+        start();
         next_x();
         compute(0, false);
     }
