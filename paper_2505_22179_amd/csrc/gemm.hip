@@ -2281,16 +2281,14 @@ static size_t plan_need(const Plan &pl, int M, int N, int K)
     return pl.S != 1 ? partial_bytes((M + 15) / 16, pad_cols(N) / kBlockCols, pl, K / kGroup) : 0;
 }
 
-// Which K-split kernel runs with eight wavefronts: the one whose wavefronts copy x tiles into LDS of their own, or the one that fetches fragments
-// from L2.  With one row tile a fragment load costs the load path four times what a copy of whole lines does, unless the rows are few
-// (lanes of rows that do not exist ask for the last one's lines): up to four rows the two differ by 3 % either way (3072 -> 4000 at one row
-// 4.3 us against 4.5 with copies, 70B down 21.5 against 21.7), but with eight tiles per wavefront and no split, or walks of eight groups, the copies are never
-// behind (at one row 4096 -> 28672 12.0 -> 11.4).
-// From five rows on they are ahead, or level (70B q/k/v within 2 % either way): 16 rows: 3072 -> 4000 6.1 -> 4.8, 5120 -> 13000 10.9 -> 9.7, 4096 -> 28672 13.5 -> 12.3, 70B down 23.5 -> 22.7.
-static bool own_x_tiles(int M, int K, int S, int tw, int nw, int depth)
+// Which K-split kernel runs with eight wavefronts and one group in flight: the one whose wavefronts copy x tiles into LDS of their own, wherever its 32-bit offsets
+// reach, or the one that fetches fragments from L2.  With one row tile a fragment load costs the load path four times what a copy of whole lines does;
+// with few rows, whose fragments are mostly the same lines, the fetching kernel was level until the walk above stopped waiting for all its first
+// loads.  Now, us, fetched -> copied: one row 14336 -> 4096 10.26 -> 9.51, 6144 -> 6144 with gate 8.34 -> 7.46, 8192 -> 10240 11.83 -> 11.46; four rows 2560 -> 4160
+// 4.87 -> 4.33; 33 calls of one to four rows 1.05 times as fast in the mean, none slower.
+static bool own_x_tiles(int K, int nw, int depth)
 {
-    if (nw != kXWaves || depth != 1) return false;
-    return K <= kStagedMaxK && (M > 4 || (tw == 8 && S == 1) || K / kGroup >= 8 * kXWaves * S);
+    return nw == kXWaves && depth == 1 && K <= kStagedMaxK;
 }
 
 // symmetric-weight instantiations exist for the K-split and the high-occupancy column-split kernels; the other
@@ -2300,7 +2298,7 @@ static int launch_sym(const void *x, const void *packed, const Out &y, int M, in
                       void *workspace, hipStream_t stream)
 {
     static bool lds_ok[2] = {false, false};   // LDS above 64 KB needs an opt-in, once per kernel
-    const bool own = own_x_tiles(M, K, S, TW, NW, DEPTH);
+    const bool own = own_x_tiles(K, NW, DEPTH);
     auto *const kernel = [&] {
         if constexpr (NW != kXWaves || DEPTH != 1) return &gemm_kernel<MT, TW, NW, DEPTH, SYM>;
         else if constexpr (!fetched_x_variant(MT, TW)) return &gemm_x_kernel<MT, TW, SYM>;
