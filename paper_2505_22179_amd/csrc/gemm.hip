@@ -1626,7 +1626,8 @@ __global__ __launch_bounds__(kXWaves * 64) void gemm_x_kernel(
 // and the walk reads its first MFMA operands there.  DEPTH groups of codes are in flight per wavefront, and every wavefront has at least
 // DEPTH groups (checked by the host): with DEPTH == the number of groups this is the all-loads-up-front walk.
 // Whole layer (two norms), us, with norms of their own -> now, prefix 1000: 8B one row 49.3 -> 45.3, two 48.9 -> 45.2, four 49.9 -> 48.4; 70B one row
-// 101.7 -> 96.9, four 105.6 -> 104.8; hidden 2048, one row 37.3 -> 33.5, four 38.1 -> 36.5.  Forms for one, two and four rows are compiled: the
+// 101.7 -> 96.9, four 105.6 -> 104.8; hidden 2048, one row 37.3 -> 33.5, four 38.1 -> 36.5.  (Before the loads were pinned to their order, which took
+// another 1 - 2.7 %: 70B four rows 100.7 -> 98.0 beside the linears as they were then.)  Forms for one, two and four rows are compiled: the
 // rows' arithmetic stands ahead of the first product, and what four rows cost over one (about 1 us a norm) is the gain that shrinks; with more rows, or
 // the 128 KB of sixteen, it would be gone.  Two groups of eight tiles in flight: the 8B layer 45.4 -> 45.5, the 70B layer 97.6 -> 98.9, so one.
 constexpr int kNormedMaxK = 8192;
@@ -1672,9 +1673,12 @@ __global__ __launch_bounds__(NW * 64) void gemm_normed_kernel(
         const uint32_t rec = (uint32_t)d * (NW * kRecordBytes);
         load_quant<TW, SYM>(qw[d], recs, rec, scale_off, zero_off);
 #pragma unroll
-        for (int t = 0; t < TW; ++t) w[d][t] = stream_quad(recs, code_off + (uint32_t)(t * 1024), rec);
+        for (int t = 0; t < TW; ++t) {
+            __builtin_amdgcn_sched_barrier(0);   // in the order of use: what the loop waits for at its head is then as new in its first trip
+            w[d][t] = stream_quad(recs, code_off + (uint32_t)(t * 1024), rec);
+        }
+        __builtin_amdgcn_sched_barrier(0);
     }
-    __builtin_amdgcn_sched_barrier(0);
     // 3. the norm
     float ss[ROWS][kSlots];
 #pragma unroll
@@ -1745,6 +1749,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_normed_kernel(
         const StagedQuant<TW> q = qd;
         const uint32_t zbits = q.z >> (4 * t0), rec = (uint32_t)(i + DEPTH) * (NW * kRecordBytes);
         if (refill) load_quant<TW, SYM>(qd, recs, rec, scale_off, zero_off);
+        __builtin_amdgcn_sched_barrier(0);
         float4v negc[1], xsum[1];
         if constexpr (SYM) group_sums_symmetric<1>(a, negc);
         else group_sums<1>(a, negc, xsum);
@@ -1765,13 +1770,20 @@ __global__ __launch_bounds__(NW * 64) void gemm_normed_kernel(
         }
     };
     int i = 0;
-    for (; i + 2 * DEPTH <= n_w; i += DEPTH) {   // every group here has a successor DEPTH groups on
+    if (n_w >= 2 * DEPTH) {   // uniform; the loop is entered with a round to go, as in gemm_x_kernel
+        do {   // every group here has a successor DEPTH groups on
 #pragma unroll
-        for (int u = 0; u < DEPTH; ++u) compute(i + u, w[u], qw[u], true);
+            for (int u = 0; u < DEPTH; ++u) compute(i + u, w[u], qw[u], true);
+            i += DEPTH;
+        } while (i + 2 * DEPTH <= n_w);
+#pragma unroll
+        for (int u = 0; u < 2 * DEPTH - 1; ++u)
+            if (i + u < n_w) compute(i + u, w[u % DEPTH], qw[u % DEPTH], i + u + DEPTH < n_w);   // uniform
+    } else {
+#pragma unroll
+        for (int u = 0; u < 2 * DEPTH - 1; ++u)
+            if (u < n_w) compute(u, w[u % DEPTH], qw[u % DEPTH], u + DEPTH < n_w);
     }
-#pragma unroll
-    for (int u = 0; u < 2 * DEPTH - 1; ++u)
-        if (i + u < n_w) compute(i + u, w[u % DEPTH], qw[u % DEPTH], i + u + DEPTH < n_w);   // uniform
     __syncthreads();   // the rows are dead: the epilogue reuses their LDS
     finish_unit<1, TW, NW>(acc, lds4, ticket_sh, y, partial, tickets, M, N, S, fused, unit, ks, nb, t0, tid, lane, wave);
 }
