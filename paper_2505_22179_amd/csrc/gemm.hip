@@ -2473,7 +2473,8 @@ static int dispatch(int mt, const Plan &pl, const void *x, const void *packed, c
 
 // ---- linears behind a norm (gemm_normed) ------------------------------------------------------------
 // The K-split shapes compiled with the norm of their rows in front: {tiles per wavefront, wavefronts, groups in flight}.  The walk of a plan
-// is kept (tiles, wavefronts, K splits, and with them the order of all sums), so the results are those of the two kernels bit for bit.
+// is kept (tiles, wavefronts, K splits, and with them the order of all sums), and the symmetric form runs for plans whose own kernel has one,
+// so the results are those of the two kernels bit for bit.
 template <int TW, int NW, int DEPTH, int ROWS, bool SYM>
 static int launch_normed(const void *h, const void *gamma, float eps, const void *packed, const Out &y, int M, int N, int K, const Plan &pl,
                          void *workspace, hipStream_t stream)
@@ -2508,12 +2509,13 @@ static int dispatch_normed(const void *h, const void *gamma, float eps, const vo
     if (M > kFlatMaxRows || K > kNormedMaxK || pl.S < 1 || pl.ks > 0 || (pl.nw != 8 && pl.nw != 4)) return W4A16_EUNSUP;
     const int least = K / kGroup / pl.S / pl.nw;   // groups of the wavefront that has fewest
     if (least < 1) return W4A16_EUNSUP;
+    const bool sym = y.sym && pl.ng == 0;   // launch_flat has no symmetric form: zero-points are read whatever the caller says
 #define N1(TW_, NW_, D_, ROWS_, SYM_) return launch_normed<TW_, NW_, D_, ROWS_, SYM_>(h, gamma, eps, packed, y, M, N, K, pl, workspace, stream)
 #define N2(TW_, NW_, D_)                                                                       \
     do {                                                                                       \
-        if (y.sym && M == 1) N1(TW_, NW_, D_, 1, true);                                        \
-        if (y.sym && M == 2) N1(TW_, NW_, D_, 2, true);                                        \
-        if (y.sym) N1(TW_, NW_, D_, kFlatMaxRows, true);                                       \
+        if (sym && M == 1) N1(TW_, NW_, D_, 1, true);                                          \
+        if (sym && M == 2) N1(TW_, NW_, D_, 2, true);                                          \
+        if (sym) N1(TW_, NW_, D_, kFlatMaxRows, true);                                         \
         if (M == 1) N1(TW_, NW_, D_, 1, false);                                                \
         if (M == 2) N1(TW_, NW_, D_, 2, false);                                                \
         N1(TW_, NW_, D_, kFlatMaxRows, false);                                                 \

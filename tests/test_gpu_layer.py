@@ -563,48 +563,70 @@ NORMED = [(1152, 2, 8, 1), (4224, 2, 8, 1), (8192, 2, 8, 1), (1024, 4, 8, 1), (2
           (4096, 8, 4, 2), (8320, 8, 8, 1)]
 
 
-@pytest.mark.parametrize("H,tw,nw,split", NORMED)
-@pytest.mark.parametrize("symmetric", [False, True])
-def test_layer_of_few_rows_is_its_steps_bit_for_bit(H, tw, nw, split, symmetric, big_ws):
-    P, Hq, Hkv, D, F = 40, 2, 1, 128, 384
+def layer_beside_its_steps(lin, H, F, Hq, Hkv, symmetric, heads, rows, knobs, ws):
+    """a layer of each number of rows, bit for bit the entry points it stands for; yields the rows and what the layer left in its norm scratch,
+    which held SENTINEL.  The steps of a symmetric layer are w4a16_gemm_fused and rope_append: w4a16_gemm_rope itself does not take the symmetric form."""
+    P, D = 40, 128
     N = (Hq + 2 * Hkv) * D
-    lin = [I.make_linear(9400 + i, 1, K, N_) for i, (K, N_) in enumerate(((H, N), (Hq * D, H), (H, 2 * F), (F, H)))]
-    if symmetric:
-        for inp in lin:
-            inp.qzeros[...] = np.uint32(0x88888888).astype(inp.qzeros.dtype)
-    heads = not symmetric   # w4a16_gemm_rope itself does not take the symmetric form
-    packed = [B.pack_from_numpy(lin[0], head_dim=D if heads else 0), B.pack_from_numpy(lin[1]), B.pack_from_numpy(lin[2], gate_up=True),
-              B.pack_from_numpy(lin[3])]
+    qkv_plain = B.pack_from_numpy(lin[0])
+    qkv_heads = B.pack_from_numpy(lin[0], head_dim=D)
+    rest = [B.pack_from_numpy(lin[1]), B.pack_from_numpy(lin[2], gate_up=True), B.pack_from_numpy(lin[3])]
     code = B.SYMMETRIC if symmetric else 0
     dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
     f16 = lambda *shape: torch.empty(shape, dtype=torch.float16, device=DEV)
     g1, g2 = dev(I.make_gamma(9411, H)), dev(I.make_gamma(9412, H))
     cos, sin = (dev(t) for t in I.make_rope_tables(P + 16, D))
-    for M in (1, 2, 3, 4, 5):
-        print(f"   H={H} tw={tw} nw={nw} split={split} M={M}", flush=True)
+    for M in rows:
+        print(f"   H={H} symmetric={symmetric} heads={heads} {knobs} M={M}", flush=True)
         rng = np.random.default_rng(9420 + M)
         h0 = dev(I.make_hidden(9430 + M, M, H))
         pos, mask = dev(np.arange(P, P + M, dtype=np.int32)), dev(np.tril(np.ones((M, M), dtype=np.uint8)))
         kc, vc = (dev(rng.standard_normal((P + M, Hkv, D), dtype=np.float32).astype(np.float16)) for _ in range(2))
-        bufs = [f16(M, H), f16(M, N), f16(M, Hq, D), f16(M, Hq, D), f16(M, F)]
+        norm, qkv, q, att, act = bufs = [f16(M, H), f16(M, N), f16(M, Hq, D), f16(M, Hq, D), f16(M, F)]
+        layer_norm = torch.full((M, H), SENTINEL, dtype=torch.float16, device=DEV)
         aws = B.new_workspace(B.tree_verify_attn_workspace_bytes(M, P, Hq, Hkv, D))
-        set_knobs(tw=tw, nw=nw, depth=1, split=split)
+        set_knobs(**knobs)
         h, k, v = h0.clone(), kc.clone(), vc.clone()
-        weights = B.layer_weights(*packed, g1, g2, H, Hq, Hkv, D, F, 1e-5, qkv_heads_packed=heads, symmetric=symmetric)
-        B.w4a16_decoder_layer(weights, h, M, P, pos, cos, sin, P + 16, mask, k, v, B.layer_scratch(*bufs, big_ws, aws))
-        norm, qkv, q, att, act = bufs
+        weights = B.layer_weights(qkv_heads if heads else qkv_plain, *rest, g1, g2, H, Hq, Hkv, D, F, 1e-5, qkv_heads_packed=heads, symmetric=symmetric)
+        B.w4a16_decoder_layer(weights, h, M, P, pos, cos, sin, P + 16, mask, k, v, B.layer_scratch(layer_norm, *bufs[1:], ws, aws))
         h2, k2, v2 = h0.clone(), kc.clone(), vc.clone()
         B.rms_norm(h2, g1, norm, M, H, 1e-5)
-        if heads:
-            B.w4a16_gemm_rope(norm, packed[0], M, H, 128, pos, cos, sin, P + 16, q, k2, v2, P, Hq, Hkv, D, big_ws)
+        if heads and not symmetric:
+            B.w4a16_gemm_rope(norm, qkv_heads, M, H, 128, pos, cos, sin, P + 16, q, k2, v2, P, Hq, Hkv, D, ws)
         else:
-            B.w4a16_gemm_fused(norm, packed[0], qkv, M, N, H, 128, code, None, big_ws)
+            B.w4a16_gemm_fused(norm, qkv_plain, qkv, M, N, H, 128, code, None, ws)
             B.rope_append(qkv, pos, cos, sin, P + 16, q, k2, v2, M, P, Hq, Hkv, D)
         B.tree_verify_attn(q, k2, v2, mask, att, M, P, Hq, Hkv, D, 1.0 / np.sqrt(D), aws)
-        B.w4a16_gemm_fused(att.view(M, Hq * D), packed[1], h2, M, H, Hq * D, 128, B.EPI_RESIDUAL | code, h2, big_ws)
+        B.w4a16_gemm_fused(att.view(M, Hq * D), rest[0], h2, M, H, Hq * D, 128, B.EPI_RESIDUAL | code, h2, ws)
         B.rms_norm(h2, g2, norm, M, H, 1e-5)
-        B.w4a16_gemm_fused(norm, packed[2], act, M, 2 * F, H, 128, B.EPI_SILU_MUL | code, None, big_ws)
-        B.w4a16_gemm_fused(act, packed[3], h2, M, H, F, 128, B.EPI_RESIDUAL | code, h2, big_ws)
+        B.w4a16_gemm_fused(norm, rest[1], act, M, 2 * F, H, 128, B.EPI_SILU_MUL | code, None, ws)
+        B.w4a16_gemm_fused(act, rest[2], h2, M, H, F, 128, B.EPI_RESIDUAL | code, h2, ws)
         torch.cuda.synchronize()
         for a, b, what in ((h, h2, "h"), (k, k2, "k"), (v, v2, "v")):
             assert torch.equal(a.view(torch.int16), b.view(torch.int16)), f"{what}, M={M}"
+        yield M, layer_norm
+
+
+def layer_linears(H, F, Hq, Hkv, symmetric):
+    return [I.make_linear(9400 + i, 1, K, N, zero_kind="eight" if symmetric else "uniform")
+            for i, (K, N) in enumerate(((H, (Hq + 2 * Hkv) * 128), (Hq * 128, H), (H, 2 * F), (F, H)))]
+
+
+@pytest.mark.parametrize("H,tw,nw,split", NORMED)
+@pytest.mark.parametrize("symmetric", [False, True])
+def test_layer_of_few_rows_is_its_steps_bit_for_bit(H, tw, nw, split, symmetric, big_ws):
+    F, Hq, Hkv = 384, 2, 1
+    lin = layer_linears(H, F, Hq, Hkv, symmetric)
+    for _ in layer_beside_its_steps(lin, H, F, Hq, Hkv, symmetric, not symmetric, (1, 2, 3, 4, 5), dict(tw=tw, nw=nw, depth=1, split=split), big_ws):
+        pass
+
+
+@pytest.mark.parametrize("heads", [False, True])
+@pytest.mark.parametrize("symmetric", [False, True])
+def test_layer_of_few_rows_by_default_plans(symmetric, heads, big_ws):
+    """Llama-3 8B: the plan of q/k/v requests all its loads up front, and no such kernel has a symmetric form: the norm in front must not bring one in"""
+    H, F, Hq, Hkv = 4096, 14336, 32, 8
+    assert [B.w4a16_plan_describe(M, 6144, H, 128)[0] for M in (1, 4)] == [1, 1]
+    lin = layer_linears(H, F, Hq, Hkv, symmetric)
+    for M, norm in layer_beside_its_steps(lin, H, F, Hq, Hkv, symmetric, heads, (1, 2, 3, 4, 5), {}, big_ws):
+        assert (norm == SENTINEL).all().item() == (M <= 4), "few rows are normed inside the linears, others are not"
