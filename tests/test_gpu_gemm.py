@@ -114,7 +114,7 @@ def test_parity_wide_workgroups(M, K, N, big_ws):
 
 @pytest.mark.parametrize("M,K,N", [(1, 1152, 136), (4, 640, 264), (2, 8192, 136), (5, 128, 8), (8, 2176, 1000), (16, 3200, 128), (17, 128, 8), (32, 640, 264), (33, 1024, 136), (48, 1152, 1000), (49, 2176, 128), (64, 3200, 520), (24, 14336, 256)])
 def test_parity_own_x_tiles(M, K, N, big_ws):
-    """eight wavefronts that split K and keep an x tile each (up to four rows with eight unsplit column tiles or a long walk only): fewer groups than wavefronts, one group
+    """eight wavefronts that split K and keep an x tile each, at any number of rows: fewer groups than wavefronts, one group
     each, one or two wavefronts with one more, splits across workgroups that leave some without a group, partial row tiles"""
     print(f"gemm parity (own x tiles) M={M} K={K} N={N}", flush=True)
     inp = I.make_linear(5700 + M + K + N, M, K, N)
@@ -149,14 +149,16 @@ def test_parity_fetched_x(M, K, N, big_ws):
         check_gemm(run_gemm(inp, packed, big_ws), y32, f"M={M} K={K} N={N} variant={variant}")
 
 
-def test_eight_wavefronts_beyond_32_bit_offsets(big_ws):
-    """17 rows of 2 ** 25 elements: x zero but for some single ones all along K, all scales one, so the sums are whole numbers"""
-    M, K, N = 17, 2 ** 25, 8
+@pytest.mark.parametrize("M", [1, 16, 17])
+def test_eight_wavefronts_beyond_32_bit_offsets(M, big_ws):
+    """rows of 2 ** 25 elements, where x is fetched from L2 with one and two row tiles: x zero but for some single ones all along K, all scales
+    one, so the sums are whole numbers; one row tile with the symmetric forms too, which leave the zero-points unread"""
+    K, N = 2 ** 25, 8
     g = torch.Generator(device=DEV).manual_seed(5900)
     records = torch.randint(0, 256, (K // 128, 8512), dtype=torch.uint8, device=DEV, generator=g)
     records[:, 8192:8448] = torch.ones(128, dtype=torch.float16, device=DEV).view(torch.uint8)
     x = torch.zeros(M, K, dtype=torch.float16, device=DEV)
-    want = np.zeros((M, N))
+    want, want_symmetric = np.zeros((M, N)), np.zeros((M, N))
     rng = np.random.default_rng(5901)
     for k in sorted({0, K - 1, *rng.integers(0, K, 60).tolist()}):
         record = records[k // 128].cpu().numpy()
@@ -165,16 +167,22 @@ def test_eight_wavefronts_beyond_32_bit_offsets(big_ws):
         x[:, k] = torch.from_numpy(ones).to(DEV, torch.float16)
         for n in range(N):
             word = int(record[(16 * r + n) * 16 + 4 * j:][:4].view(np.uint32)[0])
-            zero = int(record[8448 + 4 * n]) & 15
-            want[:, n] += ones * ((word >> 4 * ((p >> 1) + 4 * (p & 1)) & 15) - zero)
-    assert np.abs(want).max() < 2048
-    for tw, depth in ((2, 1), (4, 1), (2, 2)):
+            zero, code = int(record[8448 + 4 * n]) & 15, word >> 4 * ((p >> 1) + 4 * (p & 1)) & 15
+            want[:, n] += ones * (code - zero)
+            want_symmetric[:, n] += ones * (code - 8)
+    assert np.abs(want).max() < 2048 and np.abs(want_symmetric).max() < 2048
+    for tw, depth in ((2, 1), (4, 1), (2, 2)) + (((8, 1),) if M <= 16 else ()):
         for split in (1, 3):
             set_variant(tw, 8, depth, split, 1)
-            assert B.w4a16_plan_describe(M, N, K, 128)[:5] == (0, 2, tw, 8, depth)
-            y = torch.full((M, N), 7.0, dtype=torch.float16, device=DEV)
-            B.w4a16_gemm(x, records, y, M, N, K, 128, big_ws)
-            assert np.array_equal(y.cpu().numpy(), want), (tw, depth, split)
+            assert B.w4a16_plan_describe(M, N, K, 128)[:5] == (0, (M + 15) // 16, tw, 8, depth)
+            for symmetric in (False, True) if M <= 16 else (False,):
+                print(f"   M={M} K=2^25 tw={tw} depth={depth} split={split} symmetric={symmetric}", flush=True)
+                y = torch.full((M, N), 7.0, dtype=torch.float16, device=DEV)
+                if symmetric:
+                    B.w4a16_gemm_fused(x, records, y, M, N, K, 128, B.SYMMETRIC, None, big_ws)
+                else:
+                    B.w4a16_gemm(x, records, y, M, N, K, 128, big_ws)
+                assert np.array_equal(y.cpu().numpy(), want_symmetric if symmetric else want), (tw, depth, split, symmetric)
 
 
 # high-occupancy column-split workgroups, M > 16 only: (tiles_per_wave, k_sets, prefetch_depth, split_k)

@@ -557,10 +557,11 @@ def test_fused_epilogues_full_size_sampled_columns(M):
 
 # ---- linears that work the norm of few rows out themselves -------------------------------------------
 # (hidden, tiles per wavefront, wavefronts, K splits) of the forms compiled with the norm in front, one and several groups in flight,
-# ragged walks among them (9, 21 and 33 groups), the longest row, and a row beyond it, which takes the two kernels
+# ragged walks among them (9, 21, 33 and 37 groups), walks of less than two rounds of the groups in flight and of more, the longest row, and a row
+# beyond it, which takes the two kernels
 
-NORMED = [(1152, 2, 8, 1), (4224, 2, 8, 1), (8192, 2, 8, 1), (1024, 4, 8, 1), (2688, 4, 8, 1), (1152, 8, 8, 1), (8192, 8, 8, 3), (640, 8, 4, 1),
-          (4096, 8, 4, 2), (8320, 8, 8, 1)]
+NORMED = [(1152, 2, 8, 1), (4224, 2, 8, 1), (8192, 2, 8, 1), (1024, 4, 8, 1), (2688, 4, 8, 1), (4096, 4, 8, 1), (4736, 4, 8, 1), (1152, 8, 8, 1),
+          (8192, 8, 8, 3), (640, 8, 4, 1), (4096, 8, 4, 2), (8320, 8, 8, 1)]
 
 
 def layer_beside_its_steps(lin, H, F, Hq, Hkv, symmetric, heads, rows, knobs, ws):
@@ -613,12 +614,12 @@ def layer_linears(H, F, Hq, Hkv, symmetric):
 
 
 @pytest.mark.parametrize("H,tw,nw,split", NORMED)
-@pytest.mark.parametrize("symmetric", [False, True])
-def test_layer_of_few_rows_is_its_steps_bit_for_bit(H, tw, nw, split, symmetric, big_ws):
+@pytest.mark.parametrize("symmetric,heads", [(False, True), (True, False), (True, True)])
+def test_layer_of_few_rows_is_its_steps_bit_for_bit(H, tw, nw, split, symmetric, heads, big_ws):
     F, Hq, Hkv = 384, 2, 1
     lin = layer_linears(H, F, Hq, Hkv, symmetric)
-    for _ in layer_beside_its_steps(lin, H, F, Hq, Hkv, symmetric, not symmetric, (1, 2, 3, 4, 5), dict(tw=tw, nw=nw, depth=1, split=split), big_ws):
-        pass
+    for M, norm in layer_beside_its_steps(lin, H, F, Hq, Hkv, symmetric, heads, (1, 2, 3, 4, 5), dict(tw=tw, nw=nw, depth=1, split=split), big_ws):
+        assert (norm == SENTINEL).all().item() == (M <= 4 and H <= 8192), "few rows are normed inside the linears, others are not"
 
 
 @pytest.mark.parametrize("heads", [False, True])

@@ -99,6 +99,15 @@ def test_lm_head_shared_rows(M, K, V):
         B.w4a16_set_param("lm_tiles", 0)
 
 
+@pytest.mark.parametrize("M,K,V", [(24, 2048, 16000), (17, 1152, 10241), (40, 1920, 12001), (48, 640, 16384), (60, 2048, 16000), (64, 4096, 10300)])
+def test_lm_head_shared_rows_in_small_workgroups(M, K, V):
+    """the form with four wavefronts, which the size rule alone picks, on walks beyond its pipeline of four steps: whole and ragged rounds"""
+    assert B.lm_head_plan_describe(M, V, K) == (1, 4, 1)
+    x, W = I.make_lm_head(9930 + M + K + V, M, K, V)
+    print(f"lm_head shared rows, four wavefronts, M={M} K={K} V={V}", flush=True)
+    check(x, W, 3, f"M={M} K={K} V={V}")
+
+
 @pytest.mark.parametrize("M,K,V", [(64, 2048, 49501), (32, 2048, 33001), (48, 1024, 34000),   # an even number of k steps
                                    (17, 1152, 34000), (48, 896, 33001),                       # an odd one
                                    (50, 2 ** 20 + 128, 70)])                                  # beyond the 32-bit offsets of the other
@@ -231,11 +240,13 @@ def test_many_top_tokens(M, K, V, top_k):
     check(x, W, top_k, f"M={M} K={K} V={V} k={top_k}")
 
 
-@pytest.mark.parametrize("M", [2, 20])
-def test_infinite_and_nan_logits(M):
+# the kernels of short walks, and the one that keeps x in LDS (with four and two steps in flight, one to three row tiles)
+@pytest.mark.parametrize("M,K,kept", [(2, 128, False), (20, 128, False), (2, 2048, True), (8, 1024, True), (20, 2048, True), (40, 1152, True)])
+def test_infinite_and_nan_logits(M, K, kept):
     """-inf logits (whole granules of them) take no part in sum and order, fewer finite ones than top_k leave the rest of the
     list empty, and a NaN makes the row's log-probabilities NaN but wins no place"""
-    K, V, top_k = 128, 3000, 8
+    V, top_k = 3000, 8
+    assert (B.lm_head_plan_describe(M, V, K) == (1, 16, 1)) == kept
     x, W = I.make_lm_head(9980, M, K, V)
     x[:, 0] = 1
     W[512:1700, 0] = -np.inf
@@ -253,17 +264,18 @@ def test_infinite_and_nan_logits(M):
     assert (np.sort(Ix[:, :5], axis=1) == np.arange(5)).all() and np.isnan(P).all()
 
 
-@pytest.mark.parametrize("M", [1, 20])
-def test_rows_without_a_finite_logit(M):
+@pytest.mark.parametrize("M,K,kept", [(1, 128, False), (20, 128, False), (1, 2048, True), (16, 1024, True), (33, 1152, True)])
+def test_rows_without_a_finite_logit(M, K, kept):
     """the logarithm of their sum of exponentials does not exist: no token, and NaN as in any log-softmax"""
-    K, V, top_k = 128, 1500, 4
+    V, top_k = 1500, 4
+    assert (B.lm_head_plan_describe(M, V, K) == (1, 16, 1)) == kept
     x, W = np.zeros((M, K), np.float16), np.zeros((V, K), np.float16)
     x[:, 0], W[:, 0] = 1, -np.inf
     L, Ix, P = run(x, W, top_k)
     assert np.isneginf(L).all() and (Ix == 0x7FFFFFFF).all() and np.isnan(P).all()
 
 
-@pytest.mark.parametrize("M,K,V,top_k", [(1, 256, 5000, 1), (30, 256, 5001, 2)])
+@pytest.mark.parametrize("M,K,V,top_k", [(1, 256, 5000, 1), (30, 256, 5001, 2), (1, 2048, 4000, 1), (16, 1024, 5000, 3), (30, 1152, 5001, 2)])
 def test_workspace_below_the_stated_size(M, K, V, top_k):
     """the least accepted workspace (statistics and candidates of 512-token chunks) gives the same tokens through a pass over
     the logits; anything below is refused"""
