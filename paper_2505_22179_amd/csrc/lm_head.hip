@@ -789,13 +789,14 @@ struct LmPlan { bool shared; int nw, twl; bool kept = false; };   // kept: the k
 // 160 of them with more rows, which the kernel with shared x tiles serves better by then (16000 tokens, K = 2048, 60 rows 24.3 against 25.9; 10000
 // tokens 21.4 against 20.7); up to 64 with four rows or fewer, whose x is little to fetch either way (16000 tokens, K = 4096, one row 27.4 against 33.6; 4000
 // tokens, K = 5120 21.6 against 20.5).  Its walk goes in phases, the fewest whose x tiles fit LDS, each with two or four steps for every wavefront at least;
-// with few rows two were no gain (K = 1024, 10000 tokens, two rows 11.5 against 11.7).
+// with four rows or fewer, four.  On the shortest walks below that (K = 1024) this kernel is no gain: 4000 tokens, one row 9.8 against 9.6 us, two 9.9 against 9.8,
+// four 10.0 against 10.1.  (From K = 1408 on it would be, K = 1920 10.7 against 11.2, 10.9 against 11.6 and 10.9 against 12.2: the line could lie lower.)
 struct LmKept { int hb, depth, phases, q, rem; size_t lds; };
 static LmKept lm_kept(int M, int K)
 {
     const int hb = M <= 8 ? 1 : 2 * ((M + 15) / 16), steps = K / kLmStepK, tile = hb * 2048, most = kLmKeptLds / tile;
     const int phases = (steps + most - 1) / most, q = steps / phases, rem = steps % phases;
-    const int depth = q >= 4 * kLmKeptSets ? 4 : q >= 2 * kLmKeptSets ? 2 : 0;
+    const int depth = q >= 4 * kLmKeptSets ? 4 : q >= 2 * kLmKeptSets ? 2 : 0;   // never 4 with more than 32 rows: q <= most
     const size_t x_bytes = (size_t)(q + (rem > 0)) * tile, sum_bytes = (size_t)kLmKeptWaves * ((hb + 1) / 2) * 1024;
     return {hb, depth, phases, q, rem, x_bytes > sum_bytes ? x_bytes : sum_bytes};
 }
@@ -920,6 +921,7 @@ int lm_head_topk(const void *x, const void *packed, int M, int V, int K, int top
         static bool lds_ok[9][2] = {};
 #define W4_LM_KEPT(HB_, D_)                                                                                                                \
     if (walk.hb == HB_ && walk.depth == D_) {                                                                                              \
+        static_assert(kLmKeptLds / (HB_ * 2048) >= D_ * kLmKeptSets, "a phase holds D_ steps for every set");                              \
         const auto kernel = &lm_head_logits_kept_kernel<HB_, D_>;                                                                          \
         bool &ok = lds_ok[HB_][D_ == 4];                                                                                                   \
         if (!ok && walk.lds > 48 * 1024) {                                                                                                 \
@@ -931,7 +933,7 @@ int lm_head_topk(const void *x, const void *packed, int M, int V, int K, int top
                            M, V, K, tiles, walk.phases, walk.q, walk.rem);                                                                 \
     }
         W4_LM_KEPT(1, 2) W4_LM_KEPT(2, 2) W4_LM_KEPT(4, 2) W4_LM_KEPT(6, 2) W4_LM_KEPT(8, 2)
-        W4_LM_KEPT(1, 4) W4_LM_KEPT(2, 4) W4_LM_KEPT(4, 4) W4_LM_KEPT(6, 4) W4_LM_KEPT(8, 4)
+        W4_LM_KEPT(1, 4) W4_LM_KEPT(2, 4) W4_LM_KEPT(4, 4)
 #undef W4_LM_KEPT
     } else {
         const int depth = mtl > 1 ? 2 : kLmDepth;
