@@ -239,7 +239,8 @@ int w4a16_gemm_rope(const void *x, const void *packed, int M, int K, int G, cons
  * updated in place.  Weights: w4a16_pack outputs for qkv [hidden -> (n_q_heads + 2 n_kv_heads) head_dim],
  * o [n_q_heads head_dim -> hidden] and down [ffn -> hidden]; a w4a16_pack_gate_up output for
  * gate_up [hidden -> 2 ffn]; group size 128.  Scratch, all fp16 and 16-byte aligned, owned by the
- * caller: norm [M, hidden], qkv [M, (n_q_heads + 2 n_kv_heads) head_dim], q and attn [M, n_q_heads,
+ * caller: norm [M, hidden] (unspecified after the call: a linear of few rows may work the norm out
+ * itself and leave it unwritten), qkv [M, (n_q_heads + 2 n_kv_heads) head_dim], q and attn [M, n_q_heads,
  * head_dim], act [M, ffn]; gemm_workspace sized for the largest of the four linears
  * (w4a16_workspace_bytes) and attn_workspace (tree_verify_attn_workspace_bytes), both initialised with
  * w4a16_workspace_init.  With qkv_heads_packed set, qkv_packed is a w4a16_pack_heads output and the second
@@ -254,7 +255,8 @@ typedef struct {
     float eps;
     int qkv_heads_packed; /* nonzero: qkv_packed comes from w4a16_pack_heads and the layer uses w4a16_gemm_rope */
     int symmetric;        /* nonzero: all four weights have zero-points 8 throughout (W4A16_SYMMETRIC on every linear that
-                             takes the flag: o, gate_up, down, and qkv when it is not the fused-rotary projection) */
+                             takes the flag, the fused-rotary projection included: its sums are then those of
+                             w4a16_gemm_fused with the flag, as w4a16_gemm_rope itself has none) */
 } w4a16_layer_weights;
 typedef struct {
     void *norm, *qkv, *q, *attn, *act;
@@ -361,7 +363,8 @@ int tree_verify_attn_plan_describe(int M, int P, int Hq, int Hkv, int D, size_t 
 
 /* The logits kernel lm_head_topk would run with the current knobs.  out receives 3 ints: [0] 1 if the wavefronts of a
  * workgroup share x through LDS, 0 if each fetches its own, [1] wavefronts per workgroup, [2] vocabulary tiles per
- * wavefront.  Host only: touches no GPU.  Errors as lm_head_topk's shape checks. */
+ * wavefront.  16 wavefronts mean the kernel that keeps x in LDS: four of them share each of the workgroup's four tiles,
+ * a quarter of the walk each.  Host only: touches no GPU.  Errors as lm_head_topk's shape checks. */
 int lm_head_plan_describe(int M, int V, int K, int *out);
 
 /* Measurement aid, not part of the method: enqueues a kernel that only reads the first

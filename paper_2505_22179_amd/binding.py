@@ -104,7 +104,7 @@ def _ptr(t) -> int:
 
 
 # The linears and the attention write out what the helpers here do: the smallest takes 4 us on the GPU, and
-# a Python call and an attribute chain per argument were a tenth of the host time of its call (5.1 -> 4.2 us, 3.4 of it the C call with its launch).
+# a Python call and an attribute chain per argument were a fifth of the host time of its call (5.1 -> 4.2 us, 3.4 of it the C call with its launch).
 _init_cuda = torch.cuda.init
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 _current_device = getattr(torch._C, "_cuda_getDevice", None)

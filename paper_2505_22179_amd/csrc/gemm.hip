@@ -646,8 +646,8 @@ __device__ __forceinline__ void finish_unit(const float4v (&acc)[TW][MT], float4
 // MT row tiles of 16, TW column tiles per wavefront, NW wavefronts per workgroup (all on the same
 // columns, each on its own quantisation groups), DEPTH groups of codes in flight per wavefront.
 // Here and in the other linear kernels everything the first loads depend on stands in the first 64 bytes of the arguments, one line of the scalar
-// cache, and is fetched at once; left to itself the compiler fetched the sizes, waited, and then fetched the pointers.  8B q/k/v with rotary store,
-// 30 rows, 8.76 -> 8.67 us, 70B down at 7 rows 22.28 -> 22.07.
+// cache, and is fetched at once; left to itself the compiler fetched the sizes, waited, and then fetched the pointers.  Both libraries
+// in turn, operands of one copy: 8B q/k/v with rotary store at 30 rows 7.49 -> 7.30 us, 70B down at 7 rows 20.75 -> 20.51, 5120 -> 13000 at 37 rows 13.80 -> 13.59.
 template <int MT, int TW, int NW, int DEPTH, bool SYM>
 __global__ __launch_bounds__(NW * 64, min_waves_per_simd(MT, TW, NW, DEPTH)) void gemm_kernel(
     const _Float16 *__restrict__ x, const uint8_t *__restrict__ packed, int M, int N, int K, int groups, int S, int fused,
@@ -1987,7 +1987,8 @@ struct ShapeTime {
     {
         const float tw = (float)tw_;
         k_sets = ks > 0;
-        // (up to four rows the two kernels differ little, see own_x_tiles; the fit knows single passes over the chip only)
+        // (the fit knows single passes over the chip only.  Up to four rows the one of the kernel that fetches x stands for both: it was measured while
+        // that kernel served them, and does not know the twentieth that x tiles have gained there since, see own_x_tiles)
         own_x = !k_sets && (c.M > 16 || (c.M > 4 && nw == kXWaves && c.tiles / tw_ <= 256));
         if (own_x && c.M <= 16) {   // wavefronts that split K, each with an x tile of its own: one row tile
             units = c.tiles / tw_;
@@ -2082,8 +2083,8 @@ static constexpr RuleShapes rule_shapes(int mt)
 }
 constexpr RuleShapes kRuleShapesOf[4] = {rule_shapes(1), rule_shapes(2), rule_shapes(3), rule_shapes(4)};
 
-// Eight wavefronts and more than one row tile: beyond the 32-bit offsets of gemm_x_kernel the one that fetches x from L2 runs, in the forms
-// that were compiled before there was another
+// Eight wavefronts: beyond the 32-bit offsets of gemm_x_kernel the one that fetches x from L2 runs, in the forms that were compiled before there
+// was another
 static constexpr bool fetched_x_variant(int mt, int tw) { return mt == 1 || (mt == 2 && tw <= 4); }
 static bool reaches_all_of_k(int mt, int tw, int nw, int K)
 {
@@ -2474,7 +2475,8 @@ static int dispatch(int mt, const Plan &pl, const void *x, const void *packed, c
 // ---- linears behind a norm (gemm_normed) ------------------------------------------------------------
 // The K-split shapes compiled with the norm of their rows in front: {tiles per wavefront, wavefronts, groups in flight}.  The walk of a plan
 // is kept (tiles, wavefronts, K splits, and with them the order of all sums), and the symmetric form runs for plans whose own kernel has one,
-// so the results are those of the two kernels bit for bit.
+// so the results are those of the two kernels bit for bit.  Four wavefronts with two or four tiles have no such form: where the rule picks them
+// (24576 <- 4096, 17920 <- 1536, 4608 <- 3584) the norm stays a kernel of its own.
 template <int TW, int NW, int DEPTH, int ROWS, bool SYM>
 static int launch_normed(const void *h, const void *gamma, float eps, const void *packed, const Out &y, int M, int N, int K, const Plan &pl,
                          void *workspace, hipStream_t stream)
